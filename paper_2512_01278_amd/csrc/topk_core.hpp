@@ -57,28 +57,44 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(x, kWave - 1));
 }
 
+// Sum of the entries of `sums` before entry `at` (wave-uniform, at most 64 entries), and of all of them: one LDS read per
+// lane and one scan, where a loop over the entries would wait for the LDS once per entry.
+__device__ __forceinline__ uint32_t sum_before(const uint32_t* sums, int n, int at, int lane, uint32_t* total) {
+  const uint32_t incl = wave_inclusive_sum(lane < n ? sums[lane] : 0u);
+  *total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), kWave - 1));
+  return at > 0 ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), at - 1)) : 0u;
+}
+
 // LDS the selection needs (one instance per workgroup of THREADS threads holding CH chunks of keys).
 template <int THREADS, int CH> struct SelectLds {
   uint32_t hist[4096];
-  uint32_t wave_sum[2][CH][THREADS / kWave];
+  uint32_t wave_sum[2][CH * (THREADS / kWave)];
   uint32_t prefix[3], remaining[3];        // one slot per pass: no barrier between reading one and writing the next
+  uint32_t in_bin;                         // keys that share the first digit of the K-th largest
+  uint32_t n_cand;
+  uint32_t cand[kWave];                    // those keys, where one wavefront's lanes hold them all
 };
 
 // The workgroup holds CH * THREADS * KPC keys: key[c][j] of thread t belongs to position
 // c * (THREADS * KPC) + t * KPC + j; positions >= L are ignored.  Writes the K selected positions in
-// ascending order to out[0..K).  Three histogram passes of 12, 12 and 8 bits find the K-th largest key:
-// the wide first digit (sign, exponent and three mantissa bits) spreads attention scores, which share a
-// few exponents, over many more bins than an 8-bit digit does, and that is what keeps the LDS histogram
-// increments from serialising.  Equal keys go to the lower position.  Every thread of the workgroup must
-// call this.
+// ascending order to out[0..K).  A histogram of the upper 12 bits (sign, exponent and three or more mantissa
+// bits: attention scores share a few exponents, and a wide first digit is what keeps the LDS increments from
+// serialising) finds the first digit of the K-th largest key.  Usually few keys share it: up to 64 of them are
+// collected and every wavefront ranks them by itself, so that two barriers follow where two further histogram
+// passes (12 and 8 bits: the path for more keys) take six; and if all of them are taken there is nothing to rank.
+// Equal keys go to the lower position.  Every thread of the workgroup must call this.
+// What it costs is latency (barriers, LDS round trips): the stand-alone kernel on two rows of 512 scores 9.3 -> 5.3 us,
+// 128 rows of 28 K 30.5 -> 20.7 us with the candidates and with the scans over wavefronts done by lanes instead of loops.
 template <int THREADS, int KPC, int CH>
 __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[CH][KPC], int L, int K, int32_t* out,
                                                          SelectLds<THREADS, CH>& lds) {
   constexpr int kWaves = THREADS / kWave;
   constexpr int kChunk = THREADS * KPC;
   static_assert(4096 % THREADS == 0 && THREADS >= 256, "bins are dealt out evenly");
+  static_assert(CH * kWaves <= kWave, "one lane per (chunk, wavefront)");
+  static_assert(CH * kChunk < 65536, "two counts of positions share 32 bits");
   uint32_t* hist = lds.hist;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int t0 = static_cast<int>(threadIdx.x) * KPC;
   uint32_t prefix = 0, remaining = K;      // uniform across the workgroup
   const bool take_all = !(K < L);
@@ -92,6 +108,7 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
       const uint32_t mask = pass == 0 ? 0u : pass == 1 ? 0xfff00000u : 0xffffff00u;
       if (pass == 0) {                           // later passes find the bins zeroed by their last readers
         for (int i = threadIdx.x; i < 4096; i += THREADS) hist[i] = 0;
+        if (threadIdx.x == 0) lds.n_cand = 0;
         __syncthreads();
       }
       // A wavefront whose active keys all fall into one bin (constant or zero scores, or the few keys left in a late
@@ -141,12 +158,10 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
         tot += cnt[j];
       }
       uint32_t incl = wave_inclusive_sum(tot);   // inclusive scan over the workgroup: lanes, then wavefronts
-      if (lane == kWave - 1) lds.wave_sum[pass & 1][0][wave] = incl;
+      if (lane == kWave - 1) lds.wave_sum[pass & 1][wave] = incl;
       __syncthreads();
-      uint32_t before = 0;
-#pragma unroll 1
-      for (int w = 0; w < wave; ++w) before += lds.wave_sum[pass & 1][0][w];
-      incl += before;
+      uint32_t all;
+      incl += sum_before(lds.wave_sum[pass & 1], kWaves, wave, lane, &all);
       uint32_t above = incl - tot;           // keys in strictly higher digits than this thread's
       if (above < remaining && incl >= remaining) {
 #pragma unroll
@@ -156,6 +171,7 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
               const uint32_t digit = static_cast<uint32_t>(bins - 1 - per * static_cast<int>(threadIdx.x) - j);
               lds.prefix[pass] = prefix | (digit << shift);
               lds.remaining[pass] = remaining - above;
+              if (pass == 0) lds.in_bin = cnt[j];
               above = remaining;               // stop: only one digit can match
             } else {
               above += cnt[j];
@@ -166,6 +182,36 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
       __syncthreads();
       prefix = lds.prefix[pass];
       remaining = lds.remaining[pass];
+      if (pass == 0) {
+        const uint32_t in_bin = lds.in_bin;
+        if (in_bin == remaining && prefix > 0) {     // every key with this digit is taken: all keys above prefix - 1
+          prefix -= 1;
+          remaining = 0;
+          break;
+        }
+        if (in_bin <= kWave) {
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            if (c >= nch) continue;
+#pragma unroll
+            for (int j = 0; j < KPC; ++j)
+              if (c * kChunk + t0 + j < L && (key[c][j] & 0xfff00000u) == prefix) lds.cand[atomicAdd(&lds.n_cand, 1u)] = key[c][j];
+          }
+          __syncthreads();
+          const uint32_t mine_key = lane < static_cast<int>(in_bin) ? lds.cand[lane] : 0u;
+          uint32_t n_above = 0, n_equal = 0;         // candidates above this lane's key, and equal to it
+          for (int i = 0; i < static_cast<int>(in_bin); ++i) {
+            const uint32_t other = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mine_key), i));
+            n_above += other > mine_key ? 1u : 0u;
+            n_equal += other == mine_key ? 1u : 0u;
+          }
+          const uint64_t kth = __ballot(lane < static_cast<int>(in_bin) && n_above < remaining && n_above + n_equal >= remaining);
+          const int at = __ffsll(static_cast<unsigned long long>(kth)) - 1;      // the lanes of one value: the K-th largest key's
+          prefix = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mine_key), at));
+          remaining -= static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(n_above), at));
+          break;
+        }
+      }
     }
   } else {
     remaining = 0;
@@ -173,38 +219,32 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
   const uint32_t T = prefix;
   // remaining = how many keys equal to T are taken (lowest positions first)
 
-  // per chunk: how many of this thread's keys lie above T, and how many equal it
-  uint32_t n_gt[CH], n_eq[CH], s_gt[CH], s_eq[CH];
+  // per chunk: how many of this thread's keys lie above T (low half), and how many equal it (high half); exclusive
+  // scans of both over the workgroup, in position order (positions grow with the chunk first, then with the thread)
+  uint32_t n_sel[CH], s_sel[CH];
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    n_gt[c] = n_eq[c] = s_gt[c] = s_eq[c] = 0;
-    if (c >= nch) continue;
+    n_sel[c] = s_sel[c] = 0;
+    if (c < nch) {
 #pragma unroll
-    for (int j = 0; j < KPC; ++j) {
-      const bool in = c * kChunk + t0 + j < L;
-      n_gt[c] += (in && (take_all || key[c][j] > T)) ? 1u : 0u;
-      n_eq[c] += (in && !take_all && key[c][j] == T) ? 1u : 0u;
+      for (int j = 0; j < KPC; ++j) {
+        const bool in = c * kChunk + t0 + j < L;
+        n_sel[c] += (in && (take_all || key[c][j] > T)) ? 1u : 0u;
+        n_sel[c] += (in && !take_all && key[c][j] == T) ? 0x10000u : 0u;
+      }
+      s_sel[c] = wave_inclusive_sum(n_sel[c]);
     }
-    // exclusive scans of both counts over the workgroup, in position order (positions grow with the
-    // chunk first, then with the thread)
-    s_gt[c] = wave_inclusive_sum(n_gt[c]);
-    s_eq[c] = wave_inclusive_sum(n_eq[c]);
-    if (lane == kWave - 1) { lds.wave_sum[0][c][wave] = s_gt[c]; lds.wave_sum[1][c][wave] = s_eq[c]; }
+    if (lane == kWave - 1) lds.wave_sum[1][c * kWaves + wave] = s_sel[c];       // (last read before the barrier above)
   }
   __syncthreads();
-  uint32_t base_gt = 0, base_eq = 0;           // keys of earlier chunks
+  const uint32_t before = wave_inclusive_sum(lane < CH * kWaves ? lds.wave_sum[1][lane] : 0u);     // (chunk, wavefront) in position order
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     if (c >= nch) continue;
-    uint32_t b_gt = 0, b_eq = 0, t_gt = 0, t_eq = 0;
-#pragma unroll 1
-    for (int w = 0; w < kWaves; ++w) {
-      const uint32_t a = lds.wave_sum[0][c][w], e = lds.wave_sum[1][c][w];
-      if (w < wave) { b_gt += a; b_eq += e; }
-      t_gt += a;
-      t_eq += e;
-    }
-    uint32_t gt_before = base_gt + b_gt + s_gt[c] - n_gt[c], eq_before = base_eq + b_eq + s_eq[c] - n_eq[c];
+    const int at = c * kWaves + wave;
+    const uint32_t base = at > 0 ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(before), at - 1)) : 0u;
+    const uint32_t first = base + s_sel[c] - n_sel[c];
+    uint32_t gt_before = first & 0xffffu, eq_before = first >> 16;
     // output slot of a selected key = (# greater before it) + (# equal-and-taken before it)
 #pragma unroll
     for (int j = 0; j < KPC; ++j) {
@@ -216,8 +256,6 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
       gt_before += gt ? 1u : 0u;
       eq_before += eq ? 1u : 0u;
     }
-    base_gt += t_gt;
-    base_eq += t_eq;
   }
 }
 

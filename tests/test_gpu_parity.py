@@ -515,6 +515,30 @@ def test_topk_exact_ties_synthetic_scores():
     check_topk_exact(idx.cpu().numpy(), cnt.cpu().numpy(), s, lens, bud, [0, 1, 2], "ties")
 
 
+@pytest.mark.parametrize("in_bin", [1, 2, 63, 64, 65, 300])
+def test_topk_around_the_candidate_limit(in_bin):
+    """`in_bin` scores share their upper 12 bits with the K-th largest: up to 64 of them are ranked by the lanes of a
+    wavefront, more go through the further histogram passes.  K takes one of them, some, all but one and all (nothing to
+    rank); the second head has ties among them."""
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(100 + in_bin)
+    L, higher = 5000, 37
+    s = np.empty((4, 2, L), dtype=np.float32)
+    for b in range(4):
+        for g in range(2):
+            row = np.concatenate([1.0 + rng.integers(0, 3 if g else 2 ** 15, size=in_bin) * 2.0 ** -19,     # [1, 1.125)
+                                  2.0 + rng.random(higher), 0.9 * rng.random(L - in_bin - higher)])
+            s[b, g] = rng.permutation(row.astype(np.float32))
+    lens = np.full(4, L, dtype=np.int32)
+    bud = higher + np.array([1, (in_bin + 1) // 2, max(1, in_bin - 1), in_bin], dtype=np.int32)
+    idx = torch.full((4, 2, higher + in_bin), -9, dtype=torch.int32, device=dev)
+    cnt = torch.zeros(4, dtype=torch.int32, device=dev)
+    pa.pillar_select_topk(torch.from_numpy(s).to(dev), torch.from_numpy(lens).to(dev), torch.from_numpy(bud).to(dev), L,
+                          higher + in_bin, idx, cnt)
+    torch.cuda.synchronize()
+    check_topk_exact(idx.cpu().numpy(), cnt.cpu().numpy(), s, lens, bud, range(4), f"{in_bin} scores in the bin")
+
+
 def test_decode_accepts_unsorted_and_repeated_free_lists():
     w = small(206, seq_lens=[50, 300, 900], budgets=[10, 100, 300])
     run = GpuRun(w)
