@@ -81,6 +81,13 @@ __device__ __forceinline__ int queries_of(const KvView& kv, const RangeWs& ws, i
   return ws.spec_lens ? min(ws.spec_lens[request_of(kv, b)] + 1, n_q) : n_q;
 }
 
+// Ranges in use: all that the chip holds at once, but none shorter than kMinTiles tiles.  A tile costs a lone
+// wavefront 1.6 to 3.8 us, a segment more to merge about 0.2 us in the finish kernel: pass + finish at one request of
+// 2100 tokens 12.4 + 20.4 us with 1 tile, 12.0 + 15.5 with 2, 16.2 + 13.8 with 4, 23.3 + 12.4 with 8; 24 requests of 5 to
+// 3000 tokens 14.3 + 20.4, 15.9 + 15.8, 23.8 + 13.8, 40.5 + 12.6.
+constexpr int kMinTiles = 2;
+__device__ __forceinline__ int ranges_used(const RangeWs& ws, int total) { return max(1, min(ws.n_ranges, total / kMinTiles)); }
+
 // first unit of range w, and the range a unit falls in
 __device__ __forceinline__ int range_begin(int w, int total, int n) { return static_cast<int>(static_cast<int64_t>(w) * total / n); }
 __device__ __forceinline__ int range_of(int unit, int total, int n) {
@@ -377,9 +384,10 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
   if (ws.plan_in_wave) {                       // the same for the whole grid
     const WavePlan p = wave_plan(kv, lane);
     publish_plan(kv, ws, p, w, lane);
-    c.unit = range_begin(c.w, p.total, ws.n_ranges);
-    c.end = range_begin(c.w + 1, p.total, ws.n_ranges);
-    c.live = c.unit < c.end;
+    const int n = ranges_used(ws, p.total);
+    c.unit = range_begin(c.w, p.total, n);
+    c.end = range_begin(c.w + 1, p.total, n);
+    c.live = c.w < n;
     if (!c.live) return c;
     int upto = 0;                              // requests that begin at or before the unit
 #pragma unroll
@@ -392,9 +400,10 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
     first_unit = plan_get(p.first, sg.b);
   } else {
     const int total = ws.ctrl[0];
-    c.unit = range_begin(c.w, total, ws.n_ranges);
-    c.end = range_begin(c.w + 1, total, ws.n_ranges);
-    c.live = c.unit < c.end;
+    const int n = ranges_used(ws, total);
+    c.unit = range_begin(c.w, total, n);
+    c.end = range_begin(c.w + 1, total, n);
+    c.live = c.w < n;
     if (!c.live) return c;
     sg.b = find_request(ws, kv.batch, c.unit, lane);
     sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
@@ -587,13 +596,12 @@ __global__ __launch_bounds__(256) void verify_lse_combine_range(KvView kv, int n
   const int rq = request_of(kv, b);
   const int tiles = tiles_of_len(kv.seq_lens[rq]);
   const int u0 = ws.ureq[b] + g * tiles;
-  const int w0 = range_of(u0, total, ws.n_ranges), w1 = range_of(u0 + tiles - 1, total, ws.n_ranges);
+  const int n_used = ranges_used(ws, total);
+  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
   const float* pm = ws.part_m + static_cast<int64_t>(pair + w0) * rows + row;
   const float* pl = ws.part_l + static_cast<int64_t>(pair + w0) * rows + row;
   float m = -INFINITY, l = 0.f;
   for (int c = 0; c <= w1 - w0; ++c) {
-    // with fewer units than ranges some ranges are empty and own no segment
-    if (range_begin(w0 + c, total, ws.n_ranges) == range_begin(w0 + c + 1, total, ws.n_ranges)) continue;
     const float mc = pm[static_cast<int64_t>(c) * rows], lc = pl[static_cast<int64_t>(c) * rows];
     const float mn = fmaxf(m, mc);
     const float mu = (mn == -INFINITY) ? 0.f : mn;
@@ -758,16 +766,15 @@ __global__ __launch_bounds__(256) void verify_o_merge_range(KvView kv, int n_q, 
   const int rq = request_of(kv, b);
   const int tiles = tiles_of_len(kv.seq_lens[rq]);
   const int u0 = ws.ureq[b] + g * tiles;
-  const int w0 = range_of(u0, total, ws.n_ranges), w1 = range_of(u0 + tiles - 1, total, ws.n_ranges);
+  const int n_used = ranges_used(ws, total);
+  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
   if (w1 == w0) return;
   for (int idx = threadIdx.x; idx < R * (kHeadDim / 4); idx += 256) {
     const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-    for (int w = w0; w <= w1; ++w) {
-      if (range_begin(w, total, ws.n_ranges) == range_begin(w + 1, total, ws.n_ranges)) continue;   // empty range
+    for (int w = w0; w <= w1; ++w)
       acc += *reinterpret_cast<const f32x4*>(ws.part_o + (static_cast<int64_t>(pair + w) * R + r) * kHeadDim + 4 * d4);
-    }
     const int i = r / G, hg = r - i * G;
     uint16_t* dst = out + ((static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg) * kHeadDim;
     u32x2 pk;
@@ -1411,7 +1418,8 @@ __global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, Ran
   constexpr int rows = RB * 16;
   const int total = ws.ctrl[0];
   const int u0 = ws.ureq[b] + g * tiles;
-  const int w0 = range_of(u0, total, ws.n_ranges), w1 = range_of(u0 + tiles - 1, total, ws.n_ranges);
+  const int n_used = ranges_used(ws, total);
+  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
   const int my_chunk = SPLIT ? static_cast<int>(blockIdx.y) : 0;
   if (SPLIT && my_chunk * kChunk >= L) return;          // this pair has fewer chunks (uniform over the workgroup)
   const bool lead = my_chunk == 0;                       // the workgroup that writes what exists once per pair
@@ -1455,62 +1463,65 @@ __global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, Ran
   };
   if (want_scores) prime(my_chunk);                    // needs nothing of steps 1 and 2: in flight meanwhile
 
-  // 1. log-sum-exp per row (log2 domain).  Rows beyond the request's own, and rows that see no token at all,
-  // get +inf: their probabilities vanish wherever the log-sum-exp is applied.
-  // 2. O of a pair cut into several segments.  The partials of up to kSegs segments are fetched before the
-  // log-sum-exp is known (every thread owns up to kOuts pieces of 4 dims), so both waits overlap.
-  constexpr int kSegs = THREADS >= 1024 ? 2 : 5;
-  constexpr int kOuts = (RB * 16 * (kHeadDim / 4) + THREADS - 1) / THREADS;
+  // 1. log-sum-exp per row (log2 domain).  kPar threads per row take the segments in turn, so that the (m, l) of all
+  // segments leave together, and combine through LDS.  Rows beyond the request's own, and rows that see no token at
+  // all, get +inf: their probabilities vanish wherever the log-sum-exp is applied.
+  // 2. O of a pair cut into several segments.  The partials of the first kSegs segments are fetched before the
+  // log-sum-exp is known (every thread owns up to kOuts pieces of 4 dims), so both waits overlap; the weights of kPar
+  // segments at a time wait in LDS.  The workgroups that share a pair (SPLIT) share its pieces too.
+  // A loop over the segments by one thread per row was a round trip to memory per segment: one request of 2100 tokens
+  // (66 segments of one tile) 96 -> 20 us, 32 of 4096 tokens (5) 25 -> 19 us, 26 of up to 8 K tokens (10) 47 -> 30 us.
+  constexpr int kPar = 512 / rows;                       // (the same for every THREADS: the order of the sums is, too)
+  constexpr int kSegs = THREADS >= 1024 ? 4 : 5;
+  constexpr int kOuts = (rows * (kHeadDim / 4) + THREADS - 1) / THREADS;
+  static_assert(2 * kPar * rows <= kChunk, "the (m, l) of the segments wait where the scores will be");
   const int nseg = w1 - w0 + 1;
-  const bool split = w1 > w0 && lead;
-  const bool early = split && nseg <= kSegs && total >= ws.n_ranges;     // (no empty ranges when there are as many units as ranges)
+  const bool split = w1 > w0;
+  const int n_share = SPLIT ? (L + kChunk - 1) / kChunk : 1;             // workgroups of this pair
+  const int pieces = Rb * (kHeadDim / 4);
+  const int my_first = my_chunk * pieces / n_share, my_end = (my_chunk + 1) * pieces / n_share;
   f32x4 po[kOuts][kSegs];
-  float pm[kOuts][kSegs];
-  if (early) {
+  if (split) {
 #pragma unroll
     for (int o = 0; o < kOuts; ++o) {
-      const int idx = threadIdx.x + o * THREADS;
-      const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
+      const int idx = my_first + static_cast<int>(threadIdx.x) + o * THREADS;
 #pragma unroll
       for (int sg = 0; sg < kSegs; ++sg) {
         po[o][sg] = f32x4{0.f, 0.f, 0.f, 0.f};
-        pm[o][sg] = -INFINITY;
-        if (r < Rb && sg < nseg) {
-          po[o][sg] = *reinterpret_cast<const f32x4*>(ws.part_o + (static_cast<int64_t>(pair + w0 + sg) * R + r) * kHeadDim + 4 * d4);
-          pm[o][sg] = ws.part_m[static_cast<int64_t>(pair + w0 + sg) * rows + r];
-        }
+        if (idx < my_end && sg < nseg)
+          po[o][sg] = *reinterpret_cast<const f32x4*>(ws.part_o + static_cast<int64_t>(pair + w0 + sg) * R * kHeadDim + 4 * idx);
       }
     }
   }
+  float* s_m = s_scores;                                 // [kPar][rows] maximum, then weight, of a segment's rows
+  float* s_l = s_scores + kPar * rows;
+  const int my_row = static_cast<int>(threadIdx.x) % rows, my_sg = static_cast<int>(threadIdx.x) / rows;
+  const bool merging = my_sg < kPar;
+  float m_seg = -INFINITY;                               // of this thread's first segment
+  {
+    float m = -INFINITY, l = 0.f;
+    if (merging) {
+      for (int sg = my_sg; sg < nseg; sg += kPar) {
+        const float mc = ws.part_m[static_cast<int64_t>(pair + w0 + sg) * rows + my_row];
+        const float lc = ws.part_l[static_cast<int64_t>(pair + w0 + sg) * rows + my_row];
+        if (sg == my_sg) m_seg = mc;
+        const float mn = fmaxf(m, mc);
+        const float mu = (mn == -INFINITY) ? 0.f : mn;
+        l = l * fast_exp2(m - mu) + lc * fast_exp2(mc - mu);
+        m = mn;
+      }
+      s_m[threadIdx.x] = m;
+      s_l[threadIdx.x] = l;
+    }
+  }
+  __syncthreads();
   if (threadIdx.x < rows) {
     const int row = threadIdx.x;
+    const int live_sg = min(nseg, kPar);
     float m = -INFINITY, l = 0.f;
-    auto add = [&](float mc, float lc) {
-      const float mn = fmaxf(m, mc);
-      const float mu = (mn == -INFINITY) ? 0.f : mn;
-      l = l * fast_exp2(m - mu) + lc * fast_exp2(mc - mu);
-      m = mn;
-    };
-    if (nseg <= kSegs && total >= ws.n_ranges) {       // all segments exist: their (m, l) leave together
-      float mc[kSegs], lc[kSegs];
-#pragma unroll
-      for (int sg = 0; sg < kSegs; ++sg) {
-        mc[sg] = -INFINITY;
-        lc[sg] = 0.f;
-        if (sg < nseg) {
-          mc[sg] = ws.part_m[static_cast<int64_t>(pair + w0 + sg) * rows + row];
-          lc[sg] = ws.part_l[static_cast<int64_t>(pair + w0 + sg) * rows + row];
-        }
-      }
-#pragma unroll
-      for (int sg = 0; sg < kSegs; ++sg) add(mc[sg], lc[sg]);     // an absent segment adds exp2(-inf) * 0
-    } else {
-      for (int w = w0; w <= w1; ++w) {
-        // with fewer units than ranges some ranges are empty and own no segment
-        if (range_begin(w, total, ws.n_ranges) == range_begin(w + 1, total, ws.n_ranges)) continue;
-        add(ws.part_m[static_cast<int64_t>(pair + w) * rows + row], ws.part_l[static_cast<int64_t>(pair + w) * rows + row]);
-      }
-    }
+    for (int sg = 0; sg < live_sg; ++sg) m = fmaxf(m, s_m[sg * rows + row]);
+    const float mu = (m == -INFINITY) ? 0.f : m;
+    for (int sg = 0; sg < live_sg; ++sg) l += s_l[sg * rows + row] * fast_exp2(s_m[sg * rows + row] - mu);
     const bool live = row < Rb && l > 0.f;
     const float v = live ? m + log2f(l) : INFINITY;
     s_lse[row] = v;
@@ -1521,40 +1532,47 @@ __global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, Ran
   }
   __syncthreads();
   if (split) {
-    auto store_o = [&](int r, int d4, const f32x4& acc) {
+    f32x4 acc[kOuts];
+#pragma unroll
+    for (int o = 0; o < kOuts; ++o) acc[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < nseg; c0 += kPar) {            // (one turn unless a pair spans very many ranges)
+      if (c0 > 0) __syncthreads();                       // the weights of the previous turn have been read
+      if (merging && c0 + my_sg < nseg) {
+        const float m = c0 == 0 ? m_seg : ws.part_m[static_cast<int64_t>(pair + w0 + c0 + my_sg) * rows + my_row];
+        s_m[threadIdx.x] = fast_exp2(m - s_lse[my_row]);
+      }
+      __syncthreads();
+      const int n_here = min(kPar, nseg - c0);
+#pragma unroll
+      for (int o = 0; o < kOuts; ++o) {
+        const int idx = my_first + static_cast<int>(threadIdx.x) + o * THREADS;
+        if (idx >= my_end) continue;
+        const float* wgt = s_m + idx / (kHeadDim / 4);
+        const float* src = ws.part_o + static_cast<int64_t>(pair + w0 + c0) * R * kHeadDim + 4 * idx;
+        int sg = 0;
+        if (c0 == 0) {
+#pragma unroll
+          for (int j = 0; j < kSegs; ++j)
+            if (j < n_here) acc[o] += po[o][j] * wgt[j * rows];
+          sg = kSegs;
+        }
+#pragma unroll 4
+        for (; sg < n_here; ++sg) acc[o] += *reinterpret_cast<const f32x4*>(src + static_cast<int64_t>(sg) * R * kHeadDim) * wgt[sg * rows];
+      }
+    }
+#pragma unroll
+    for (int o = 0; o < kOuts; ++o) {
+      const int idx = my_first + static_cast<int>(threadIdx.x) + o * THREADS;
+      if (idx >= my_end) continue;
+      const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
       const int i = r / G, hg = r - i * G;
       uint16_t* dst = out + ((static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg) * kHeadDim;
       u32x2 pk;
-      pk.x = pack2(acc.x, acc.y);
-      pk.y = pack2(acc.z, acc.w);
+      pk.x = pack2(acc[o].x, acc[o].y);
+      pk.y = pack2(acc[o].z, acc[o].w);
       *reinterpret_cast<u32x2*>(dst + 4 * d4) = pk;
-    };
-    if (early) {
-#pragma unroll
-      for (int o = 0; o < kOuts; ++o) {
-        const int idx = threadIdx.x + o * THREADS;
-        const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
-        if (r < Rb) {
-          const float lse = s_lse[r];
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int sg = 0; sg < kSegs; ++sg) acc += po[o][sg] * fast_exp2(pm[o][sg] - lse);   // absent segments: exp2(-inf) = 0
-          store_o(r, d4, acc);
-        }
-      }
-    } else {
-      for (int idx = threadIdx.x; idx < Rb * (kHeadDim / 4); idx += THREADS) {
-        const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
-        const float lse = s_lse[r];
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int w = w0; w <= w1; ++w) {
-          if (range_begin(w, total, ws.n_ranges) == range_begin(w + 1, total, ws.n_ranges)) continue;   // empty range
-          const float f = fast_exp2(ws.part_m[static_cast<int64_t>(pair + w) * rows + r] - lse);
-          acc += *reinterpret_cast<const f32x4*>(ws.part_o + (static_cast<int64_t>(pair + w) * R + r) * kHeadDim + 4 * d4) * f;
-        }
-        store_o(r, d4, acc);
-      }
     }
+    __syncthreads();                                     // the scores take the place of the weights
   }
   if (!want_scores) return;
 

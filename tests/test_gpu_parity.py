@@ -292,6 +292,16 @@ def test_verify_select_reduced_configs():
         _same_as_two_calls(gen.make_workload(cfg, batch=batch), f"fused select config{cfg}[:{batch}]")
 
 
+@pytest.mark.parametrize("k,segments", [(2, 32), (4, 16), (8, 10), (15, 8)])
+def test_many_segments_per_pair(k, segments):
+    """Small batches are cut into ranges of two tiles, so a pair of 64 n tokens has about n segments: one less than, as
+    many as, one more than and several times the number the finish kernel merges per turn (1 to 4 row blocks); and rows
+    beyond 8192 tokens, whose segments several workgroups merge piece by piece."""
+    lens = [64 * (segments - 1), 64 * segments, 64 * (segments + 1), 64 * 3 * segments + 5, 17]
+    _same_as_two_calls(small(180 + k, B=5, Hq=4, Hkv=1, spec_k=k, seq_lens=lens, budgets=[64, 64, 64, 200, 5]), f"{segments} segments")
+    _same_as_two_calls(small(190 + k, B=2, Hq=8, Hkv=2, spec_k=k, seq_lens=[17000, 8200], budgets=[300, 64]), "segments of long rows")
+
+
 # -------------------------------------------- index lists from other sources ----
 def test_window_and_tail_lists_match_the_oracle_and_feed_the_draft():
     """Static sink + window lists and the post-verification tail: integer-exact against the oracle,
