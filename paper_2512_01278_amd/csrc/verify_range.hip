@@ -10,10 +10,11 @@
 //                     flash-decoding way (running max and sum per row, one
 //                     unnormalised (m, l, O) partial per segment); the
 //                     exponentials e = exp2(s - m_tile) are left behind as
-//                     16-bit values (verify_flash_range; verify_flash_pair
-//                     with two wavefronts per range for more than 32 rows;
-//                     mixed_flash_span with the draft step of other requests
-//                     in the same grid, paper Section 4.2)
+//                     16-bit values (verify_flash_team with four wavefronts
+//                     per range, up to 32 rows, 48 with fp8;
+//                     verify_flash_pair with two for more; mixed_flash_team
+//                     and mixed_flash_pair with the draft step of other
+//                     requests in the same grid, paper Section 4.2)
 //   finish            per (request, KV head), one launch (verify_finish):
 //                     log-sum-exp per row from the segments, O of pairs cut
 //                     into several segments, scores = mean over rows of
@@ -32,8 +33,8 @@
 //
 // Work division.  The unit of work is a tile of 32 tokens of one (request, KV
 // head) pair; all units are laid out pair-major (request, head, tile) and the
-// T units are cut into N equal contiguous ranges, one per wavefront, N being
-// the number of wavefronts the chip holds at once.  Every wavefront therefore
+// T units are cut into N equal contiguous ranges, one per workgroup, N being
+// the number of workgroups the chip holds at once.  Every workgroup therefore
 // streams the same number of bytes and the grid drains all at once; a fixed
 // slice size instead leaves the last round of workgroups on a half-empty chip
 // (measured: a third of the pass-2 time at batch 128).  A range crosses pair
@@ -43,6 +44,8 @@
 // The plan (unit prefix per request, order of the pairs for the finish kernel)
 // is a small kernel of its own (range_plan), or, for the single pass with up to
 // 1024 requests, worked out by the wavefronts of the pass themselves (wave_plan).
+#include <type_traits>
+
 #include "launch.hpp"
 #include "mfma_tile.hpp"
 #include "topk_core.hpp"
@@ -81,7 +84,7 @@ __device__ __forceinline__ int queries_of(const KvView& kv, const RangeWs& ws, i
   return ws.spec_lens ? min(ws.spec_lens[request_of(kv, b)] + 1, n_q) : n_q;
 }
 
-// Ranges in use: all that the chip holds at once, but none shorter than kMinTiles tiles.  A tile costs a lone
+// Ranges in use: all that the chip holds at once, but none shorter than kMinTiles.  A tile costs a lone
 // wavefront 1.6 to 3.8 us, a segment more to merge about 0.2 us in the finish kernel: pass + finish at one request of
 // 2100 tokens 12.4 + 20.4 us with 1 tile, 12.0 + 15.5 with 2, 16.2 + 13.8 with 4, 23.3 + 12.4 with 8; 24 requests of 5 to
 // 3000 tokens 14.3 + 20.4, 15.9 + 15.8, 23.8 + 13.8, 40.5 + 12.6.
@@ -371,7 +374,8 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
   }
 }
 
-__device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& ws, int w, int lane) {
+// `publish`: this wavefront also writes its share of the plan to memory (one of those that share a range)
+__device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish = true) {
   Cursor c;
   c.w = w;
   c.sg = Segment{};
@@ -383,7 +387,7 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
   int first_unit;                              // of the request the range begins in
   if (ws.plan_in_wave) {                       // the same for the whole grid
     const WavePlan p = wave_plan(kv, lane);
-    publish_plan(kv, ws, p, w, lane);
+    if (publish) publish_plan(kv, ws, p, w, lane);
     const int n = ranges_used(ws, p.total);
     c.unit = range_begin(c.w, p.total, n);
     c.end = range_begin(c.w + 1, p.total, n);
@@ -471,32 +475,6 @@ __device__ __forceinline__ Flight issue_next(const KvView& kv, Cursor& c, const 
   fetch_scales<FP8>(kv, f);
   advance_cursor(kv, c, lane);
   return f;
-}
-
-// The same in two steps, so that the K rows of the next tile can leave as soon as the K registers are free
-// and its V rows as soon as the V registers are: issue_next_k fills the flight and leaves the cursor on the
-// tile, issue_next_v sends the V loads of that tile and steps the cursor.
-template <bool FP8>
-__device__ __forceinline__ Flight issue_next_k(const KvView& kv, Cursor& c, const LaneGeom<FP8>& geo, int lane,
-                                               u32x4 (&rk)[TileRegs<FP8>::kLoads], u32x4 (&rv)[TileRegs<FP8>::kLoads]) {
-  Flight f;
-  f.valid = c.live;
-  f.sg = c.sg;
-  f.tb = c.tile * kTileTokens;
-  f.pages[0] = f.pages[1] = 0;
-  f.ks[0] = f.ks[1] = f.vs[0] = f.vs[1] = 1.f;
-  if (!c.live) return f;
-  issue_tile<FP8, true, false>(kv, c.sg, f.tb, c.pw, geo, lane, rk, rv, f.pages);
-  fetch_scales<FP8>(kv, f);
-  return f;
-}
-template <bool FP8>
-__device__ __forceinline__ void issue_next_v(const KvView& kv, Cursor& c, const Flight& f, const LaneGeom<FP8>& geo, int lane,
-                                             u32x4 (&rk)[TileRegs<FP8>::kLoads], u32x4 (&rv)[TileRegs<FP8>::kLoads]) {
-  if (!f.valid) return;
-  int pages[2];
-  issue_tile<FP8, false, true>(kv, f.sg, f.tb, c.pw, geo, lane, rk, rv, pages);
-  advance_cursor(kv, c, lane);
 }
 
 // ---------------------------------------------------------------- pass 1 ----
@@ -817,203 +795,432 @@ __device__ __forceinline__ int stash_lane(int rb, int nblocks, int nv, int n, in
   return rb < nblocks - 1 ? rb * 64 + lane : (n < nv ? (nblocks - 1) * 64 + g4 * nv + n : -1);
 }
 
-// Range w of the single pass, by one wavefront (lane = its lane index) with its own LDS: a tile buffer of
-// kVTileBytes and (RB * 16 + 1) query rows of kKRow bytes.
-template <int RB, bool FP8, bool STASH>
-__device__ __forceinline__ void flash_range_body(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
-                                                 uint8_t* s_tile, uint8_t* s_q, int w, int lane) {
-  static_assert(RB <= 2, "3 and 4 row blocks run verify_flash_pair");
-  constexpr int DEPTH = 1;                     // tiles in flight (two wavefronts share a SIMD's registers: no room for more)
+// What a wavefront of the single pass carries from tile to tile of one pair.
+template <int RB> struct FlashRows {
+  float m[RB], l[RB];    // running maximum of the lane's row of each block; this lane group's share of the running sum
+  f32x4 o[RB][8];        // unnormalised output
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      m[rb] = -INFINITY;
+      l[rb] = 0.f;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) o[rb][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+};
+
+// Shapes of the query rows of one KV head, the same for a whole launch (R, nv, tile_lanes) or for one request (nq_b, Rb).
+struct RowGeom {
+  int n_q, G, R;         // query slots, heads per KV head, rows
+  int nv, tile_lanes;    // rows of the last block; lanes that stash a tile
+  int nq_b, Rb;          // query positions and rows of the request
+};
+
+__device__ __forceinline__ RowGeom row_geom(const KvView& kv, int n_q, int row_blocks) {
+  RowGeom r;
+  r.n_q = n_q;
+  r.G = kv.num_q_heads / kv.num_kv_heads;
+  r.R = n_q * r.G;
+  r.nv = r.R - 16 * (row_blocks - 1);
+  r.tile_lanes = (row_blocks - 1) * 64 + 4 * r.nv;
+  r.nq_b = n_q;
+  r.Rb = r.R;
+  return r;
+}
+
+// Q rows of a pair -> LDS by THREADS threads, in K-tile layout (row R is the zero row of the padding)
+template <int RB, int THREADS>
+__device__ __forceinline__ void q_to_lds(const KvView& kv, const uint16_t* q, const RowGeom& rg, int rq, int g, uint8_t* s_q, int tid) {
+  constexpr int kQIters = ((RB * 16 + 1) * 16 + THREADS - 1) / THREADS;
+  u32x4 qtmp[kQIters];
+#pragma unroll
+  for (int j = 0; j < kQIters; ++j) {
+    const int ch = tid + THREADS * j;
+    const int r = ch >> 4, c = ch & 15;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (r < rg.Rb) {
+      const int i = r / rg.G, hg = r - i * rg.G;
+      v = *reinterpret_cast<const u32x4*>(q + ((static_cast<int64_t>(rq) * rg.n_q + i) * kv.num_q_heads + g * rg.G + hg) * kHeadDim + 8 * c);
+    }
+    qtmp[j] = v;
+  }
+#pragma unroll
+  for (int j = 0; j < kQIters; ++j) {
+    const int ch = tid + THREADS * j;
+    if (ch < (rg.R + 1) * 16) *reinterpret_cast<u32x4*>(s_q + k_lds_addr(ch >> 4, ch & 15)) = qtmp[j];
+  }
+}
+
+// ------------------------------------------ stream of one stretch ----------
+// The tiles of one stretch of one pair, for one wavefront, with as little per tile as possible: the byte offset of a page
+// (and, for fp8, its scales) is worked out for 64 pages at a time, a page per lane, and read from its lane.
+template <bool FP8> struct Stretch {
+  int rq, g, L, last_page;
+  int tile;                // next tile to send for
+  int win, next;           // window of 64 pages that lane j holds page j of; page ids of the following window
+  uint32_t lo, hi;         // byte offset of the page and head in the pools
+  float ks, vs;            // its scales
+};
+template <bool FP8> struct StretchTile {
+  TileRegs<FP8> rows;
+  uint64_t base[2];        // byte offsets of the two 16-token groups in the pools
+  float ks[2], vs[2];
+};
+
+template <bool FP8>
+__device__ __forceinline__ int stretch_ids(const KvView& kv, const Stretch<FP8>& c, int win, int lane) {
+  return kv.block_table[static_cast<int64_t>(c.rq) * kv.block_table_stride + min(win * kWindowPages + lane, c.last_page)];
+}
+template <bool FP8>
+__device__ __forceinline__ void stretch_window(const KvView& kv, Stretch<FP8>& c, int ids) {
+  const int64_t off = (static_cast<int64_t>(ids) * kv.stride_page + static_cast<int64_t>(c.g) * kv.stride_head) * (FP8 ? 1 : 2);
+  c.lo = static_cast<uint32_t>(off);
+  c.hi = static_cast<uint32_t>(off >> 32);
+  if constexpr (FP8) {
+    c.ks = kv.k_scale[static_cast<int64_t>(ids) * kv.num_kv_heads + c.g];
+    c.vs = kv.v_scale[static_cast<int64_t>(ids) * kv.num_kv_heads + c.g];
+  }
+}
+template <bool FP8>
+__device__ __forceinline__ Stretch<FP8> open_stretch(const KvView& kv, int rq, int g, int L, int t0, int lane) {
+  Stretch<FP8> c;
+  c.rq = rq;
+  c.g = g;
+  c.L = L;
+  c.last_page = (L - 1) >> kv.page_shift;
+  c.tile = t0;
+  c.win = ((t0 * kTileTokens) >> kv.page_shift) / kWindowPages;
+  c.ks = c.vs = 1.f;
+  const int ids = stretch_ids(kv, c, c.win, lane);
+  c.next = stretch_ids(kv, c, c.win + 1, lane);
+  stretch_window(kv, c, ids);
+  return c;
+}
+
+// sends for the K rows of the next tile / for the V rows of the same tile
+template <bool FP8>
+__device__ __forceinline__ void stretch_k(const KvView& kv, Stretch<FP8>& c, StretchTile<FP8>& t, const LaneGeom<FP8>& geo, int lane) {
+  constexpr int kPerGroup = TileRegs<FP8>::kLoads / 2;
+  const int tb = c.tile * kTileTokens;
+  // both groups of a tile lie in one window: pages hold >= 16 tokens and a tile starts at a multiple of 32
+  if (min(tb >> kv.page_shift, c.last_page) / kWindowPages > c.win) {
+    c.win += 1;
+    stretch_window(kv, c, c.next);
+    c.next = stretch_ids(kv, c, c.win + 1, lane);
+  }
+#pragma unroll
+  for (int grp = 0; grp < 2; ++grp) {
+    const int tok0 = tb + 16 * grp;
+    // groups beyond the end of the sequence read the last page of the request: pages are whole, so the rows exist
+    const int at = min(tok0 >> kv.page_shift, c.last_page) - c.win * kWindowPages;
+    const uint64_t page = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c.hi), at))) << 32) |
+                          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c.lo), at));
+    t.base[grp] = page + static_cast<uint32_t>((tok0 & (kv.page_size - 1)) * static_cast<int>(kv.stride_slot) * (FP8 ? 1 : 2));
+    if constexpr (FP8) {
+      t.ks[grp] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c.ks), at));
+      t.vs[grp] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c.vs), at));
+    } else {
+      t.ks[grp] = t.vs[grp] = 1.f;
+    }
+    const char* src = static_cast<const char*>(kv.k_pool) + t.base[grp];
+#pragma unroll
+    for (int u = 0; u < kPerGroup; ++u)
+      t.rows.k[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + geo.lane_off + u * geo.row_step));
+  }
+}
+template <bool FP8>
+__device__ __forceinline__ void stretch_v(const KvView& kv, Stretch<FP8>& c, StretchTile<FP8>& t, const LaneGeom<FP8>& geo) {
+  constexpr int kPerGroup = TileRegs<FP8>::kLoads / 2;
+#pragma unroll
+  for (int grp = 0; grp < 2; ++grp) {
+    const char* src = static_cast<const char*>(kv.v_pool) + t.base[grp];
+#pragma unroll
+    for (int u = 0; u < kPerGroup; ++u)
+      t.rows.v[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + geo.lane_off + u * geo.row_step));
+  }
+  c.tile += 1;
+}
+
+// K rows of a tile in LDS.  bf16: the padded rows of mfma_tile.hpp.  fp8 stays fp8 (half the LDS traffic; it is widened on the
+// way into the matrix cores): rows of 128 bytes, 16-byte chunk c of row r at place c ^ (r / 2 % 8), so that two rows written
+// and 16 rows read at one chunk both cover all banks.
+template <bool FP8>
+__device__ __forceinline__ void stretch_park_k(const u32x4 (&rk)[TileRegs<FP8>::kLoads], uint8_t* tile, int lane) {
+  if constexpr (FP8) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = 8 * u + (lane >> 3);
+      *reinterpret_cast<u32x4*>(tile + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4)) = rk[u];
+    }
+  } else {
+    rows_to_lds<false, false>(rk, tile, lane);
+  }
+}
+
+// S^T of the tile, Q rows from LDS too (row R is the zero row that padded rows read).  The contraction over the head
+// dimension may run in any order as long as Q follows: step s takes dims 32 s + 8 g4 .. + 7 of bf16 rows, and half s % 2 of
+// the 16 dims 64 (s / 2) + 16 g4 .. of fp8 rows, which one read brings for two steps.
+template <int RB, bool FP8>
+__device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s_q, int R, f32x4 (&acc)[2][RB], int lane) {
   const int n = lane & 15, g4 = lane >> 4;
-  const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int R = n_q * G;
-  const int nv = R - 16 * (RB - 1);
-  const int tile_lanes = (RB - 1) * 64 + 4 * nv;
-  const float c2 = kv.sm_scale * kLog2e;
-  const LaneGeom<FP8> geo = lane_geom<FP8>(kv, lane);
-  constexpr int kLoads = TileRegs<FP8>::kLoads;
-  constexpr int kQIters = ((RB * 16 + 1) * 16 + kThreads - 1) / kThreads;
-  Cursor cur = open_cursor(kv, ws, w, lane);
-  if (!cur.live) return;
-  int unit = cur.unit;                         // global index of the tile being computed
-  u32x4 rk[DEPTH][kLoads], rv[DEPTH][kLoads];
-  Flight fl[DEPTH];
+  int qrow[RB];
 #pragma unroll
-  for (int j = 0; j < DEPTH; ++j) fl[j] = issue_next<FP8, true>(kv, cur, geo, lane, rk[j], rv[j]);
-  Segment cs = fl[0].sg;
-  bool started = false;
-  float m_run[RB], l_run[RB];
-  f32x4 o[RB][8];
-  int nq_b = n_q, Rb = R;                      // query positions and rows of the current pair's request
-  auto finish = [&]() {
-    const bool whole = cs.tile0 == 0 && cs.tile1 == cs.tiles;
+  for (int rb = 0; rb < RB; ++rb) qrow[rb] = min(16 * rb + n, R);
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      float l = l_run[rb];
-      l = sum_over_groups(l);
-      const int r = 16 * rb + n;
-      if (g4 == 0) {
-        ws.part_m[static_cast<int64_t>(cs.slot) * (RB * 16) + r] = m_run[rb];
-        ws.part_l[static_cast<int64_t>(cs.slot) * (RB * 16) + r] = l;
-      }
-      if (r >= Rb) continue;               // rows of query slots the request does not use are left alone
-      if (whole) {
-        const float inv = l > 0.f ? 1.0f / l : 0.f;       // a row that sees no token: zeros
-        const int i = r / G, hg = r - i * G;
-        uint16_t* dst = out + ((static_cast<int64_t>(cs.rq) * n_q + i) * kv.num_q_heads + cs.g * G + hg) * kHeadDim;
+  for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-        for (int db = 0; db < 8; ++db) {
-          u32x2 pk;
-          pk.x = pack2(o[rb][db][0] * inv, o[rb][db][1] * inv);
-          pk.y = pack2(o[rb][db][2] * inv, o[rb][db][3] * inv);
-          *reinterpret_cast<u32x2*>(dst + 16 * db + 4 * g4) = pk;
-        }
-      } else {
-        float* dst = ws.part_o + (static_cast<int64_t>(cs.slot) * R + r) * kHeadDim + 4 * g4;
+    for (int rb = 0; rb < RB; ++rb) acc[sub][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto q_of = [&](int s, bf16x8 (&b)[RB]) {
+    const int chunk = FP8 ? 8 * (s >> 1) + 2 * g4 + (s & 1) : 4 * s + g4;
 #pragma unroll
-        for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = o[rb][db];
-      }
-    }
+    for (int rb = 0; rb < RB; ++rb) b[rb] = as_bf16x8(*reinterpret_cast<const u32x4*>(s_q + k_lds_addr(qrow[rb], chunk)));
   };
-  auto tile = [&](Flight& f, u32x4 (&rk)[kLoads], u32x4 (&rv)[kLoads]) {
-    if (!started || f.sg.slot != cs.slot) {    // wave-uniform: the stream has entered another pair
-      if (started) finish();
-      cs = f.sg;
-      started = true;
-      nq_b = __builtin_amdgcn_readfirstlane(queries_of(kv, ws, cs.b, n_q));
-      Rb = nq_b * G;
-      {                                        // Q rows of the pair -> LDS (row R is the zero row of the padding)
-        u32x4 qtmp[kQIters];
+  auto k_of = [&](int s, u32x4 (&k)[2]) {                    // of the two 16-token groups
 #pragma unroll
-        for (int j = 0; j < kQIters; ++j) {
-          const int ch = lane + kThreads * j;
-          const int r = ch >> 4, c = ch & 15;
-          u32x4 v = {0u, 0u, 0u, 0u};
-          if (r < Rb) {
-            const int i = r / G, hg = r - i * G;
-            v = *reinterpret_cast<const u32x4*>(q + ((static_cast<int64_t>(cs.rq) * n_q + i) * kv.num_q_heads + cs.g * G + hg) * kHeadDim + 8 * c);
-          }
-          qtmp[j] = v;
-        }
+    for (int sub = 0; sub < 2; ++sub)
+      k[sub] = FP8 ? *reinterpret_cast<const u32x4*>(tile + (16 * sub + n) * 128 + (((4 * (s >> 1) + g4) ^ ((n >> 1) & 7)) << 4))
+                   : *reinterpret_cast<const u32x4*>(tile + k_lds_addr(16 * sub + n, 4 * s + g4));
+  };
+  u32x4 k[2];
 #pragma unroll
-        for (int j = 0; j < kQIters; ++j) {
-          const int ch = lane + kThreads * j;
-          if (ch < (R + 1) * 16) *reinterpret_cast<u32x4*>(s_q + k_lds_addr(ch >> 4, ch & 15)) = qtmp[j];
-        }
-      }
+  for (int s = 0; s < 4; ++s) {
+    if (!FP8 || s % 2 == 0) k_of(s, k);
+    bf16x8 a[2], b[RB];
+    q_of(s, b);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        m_run[rb] = -INFINITY;
-        l_run[rb] = 0.f;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) o[rb][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int sub = 0; sub < 2; ++sub) {
+      if constexpr (FP8) {
+        const u32x4& raw = k[sub];
+        const uint32_t x = (s & 1) ? raw.z : raw.x, y = (s & 1) ? raw.w : raw.y;
+        u32x4 w;
+        w.x = fp8x2_to_bf16x2(x, false); w.y = fp8x2_to_bf16x2(x, true);
+        w.z = fp8x2_to_bf16x2(y, false); w.w = fp8x2_to_bf16x2(y, true);
+        a[sub] = as_bf16x8(w);
+      } else {
+        a[sub] = as_bf16x8(k[sub]);
       }
     }
-    const int tb = f.tb;
-    rows_to_lds<FP8, false>(rk, s_tile, lane);
-    const float ks[2] = {f.ks[0], f.ks[1]}, vs[2] = {f.vs[0], f.vs[1]};
-    f = issue_next_k<FP8>(kv, cur, geo, lane, rk, rv);       // the K registers are free: next tile's K rows leave now
-    f32x4 s[2][RB];
-    tile_qk_ldsq<RB>(s_tile, s_q, R, s, lane);
-    if (tb + kTileTokens > cs.L) zero_tail_rows<FP8>(rv, tb, cs.L, geo);
-    rows_to_lds<FP8, true>(rv, s_tile, lane);
-    issue_next_v<FP8>(kv, cur, f, geo, lane, rk, rv);        // and its V rows once the V registers are
-    const bool edge = tb + kTileTokens > cs.L - n_q;
-    bf16x8 p[RB];
-    uint8_t* st_base = ws.stash + static_cast<int64_t>(unit) * tile_lanes * 16;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      // logits stay unscaled until the exponential: the scales are positive, so the maximum commutes with them
-      f32x4 pr[2] = {s[0][rb], s[1][rb]};
-      if (edge) {
-        const int r = 16 * rb + n;
-        const int last = cs.L - nq_b + (r < Rb ? r / G : nq_b - 1);
+      acc[0][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[rb], acc[0][rb], 0, 0, 0);
+      acc[1][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[rb], acc[1][rb], 0, 0, 0);
+    }
+    if (RB > 1) __builtin_amdgcn_sched_barrier(0);           // keeps the operand reads from piling up in registers
+  }
+}
+
+// One tile of the single pass without a stash.  Nothing crosses lanes unless a logit exceeds its row's running maximum.  With
+// fp8 the maximum may lag by up to 2^kSlack, which after the first tiles spares the rescaling (exponentials up to 2^kSlack
+// keep their relative precision, and their product with the page scale is rounded to bf16 anyway); with bf16 it may not: the
+// probability 1 of a row's largest logit is exact.
+// LAST: the last tile of the stretch, after which nothing is sent for, and the only one that may reach past the sequence.
+// (A branch around the loads instead makes the compiler wait for all of them where it needs the first.)
+template <int RB, bool FP8, bool STASH, bool LAST>
+__device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, StretchTile<FP8>& t, const LaneGeom<FP8>& geo, const RowGeom& rg,
+                                             int tb, float c2, FlashRows<RB>& st, uint8_t* s_tile, const uint8_t* s_q, uint8_t* stash, float* m_ref, int lane) {
+  constexpr float kSlack = FP8 && !STASH ? 8.f : 0.f;
+  const int n = lane & 15, g4 = lane >> 4;
+  f32x4 s[2][RB];
+  stretch_park_k<FP8>(t.rows.k, s_tile, lane);
+  const float sc[2] = {c2 * t.ks[0], c2 * t.ks[1]}, vs[2] = {t.vs[0], t.vs[1]};
+  if constexpr (!LAST) stretch_k<FP8>(kv, c, t, geo, lane);        // the K registers are free: next tile's K rows leave now
+  stretch_qk<RB, FP8>(s_tile, s_q, rg.R, s, lane);
+  if constexpr (LAST) {
+    if (tb + kTileTokens > c.L) zero_tail_rows<FP8>(t.rows.v, tb, c.L, geo);
+  }
+  rows_to_lds<FP8, true>(t.rows.v, s_tile, lane);
+  if constexpr (!LAST) stretch_v<FP8>(kv, c, t, geo);              // and its V rows once the V registers are
+  if (tb + kTileTokens > c.L - rg.n_q) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (tb + 16 * sub + 4 * g4 + i > last) pr[sub][i] = -INFINITY;
-      }
-      const float sc0 = c2 * ks[0], sc1 = c2 * ks[1];
-      float mx = fmaxf(fmaxf(fmaxf(pr[0][0], pr[0][1]), fmaxf(pr[0][2], pr[0][3])) * sc0,
-                       fmaxf(fmaxf(pr[1][0], pr[1][1]), fmaxf(pr[1][2], pr[1][3])) * sc1);
-      mx = max_over_groups(mx);                 // the same in the four lanes of a row
-      const float m_new = fmaxf(m_run[rb], mx);
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      if (__any(m_new > m_run[rb])) {          // some row's maximum moved: rescale what is accumulated
-        const float alpha = fast_exp2(m_run[rb] - m_use);
-        l_run[rb] *= alpha;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) o[rb][d] *= alpha;
-      }
-      m_run[rb] = m_new;
-      float sum = 0.f;
+    for (int rb = 0; rb < RB; ++rb) {
+      const int r = 16 * rb + n;
+      const int last = c.L - rg.nq_b + (r < rg.Rb ? r / rg.G : rg.nq_b - 1);
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          pr[sub][i] = fast_exp2(fmaf(pr[sub][i], sub == 0 ? sc0 : sc1, -m_use));
-          sum += pr[sub][i];
-        }
-      l_run[rb] += sum;
-      // the exponentials, 24 bits each, and the maximum they refer to
-      const int sl = STASH ? stash_lane(rb, RB, nv, n, g4, lane) : -1;
-      if (sl >= 0) {
-        uint32_t c[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) c[k] = stash_encode(pr[k >> 2][k & 3]);
-        u32x4 packed;
-        packed.x = c[0] | (c[1] << 16);
-        packed.y = c[2] | (c[3] << 16);
-        packed.z = c[4] | (c[5] << 16);
-        packed.w = c[6] | (c[7] << 16);
-        *reinterpret_cast<u32x4*>(st_base + sl * 16) = packed;
-      }
-      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * rb + n] = m_use;
-      if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
-      p[rb] = pack_p(pr[0], pr[1]);
-    }
-    tile_pv<RB>(s_tile, p, o, lane);
-    unit += 1;
-  };
-  for (bool more = true; more;) {
-#pragma unroll
-    for (int j = 0; j < DEPTH; ++j) {
-      if (!fl[j].valid) { more = false; break; }     // slots are refilled in order: the first empty one ends the stream
-      tile(fl[j], rk[j], rv[j]);
+        for (int i = 0; i < 4; ++i)
+          if (tb + 16 * sub + 4 * g4 + i > last) s[sub][rb][i] = -INFINITY;
     }
   }
-  finish();
+  bf16x8 p[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    // the scales are positive, so the maximum commutes with them
+    const float mx = fmaxf(fmaxf(fmaxf(s[0][rb][0], s[0][rb][1]), fmaxf(s[0][rb][2], s[0][rb][3])) * sc[0],
+                           fmaxf(fmaxf(s[1][rb][0], s[1][rb][1]), fmaxf(s[1][rb][2], s[1][rb][3])) * sc[1]);
+    if (__any(mx > st.m[rb] + kSlack)) {
+      const float m_new = fmaxf(st.m[rb], max_over_groups(mx));
+      const float alpha = fast_exp2(st.m[rb] - (m_new == -INFINITY ? 0.f : m_new));
+      st.l[rb] *= alpha;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) st.o[rb][d] *= alpha;
+      st.m[rb] = m_new;
+    }
+    const float m_use = st.m[rb] == -INFINITY ? 0.f : st.m[rb];
+    f32x4 pr[2];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pr[sub][i] = fast_exp2(fmaf(s[sub][rb][i], sc[sub], -m_use));
+    st.l[rb] += ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
+    if constexpr (STASH) {                                   // the exponentials, 16 bits each, and the maximum they refer to
+      const int sl = stash_lane(rb, RB, rg.nv, n, g4, lane);
+      if (sl >= 0) {
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = stash_encode(pr[i >> 2][i & 3]);
+        u32x4 packed;
+        packed.x = e[0] | (e[1] << 16);
+        packed.y = e[2] | (e[3] << 16);
+        packed.z = e[4] | (e[5] << 16);
+        packed.w = e[6] | (e[7] << 16);
+        *reinterpret_cast<u32x4*>(stash + sl * 16) = packed;
+      }
+      if (g4 == 0) m_ref[16 * rb + n] = m_use;
+    }
+    if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
+    p[rb] = pack_p(pr[0], pr[1]);
+  }
+  tile_pv<RB>(s_tile, p, st.o, lane);
+}
+
+// ------------------------------------------ a range per workgroup ----------
+// Up to two row blocks (three with fp8): range w belongs to a workgroup of kTeamWaves wavefronts that share the Q rows.  Each
+// takes an equal stretch of every segment's tiles, and the segment's state is put together in LDS, so that it leaves one
+// partial.  Bound by the memory system at 128 requests of 1-8 K tokens (bf16, 20 rows: 2.29 GB of K and V in 383 us without
+// the stash, 6.0 of 6.7 TB/s; the 200 MB of stash written cost 75 us more), by its vector instructions with 40 rows and fp8
+// (258 us without, 360 with; no memory traffic at all would leave 246).  One range per wavefront, each with its own Q rows and
+// partials and a cursor that ran on across pairs without draining, spilled 22 registers, needed four times the segments
+// and waited for V where it needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish)
+// where this takes 466 + 63; 32 requests of 4096 tokens 112 + 19, now 104 + 18; without the statistic 414, now 386.
+// Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the statistic and the selection in the same
+// launch: 523 / 545 us in all at the first, but a long row then waits for one compute unit.
+constexpr int kTeamWaves = 4;                  // two such workgroups fill a compute unit (registers)
+template <int RB, int W> struct TeamLds {
+  static constexpr int kORow = kHeadDim * 4 + 16;            // a row of O on its way between wavefronts
+  static_assert(16 * kORow <= kVTileBytes, "a block of O fits a tile buffer");
+  __attribute__((aligned(16))) uint8_t tile[W * kVTileBytes];
+  __attribute__((aligned(16))) uint8_t q[(RB * 16 + 1) * kKRow];
+  float m[W * RB * 16], l[W * RB * 16];
+};
+
+template <int RB, bool FP8, int W, bool STASH>
+__device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
+                                                TeamLds<RB, W>& lds, int w) {
+  constexpr int THREADS = W * kWave, rows = RB * 16, kORow = TeamLds<RB, W>::kORow;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 15, g4 = lane >> 4;
+  RowGeom rg = row_geom(kv, n_q, RB);
+  const float c2 = kv.sm_scale * kLog2e;
+  const LaneGeom<FP8> geo = lane_geom<FP8>(kv, lane);
+  uint8_t* s_tile = lds.tile + wave * kVTileBytes;
+  Cursor team = open_cursor(kv, ws, w, lane, wave == 0);     // the segments of the range, the same for all wavefronts
+  if (!team.live) return;
+  FlashRows<RB> st;
+  while (team.live) {
+    const Segment cs = team.sg;
+    rg.nq_b = __builtin_amdgcn_readfirstlane(queries_of(kv, ws, cs.b, n_q));
+    rg.Rb = rg.nq_b * rg.G;
+    const int nt = cs.tile1 - cs.tile0;
+    const int t0 = cs.tile0 + wave * nt / W, t1 = cs.tile0 + (wave + 1) * nt / W;
+    Stretch<FP8> cur = open_stretch<FP8>(kv, cs.rq, cs.g, cs.L, t0, lane);
+    StretchTile<FP8> tl;
+    if (t0 < t1) {
+      stretch_k<FP8>(kv, cur, tl, geo, lane);
+      stretch_v<FP8>(kv, cur, tl, geo);
+    }
+    q_to_lds<RB, THREADS>(kv, q, rg, cs.rq, cs.g, lds.q, threadIdx.x);
+    st.clear();
+    __syncthreads();
+    const int64_t u0 = team.unit - cs.tile0;                 // unit of the pair's first tile
+    auto tile = [&](int t, auto last) {
+      stretch_tile<RB, FP8, STASH, decltype(last)::value>(kv, cur, tl, geo, rg, t * kTileTokens, c2, st, s_tile, lds.q,
+                                                          ws.stash + (u0 + t) * rg.tile_lanes * 16, ws.m_ref + (u0 + t) * rows, lane);
+    };
+    for (int t = t0; t + 1 < t1; ++t) tile(t, std::false_type{});
+    if (t0 < t1) tile(t1 - 1, std::true_type{});
+    // the team's (m, l) per row
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float l = sum_over_groups(st.l[rb]);
+      if (g4 == 0) {
+        lds.m[wave * rows + 16 * rb + n] = st.m[rb];
+        lds.l[wave * rows + 16 * rb + n] = l;
+      }
+    }
+    __syncthreads();
+    const bool whole = cs.tile0 == 0 && cs.tile1 == cs.tiles;
+    float wgt[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int r = 16 * rb + n;
+      float m = -INFINITY, l = 0.f;
+#pragma unroll
+      for (int i = 0; i < W; ++i) m = fmaxf(m, lds.m[i * rows + r]);
+      const float mu = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+      for (int i = 0; i < W; ++i) l += lds.l[i * rows + r] * fast_exp2(lds.m[i * rows + r] - mu);
+      if (wave == 0 && g4 == 0) {
+        ws.part_m[static_cast<int64_t>(cs.slot) * rows + r] = m;
+        ws.part_l[static_cast<int64_t>(cs.slot) * rows + r] = l;
+      }
+      wgt[rb] = fast_exp2(st.m[rb] - mu);                    // no tile, or a row that sees no token: exp2(-inf)
+      if (whole) wgt[rb] *= l > 0.f ? 1.0f / l : 0.f;
+    }
+    // O, one block of 16 rows at a time: every wavefront leaves its weighted share in its tile buffer
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+      for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(s_tile + n * kORow + 64 * db + 16 * g4) = st.o[rb][db] * wgt[rb];
+      __syncthreads();
+      for (int idx = threadIdx.x; idx < 16 * (kHeadDim / 4); idx += THREADS) {
+        const int rr = idx / (kHeadDim / 4), d4 = idx - rr * (kHeadDim / 4), r = 16 * rb + rr;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < W; ++i) acc += *reinterpret_cast<const f32x4*>(lds.tile + i * kVTileBytes + rr * kORow + 16 * d4);
+        if (r < rg.Rb) {                                     // rows of query slots the request does not use are left alone
+          if (whole) {
+            const int i = r / rg.G, hg = r - i * rg.G;
+            u32x2 pk;
+            pk.x = pack2(acc.x, acc.y);
+            pk.y = pack2(acc.z, acc.w);
+            *reinterpret_cast<u32x2*>(out + ((static_cast<int64_t>(cs.rq) * n_q + i) * kv.num_q_heads + cs.g * rg.G + hg) * kHeadDim + 4 * d4) = pk;
+          } else {
+            *reinterpret_cast<f32x4*>(ws.part_o + (static_cast<int64_t>(cs.slot) * rg.R + r) * kHeadDim + 4 * d4) = acc;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    // on to the next segment: advance_cursor steps by one unit, so step by the rest first
+    team.unit = team.unit + nt - 1;
+    team.tile = cs.tile1 - 1;
+    advance_cursor(kv, team, lane);
+  }
 }
 
 template <int RB, bool FP8, bool STASH>
-__global__ __launch_bounds__(kThreads, 2) void verify_flash_range(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
-  __shared__ __attribute__((aligned(16))) uint8_t s_tile[kVTileBytes];
-  __shared__ __attribute__((aligned(16))) uint8_t s_q[(RB * 16 + 1) * kKRow];
-  flash_range_body<RB, FP8, STASH>(kv, q, n_q, ws, out, s_tile, s_q, blockIdx.x, threadIdx.x);
+__global__ __launch_bounds__(kTeamWaves * kWave, 2) void verify_flash_team(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
+  __shared__ TeamLds<RB, kTeamWaves> lds;
+  flash_team_body<RB, FP8, kTeamWaves, STASH>(kv, q, n_q, ws, out, lds, blockIdx.x);
 }
 
-// A unified batch in one grid (paper Section 4.2, "Fused Sparse and Full Attention"): the first n_groups
-// workgroups carry four ranges of the verification pass each (one per wavefront, as independent as in their own
-// kernel), the workgroups after them one (request, KV head, span) of the draft step each.  Which path a
-// workgroup takes is decided on the chip from its index; the draft workgroups come last in dispatch order, so
-// they fill the compute units as the ranges drain.
+// A unified batch in one grid (paper Section 4.2, "Fused Sparse and Full Attention"): the first n_ranges workgroups carry a
+// range of the verification pass each, as in their own kernel, the workgroups after them one (request, KV head, span) of
+// the draft step each.  Which path a workgroup takes is decided on the chip from its index; the draft workgroups come last
+// in dispatch order, so they fill the compute units as the ranges drain.
 template <int RB, bool FP8>
-__global__ __launch_bounds__(4 * kThreads, 2) void mixed_flash_span(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out,
-                                                                    int n_groups, DecodeArgs da, DecWs dws, int span_rows, int nspan) {
-  constexpr int kFlashLds = kVTileBytes + (RB * 16 + 1) * kKRow;        // of one wavefront of the verification pass
-  static_assert(kFlashLds % 16 == 0 && kFlashLds >= kVTileBytes, "the draft path uses the same memory as four tile buffers");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[4 * kFlashLds];
-  if (static_cast<int>(blockIdx.x) < n_groups) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), lane = threadIdx.x & (kThreads - 1);   // scalar: LDS bases stay out of the vector registers
-    const int w = blockIdx.x * 4 + wave;
-    if (w < ws.n_ranges)
-      flash_range_body<RB, FP8, true>(kv, q, n_q, ws, out, smem + wave * kFlashLds, smem + wave * kFlashLds + kVTileBytes, w, lane);
+__global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out,
+                                                                          DecodeArgs da, DecWs dws, int span_rows, int nspan) {
+  __shared__ TeamLds<RB, kTeamWaves> lds;      // its tile buffers serve the draft path too
+  if (static_cast<int>(blockIdx.x) < ws.n_ranges) {
+    flash_team_body<RB, FP8, kTeamWaves, true>(kv, q, n_q, ws, out, lds, blockIdx.x);
   } else {
-    const int i = blockIdx.x - n_groups;
+    const int i = blockIdx.x - ws.n_ranges;
     const int sp = i % nspan, pg = i / nspan;
-    decode_span_body<FP8, 4>(da, dws, span_rows, nspan, pg / da.kv.num_kv_heads, pg % da.kv.num_kv_heads, sp,
-                          reinterpret_cast<uint8_t (*)[kVTileBytes]>(smem));
+    decode_span_body<FP8, kTeamWaves>(da, dws, span_rows, nspan, pg / da.kv.num_kv_heads, pg % da.kv.num_kv_heads, sp,
+                                      reinterpret_cast<uint8_t (*)[kVTileBytes]>(lds.tile));
   }
 }
 
@@ -1121,26 +1328,6 @@ __device__ __forceinline__ void tile_qk_ldsq_at(const uint8_t* ktile, const uint
   }
 }
 
-// the same with the Q operand in registers: qf[rb][s] holds, for lane (n, g), Q[16 (RB0 + rb) + n][32 s + 8 g .. + 7]
-template <int RBW>
-__device__ __forceinline__ void tile_qk_regq(const uint8_t* ktile, const bf16x8 (&qf)[RBW][4], f32x4 (&acc)[2][RBW], int lane) {
-  const int n = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int rb = 0; rb < RBW; ++rb) acc[sub][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const bf16x8 a0 = as_bf16x8(*reinterpret_cast<const u32x4*>(ktile + k_lds_addr(n, 4 * s + g)));
-    const bf16x8 a1 = as_bf16x8(*reinterpret_cast<const u32x4*>(ktile + k_lds_addr(16 + n, 4 * s + g)));
-#pragma unroll
-    for (int rb = 0; rb < RBW; ++rb) {
-      acc[0][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, qf[rb][s], acc[0][rb], 0, 0, 0);
-      acc[1][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, qf[rb][s], acc[1][rb], 0, 0, 0);
-    }
-  }
-}
-
 // one of the two wavefronts: `half` = which 16 tokens of every tile it fetches, RB0 / RBW = its row blocks
 template <int RB, bool FP8, bool STASH, int RBW, int RB0>
 __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
@@ -1163,7 +1350,7 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
   // Half tiles in flight per wavefront: two where the registers allow it.  Three row blocks of bf16: 402 against
   // 414 us at 16 requests of 24-32 K tokens (four row blocks would spill).  fp8: the dequantisation scales of a
   // tile must then be fetched along with its rows (issue_next_half), or their load at the tile's turn keeps a
-  // round trip to memory in every tile: 394 against 415 us at 64 requests, neither change gains anything alone.
+  // round trip to memory in every tile.
   constexpr int DEPTH = (FP8 || RB == 3) ? 2 : 1;
   u32x4 rk[DEPTH][kHalf], rv[DEPTH][kHalf];
   Flight fl[DEPTH];
@@ -1174,11 +1361,6 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
   float m_run[RBW], l_run[RBW];
   f32x4 o[RBW][8];
   int nq_b = n_q, Rb = R;                      // query positions and rows of the current pair's request
-  // fp8 with three row blocks: the Q operand lives in registers (there is room, and the LDS of the two-wavefront
-  // pass is its busiest unit: 416 -> 407 us at 64 requests of 40 query rows)
-  constexpr bool kQRegs = FP8 && RB == 3;
-  [[maybe_unused]] bf16x8 qf[RBW][4];
-  [[maybe_unused]] bool q_stale = true;
   auto finish = [&]() {
     const bool whole = cs.tile0 == 0 && cs.tile1 == cs.tiles;
 #pragma unroll
@@ -1214,7 +1396,6 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
       if (started) finish();
       cs = f.sg;
       started = true;
-      q_stale = true;
       nq_b = __builtin_amdgcn_readfirstlane(queries_of(kv, ws, cs.b, n_q));
       Rb = nq_b * G;
       {                                        // Q rows of the pair -> LDS, by both wavefronts (row R is the zero row)
@@ -1249,20 +1430,7 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
     const float ks[2] = {f.ks[0], f.ks[1]}, vs[2] = {f.vs[0], f.vs[1]};
     __syncthreads();                           // the K tile (and Q) is complete
     f32x4 s[2][RBW];
-    if constexpr (kQRegs) {
-      if (q_stale) {                           // first tile of a pair: this wavefront's Q rows, once, from LDS
-#pragma unroll
-        for (int rb = 0; rb < RBW; ++rb) {
-          const int qrow = min(16 * (RB0 + rb) + n, R);
-#pragma unroll
-          for (int sx = 0; sx < 4; ++sx) qf[rb][sx] = as_bf16x8(*reinterpret_cast<const u32x4*>(s_q + k_lds_addr(qrow, 4 * sx + g4)));
-        }
-        q_stale = false;
-      }
-      tile_qk_regq<RBW>(s_tile, qf, s, lane);
-    } else {
-      tile_qk_ldsq_at<RBW>(s_tile, s_q, R, RB0, s, lane);
-    }
+    tile_qk_ldsq_at<RBW>(s_tile, s_q, R, RB0, s, lane);
     if (tb + kTileTokens > cs.L) {
 #pragma unroll
       for (int u = 0; u < kHalf; ++u)
@@ -1355,7 +1523,7 @@ __global__ __launch_bounds__(2 * kThreads, RB >= 3 ? 2 : 3) void verify_flash_pa
 template <int RB, bool FP8>
 __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out,
                                                                     DecodeArgs da, DecWs dws, int span_rows, int nspan) {
-  static_assert(RB >= 3, "up to two row blocks run mixed_flash_span");
+  static_assert(RB >= 3, "up to two row blocks run mixed_flash_team");
   constexpr int kFirst = (RB + 1) / 2;
   constexpr int kPassLds = kVTileBytes + (RB * 16 + 1) * kKRow;
   static_assert(kPassLds >= 2 * kVTileBytes, "the draft path uses the same memory as two tile buffers");
@@ -1718,6 +1886,12 @@ int ranges_for(const KvView& kv, int rb) {
   return per_cu * num_cus();
 }
 
+// ranges of the passes with a workgroup per range: as many as the chip holds at once
+int team_ranges() {
+  const int opt = options().verify_waves;
+  return std::max(1, (opt > 0 ? opt : 8) * num_cus() / kTeamWaves);
+}
+
 int row_blocks(const KvView& kv, int n_q) { return (n_q * (kv.num_q_heads / kv.num_kv_heads) + 15) / 16; }
 
 RangeWs carve(const KvView& kv, int n_q, void* workspace, size_t* total_bytes) {
@@ -1769,44 +1943,40 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     hipLaunchKernelGGL(range_plan, dim3(1), dim3(1024), 0, st, kv, ws);
   }
   if (single_pass) {
-    bool fused = false;
-    if constexpr (RB <= 2) {
-      if (draft) {                             // a unified batch: the draft step of other requests rides in the same grid
-        fused = true;
-        KernelTimer t("mixed_flash_span", st);
-        const int span_rows = decode_span_rows(draft->kv, draft->max_budget);
-        const int nspan = (draft->max_budget + span_rows - 1) / span_rows;
-        const DecWs dws = decode_carve(draft->kv, draft->max_budget, draft->workspace);
-        const int n_groups = (ws.n_ranges + 3) / 4;
-        const int n_draft = nspan * draft->kv.num_kv_heads * draft->kv.batch;
-        hipLaunchKernelGGL((mixed_flash_span<RB, FP8>), dim3(n_groups + n_draft), dim3(4 * kThreads), 0, st, kv, q, a.n_q, ws, out,
-                           n_groups, *draft, dws, span_rows, nspan);
+    const bool stats = a.scores || a.select;
+    const bool fused = draft != nullptr;       // a unified batch: the draft step of other requests rides in the same grid
+    DecWs dws{};
+    int span_rows = 0, nspan = 0, n_draft = 0;
+    if (fused) {
+      span_rows = decode_span_rows(draft->kv, draft->max_budget);
+      nspan = (draft->max_budget + span_rows - 1) / span_rows;
+      dws = decode_carve(draft->kv, draft->max_budget, draft->workspace);
+      n_draft = nspan * draft->kv.num_kv_heads * draft->kv.batch;
+    }
+    if constexpr (RB <= 2 || (FP8 && RB == 3)) {     // a range per workgroup
+      ws.n_ranges = team_ranges();
+      if (fused) {
+        KernelTimer t("mixed_flash_team", st);
+        hipLaunchKernelGGL((mixed_flash_team<RB, FP8>), dim3(ws.n_ranges + n_draft), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out,
+                           *draft, dws, span_rows, nspan);
+      } else {
+        KernelTimer t("verify_flash_team", st);
+        if (stats)
+          hipLaunchKernelGGL((verify_flash_team<RB, FP8, true>), dim3(ws.n_ranges), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out);
+        else                                   // plain multi-query decode: nothing is stashed, nothing rebuilt
+          hipLaunchKernelGGL((verify_flash_team<RB, FP8, false>), dim3(ws.n_ranges), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out);
       }
-    } else {
-      if (draft) {                             // the same with two wavefronts per range and per draft workgroup
-        fused = true;
+    } else {                                         // two wavefronts per range and per draft workgroup
+      if (fused) {
         KernelTimer t("mixed_flash_pair", st);
-        const int span_rows = decode_span_rows(draft->kv, draft->max_budget);
-        const int nspan = (draft->max_budget + span_rows - 1) / span_rows;
-        const DecWs dws = decode_carve(draft->kv, draft->max_budget, draft->workspace);
-        const int n_draft = nspan * draft->kv.num_kv_heads * draft->kv.batch;
         hipLaunchKernelGGL((mixed_flash_pair<RB, FP8>), dim3(ws.n_ranges + n_draft), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out,
                            *draft, dws, span_rows, nspan);
-      }
-    }
-    if (!fused) {
-      KernelTimer t("verify_flash_range", st);
-      const bool stash = a.scores || a.select;
-      if constexpr (RB >= 3) {                 // two wavefronts per range
-        if (stash)
-          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, true>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
-        else                                   // plain multi-query decode: nothing is stashed, nothing rebuilt
-          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, false>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
       } else {
-        if (stash)
-          hipLaunchKernelGGL((verify_flash_range<RB, FP8, true>), dim3(ws.n_ranges), dim3(kThreads), 0, st, kv, q, a.n_q, ws, out);
+        KernelTimer t("verify_flash_pair", st);
+        if (stats)
+          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, true>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
         else
-          hipLaunchKernelGGL((verify_flash_range<RB, FP8, false>), dim3(ws.n_ranges), dim3(kThreads), 0, st, kv, q, a.n_q, ws, out);
+          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, false>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
       }
     }
     int split_select = 0;                      // chunks per row when the selection is a launch of its own
