@@ -7,109 +7,110 @@
 //
 // One workgroup per (request, KV head) walks the index list in tiles of kTile
 // rows with a running (max, sum, output): the textbook online softmax.
+#include "generic_rows.hpp"
 #include "launch.hpp"
 
 namespace pillar {
 namespace {
 
-constexpr int kTile = 128;
-constexpr int kThreads = 256;
+constexpr int kTile = 128;                     // (what softmax128 takes)
+constexpr int kThreads = kGenThreads;
 constexpr int kMaxG = 16;
-constexpr int kMaxD = 128;
-constexpr int kAccPerThread = kMaxG * kMaxD / kThreads;   // 8
 
-template <int QDT, int KVDT>
+template <int QDT, int KVDT, int D>
 __global__ __launch_bounds__(kThreads) void decode_generic(DecodeArgs a) {
-  __shared__ float qs[kMaxG * kMaxD];
-  __shared__ float s[kMaxG * kTile];
+  __shared__ __attribute__((aligned(16))) float s_q[kMaxG * kGenMaxD];
+  __shared__ __attribute__((aligned(16))) float s[kMaxG * kTile];
+  __shared__ __attribute__((aligned(16))) float s_k[kPiece * kPieceStride];
   __shared__ float row_m[kMaxG], row_l[kMaxG], row_alpha[kMaxG];
-  __shared__ int32_t tok[kTile];
-  __shared__ int32_t tok_page[kTile];
+  __shared__ int64_t s_off[kTile];
+  __shared__ float s_ks[kTile], s_vs[kTile];
 
   const KvView& kv = a.kv;
   const int b = blockIdx.y, g = blockIdx.x;
   const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int D = kv.head_dim;
   const int n = min(max(a.counts[b], 0), a.max_budget);
   const int32_t* list = a.indices + (static_cast<int64_t>(b) * kv.num_kv_heads + g) * a.max_budget;
 
-  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
-    const int r = idx / D, d = idx - r * D;
-    qs[idx] = Storage<QDT>::load(a.q, (static_cast<int64_t>(b) * kv.num_q_heads + g * G + r) * D + d);
-  }
+  for (int idx = threadIdx.x; idx < G * D; idx += kThreads)
+    s_q[idx] = Storage<QDT>::load(a.q, (static_cast<int64_t>(b) * kv.num_q_heads + g * G) * D + idx);
   if (threadIdx.x < kMaxG) { row_m[threadIdx.x] = -INFINITY; row_l[threadIdx.x] = 0.f; }
-  float acc[kAccPerThread];
+  constexpr int step = kThreads / D, kPieces = kTile / kPiece;
+  float acc[kMaxG / step];                     // dimension threadIdx.x % D of rows threadIdx.x / D + step * j
 #pragma unroll
-  for (int j = 0; j < kAccPerThread; ++j) acc[j] = 0.f;
-  __syncthreads();
+  for (int j = 0; j < kMaxG / step; ++j) acc[j] = 0.f;
 
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int j0 = 0; j0 < n; j0 += kTile) {
     const int nj = min(kTile, n - j0);
-    for (int jj = threadIdx.x; jj < kTile; jj += kThreads) tok[jj] = jj < nj ? list[j0 + jj] : 0;
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < G * kTile; idx += kThreads) {
-      const int r = idx / kTile, jj = idx - r * kTile;
-      float v = -INFINITY;
-      if (jj < nj) {
-        int page;
-        const int64_t off = row_offset(kv, b, g, tok[jj], &page);
-        if (r == 0) tok_page[jj] = page;
-        const float* qr = qs + r * D;
-        float dot = 0.f;
-        for (int d = 0; d < D; ++d) dot = fmaf(qr[d], Storage<KVDT>::load(kv.k_pool, off + d), dot);
-        if (KVDT == PILLAR_FP8_E4M3) dot *= kv.k_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
-        v = dot * kv.sm_scale;
-      }
-      s[idx] = v;
-    }
-    __syncthreads();
-    for (int r = wave; r < G; r += kThreads / kWave) {
-      float* sr = s + r * kTile;
-      float m = -INFINITY;
-      for (int jj = lane; jj < kTile; jj += kWave) m = fmaxf(m, sr[jj]);
-      m = fmaxf(wave_max(m), row_m[r]);                 // nj >= 1, so m is finite
-      float l = 0.f;
-      for (int jj = lane; jj < kTile; jj += kWave) {
-        const float p = __expf(sr[jj] - m);             // exp(-inf) = 0 for the padding
-        sr[jj] = p;
-        l += p;
-      }
-      l = wave_sum(l);
-      if (lane == 0) {
-        const float alpha = (row_m[r] == -INFINITY) ? 0.f : __expf(row_m[r] - m);
-        row_alpha[r] = alpha;
-        row_l[r] = row_l[r] * alpha + l;
-        row_m[r] = m;
+    if (static_cast<int>(threadIdx.x) < nj) {
+      int page;
+      s_off[threadIdx.x] = row_offset(kv, b, g, list[j0 + threadIdx.x], &page);
+      if (KVDT == PILLAR_FP8_E4M3) {
+        s_ks[threadIdx.x] = kv.k_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
+        s_vs[threadIdx.x] = kv.v_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
       }
     }
     __syncthreads();
+    StagedPiece<KVDT, D> k[kPieces], v[kPieces];       // all rows are sent for before the first is needed
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
-      const int idx = threadIdx.x + j * kThreads;
-      if (idx < G * D) {
-        const int r = idx / D, d = idx - r * D;
-        const float* pr = s + r * kTile;
-        float o = acc[j] * row_alpha[r];
-        for (int jj = 0; jj < nj; ++jj) {
-          const int t = tok[jj];
-          const int page = tok_page[jj];
-          const int64_t off = static_cast<int64_t>(page) * kv.stride_page + static_cast<int64_t>(g) * kv.stride_head +
-                              static_cast<int64_t>(t & (kv.page_size - 1)) * kv.stride_slot;
-          float v = Storage<KVDT>::load(kv.v_pool, off + d);
-          if (KVDT == PILLAR_FP8_E4M3) v *= kv.v_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
-          o = fmaf(pr[jj], v, o);
+    for (int p = 0; p < kPieces; ++p) k[p].fetch(kv.k_pool, s_off, p * kPiece, nj);
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) v[p].fetch(kv.v_pool, s_off, p * kPiece, nj);
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+      const int p0 = p * kPiece;
+      float dot[kMaxG / 8];
+      if (p0 < nj) {                           // uniform
+        if (p0 > 0) __syncthreads();           // the previous piece has been read
+        k[p].store(s_k);
+        __syncthreads();
+        piece_dots<kMaxG, D>(s_k, s_q, G, dot);
+      }
+      const int jj = p0 + (threadIdx.x & (kPiece - 1));
+#pragma unroll
+      for (int j = 0; j < kMaxG / 8; ++j) {
+        const int r = threadIdx.x / kPiece + 8 * j;
+        if (r < G) {
+          float x = -INFINITY;
+          if (jj < nj) {
+            x = dot[j];
+            if (KVDT == PILLAR_FP8_E4M3) x *= s_ks[jj];
+            x *= kv.sm_scale;
+          }
+          s[r * kTile + jj] = x;
         }
-        acc[j] = o;
+      }
+    }
+    __syncthreads();
+    softmax128(s, G, [&](int r) { return row_m[r]; }, [&](int r, float m, float l) {      // nj >= 1, so m is finite
+      const float alpha = (row_m[r] == -INFINITY) ? 0.f : __expf(row_m[r] - m);
+      row_alpha[r] = alpha;
+      row_l[r] = row_l[r] * alpha + l;
+      row_m[r] = m;
+    });
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+      if (p * kPiece < nj) {                   // uniform
+        __syncthreads();                       // the softmax is done; the K rows, or the previous piece, have been read
+        if (KVDT == PILLAR_FP8_E4M3) v[p].scale(s_vs, p * kPiece, nj);
+        v[p].store(s_k);
+        if (p == 0) {
+#pragma unroll
+          for (int j = 0; j < kMaxG / step; ++j) {
+            const int r = threadIdx.x / D + step * j;
+            if (r < G) acc[j] *= row_alpha[r];
+          }
+        }
+        __syncthreads();
+        piece_pv<kMaxG, D>(s_k, s, kTile, p * kPiece, G, acc);
       }
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int j = 0; j < kAccPerThread; ++j) {
-    const int idx = threadIdx.x + j * kThreads;
-    if (idx < G * D) {
-      const int r = idx / D, d = idx - r * D;
+  for (int j = 0; j < kMaxG / step; ++j) {
+    const int r = threadIdx.x / D + step * j, d = threadIdx.x & (D - 1);
+    if (r < G) {
       const int64_t row = static_cast<int64_t>(b) * kv.num_q_heads + g * G + r;
       const float l = row_l[r];
       Storage<QDT>::store(a.out, row * D + d, n > 0 ? acc[j] / l : 0.f);
@@ -125,7 +126,8 @@ hipError_t launch_decode_generic(const DecodeArgs& a, hipStream_t s) {
   KernelTimer t("decode_generic", s);
 #define PILLAR_CASE(Q, K)                                                            \
   if (a.q_dtype == Q && a.kv_dtype == K) {                                           \
-    hipLaunchKernelGGL((decode_generic<Q, K>), grid, dim3(kThreads), 0, s, a);       \
+    if (a.kv.head_dim == 64) hipLaunchKernelGGL((decode_generic<Q, K, 64>), grid, dim3(kThreads), 0, s, a);       \
+    else hipLaunchKernelGGL((decode_generic<Q, K, 128>), grid, dim3(kThreads), 0, s, a);                         \
     return hipGetLastError();                                                        \
   }
   PILLAR_CASE(PILLAR_F32, PILLAR_F32)

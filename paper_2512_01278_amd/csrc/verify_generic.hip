@@ -7,175 +7,224 @@
 // the softmax probabilities, averaged over those rows and the query heads of
 // one GQA group, are the score statistic that Top-K later reads.
 //
-// Three launches:
-//   split   one workgroup per (request, KV head, chunk of kChunk tokens):
-//           logits of all R=(k+1)*G rows against the chunk, chunk-local
+// Two launches, both with one workgroup per (request, KV head, chunk of kChunk
+// tokens):
+//   split   logits of all R=(k+1)*G rows against the chunk, chunk-local
 //           softmax, partial output -> workspace
-//   merge   one workgroup per (request, KV head): combines the partials by
-//           their log-sum-exp, writes out and lse
-//   scores  same grid as split: logits again, now against the final lse:
-//           exp(s - lse) is the exact softmax probability; mean over rows
+//   finish  log-sum-exp of every row from the partials; the workgroups of a
+//           (request, KV head) share its output; then logits again, now
+//           against the final lse: exp(s - lse) is the exact softmax
+//           probability; mean over rows
+// (The merge was a launch of its own with one workgroup per (request, KV head).)
+#include "generic_rows.hpp"
 #include "launch.hpp"
 
 namespace pillar {
 namespace {
 
 constexpr int kChunk = 128;     // tokens per workgroup
-constexpr int kThreads = 256;
+constexpr int kThreads = kGenThreads;
 
 struct GenericWs {
   float* part_m;   // [B][Hkv][NC][R]
   float* part_l;   // [B][Hkv][NC][R]
   float* part_o;   // [B][Hkv][NC][R][D]
-  float* lse;      // [B][Hkv][R]  natural log
   int nc;
 };
 
 __host__ __device__ inline int num_chunks(int max_seq_len) { return (max_seq_len + kChunk - 1) / kChunk; }
 
-// Logits of rows r<R against tokens t0..t0+kChunk-1 of (b, g) into s[r][tt]
-// (sm_scale applied, -inf where masked or beyond the sequence).  q rows are
-// staged in qs[R][D] first.
-template <int QDT, int KVDT>
-__device__ void logits_tile(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int L,
-                            float* qs, float* s) {
-  const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int R = n_q * G;
-  const int D = kv.head_dim;
-  for (int idx = threadIdx.x; idx < R * D; idx += kThreads) {
-    const int r = idx / D, d = idx - r * D;
-    const int i = r / G, hg = r - i * G;
-    const int64_t off = ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d;
-    qs[idx] = Storage<QDT>::load(q, off);
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < R * kChunk; idx += kThreads) {
-    const int r = idx / kChunk, tt = idx - r * kChunk;
-    const int i = r / G;
-    const int t = t0 + tt;
-    float v = -INFINITY;
-    if (t < L && t <= L - n_q + i) {
-      int page;
-      const int64_t off = row_offset(kv, b, g, t, &page);
-      float acc = 0.f;
-      const float* qr = qs + r * D;
-      for (int d = 0; d < D; ++d) acc = fmaf(qr[d], Storage<KVDT>::load(kv.k_pool, off + d), acc);
-      if (KVDT == PILLAR_FP8_E4M3) acc *= kv.k_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
-      v = acc * kv.sm_scale;
+struct GenericLds {
+  __attribute__((aligned(16))) float q[kPieceRows * kGenMaxD];       // query rows at work
+  __attribute__((aligned(16))) float s[kPieceRows * kChunk];         // their logits, then probabilities
+  __attribute__((aligned(16))) float rows[kPiece * kPieceStride];    // K or V rows of a piece
+  int64_t off[kChunk];                                               // element offset of every token's row
+  float ks[kChunk], vs[kChunk];                                      // fp8: scales of its page
+  float lse[kMaxRows];
+};
+
+template <int KVDT>
+__device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, int t0, int nt, GenericLds& lds) {
+  for (int tt = threadIdx.x; tt < nt; tt += kThreads) {
+    int page;
+    lds.off[tt] = row_offset(kv, b, g, t0 + tt, &page);
+    if (KVDT == PILLAR_FP8_E4M3) {
+      lds.ks[tt] = kv.k_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
+      lds.vs[tt] = kv.v_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
     }
-    s[idx] = v;
+  }
+}
+
+// Logits of query rows row0 .. row0+rows-1 against the chunk's tokens into lds.s[r][tt] (sm_scale applied, -inf where masked or
+// beyond the sequence).  Every thread of the workgroup calls this; lds.off is complete (a barrier ago).
+// All K rows are sent for before the first is needed, and `ahead` is called right after (to send for V rows).
+constexpr int kPieces = kChunk / kPiece;
+template <int QDT, int KVDT, int D, typename Ahead>
+__device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int nt, int L, int row0, int rows,
+                                             GenericLds& lds, Ahead ahead) {
+  const int G = kv.num_q_heads / kv.num_kv_heads;
+  StagedPiece<KVDT, D> piece[kPieces];
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
+  ahead();
+  for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
+    const int r = row0 + idx / D, d = idx & (D - 1);
+    const int i = r / G, hg = r - i * G;
+    lds.q[idx] = Storage<QDT>::load(q, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d);
+  }
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p) {
+    const int p0 = p * kPiece;
+    float dot[kPieceRows / 8];
+    if (p0 < nt) {                             // uniform
+      __syncthreads();                         // the previous piece has been read
+      piece[p].store(lds.rows);
+      __syncthreads();
+      piece_dots<kPieceRows, D>(lds.rows, lds.q, rows, dot);
+    }
+    const int tt = p0 + (threadIdx.x & (kPiece - 1)), t = t0 + tt;
+#pragma unroll
+    for (int j = 0; j < kPieceRows / 8; ++j) {
+      const int r = threadIdx.x / kPiece + 8 * j;
+      if (r < rows) {
+        float v = -INFINITY;
+        if (t < L && t <= L - n_q + (row0 + r) / G) {
+          v = dot[j];
+          if (KVDT == PILLAR_FP8_E4M3) v *= lds.ks[tt];
+          v *= kv.sm_scale;
+        }
+        lds.s[r * kChunk + tt] = v;
+      }
+    }
   }
   __syncthreads();
 }
 
-template <int QDT, int KVDT>
-__global__ __launch_bounds__(kThreads) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
-  extern __shared__ float smem[];
+template <int QDT, int KVDT, int D>
+__global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
+  __shared__ GenericLds lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
   const int t0 = c * kChunk;
   if (t0 >= L) return;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int D = kv.head_dim;
-  float* qs = smem;                  // [R][D]
-  float* s = smem + R * D;           // [R][kChunk]
-  logits_tile<QDT, KVDT>(kv, q, n_q, b, g, t0, L, qs, s);
-
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t slot = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc + c;
-  for (int r = wave; r < R; r += kThreads / kWave) {
-    float* sr = s + r * kChunk;
-    float m = -INFINITY;
-    for (int tt = lane; tt < kChunk; tt += kWave) m = fmaxf(m, sr[tt]);
-    m = wave_max(m);
-    float l = 0.f;
-    for (int tt = lane; tt < kChunk; tt += kWave) {
-      const float p = (m == -INFINITY) ? 0.f : __expf(sr[tt] - m);
-      sr[tt] = p;
-      l += p;
-    }
-    l = wave_sum(l);
-    if (lane == 0) {
-      ws.part_m[slot * R + r] = m;
-      ws.part_l[slot * R + r] = l;
-    }
-  }
-  __syncthreads();
   const int nt = min(kChunk, L - t0);
-  for (int idx = threadIdx.x; idx < R * D; idx += kThreads) {
-    const int r = idx / D, d = idx - r * D;
-    const float* pr = s + r * kChunk;
-    float acc = 0.f;
-    for (int tt = 0; tt < nt; ++tt) {
-      int page;
-      const int64_t off = row_offset(kv, b, g, t0 + tt, &page);
-      float v = Storage<KVDT>::load(kv.v_pool, off + d);
-      if (KVDT == PILLAR_FP8_E4M3) v *= kv.v_scale[static_cast<int64_t>(page) * kv.num_kv_heads + g];
-      acc = fmaf(pr[tt], v, acc);
+  const int64_t slot = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc + c;
+  resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
+  __syncthreads();
+  for (int row0 = 0; row0 < R; row0 += kPieceRows) {
+    const int rows = min(kPieceRows, R - row0);
+    StagedPiece<KVDT, D> piece[kPieces];
+    chunk_logits<QDT, KVDT, D>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, [&]() {
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.v_pool, lds.off, p * kPiece, nt);
+    });
+    softmax128(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
+      ws.part_m[slot * R + row0 + r] = m;
+      ws.part_l[slot * R + row0 + r] = l;
+    });
+    constexpr int step = kThreads / D;
+    float acc[kPieceRows / step];
+#pragma unroll
+    for (int j = 0; j < kPieceRows / step; ++j) acc[j] = 0.f;
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+      if (p * kPiece < nt) {                   // uniform
+        __syncthreads();                       // the K rows, or the previous piece, have been read; the softmax is done
+        if (KVDT == PILLAR_FP8_E4M3) piece[p].scale(lds.vs, p * kPiece, nt);
+        piece[p].store(lds.rows);
+        __syncthreads();
+        piece_pv<kPieceRows, D>(lds.rows, lds.s, kChunk, p * kPiece, rows, acc);
+      }
     }
-    ws.part_o[(slot * R + r) * D + d] = acc;
+    const int d = threadIdx.x & (D - 1);
+#pragma unroll
+    for (int j = 0; j < kPieceRows / step; ++j) {
+      const int r = threadIdx.x / D + step * j;
+      if (r < rows) ws.part_o[(slot * R + row0 + r) * D + d] = acc[j];
+    }
+    __syncthreads();                           // before the next rows' logits
   }
 }
 
-template <int QDT>
-__global__ __launch_bounds__(kThreads) void verify_merge_generic(KvView kv, int n_q, GenericWs ws, void* out,
-                                                                  float* lse_out) {
-  const int b = blockIdx.y, g = blockIdx.x;
+template <int QDT, int KVDT, int D>
+__global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, const void* q, int n_q, GenericWs ws, void* out, float* lse_out,
+                                                                   float* scores, int64_t score_stride) {
+  __shared__ GenericLds lds;
+  const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
+  const int t0 = c * kChunk;
+  if (t0 >= L) return;
   const int nc = (L + kChunk - 1) / kChunk;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int D = kv.head_dim;
+  const int nt = min(kChunk, L - t0);
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
-  for (int idx = threadIdx.x; idx < R * D; idx += kThreads) {
-    const int r = idx / D, d = idx - r * D;
-    float m = -INFINITY;
-    for (int c = 0; c < nc; ++c) m = fmaxf(m, ws.part_m[(base + c) * R + r]);
-    float l = 0.f, o = 0.f;
-    for (int c = 0; c < nc; ++c) {
-      const float mc = ws.part_m[(base + c) * R + r];
-      const float w = (mc == -INFINITY) ? 0.f : __expf(mc - m);
-      l = fmaf(ws.part_l[(base + c) * R + r], w, l);
-      o = fmaf(ws.part_o[((base + c) * R + r) * D + d], w, o);
+  if (scores) resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
+  // log-sum-exp of every row: four threads per row take the chunks in turn
+  {
+    const int r = threadIdx.x / 4, part = threadIdx.x & 3;
+    float m = -INFINITY, l = 0.f;
+    if (r < R)
+#pragma unroll 4
+      for (int i = part; i < nc; i += 4) m = fmaxf(m, ws.part_m[(base + i) * R + r]);
+    m = fmaxf(m, __shfl_xor(m, 1, kWave));
+    m = fmaxf(m, __shfl_xor(m, 2, kWave));
+    if (r < R)
+#pragma unroll 4
+      for (int i = part; i < nc; i += 4) {
+        const float mc = ws.part_m[(base + i) * R + r];
+        if (mc != -INFINITY) l = fmaf(ws.part_l[(base + i) * R + r], __expf(mc - m), l);
+      }
+    l += __shfl_xor(l, 1, kWave);
+    l += __shfl_xor(l, 2, kWave);
+    if (r < R && part == 0) {
+      const bool live = l > 0.f;               // false for a row that sees no token at all: zeros, lse = -inf
+      const float v = m + __logf(l);
+      lds.lse[r] = live ? v : INFINITY;        // +inf: no weight in the output and the statistic
+      if (c == 0 && lse_out) {
+        const int i = r / G, hg = r - i * G;
+        lse_out[(static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg] = live ? v : -INFINITY;
+      }
+      lds.q[r] = m;                            // for the weights of the output (the query rows come later)
+      lds.q[kMaxRows + r] = live ? l : 0.f;
+    }
+  }
+  __syncthreads();
+  // this workgroup's share of the output
+  for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {
+    const int r = idx / D, d = idx & (D - 1);
+    float o = 0.f;
+#pragma unroll 4
+    for (int i = 0; i < nc; ++i) {
+      const float mc = ws.part_m[(base + i) * R + r];
+      const float w = (mc == -INFINITY) ? 0.f : __expf(mc - lds.q[r]);
+      o = fmaf(ws.part_o[((base + i) * R + r) * D + d], w, o);
     }
     const int i = r / G, hg = r - i * G;
-    const int64_t row = (static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg;
-    const bool live = l > 0.f;                 // false for a row that sees no token at all: zeros, lse = -inf
-    Storage<QDT>::store(out, row * D + d, live ? o / l : 0.f);
-    if (d == 0) {
-      const float v = m + __logf(l);
-      ws.lse[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * R + r] = live ? v : INFINITY;   // +inf: no weight in the statistic
-      if (lse_out) lse_out[row] = live ? v : -INFINITY;
-    }
+    Storage<QDT>::store(out, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d,
+                        lds.q[kMaxRows + r] > 0.f ? o / lds.q[kMaxRows + r] : 0.f);
   }
-}
-
-template <int QDT, int KVDT>
-__global__ __launch_bounds__(kThreads) void verify_scores_generic(KvView kv, const void* q, int n_q, GenericWs ws,
-                                                                   float* scores, int64_t score_stride) {
-  extern __shared__ float smem[];
-  const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
-  const int L = kv.seq_lens[b];
-  const int t0 = c * kChunk;
-  if (t0 >= L) return;
-  const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int R = n_q * G;
-  const int D = kv.head_dim;
-  float* qs = smem;
-  float* s = smem + R * D;
-  logits_tile<QDT, KVDT>(kv, q, n_q, b, g, t0, L, qs, s);
-  const float* lse = ws.lse + (static_cast<int64_t>(b) * kv.num_kv_heads + g) * R;
+  if (!scores) return;
+  __syncthreads();                             // the query rows take the place of the weights
   const float inv_r = 1.0f / static_cast<float>(R);
-  for (int tt = threadIdx.x; tt < kChunk; tt += kThreads) {
-    if (t0 + tt >= L) continue;
-    float acc = 0.f;
-    for (int r = 0; r < R; ++r) {
-      const float v = s[r * kChunk + tt];
-      acc += (v == -INFINITY) ? 0.f : __expf(v - lse[r]);
+  float sum = 0.f;                             // of this thread's token
+  for (int row0 = 0; row0 < R; row0 += kPieceRows) {
+    const int rows = min(kPieceRows, R - row0);
+    chunk_logits<QDT, KVDT, D>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, []() {});
+    // two threads per token: even rows, odd rows
+    const int tt = threadIdx.x >> 1;
+#pragma unroll 4
+    for (int r = threadIdx.x & 1; r < rows; r += 2) {
+      const float v = lds.s[r * kChunk + tt];
+      sum += (v == -INFINITY) ? 0.f : __expf(v - lds.lse[row0 + r]);
     }
-    scores[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * score_stride + t0 + tt] = acc * inv_r;
+    __syncthreads();
   }
+  sum += __shfl_xor(sum, 1, kWave);
+  const int tt = threadIdx.x >> 1;
+  if ((threadIdx.x & 1) == 0 && tt < nt) scores[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * score_stride + t0 + tt] = sum * inv_r;
 }
 
 GenericWs carve(const KvView& kv, int n_q, void* workspace) {
@@ -188,32 +237,23 @@ GenericWs carve(const KvView& kv, int n_q, void* workspace) {
   w.nc = static_cast<int>(nc);
   w.part_m = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
   w.part_l = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
-  w.part_o = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * kv.head_dim * 4, 256);
-  w.lse = reinterpret_cast<float*>(p);
+  w.part_o = reinterpret_cast<float*>(p);
   return w;
 }
 
-template <int QDT, int KVDT>
+template <int QDT, int KVDT, int D>
 hipError_t run(const VerifyArgs& a, hipStream_t st) {
   const KvView& kv = a.kv;
   const GenericWs ws = carve(kv, a.n_q, a.workspace);
-  const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int R = a.n_q * G;
-  const size_t smem = (static_cast<size_t>(R) * kv.head_dim + static_cast<size_t>(R) * kChunk) * sizeof(float);
   const dim3 grid(ws.nc, kv.num_kv_heads, kv.batch);
   {
     KernelTimer t("verify_split_generic", st);
-    hipLaunchKernelGGL((verify_split_generic<QDT, KVDT>), grid, dim3(kThreads), smem, st, kv, a.q, a.n_q, ws);
+    hipLaunchKernelGGL((verify_split_generic<QDT, KVDT, D>), grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws);
   }
   {
-    KernelTimer t("verify_merge_generic", st);
-    hipLaunchKernelGGL((verify_merge_generic<QDT>), dim3(kv.num_kv_heads, kv.batch), dim3(kThreads), 0, st, kv,
-                       a.n_q, ws, a.out, a.lse);
-  }
-  if (a.scores) {
-    KernelTimer t("verify_scores_generic", st);
-    hipLaunchKernelGGL((verify_scores_generic<QDT, KVDT>), grid, dim3(kThreads), smem, st, kv, a.q, a.n_q, ws,
-                       a.scores, a.score_stride);
+    KernelTimer t("verify_finish_generic", st);
+    hipLaunchKernelGGL((verify_finish_generic<QDT, KVDT, D>), grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws, a.out, a.lse, a.scores,
+                       a.score_stride);
   }
   return hipGetLastError();
 }
@@ -225,13 +265,12 @@ size_t verify_generic_workspace(const KvView& kv, int n_q) {
   const size_t R = static_cast<size_t>(n_q) * G;
   const size_t nc = num_chunks(kv.max_seq_len);
   const size_t pairs = static_cast<size_t>(kv.batch) * kv.num_kv_heads;
-  return 2 * align_up(pairs * nc * R * 4, 256) + align_up(pairs * nc * R * kv.head_dim * 4, 256) +
-         align_up(pairs * R * 4, 256);
+  return 2 * align_up(pairs * nc * R * 4, 256) + align_up(pairs * nc * R * kv.head_dim * 4, 256);
 }
 
 hipError_t launch_verify_generic(const VerifyArgs& a, hipStream_t s) {
 #define PILLAR_CASE(Q, K) \
-  if (a.q_dtype == Q && a.kv_dtype == K) return run<Q, K>(a, s);
+  if (a.q_dtype == Q && a.kv_dtype == K) return a.kv.head_dim == 64 ? run<Q, K, 64>(a, s) : run<Q, K, 128>(a, s);
   PILLAR_CASE(PILLAR_F32, PILLAR_F32)
   PILLAR_CASE(PILLAR_F32, PILLAR_BF16)
   PILLAR_CASE(PILLAR_F32, PILLAR_FP8_E4M3)

@@ -157,6 +157,17 @@ def test_generic_kernels_on_a_matrix_core_shape():
     assert np.abs(to_f64(slow.lse) - to_f64(fast.lse)).max() <= LSE_ABS
 
 
+@pytest.mark.parametrize("q_dtype,kv_dtype,D,heads,k", [("f32", "f32", 64, 4, 3), ("f32", "f32", 128, 8, 4), ("bf16", "bf16", 128, 16, 3),
+                                                         ("f32", "fp8_e4m3", 64, 2, 15), ("bf16", "fp8_e4m3", 128, 1, 0)])
+def test_generic_kernels_at_their_edges(q_dtype, kv_dtype, D, heads, k):
+    """Contexts and lists around the 32 tokens a workgroup stages at a time and the 128 it takes, pages of 8 tokens, 1 to
+    64 query rows (32 at a time)."""
+    lens = [k + 1, 31, 32, 33, 96, 127, 128, 129, 160, 257]
+    w = small(230 + k, q_dtype=q_dtype, kv_dtype=kv_dtype, D=D, P=8, B=len(lens), Hq=heads, Hkv=1, spec_k=k, seq_lens=lens,
+              budgets=[min(n, b) for n, b in zip(lens, [1, 31, 32, 33, 64, 127, 128, 129, 96, 200])])
+    round_trip(w, what="generic kernels, edges", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
+
+
 def _floor_workload():
     """One request, one KV head, every query row the same vector 8 e_0, keys x_t e_0: the base-2 logit of token t is
     1.02 x_t for every row.  Token 0 has x = 64, the others sweep [-6, 6] every 128 tokens: their probabilities run from 2^-71 to
@@ -300,6 +311,27 @@ def test_many_segments_per_pair(k, segments):
     lens = [64 * (segments - 1), 64 * segments, 64 * (segments + 1), 64 * 3 * segments + 5, 17]
     _same_as_two_calls(small(180 + k, B=5, Hq=4, Hkv=1, spec_k=k, seq_lens=lens, budgets=[64, 64, 64, 200, 5]), f"{segments} segments")
     _same_as_two_calls(small(190 + k, B=2, Hq=8, Hkv=2, spec_k=k, seq_lens=[17000, 8200], budgets=[300, 64]), "segments of long rows")
+
+
+@pytest.mark.parametrize("kv_dtype,page,heads,k", [("bf16", 16, 8, 2), ("bf16", 64, 16, 4), ("fp8_e4m3", 16, 8, 2), ("fp8_e4m3", 32, 16, 4),
+                                                   ("fp8_e4m3", 16, 16, 5)])
+def test_stretches_at_their_edges(kv_dtype, page, heads, k):
+    """Four wavefronts share a range: contexts of one token group, of a tile, of a page window (64 pages) and one more or
+    less of each, so that stretches are empty, one tile, start and end inside a page window or straddle two (up to 48 rows)."""
+    lens = [k + 1, 15, 16, 17, 31, 32, 33, 64, 65, 127, 129, 64 * page - 1, 64 * page, 64 * page + 1, 64 * page + 33, 1000]
+    w = small(210 + k, kv_dtype=kv_dtype, P=page, B=len(lens), Hq=heads, Hkv=2, spec_k=k, seq_lens=lens, budgets=[min(n, 40) for n in lens])
+    for waves in (0, 1):
+        pa.pillar_set_option("verify_waves", waves)
+        try:
+            round_trip(w, what=f"edges, verify_waves={waves}", fused_select=True)
+            run = GpuRun(w)                              # and without the statistic
+            run.verify(with_scores=False)
+            torch.cuda.synchronize()
+            want, want_lse, _ = oracle.verify_attn(w)
+            check_out(to_f64(run.out), want, w.kv_dtype, "edges, no statistic")
+            assert np.abs(to_f64(run.lse) - want_lse).max() <= LSE_ABS
+        finally:
+            pa.pillar_set_option("verify_waves", 0)
 
 
 # -------------------------------------------- index lists from other sources ----
