@@ -135,10 +135,10 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
         const Rows& cur = (k & 2) ? rr[1] : rr[0];
         const int half = k & 1;
         const bool more = k < 3 && ti + WAVES < ntiles;
-        rows_to_lds<FP8, false>(regs.k, s_tile, lane);
+        rows_to_lds<FP8, false, true>(regs.k, s_tile, lane);
         f32x4 s[2][1];
         tile_qk<1>(s_tile, qf, s, lane);
-        rows_to_lds<FP8, true>(regs.v, s_tile, lane);
+        rows_to_lds<FP8, true, true>(regs.v, s_tile, lane);
         if (more) issue_rows<FP8>(kv, ((k + 1) & 2) ? rr[1] : rr[0], (k + 1) & 1, regs, lane);
         f32x4 vsc[2];
 #pragma unroll
