@@ -1024,11 +1024,14 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
 // fp8 the maximum may lag by up to 2^kSlack, which after the first tiles spares the rescaling (exponentials up to 2^kSlack
 // keep their relative precision, and their product with the page scale is rounded to bf16 anyway); with bf16 it may not: the
 // probability 1 of a row's largest logit is exact.
+// stash, m_ref: buffers of exactly the tile's stash and maxima (STASH).
 // LAST: the last tile of the stretch, after which nothing is sent for, and the only one that may reach past the sequence.
 // (A branch around the loads instead makes the compiler wait for all of them where it needs the first.)
+constexpr int kRawBuffer = 0x00020000;          // third word of a raw buffer descriptor: no stride, no swizzle, range checked
+constexpr int kDropped = 0x7ffffff0;            // an offset past the end of every buffer here
 template <int RB, bool FP8, bool STASH, bool LAST>
 __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, StretchTile<FP8>& t, const LaneGeom<FP8>& geo, const RowGeom& rg,
-                                             int tb, float c2, FlashRows<RB>& st, uint8_t* s_tile, const uint8_t* s_q, uint8_t* stash, float* m_ref, int lane) {
+                                             int tb, float c2, FlashRows<RB>& st, uint8_t* s_tile, const uint8_t* s_q, __amdgpu_buffer_rsrc_t stash, __amdgpu_buffer_rsrc_t m_ref, int lane) {
   constexpr float kSlack = FP8 && !STASH ? 8.f : 0.f;
   const int n = lane & 15, g4 = lane >> 4;
   f32x4 s[2][RB];
@@ -1075,11 +1078,11 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
       for (int i = 0; i < 4; ++i) pr[sub][i] = fast_exp2(fmaf(s[sub][rb][i], sc[sub], -m_use));
     st.l[rb] += ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
     if constexpr (STASH) {                                   // the exponentials, 16 bits each, and the maximum they refer to
+      // Stores past a buffer's end are dropped: lanes with nothing to store need no branch, behind which the compiler
+      // could not count the stores and would wait for them, and for V, where the next tile needs K.
       const int sl = stash_lane(rb, RB, rg.nv, n, g4, lane);
-      if (sl >= 0) {
-        *reinterpret_cast<u32x4*>(stash + sl * 16) = stash_pack8(pr);
-      }
-      if (g4 == 0) m_ref[16 * rb + n] = m_use;
+      __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_use), m_ref, g4 == 0 ? 4 * (16 * rb + n) : kDropped, 0, 0);
     }
     if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
     p[rb] = pack_p(pr[0], pr[1]);
@@ -1137,8 +1140,10 @@ __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t
     __syncthreads();
     const int64_t u0 = team.unit - cs.tile0;                 // unit of the pair's first tile
     auto tile = [&](int t, auto last) {
-      stretch_tile<RB, FP8, STASH, decltype(last)::value>(kv, cur, tl, geo, rg, t * kTileTokens, c2, st, s_tile, lds.q,
-                                                          ws.stash + (u0 + t) * rg.tile_lanes * 16, ws.m_ref + (u0 + t) * rows, lane);
+      stretch_tile<RB, FP8, STASH, decltype(last)::value>(
+          kv, cur, tl, geo, rg, t * kTileTokens, c2, st, s_tile, lds.q,
+          __builtin_amdgcn_make_buffer_rsrc(ws.stash + (u0 + t) * rg.tile_lanes * 16, 0, rg.tile_lanes * 16, kRawBuffer),
+          __builtin_amdgcn_make_buffer_rsrc(ws.m_ref + (u0 + t) * rows, 0, rows * 4, kRawBuffer), lane);
     };
     for (int t = t0; t + 1 < t1; ++t) tile(t, std::false_type{});
     if (t0 < t1) tile(t1 - 1, std::true_type{});
