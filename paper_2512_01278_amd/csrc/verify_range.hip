@@ -84,10 +84,10 @@ __device__ __forceinline__ int queries_of(const KvView& kv, const RangeWs& ws, i
   return ws.spec_lens ? min(ws.spec_lens[request_of(kv, b)] + 1, n_q) : n_q;
 }
 
-// Ranges in use: all that the chip holds at once, but none shorter than kMinTiles.  A tile costs a lone
-// wavefront 1.6 to 3.8 us, a segment more to merge about 0.2 us in the finish kernel: pass + finish at one request of
-// 2100 tokens 12.4 + 20.4 us with 1 tile, 12.0 + 15.5 with 2, 16.2 + 13.8 with 4, 23.3 + 12.4 with 8; 24 requests of 5 to
-// 3000 tokens 14.3 + 20.4, 15.9 + 15.8, 23.8 + 13.8, 40.5 + 12.6.
+// Ranges in use: all that the chip holds at once, but none shorter than kMinTiles tiles.  A segment more to merge costs the
+// finish kernel little, a segment more in a range a workgroup one after the other: pass + finish at one request of 2100
+// tokens 11.3 + 15.2 us with 2 tiles, 13.2 + 14.2 with 4, 14.8 + 12.8 with 8; 24 requests of 5 to 3000 tokens 17.0 + 16.2,
+// 23.0 + 14.2, 39.6 + 12.8.  (With 1, every tile a segment: 12.4 + 20.4 and 14.3 + 20.4 with a range per wavefront.)
 constexpr int kMinTiles = 2;
 __device__ __forceinline__ int ranges_used(const RangeWs& ws, int total) { return max(1, min(ws.n_ranges, total / kMinTiles)); }
 
@@ -926,7 +926,7 @@ __device__ __forceinline__ void stretch_k(const KvView& kv, Stretch<FP8>& c, Str
     const int at = min(tok0 >> kv.page_shift, c.last_page) - c.win * kWindowPages;
     const uint64_t page = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c.hi), at))) << 32) |
                           static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c.lo), at));
-    t.base[grp] = page + static_cast<uint32_t>((tok0 & (kv.page_size - 1)) * static_cast<int>(kv.stride_slot) * (FP8 ? 1 : 2));
+    t.base[grp] = page + static_cast<uint64_t>(static_cast<int64_t>(tok0 & (kv.page_size - 1)) * kv.stride_slot * (FP8 ? 1 : 2));
     if constexpr (FP8) {
       t.ks[grp] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c.ks), at));
       t.vs[grp] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c.vs), at));

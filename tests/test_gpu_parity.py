@@ -531,6 +531,22 @@ def test_strided_pool_layout_and_wide_block_table():
     compare_with_oracle(w, run)
 
 
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+def test_slot_major_pool(kv_dtype):
+    # pool stored [slot][page][head][dim]: rows of one page are a whole plane apart
+    w = small(207, kv_dtype=kv_dtype, P=32, Hq=16, Hkv=2, spec_k=4, seq_lens=[5, 255, 1000], budgets=[5, 16, 512])
+    run = GpuRun(w)
+    kv = run.dw.kv
+    kv.k_pool = kv.k_pool.permute(2, 0, 1, 3).contiguous().permute(1, 2, 0, 3)
+    kv.v_pool = kv.v_pool.permute(2, 0, 1, 3).contiguous().permute(1, 2, 0, 3)
+    assert kv.k_pool.stride(2) == w.num_pages * w.Hkv * w.D
+    run.run_all()
+    compare_with_oracle(w, run)
+    run.verify(with_scores=False)
+    torch.cuda.synchronize()
+    check_out(to_f64(run.out), oracle.verify_attn(w)[0], w.kv_dtype, "slot-major pool, no statistic")
+
+
 def test_empty_selection_and_zero_budget():
     w = small(205, budgets=[0, 5, 0])
     run = GpuRun(w)
