@@ -128,6 +128,9 @@ def verify_attn(w, requests=None, spec_lens=None):
         L = int(w.seq_lens[b])
         n_q = n_q_max if spec_lens is None else int(spec_lens[b]) + 1
         R = n_q * G
+        if L == 0:                                        # no query sees a token
+            lse[b, :n_q] = -np.inf
+            continue
         k, v = gather_request(w, b)
         pos = L - n_q + np.arange(n_q)                    # position of query i
         visible = np.arange(L)[None, :] <= pos[:, None]   # [n_q, L]

@@ -155,11 +155,11 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
   const int t0 = c * kChunk;
-  if (t0 >= L) return;
-  const int nc = (L + kChunk - 1) / kChunk;
+  if (t0 >= L && c > 0) return;                // an empty context has a workgroup too: zeros, lse = -inf
+  const int nc = (max(L, 0) + kChunk - 1) / kChunk;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int nt = min(kChunk, L - t0);
+  const int nt = min(kChunk, max(L - t0, 0));
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
   if (scores) resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
   // log-sum-exp of every row: four threads per row take the chunks in turn
@@ -193,7 +193,8 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   }
   __syncthreads();
   // this workgroup's share of the output
-  for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {
+  const int n_share = max(nc, 1);
+  for (int idx = c * R * D / n_share + threadIdx.x; idx < (c + 1) * R * D / n_share; idx += kThreads) {
     const int r = idx / D, d = idx & (D - 1);
     float o = 0.f;
 #pragma unroll 4
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
     Storage<QDT>::store(out, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d,
                         lds.q[kMaxRows + r] > 0.f ? o / lds.q[kMaxRows + r] : 0.f);
   }
-  if (!scores) return;
+  if (!scores || L <= 0) return;
   __syncthreads();                             // the query rows take the place of the weights
   const float inv_r = 1.0f / static_cast<float>(R);
   float sum = 0.f;                             // of this thread's token

@@ -234,6 +234,46 @@ def test_context_shorter_than_its_queries(flags):
                      w.seq_lens, w.budgets, range(w.B), "short contexts")
 
 
+def _check_with_empty_contexts(w, run, what):
+    """out, lse, scores and lists of a batch in which some contexts have no token at all."""
+    from tests.harness import check_scores, check_topk_exact
+    want_out, want_lse, want_scores = oracle.verify_attn(w)
+    check_out(to_f64(run.out), want_out, w.kv_dtype, f"{what}: out")
+    lse = to_f64(run.lse)
+    assert np.array_equal(np.isneginf(lse), np.isneginf(want_lse)), f"{what}: rows that see no token"
+    seen = np.isfinite(want_lse)
+    assert np.abs(lse[seen] - want_lse[seen]).max(initial=0.0) <= LSE_ABS, f"{what}: lse"
+    full = [b for b in range(w.B) if w.seq_lens[b] > 0]
+    check_scores(run.scores.cpu().numpy().astype(np.float64), want_scores, w.seq_lens, full, what)
+    empty = [b for b in range(w.B) if w.seq_lens[b] == 0]
+    assert run.counts.cpu().numpy()[empty].tolist() == [0] * len(empty) and (run.indices[empty] == -1).all(), f"{what}: lists of nothing"
+    assert torch.isnan(run.scores[empty]).all(), f"{what}: statistic of nothing written"
+    if full:
+        check_topk_exact(run.indices.cpu().numpy(), run.counts.cpu().numpy(), run.scores.cpu().numpy()[:, :, :w.max_seq_len], w.seq_lens,
+                         w.budgets, full, what)
+
+
+def _emptied(w, run, empty):
+    """Contexts of a workload that is on the GPU already lose all their tokens."""
+    w.seq_lens[empty] = 0
+    run.dw.kv.seq_lens[empty] = 0
+
+
+@pytest.mark.parametrize("kw", [dict(q_dtype="f32", kv_dtype="f32", D=64), dict(kv_dtype="fp8_e4m3", P=8, spec_k=15)])
+@pytest.mark.parametrize("empty", [[0], [1, 4], [0, 1, 2, 3, 4]])
+def test_empty_contexts_generic_kernels(kw, empty):
+    """seq_lens[b] == 0 is outside the documented range; as for any query that sees no token, zeros and lse = -inf."""
+    w = small(172, B=5, seq_lens=[2, 9, 300, 1, 20], budgets=[2, 9, 40, 1, 8], allow_short=True, **kw)
+    run = GpuRun(w, flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
+    _emptied(w, run, empty)
+    run.verify()
+    pa.pillar_select_topk(run.scores, run.dw.kv.seq_lens, run.dw.budgets, 300, run.max_budget, run.indices, run.counts, run.workspace)
+    run.decode()
+    torch.cuda.synchronize()
+    _check_with_empty_contexts(w, run, f"generic, contexts {empty} empty")
+    assert (run.d_out[empty] == 0).all() and torch.isneginf(run.d_lse[empty]).all()
+
+
 # ------------------------------------------ the measured configs, reduced ----
 @pytest.mark.parametrize("cfg,batch", [(2, 2), (3, 4), (4, 1), (5, 2)])
 def test_config_reduced_batch(cfg, batch):
