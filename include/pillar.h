@@ -129,8 +129,8 @@ size_t pillar_workspace_bytes(const pillar_kv_t* kv, int32_t spec_len_k, int32_t
  *          something below 2^-62; with PILLAR_FLAG_EXACT_SCORES
  *          the error is that of fp32 arithmetic.
  *   Every request must hold its own speculative tokens: seq_lens[b] >= k+1.
- *   A query row that sees no token at all (seq_lens[b] < k+1) gets out = 0 and
- *   lse = -inf and adds nothing to the statistic. */
+ *   A query row that sees no token at all (seq_lens[b] < k+1, down to 0) gets
+ *   out = 0 and lse = -inf and adds nothing to the statistic. */
 int pillar_verify_attn(const pillar_kv_t* kv, const void* q, int32_t spec_len_k,
                        void* out, float* lse, float* scores, int64_t score_stride,
                        void* workspace, size_t workspace_bytes, void* hip_stream);

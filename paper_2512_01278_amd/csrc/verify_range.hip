@@ -391,7 +391,7 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
     const int n = ranges_used(ws, p.total);
     c.unit = range_begin(c.w, p.total, n);
     c.end = range_begin(c.w + 1, p.total, n);
-    c.live = c.w < n;
+    c.live = c.w < n && c.unit < c.end;        // (a batch of empty contexts has one range of nothing)
     if (!c.live) return c;
     int upto = 0;                              // requests that begin at or before the unit
 #pragma unroll
@@ -407,7 +407,7 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
     const int n = ranges_used(ws, total);
     c.unit = range_begin(c.w, total, n);
     c.end = range_begin(c.w + 1, total, n);
-    c.live = c.w < n;
+    c.live = c.w < n && c.unit < c.end;        // (a batch of empty contexts has one range of nothing)
     if (!c.live) return c;
     sg.b = find_request(ws, kv.batch, c.unit, lane);
     sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
@@ -445,6 +445,14 @@ __device__ __forceinline__ void advance_cursor(const KvView& kv, Cursor& c, int 
       sg.b += 1;
     }
     sg.L = __builtin_amdgcn_readfirstlane(c.len_next);
+    if (__builtin_expect(sg.L <= 0 && sg.b + 1 < kv.batch, 0)) {      // an empty context has no tile: on to one that has (units are left, so there is one)
+      int b = sg.b;
+      do sg.L = kv.seq_lens[request_of(kv, ++b)];
+      while (sg.L <= 0 && b + 1 < kv.batch);
+      sg.b = __builtin_amdgcn_readfirstlane(b);
+      sg.L = __builtin_amdgcn_readfirstlane(sg.L);
+      c.pg_next = load_window(kv, sg.b, 0, lane);
+    }
     sg.tiles = tiles_of_len(sg.L);
     sg.tile0 = 0;
     sg.tile1 = min(sg.tiles, c.end - c.unit);
@@ -575,7 +583,7 @@ __global__ __launch_bounds__(256) void verify_lse_combine_range(KvView kv, int n
   const int tiles = tiles_of_len(kv.seq_lens[rq]);
   const int u0 = ws.ureq[b] + g * tiles;
   const int n_used = ranges_used(ws, total);
-  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
+  const int w0 = tiles > 0 ? range_of(u0, total, n_used) : 0, w1 = tiles > 0 ? range_of(u0 + tiles - 1, total, n_used) : -1;   // (empty context: none)
   const float* pm = ws.part_m + static_cast<int64_t>(pair + w0) * rows + row;
   const float* pl = ws.part_l + static_cast<int64_t>(pair + w0) * rows + row;
   float m = -INFINITY, l = 0.f;
@@ -745,8 +753,8 @@ __global__ __launch_bounds__(256) void verify_o_merge_range(KvView kv, int n_q, 
   const int tiles = tiles_of_len(kv.seq_lens[rq]);
   const int u0 = ws.ureq[b] + g * tiles;
   const int n_used = ranges_used(ws, total);
-  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
-  if (w1 == w0) return;
+  const int w0 = tiles > 0 ? range_of(u0, total, n_used) : 0, w1 = tiles > 0 ? range_of(u0 + tiles - 1, total, n_used) : -1;
+  if (w1 == w0) return;                        // (an empty context has no partial: zeros)
   for (int idx = threadIdx.x; idx < R * (kHeadDim / 4); idx += 256) {
     const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -1563,8 +1571,10 @@ __device__ __forceinline__ uint32_t score_key(float f) { return __float_as_uint(
 // next launch, selects from it.  The first chunk's workgroup also does step 1's output and step 2.  (Handing the
 // chunks to the last workgroup to arrive inside one launch was measured: the device-wide release every workgroup
 // then needs writes back the whole L2 behind it, 3 to 5 times the cost of the extra launch.)
+// Up to two row blocks, two workgroups of 512 threads share a compute unit, which takes 128 registers at most: with 129, 128 requests of
+// 1-8 K tokens took 539 us instead of 518 (pass and finish).
 template <int RB, int THREADS, int CH, bool SELECT, bool SPLIT>
-__global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, RangeWs ws, uint16_t* out, float* lse_out,
+__global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void verify_finish(KvView kv, int n_q, RangeWs ws, uint16_t* out, float* lse_out,
                                                          float* scores, int64_t score_stride, SelectOut sel) {
   static_assert(!SPLIT || !SELECT, "a split pair is selected by verify_select_rows");
   constexpr int KPC = 8;
@@ -1583,12 +1593,8 @@ __global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, Ran
   const int R = n_q * G;
   const int Rb = queries_of(kv, ws, b, n_q) * G;
   constexpr int rows = RB * 16;
-  const int total = ws.ctrl[0];
-  const int u0 = ws.ureq[b] + g * tiles;
-  const int n_used = ranges_used(ws, total);
-  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
   const int my_chunk = SPLIT ? static_cast<int>(blockIdx.y) : 0;
-  if (SPLIT && my_chunk * kChunk >= L) return;          // this pair has fewer chunks (uniform over the workgroup)
+  if (SPLIT && my_chunk > 0 && my_chunk * kChunk >= L) return;      // this pair has fewer chunks (uniform over the workgroup)
   const bool lead = my_chunk == 0;                       // the workgroup that writes what exists once per pair
   int K = 0;
   int32_t* out_idx = nullptr;
@@ -1598,6 +1604,20 @@ __global__ __launch_bounds__(THREADS) void verify_finish(KvView kv, int n_q, Ran
     if (g == 0 && threadIdx.x == 0) sel.counts[rq] = K;
     for (int j = K + threadIdx.x; j < sel.max_budget; j += THREADS) out_idx[j] = -1;
   }
+
+  if (L <= 0) {                                          // an empty context: no unit, no segment; no query sees a token
+    for (int idx = threadIdx.x; idx < Rb * (kHeadDim / 4); idx += THREADS) {
+      const int r = idx / (kHeadDim / 4), i = r / G, hg = r - i * G;
+      const int64_t row = (static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg;
+      *reinterpret_cast<u32x2*>(out + row * kHeadDim + 4 * (idx - r * (kHeadDim / 4))) = u32x2{0u, 0u};
+      if (lse_out && idx == r * (kHeadDim / 4)) lse_out[row] = -INFINITY;
+    }
+    return;
+  }
+  const int total = ws.ctrl[0];
+  const int u0 = ws.ureq[b] + g * tiles;
+  const int n_used = ranges_used(ws, total);
+  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
 
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int n = lane & 15, g4 = lane >> 4;

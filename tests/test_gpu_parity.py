@@ -274,6 +274,53 @@ def test_empty_contexts_generic_kernels(kw, empty):
     assert (run.d_out[empty] == 0).all() and torch.isneginf(run.d_lse[empty]).all()
 
 
+EMPTY = [[0], [3], [1, 2, 5], [0, 1, 2, 3, 4, 5]]
+
+
+@pytest.mark.parametrize("kw", [dict(spec_k=4, Hq=16, Hkv=4), dict(spec_k=8, Hq=8, Hkv=2), dict(spec_k=4, Hq=16, Hkv=2, kv_dtype="fp8_e4m3")])
+@pytest.mark.parametrize("empty", EMPTY)
+@pytest.mark.parametrize("mode", ["calls", "select", "exact", "hetero"])
+def test_empty_contexts_streaming_kernels(kw, empty, mode):
+    """The same for the streaming passes: a context without a tile has no unit, no segment and no page, wherever it stands
+    among the others; an empty one between two that share a range, and a batch of nothing else."""
+    lens = [2, 40, 300, 1, 700, 33]
+    w = small(173, B=6, seq_lens=lens, budgets=[2, 9, 40, 1, 64, 8], allow_short=True, **kw)
+    run = GpuRun(w, flags=pa.PILLAR_FLAG_EXACT_SCORES if mode == "exact" else 0)
+    _emptied(w, run, empty)
+    for waves in (0, 1):
+        pa.pillar_set_option("verify_waves", waves)
+        try:
+            if mode == "select":
+                run.verify_select()
+            elif mode == "hetero":
+                spec = torch.full((w.B,), w.spec_k, dtype=torch.int32, device=run.dev)
+                pa.pillar_verify_hetero(run.dw.kv, run.dw.q, w.spec_k, spec, run.out, run.lse, run.scores, run.workspace,
+                                        budgets=run.dw.budgets, max_budget=run.max_budget, indices=run.indices, counts=run.counts)
+            else:
+                run.verify()
+                pa.pillar_select_topk(run.scores, run.dw.kv.seq_lens, run.dw.budgets, max(lens), run.max_budget, run.indices, run.counts,
+                                      run.workspace)
+            torch.cuda.synchronize()
+        finally:
+            pa.pillar_set_option("verify_waves", 0)
+        _check_with_empty_contexts(w, run, f"{mode}, contexts {empty} empty, verify_waves={waves}")
+
+
+@pytest.mark.parametrize("B,top", [(1100, 40), (3, 9000)])
+def test_empty_contexts_of_large_batches_and_long_rows(B, top):
+    """Every third context empty: the plan of a launch of its own (more than 1024 requests), and rows whose finish is
+    shared by several workgroups."""
+    rng = np.random.default_rng(B)
+    lens = rng.integers(1, top, size=B)
+    lens[1] = top
+    w = small(174, B=B, Hq=4, Hkv=1, spec_k=2, seq_lens=lens.tolist(), budgets=[4] * B, allow_short=True)
+    run = GpuRun(w)
+    _emptied(w, run, list(range(0, B, 3)))
+    run.verify_select()
+    torch.cuda.synchronize()
+    _check_with_empty_contexts(w, run, f"{B} requests, every third empty")
+
+
 # ------------------------------------------ the measured configs, reduced ----
 @pytest.mark.parametrize("cfg,batch", [(2, 2), (3, 4), (4, 1), (5, 2)])
 def test_config_reduced_batch(cfg, batch):
