@@ -156,7 +156,8 @@ int pillar_verify_select(const pillar_kv_t* kv, const void* q, int32_t spec_len_
  * With budgets / indices / counts non-NULL the critical tokens are selected as
  * by pillar_verify_select (all three NULL and max_budget 0: no selection).
  * Served by the matrix-core kernels only: bf16 queries, bf16 or fp8 KV,
- * head_dim 128, pages of >= 16 tokens, neither flag set; anything else returns
+ * head_dim 128, pages of >= 16 tokens, slots less than 2^32 / 3 (bf16) or
+ * 2^32 / 7 (fp8) bytes apart, neither flag set; anything else returns
  * PILLAR_EUNSUPPORTED.  seq_lens[b] >= spec_lens[b]+1 as above. */
 int pillar_verify_hetero(const pillar_kv_t* kv, const void* q, int32_t spec_len_max,
                          const int32_t* spec_lens, void* out, float* lse, float* scores,
@@ -211,7 +212,8 @@ int pillar_sparse_decode(const pillar_kv_t* kv, const void* q, const int32_t* in
  * chip.  (A draft sum may be grouped differently than by pillar_sparse_decode:
  * the results agree to rounding, not necessarily bit for bit, when a KV head
  * has more than 32 query rows.)  Either list may be empty.  Matrix-core shapes only (bf16 queries, bf16 or fp8 KV, head_dim
- * 128, pages of >= 16 tokens, rows of up to 32768 tokens, flags 0); anything
+ * 128, pages of >= 16 tokens, slots as close as pillar_verify_hetero takes them,
+ * rows of up to 32768 tokens, flags 0); anything
  * else returns PILLAR_EUNSUPPORTED.  Workspace: pillar_workspace_bytes(). */
 int pillar_mixed_step(const pillar_kv_t* kv, const int32_t* verify_ids, int32_t n_verify,
                       const int32_t* draft_ids, int32_t n_draft,

@@ -210,9 +210,9 @@ __device__ __forceinline__ void issue_tile(const KvView& kv, const Segment& sg, 
     const char* gv = static_cast<const char*>(kv.v_pool) + base;
 #pragma unroll
     for (int u = 0; u < kPerGroup; ++u) {
-      const uint32_t off = geo.lane_off + u * geo.row_step;
-      if constexpr (WITH_K) rk[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gk + off));
-      if constexpr (WITH_V) rv[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gv + off));
+      const int64_t step = u * geo.row_step;
+      if constexpr (WITH_K) rk[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gk + step + geo.lane_off));
+      if constexpr (WITH_V) rv[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gv + step + geo.lane_off));
     }
   }
 }
@@ -944,7 +944,7 @@ __device__ __forceinline__ void stretch_k(const KvView& kv, Stretch<FP8>& c, Str
     const char* src = static_cast<const char*>(kv.k_pool) + t.base[grp];
 #pragma unroll
     for (int u = 0; u < kPerGroup; ++u)
-      t.rows.k[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + geo.lane_off + u * geo.row_step));
+      t.rows.k[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + u * geo.row_step + geo.lane_off));
   }
 }
 template <bool FP8>
@@ -955,7 +955,7 @@ __device__ __forceinline__ void stretch_v(const KvView& kv, Stretch<FP8>& c, Str
     const char* src = static_cast<const char*>(kv.v_pool) + t.base[grp];
 #pragma unroll
     for (int u = 0; u < kPerGroup; ++u)
-      t.rows.v[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + geo.lane_off + u * geo.row_step));
+      t.rows.v[grp * kPerGroup + u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + u * geo.row_step + geo.lane_off));
   }
   c.tile += 1;
 }
@@ -1274,9 +1274,9 @@ __device__ __forceinline__ void issue_half(const KvView& kv, const Segment& sg, 
   const char* gv = static_cast<const char*>(kv.v_pool) + base;
 #pragma unroll
   for (int u = 0; u < kPerGroup; ++u) {
-    const uint32_t off = geo.lane_off + u * geo.row_step;
-    rk[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gk + off));
-    rv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gv + off));
+    const int64_t step = u * geo.row_step;
+    rk[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gk + step + geo.lane_off));
+    rv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gv + step + geo.lane_off));
   }
 }
 
@@ -2078,6 +2078,9 @@ bool verify_range_supported(const VerifyArgs& a) {
   if ((reinterpret_cast<uintptr_t>(kv.k_pool) | reinterpret_cast<uintptr_t>(kv.v_pool) | reinterpret_cast<uintptr_t>(a.q) |
        reinterpret_cast<uintptr_t>(a.out)) & 15u)
     return false;
+  // the rows of one load are addressed in 32 bits
+  const int64_t esz = a.kv_dtype == PILLAR_BF16 ? 2 : 1, rows = a.kv_dtype == PILLAR_BF16 ? LaneGeom<false>::kRowsPerLoad : LaneGeom<true>::kRowsPerLoad;
+  if (kv.stride_slot > ((int64_t{1} << 32) - kHeadDim * esz) / ((rows - 1) * esz)) return false;
   // the statistic is stored four tokens at a time
   if (a.scores && ((reinterpret_cast<uintptr_t>(a.scores) & 15u) || (a.score_stride & 3))) return false;
   // units are counted in 32 bits

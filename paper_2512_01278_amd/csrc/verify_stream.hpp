@@ -6,21 +6,24 @@
 namespace pillar {
 namespace {
 
-// Per-lane constants of the row-coalesced tile loads.
+// Per-lane constants of the row-coalesced tile loads.  A load covers kRowsPerLoad rows; how far apart they lie is the pool's
+// stride, which in a slot-major pool is a whole plane: from load to load the address moves in 64 bits (in scalar registers),
+// within a load in 32 (verify_range_supported sees to it that this is enough).
 template <bool FP8> struct LaneGeom {
-  uint32_t lane_off;   // byte offset of this lane's row (within a 16-token group) and column
-  uint32_t row_step;   // bytes between the rows two consecutive loads of a lane cover
+  static constexpr int kLanesPerRow = FP8 ? 8 : 16, kRowsPerLoad = kWave / kLanesPerRow;
+  uint32_t lane_off;   // byte offset of this lane's row and column from the load's first row
+  int64_t row_step;    // bytes between the rows two consecutive loads of a lane cover
   int row;             // this lane's row within the tile for load 0
 };
 
 template <bool FP8>
 __device__ __forceinline__ LaneGeom<FP8> lane_geom(const KvView& kv, int lane) {
-  constexpr int kLanesPerRow = FP8 ? 8 : 16;
+  using Geom = LaneGeom<FP8>;
   const int esz = FP8 ? 1 : 2;
-  LaneGeom<FP8> g;
-  g.row = lane / kLanesPerRow;
-  g.lane_off = static_cast<uint32_t>(g.row * kv.stride_slot * esz + (lane % kLanesPerRow) * 16);
-  g.row_step = static_cast<uint32_t>((64 / kLanesPerRow) * kv.stride_slot * esz);
+  Geom g;
+  g.row = lane / Geom::kLanesPerRow;
+  g.lane_off = static_cast<uint32_t>(g.row * kv.stride_slot * esz + (lane % Geom::kLanesPerRow) * 16);
+  g.row_step = Geom::kRowsPerLoad * kv.stride_slot * esz;
   return g;
 }
 

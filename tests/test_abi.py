@@ -174,3 +174,15 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
     monkeypatch.setattr(pb, "LIB_PATH", "/nonexistent/libpillar.so")
     with pytest.raises(RuntimeError, match="no fallback"):
         pb.load()
+
+
+@pytest.mark.parametrize("dtype,limit", [(pb.PILLAR_BF16, (2 ** 32 - 256) // (3 * 2)), (pb.PILLAR_FP8_E4M3, (2 ** 32 - 128) // 7)])
+def test_streaming_kernels_take_slot_strides_whose_rows_of_one_load_fit_32_bits(lib, dtype, limit):
+    """A load covers 4 rows of bf16 or 8 of fp8; an entry point without generic kernels behind it refuses what lies further
+    apart before it looks at the workspace."""
+    def hetero(stride):
+        s = good_kv(kv_dtype=dtype, k_scale=FAKE, v_scale=FAKE, stride_slot=stride)
+        return lib.pillar_verify_hetero(C.byref(s), FAKE, 4, FAKE, FAKE, None, FAKE, 1024, None, 0, None, None, None, 0, None)
+    below = limit // 16 * 16
+    assert hetero(below) == pb.PILLAR_EWORKSPACE
+    assert hetero(below + 16) == pb.PILLAR_EUNSUPPORTED

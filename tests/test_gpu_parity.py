@@ -620,7 +620,8 @@ def test_strided_pool_layout_and_wide_block_table():
 
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 def test_slot_major_pool(kv_dtype):
-    # pool stored [slot][page][head][dim]: rows of one page are a whole plane apart
+    """Pool stored [slot][page][head][dim]: rows of one page are a whole plane apart (a small one: the stride's way through the
+    kernels, not the width of the offsets)."""
     w = small(207, kv_dtype=kv_dtype, P=32, Hq=16, Hkv=2, spec_k=4, seq_lens=[5, 255, 1000], budgets=[5, 16, 512])
     run = GpuRun(w)
     kv = run.dw.kv
@@ -632,6 +633,23 @@ def test_slot_major_pool(kv_dtype):
     run.verify(with_scores=False)
     torch.cuda.synchronize()
     check_out(to_f64(run.out), oracle.verify_attn(w)[0], w.kv_dtype, "slot-major pool, no statistic")
+
+
+@pytest.mark.parametrize("kv_dtype,k,flags", [("bf16", 4, 0), ("fp8_e4m3", 4, 0), ("bf16", 8, 0), ("bf16", 4, pa.PILLAR_FLAG_EXACT_SCORES)])
+def test_slot_major_pool_wider_than_32_bits(kv_dtype, k, flags):
+    """Planes of 300 MB: the 16 rows of a page lie up to 4.5 GB apart, every load of a row group beyond a multiple of 2^32."""
+    w = small(208, kv_dtype=kv_dtype, Hq=16, Hkv=4, spec_k=k, seq_lens=[k + 1, 255, 1000], budgets=[5, 16, 512])
+    run = GpuRun(w, flags=flags)
+    kv = run.dw.kv
+    plane = 300_000_000 // kv.k_pool.element_size()
+    for name in ("k_pool", "v_pool"):
+        small_pool = getattr(kv, name)
+        wide = torch.empty((w.P - 1) * plane + w.num_pages * w.Hkv * w.D, dtype=small_pool.dtype, device=run.dev)
+        view = wide.as_strided(small_pool.shape, (w.Hkv * w.D, w.D, plane, 1))
+        view.copy_(small_pool)
+        setattr(kv, name, view)
+    run.run_all()
+    compare_with_oracle(w, run, None, f"planes of 300 MB, {kv_dtype}, k={k}, flags={flags}")
 
 
 def test_empty_selection_and_zero_budget():
