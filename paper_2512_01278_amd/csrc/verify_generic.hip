@@ -7,15 +7,16 @@
 // the softmax probabilities, averaged over those rows and the query heads of
 // one GQA group, are the score statistic that Top-K later reads.
 //
-// Two launches, both with one workgroup per (request, KV head, chunk of kChunk
-// tokens):
-//   split   logits of all R=(k+1)*G rows against the chunk, chunk-local
+// Two or three launches:
+//   split   one workgroup per (request, KV head, chunk of kChunk tokens):
+//           logits of all R=(k+1)*G rows against the chunk, chunk-local
 //           softmax, partial output -> workspace
-//   finish  log-sum-exp of every row from the partials; the workgroups of a
-//           (request, KV head) share its output; then logits again, now
-//           against the final lse: exp(s - lse) is the exact softmax
-//           probability; mean over rows
-// (The merge was a launch of its own with one workgroup per (request, KV head).)
+//   merge   (contexts of more than kInlineChunks chunks) one workgroup per
+//           (request, KV head, row): log-sum-exp and output from the partials
+//   finish  same grid as split: (up to kInlineChunks chunks) log-sum-exp of
+//           every row from the partials, and a share of the output; then
+//           logits again, now against the final lse: exp(s - lse) is the exact
+//           softmax probability; mean over rows
 #include "generic_rows.hpp"
 #include "launch.hpp"
 
@@ -25,11 +26,17 @@ namespace {
 constexpr int kChunk = 128;     // tokens per workgroup
 constexpr int kThreads = kGenThreads;
 
+// Without a merge launch every workgroup of the finish kernel reads the (m, l) of all chunks: quadratic in the context.  With
+// one of its own / without, fp32: 64 requests of 512 tokens 372 / 339 us, 8 of 1024 96.8 / 95.2, 8 of 2048 179 / 184, 8 of 32 K
+// 2416 / 4666, one of 2 M tokens 2.7 / 139 ms (with one workgroup per (request, KV head) instead of one per row: 101).
+constexpr int kInlineChunks = 8;
+
 struct GenericWs {
   float* part_m;   // [B][Hkv][NC][R]
-  float* part_l;   // [B][Hkv][NC][R]
+  float* part_l;   // [B][Hkv][NC][R]     (merged: the rows' log-sum-exp in chunk 0's place)
   float* part_o;   // [B][Hkv][NC][R][D]
   int nc;
+  bool merged;     // a launch of its own merges (NC > kInlineChunks)
 };
 
 __host__ __device__ inline int num_chunks(int max_seq_len) { return (max_seq_len + kChunk - 1) / kChunk; }
@@ -148,22 +155,89 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
   }
 }
 
-template <int QDT, int KVDT, int D>
+// log-sum-exp of a row with maximum m and sum l; a row that sees no token at all (l = 0) has +inf, no weight in the statistic,
+// and the caller gets -inf
+__device__ __forceinline__ float row_lse(float m, float l) { return l > 0.f ? m + __logf(l) : INFINITY; }
+__device__ __forceinline__ float lse_for_caller(float v) { return v == INFINITY ? -INFINITY : v; }
+
+// Chunks are taken in turn by kParts groups of D threads, a dimension per thread.
+constexpr int kMergeThreads = 1024;
+template <int QDT, int D>
+__global__ __launch_bounds__(kMergeThreads) void verify_merge_generic(KvView kv, int n_q, GenericWs ws, void* out, float* lse_out) {
+  constexpr int kParts = kMergeThreads / D, kWaves = kMergeThreads / kWave;
+  __shared__ float s_m[kWaves], s_l[kWaves], s_o[kMergeThreads];
+  const int b = blockIdx.z, g = blockIdx.y, r = blockIdx.x;
+  const int G = kv.num_q_heads / kv.num_kv_heads;
+  const int R = n_q * G;
+  const int nc = (max(kv.seq_lens[b], 0) + kChunk - 1) / kChunk;
+  const int64_t base = ((static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc) * R + r;      // (m, l) of chunk 0; R floats from chunk to chunk
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  float m = -INFINITY;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < nc; i += kMergeThreads) m = fmaxf(m, ws.part_m[base + static_cast<int64_t>(i) * R]);
+  m = wave_max(m);
+  if (lane == 0) s_m[wave] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) m = fmaxf(m, s_m[w]);
+  auto weight = [&](float mc) { return mc == -INFINITY ? 0.f : __expf(mc - m); };
+  float l = 0.f;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < nc; i += kMergeThreads) l = fmaf(ws.part_l[base + static_cast<int64_t>(i) * R], weight(ws.part_m[base + static_cast<int64_t>(i) * R]), l);
+  l = wave_sum(l);
+  if (lane == 0) s_l[wave] = l;
+  const int d = threadIdx.x & (D - 1);
+  float o = 0.f;
+#pragma unroll 4
+  for (int i = threadIdx.x / D; i < nc; i += kParts) {
+    const int64_t at = base + static_cast<int64_t>(i) * R;
+    o = fmaf(ws.part_o[at * D + d], weight(ws.part_m[at]), o);
+  }
+  s_o[threadIdx.x] = o;
+  __syncthreads();
+  if (threadIdx.x >= D) return;
+  l = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) l += s_l[w];
+#pragma unroll
+  for (int p = 1; p < kParts; ++p) o += s_o[p * D + d];
+  const int i = r / G, hg = r - i * G;
+  const int64_t row = (static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg;
+  Storage<QDT>::store(out, row * D + d, l > 0.f ? o / l : 0.f);
+  if (d == 0) {
+    const float v = row_lse(m, l);
+    ws.part_l[base] = v;                       // (read before the last barrier by the threads that needed it)
+    if (lse_out) lse_out[row] = lse_for_caller(v);
+  }
+}
+
+template <int QDT, int KVDT, int D, bool MERGED>
 __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, const void* q, int n_q, GenericWs ws, void* out, float* lse_out,
                                                                    float* scores, int64_t score_stride) {
   __shared__ GenericLds lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
   const int t0 = c * kChunk;
-  if (t0 >= L && c > 0) return;                // an empty context has a workgroup too: zeros, lse = -inf
-  const int nc = (max(L, 0) + kChunk - 1) / kChunk;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int nt = min(kChunk, max(L - t0, 0));
+  if (t0 >= L) {
+    if (!MERGED && c == 0) {                   // an empty context: no query sees a token
+      for (int idx = threadIdx.x; idx < R * D; idx += kThreads) {
+        const int r = idx / D, i = r / G, hg = r - i * G;
+        const int64_t row = (static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg;
+        Storage<QDT>::store(out, row * D + (idx & (D - 1)), 0.f);
+        if (lse_out && (idx & (D - 1)) == 0) lse_out[row] = -INFINITY;
+      }
+    }
+    return;
+  }
+  const int nc = (L + kChunk - 1) / kChunk;
+  const int nt = min(kChunk, L - t0);
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
   if (scores) resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
-  // log-sum-exp of every row: four threads per row take the chunks in turn
-  {
+  if constexpr (MERGED) {
+    if (threadIdx.x < R) lds.lse[threadIdx.x] = ws.part_l[base * R + threadIdx.x];
+  } else {                                     // log-sum-exp of every row: four threads per row take the chunks in turn
     const int r = threadIdx.x / 4, part = threadIdx.x & 3;
     float m = -INFINITY, l = 0.f;
     if (r < R)
@@ -180,34 +254,32 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
     l += __shfl_xor(l, 1, kWave);
     l += __shfl_xor(l, 2, kWave);
     if (r < R && part == 0) {
-      const bool live = l > 0.f;               // false for a row that sees no token at all: zeros, lse = -inf
-      const float v = m + __logf(l);
-      lds.lse[r] = live ? v : INFINITY;        // +inf: no weight in the output and the statistic
+      const float v = row_lse(m, l);
+      lds.lse[r] = v;
       if (c == 0 && lse_out) {
         const int i = r / G, hg = r - i * G;
-        lse_out[(static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg] = live ? v : -INFINITY;
+        lse_out[(static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg] = lse_for_caller(v);
       }
       lds.q[r] = m;                            // for the weights of the output (the query rows come later)
-      lds.q[kMaxRows + r] = live ? l : 0.f;
+      lds.q[kMaxRows + r] = l > 0.f ? l : 0.f;
     }
-  }
-  __syncthreads();
-  // this workgroup's share of the output
-  const int n_share = max(nc, 1);
-  for (int idx = c * R * D / n_share + threadIdx.x; idx < (c + 1) * R * D / n_share; idx += kThreads) {
-    const int r = idx / D, d = idx & (D - 1);
-    float o = 0.f;
+    __syncthreads();
+    // this workgroup's share of the output
+    for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {      // (c < kInlineChunks)
+      const int r = idx / D, d = idx & (D - 1);
+      float o = 0.f;
 #pragma unroll 4
-    for (int i = 0; i < nc; ++i) {
-      const float mc = ws.part_m[(base + i) * R + r];
-      const float w = (mc == -INFINITY) ? 0.f : __expf(mc - lds.q[r]);
-      o = fmaf(ws.part_o[((base + i) * R + r) * D + d], w, o);
+      for (int i = 0; i < nc; ++i) {
+        const float mc = ws.part_m[(base + i) * R + r];
+        const float w = (mc == -INFINITY) ? 0.f : __expf(mc - lds.q[r]);
+        o = fmaf(ws.part_o[((base + i) * R + r) * D + d], w, o);
+      }
+      const int i = r / G, hg = r - i * G;
+      Storage<QDT>::store(out, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d,
+                          lds.q[kMaxRows + r] > 0.f ? o / lds.q[kMaxRows + r] : 0.f);
     }
-    const int i = r / G, hg = r - i * G;
-    Storage<QDT>::store(out, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d,
-                        lds.q[kMaxRows + r] > 0.f ? o / lds.q[kMaxRows + r] : 0.f);
   }
-  if (!scores || L <= 0) return;
+  if (!scores) return;
   __syncthreads();                             // the query rows take the place of the weights
   const float inv_r = 1.0f / static_cast<float>(R);
   float sum = 0.f;                             // of this thread's token
@@ -236,6 +308,7 @@ GenericWs carve(const KvView& kv, int n_q, void* workspace) {
   char* p = static_cast<char*>(workspace);
   GenericWs w;
   w.nc = static_cast<int>(nc);
+  w.merged = nc > kInlineChunks;
   w.part_m = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
   w.part_l = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
   w.part_o = reinterpret_cast<float*>(p);
@@ -251,10 +324,15 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
     KernelTimer t("verify_split_generic", st);
     hipLaunchKernelGGL((verify_split_generic<QDT, KVDT, D>), grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws);
   }
-  {
+  if (ws.merged) {
+    KernelTimer t("verify_merge_generic", st);
+    const int R = a.n_q * (kv.num_q_heads / kv.num_kv_heads);
+    hipLaunchKernelGGL((verify_merge_generic<QDT, D>), dim3(R, kv.num_kv_heads, kv.batch), dim3(kMergeThreads), 0, st, kv, a.n_q, ws, a.out, a.lse);
+  }
+  if (!ws.merged || a.scores) {
     KernelTimer t("verify_finish_generic", st);
-    hipLaunchKernelGGL((verify_finish_generic<QDT, KVDT, D>), grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws, a.out, a.lse, a.scores,
-                       a.score_stride);
+    const auto kernel = ws.merged ? verify_finish_generic<QDT, KVDT, D, true> : verify_finish_generic<QDT, KVDT, D, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws, a.out, a.lse, a.scores, a.score_stride);
   }
   return hipGetLastError();
 }

@@ -168,6 +168,56 @@ def test_generic_kernels_at_their_edges(q_dtype, kv_dtype, D, heads, k):
     round_trip(w, what="generic kernels, edges", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
 
 
+@pytest.mark.parametrize("q_dtype,kv_dtype,D,heads,k", [("f32", "f32", 64, 4, 4), ("bf16", "fp8_e4m3", 128, 4, 15), ("f32", "bf16", 128, 2, 0)])
+@pytest.mark.parametrize("top", [1024, 1025, 2500])
+def test_generic_kernels_around_the_merge_launch(q_dtype, kv_dtype, D, heads, k, top):
+    """Batches whose longest context has 8 chunks of 128 tokens (merged by the finish kernel), one token more, and many more
+    (a launch of its own); contexts of one chunk and of none among them."""
+    lens = [top, k + 1, 128, 129, 1023, 700]
+    w = small(240 + k, q_dtype=q_dtype, kv_dtype=kv_dtype, D=D, P=8, B=len(lens), Hq=2 * heads, Hkv=2, spec_k=k, seq_lens=lens,
+              budgets=[min(n, 40) for n in lens])
+    flags = pa.PILLAR_FLAG_GENERIC_KERNELS
+    run, _ = round_trip(w, what=f"generic kernels, {top} tokens", flags=flags)
+    alone = GpuRun(w, flags=flags)                       # and without the statistic
+    alone.verify(with_scores=False)
+    torch.cuda.synchronize()
+    assert torch.equal(alone.out, run.out) and torch.equal(alone.lse, run.lse)
+    run.scores.fill_(float("nan"))
+    _emptied(w, run, [1, 3])
+    run.verify()
+    run.topk()
+    torch.cuda.synchronize()
+    _check_with_empty_contexts(w, run, f"generic kernels, {top} tokens and empty contexts")
+
+
+def test_generic_kernels_on_a_context_whose_partials_pass_2_to_31_elements():
+    """64 rows of 128 dims and 262 500 chunks (33.6 M tokens): index products of chunk, row and dim pass 2^31.  Every page-table
+    entry names the same page, so a row sees each of its 256 tokens about 131 250 times, and the softmax over the counts is
+    the reference.  Tolerance: 262 500 partials, 1/8 of them summed in turn in fp32: 32 800 * 2^-24 = 2e-3 at worst."""
+    dev = torch.device("cuda:0")
+    chunks, P, D, G, n_q = 262_500, 256, 128, 16, 4
+    L = chunks * 128 - 77
+    gen_ = torch.Generator().manual_seed(5)
+    k, v = (torch.randn(1, 1, P, D, generator=gen_) for _ in range(2))
+    q = torch.randn(1, n_q, G, D, generator=gen_)
+    kv = pa.KvCache(k_pool=k.to(dev), v_pool=v.to(dev), block_table=torch.zeros(1, -(-L // P), dtype=torch.int32, device=dev),
+                    seq_lens=torch.tensor([L], dtype=torch.int32, device=dev), num_q_heads=G, q_dtype="f32", kv_dtype="f32",
+                    sm_scale=D ** -0.5, max_seq_len=L)
+    workspace = torch.empty(pa.pillar_workspace_bytes(kv, n_q - 1, 1), dtype=torch.uint8, device=dev)
+    out = torch.full((1, n_q, G, D), float("nan"), device=dev)
+    lse = torch.full((1, n_q, G), float("nan"), device=dev)
+    pa.pillar_verify_attn(kv, q.to(dev), n_q - 1, out, lse, None, workspace)
+    torch.cuda.synchronize()
+    for i in range(n_q):
+        seen = L - n_q + i + 1                           # tokens the query sees
+        count = (seen // P + (torch.arange(P) < seen % P)).double()
+        logits = q[0, i].double() @ k[0, 0].double().T * D ** -0.5 + count.log()
+        want = torch.softmax(logits, dim=1) @ v[0, 0].double()
+        err = (out[0, i].cpu().double() - want).norm() / want.norm()
+        assert err <= 2e-3, f"query {i}: rel error {err:.2e}"
+        assert (lse[0, i].cpu().double() - torch.logsumexp(logits, 1)).abs().max() <= 2e-3
+
+
 def _floor_workload():
     """One request, one KV head, every query row the same vector 8 e_0, keys x_t e_0: the base-2 logit of token t is
     1.02 x_t for every row.  Token 0 has x = 64, the others sweep [-6, 6] every 128 tokens: their probabilities run from 2^-71 to
