@@ -471,6 +471,23 @@ def test_stretches_at_their_edges(kv_dtype, page, heads, k):
             pa.pillar_set_option("verify_waves", 0)
 
 
+@pytest.mark.parametrize("kv_dtype,heads,k", [("fp8_e4m3", 8, 2), ("fp8_e4m3", 16, 4), ("fp8_e4m3", 16, 7), ("bf16", 16, 4), ("bf16", 8, 8)])
+def test_output_does_not_depend_on_the_statistic(kv_dtype, heads, k):
+    """With and without the score statistic the pass does the same arithmetic, so the outputs agree bit for bit: page scales that
+    bf16 holds exactly (nothing hides the rounding of a probability) and logits whose maximum keeps rising along the context."""
+    w = small(220 + k, kv_dtype=kv_dtype, Hq=heads, Hkv=2, spec_k=k, seq_lens=[k + 1, 700, 3000], budgets=[k + 1, 40, 64], pillar_gain=6.0)
+    if kv_dtype == "fp8_e4m3":
+        w.k_scale[:] = 2.0 ** -6
+        w.v_scale[:] = 2.0 ** -7
+    run, bare = GpuRun(w), GpuRun(w)
+    run.verify()
+    bare.verify(with_scores=False)
+    torch.cuda.synchronize()
+    assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
+    want, want_lse, _ = oracle.verify_attn(w)
+    check_out(to_f64(bare.out), want, kv_dtype, "output without the statistic")
+
+
 # -------------------------------------------- index lists from other sources ----
 def test_window_and_tail_lists_match_the_oracle_and_feed_the_draft():
     """Static sink + window lists and the post-verification tail: integer-exact against the oracle,
