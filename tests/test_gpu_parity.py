@@ -474,15 +474,20 @@ def test_stretches_at_their_edges(kv_dtype, page, heads, k):
 @pytest.mark.parametrize("kv_dtype,heads,k", [("fp8_e4m3", 8, 2), ("fp8_e4m3", 16, 4), ("fp8_e4m3", 16, 7), ("bf16", 16, 4), ("bf16", 8, 8)])
 def test_output_does_not_depend_on_the_statistic(kv_dtype, heads, k):
     """With and without the score statistic the pass does the same arithmetic, so the outputs agree bit for bit: page scales that
-    bf16 holds exactly (nothing hides the rounding of a probability) and logits whose maximum keeps rising along the context."""
-    w = small(220 + k, kv_dtype=kv_dtype, Hq=heads, Hkv=2, spec_k=k, seq_lens=[k + 1, 700, 3000], budgets=[k + 1, 40, 64], pillar_gain=6.0)
+    bf16 holds exactly (nothing hides the rounding of a probability), and few wide ranges, so that a wavefront takes several
+    tiles and its maximum rises on the way."""
+    w = small(220 + k, kv_dtype=kv_dtype, Hq=heads, Hkv=2, spec_k=k, seq_lens=[k + 1, 9000, 12000], budgets=[k + 1, 40, 64])
     if kv_dtype == "fp8_e4m3":
         w.k_scale[:] = 2.0 ** -6
         w.v_scale[:] = 2.0 ** -7
     run, bare = GpuRun(w), GpuRun(w)
-    run.verify()
-    bare.verify(with_scores=False)
-    torch.cuda.synchronize()
+    pa.pillar_set_option("verify_waves", 1)
+    try:
+        run.verify()
+        bare.verify(with_scores=False)
+        torch.cuda.synchronize()
+    finally:
+        pa.pillar_set_option("verify_waves", 0)
     assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
     want, want_lse, _ = oracle.verify_attn(w)
     check_out(to_f64(bare.out), want, kv_dtype, "output without the statistic")
@@ -704,11 +709,12 @@ def test_slot_major_pool(kv_dtype):
 
 @pytest.mark.parametrize("kv_dtype,k,flags", [("bf16", 4, 0), ("fp8_e4m3", 4, 0), ("bf16", 8, 0), ("bf16", 4, pa.PILLAR_FLAG_EXACT_SCORES)])
 def test_slot_major_pool_wider_than_32_bits(kv_dtype, k, flags):
-    """Planes of 300 MB: the 16 rows of a page lie up to 4.5 GB apart, every load of a row group beyond a multiple of 2^32."""
+    """Planes of 560 MB: the rows of a page lie up to 8.4 GB apart, and from a group's first load to its last it is more than
+    2^32 bytes, with fp8 (two loads of 8 rows) as with bf16 (four of 4)."""
     w = small(208, kv_dtype=kv_dtype, Hq=16, Hkv=4, spec_k=k, seq_lens=[k + 1, 255, 1000], budgets=[5, 16, 512])
     run = GpuRun(w, flags=flags)
     kv = run.dw.kv
-    plane = 300_000_000 // kv.k_pool.element_size()
+    plane = 560_000_000 // kv.k_pool.element_size()
     for name in ("k_pool", "v_pool"):
         small_pool = getattr(kv, name)
         wide = torch.empty((w.P - 1) * plane + w.num_pages * w.Hkv * w.D, dtype=small_pool.dtype, device=run.dev)
@@ -716,7 +722,7 @@ def test_slot_major_pool_wider_than_32_bits(kv_dtype, k, flags):
         view.copy_(small_pool)
         setattr(kv, name, view)
     run.run_all()
-    compare_with_oracle(w, run, None, f"planes of 300 MB, {kv_dtype}, k={k}, flags={flags}")
+    compare_with_oracle(w, run, None, f"planes of 560 MB, {kv_dtype}, k={k}, flags={flags}")
 
 
 def test_empty_selection_and_zero_budget():
