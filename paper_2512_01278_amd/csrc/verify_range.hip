@@ -374,24 +374,26 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
   }
 }
 
-// `publish`: this wavefront also writes its share of the plan to memory (one of those that share a range)
-__device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish = true) {
-  Cursor c;
-  c.w = w;
+// Where a range begins: its units and its first segment.  `publish`: this wavefront also writes its share of the plan to
+// memory (one of those that share a range).
+struct RangeStart {
+  int unit, end;
+  Segment sg;
+  bool live;
+};
+
+__device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
+  RangeStart c;
   c.sg = Segment{};
-  c.tile = 0;
-  c.pw = PageWin{};
-  c.pg_next = 0;
-  c.len_next = 0;
   Segment sg;
   int first_unit;                              // of the request the range begins in
   if (ws.plan_in_wave) {                       // the same for the whole grid
     const WavePlan p = wave_plan(kv, lane);
     if (publish) publish_plan(kv, ws, p, w, lane);
     const int n = ranges_used(ws, p.total);
-    c.unit = range_begin(c.w, p.total, n);
-    c.end = range_begin(c.w + 1, p.total, n);
-    c.live = c.w < n && c.unit < c.end;        // (a batch of empty contexts has one range of nothing)
+    c.unit = range_begin(w, p.total, n);
+    c.end = range_begin(w + 1, p.total, n);
+    c.live = w < n && c.unit < c.end;          // (a batch of empty contexts has one range of nothing)
     if (!c.live) return c;
     int upto = 0;                              // requests that begin at or before the unit
 #pragma unroll
@@ -405,9 +407,9 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
   } else {
     const int total = ws.ctrl[0];
     const int n = ranges_used(ws, total);
-    c.unit = range_begin(c.w, total, n);
-    c.end = range_begin(c.w + 1, total, n);
-    c.live = c.w < n && c.unit < c.end;        // (a batch of empty contexts has one range of nothing)
+    c.unit = range_begin(w, total, n);
+    c.end = range_begin(w + 1, total, n);
+    c.live = w < n && c.unit < c.end;
     if (!c.live) return c;
     sg.b = find_request(ws, kv.batch, c.unit, lane);
     sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
@@ -420,12 +422,27 @@ __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& w
   sg.tile0 = rel - sg.g * sg.tiles;
   sg.tile1 = min(sg.tiles, sg.tile0 + (c.end - c.unit));
   sg.pair = sg.b * kv.num_kv_heads + sg.g;
-  sg.slot = sg.pair + c.w;
+  sg.slot = sg.pair + w;
   c.sg = sg;
-  c.tile = sg.tile0;
-  c.pw.win = ((sg.tile0 * kTileTokens) >> kv.page_shift) / kWindowPages;
-  c.pw.pg_a = load_window(kv, sg.b, c.pw.win, lane);
-  c.pw.pg_b = load_window(kv, sg.b, c.pw.win + 1, lane);
+  return c;
+}
+
+__device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& ws, int w, int lane) {
+  const RangeStart start = open_range(kv, ws, w, lane, true);
+  Cursor c;
+  c.w = w;
+  c.unit = start.unit;
+  c.end = start.end;
+  c.sg = start.sg;
+  c.live = start.live;
+  c.tile = c.sg.tile0;
+  c.pw = PageWin{};
+  c.pg_next = 0;
+  c.len_next = 0;
+  if (!c.live) return c;
+  c.pw.win = ((c.sg.tile0 * kTileTokens) >> kv.page_shift) / kWindowPages;
+  c.pw.pg_a = load_window(kv, c.sg.b, c.pw.win, lane);
+  c.pw.pg_b = load_window(kv, c.sg.b, c.pw.win + 1, lane);
   prefetch_following(kv, c, lane);
   return c;
 }
@@ -828,11 +845,17 @@ template <int RB> struct FlashRows {
   }
 };
 
-// Shapes of the query rows of one KV head, the same for a whole launch (R, nv, tile_lanes) or for one request (nq_b, Rb).
+// Shapes of the query rows of one KV head, the same for a whole launch (all but the last two) or for one request (nq_b, Rb).
 struct RowGeom {
   int n_q, G, R;         // query slots, heads per KV head, rows
   int nv, tile_lanes;    // rows of the last block; lanes that stash a tile
+  int inv_g, skip;       // 2^16 / G rounded up; heads between the last of a query's rows and the first of the next query's
   int nq_b, Rb;          // query positions and rows of the request
+  // r / G: exact for r < 2^16 / G, and G <= 16, r < 64
+  __device__ __forceinline__ int query(int r) const { return (r * inv_g) >> 16; }
+  // elements of q and out between the first row of a (request, KV head) and row r of its rows
+  __device__ __forceinline__ int64_t row(int r) const { return static_cast<int64_t>(r + query(r) * skip) * kHeadDim; }
+  __device__ __forceinline__ int64_t first_row(int rq, int g) const { return (static_cast<int64_t>(rq) * n_q * (G + skip) + g * G) * kHeadDim; }
 };
 
 __device__ __forceinline__ RowGeom row_geom(const KvView& kv, int n_q, int row_blocks) {
@@ -842,31 +865,35 @@ __device__ __forceinline__ RowGeom row_geom(const KvView& kv, int n_q, int row_b
   r.R = n_q * r.G;
   r.nv = r.R - 16 * (row_blocks - 1);
   r.tile_lanes = (row_blocks - 1) * 64 + 4 * r.nv;
+  r.inv_g = ((1 << 16) + r.G - 1) / r.G;
+  r.skip = kv.num_q_heads - r.G;
   r.nq_b = n_q;
   r.Rb = r.R;
   return r;
 }
 
-// Q rows of a pair -> LDS by THREADS threads, in K-tile layout (row R is the zero row of the padding)
+// Q rows of a pair -> LDS by THREADS threads, in K-tile layout (row R is the zero row of the padding), a few pieces of a thread at
+// a time
 template <int RB, int THREADS>
-__device__ __forceinline__ void q_to_lds(const KvView& kv, const uint16_t* q, const RowGeom& rg, int rq, int g, uint8_t* s_q, int tid) {
-  constexpr int kQIters = ((RB * 16 + 1) * 16 + THREADS - 1) / THREADS;
-  u32x4 qtmp[kQIters];
+__device__ __forceinline__ void q_to_lds(const uint16_t* q, const RowGeom& rg, int rq, int g, uint8_t* s_q, int tid) {
+  constexpr int kQIters = ((RB * 16 + 1) * 16 + THREADS - 1) / THREADS, kAtOnce = kQIters > 4 ? 4 : kQIters;
+  const uint16_t* src = q + rg.first_row(rq, g);
+#pragma unroll 1
+  for (int j0 = 0; j0 < kQIters; j0 += kAtOnce) {
+    u32x4 qtmp[kAtOnce];
 #pragma unroll
-  for (int j = 0; j < kQIters; ++j) {
-    const int ch = tid + THREADS * j;
-    const int r = ch >> 4, c = ch & 15;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (r < rg.Rb) {
-      const int i = r / rg.G, hg = r - i * rg.G;
-      v = *reinterpret_cast<const u32x4*>(q + ((static_cast<int64_t>(rq) * rg.n_q + i) * kv.num_q_heads + g * rg.G + hg) * kHeadDim + 8 * c);
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int ch = tid + THREADS * (j0 + j);
+      const int r = ch >> 4, c = ch & 15;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (r < rg.Rb) v = *reinterpret_cast<const u32x4*>(src + rg.row(r) + 8 * c);
+      qtmp[j] = v;
     }
-    qtmp[j] = v;
-  }
 #pragma unroll
-  for (int j = 0; j < kQIters; ++j) {
-    const int ch = tid + THREADS * j;
-    if (ch < (rg.R + 1) * 16) *reinterpret_cast<u32x4*>(s_q + k_lds_addr(ch >> 4, ch & 15)) = qtmp[j];
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int ch = tid + THREADS * (j0 + j);
+      if (ch < (rg.R + 1) * 16) *reinterpret_cast<u32x4*>(s_q + k_lds_addr(ch >> 4, ch & 15)) = qtmp[j];
+    }
   }
 }
 
@@ -884,6 +911,16 @@ template <bool FP8> struct StretchTile {
   TileRegs<FP8> rows;
   uint64_t base[2];        // byte offsets of the two 16-token groups in the pools
   float ks[2], vs[2];
+  // No tile: any contents.  Left undefined, the registers' old contents would be kept for it all through the loop over segments.
+  __device__ __forceinline__ void leave() {
+#pragma unroll
+    for (int u = 0; u < TileRegs<FP8>::kLoads; ++u) {
+      asm volatile("" : "=v"(rows.k[u]));
+      asm volatile("" : "=v"(rows.v[u]));
+    }
+    base[0] = base[1] = 0;
+    ks[0] = ks[1] = vs[0] = vs[1] = 1.f;
+  }
 };
 
 template <bool FP8>
@@ -901,7 +938,7 @@ __device__ __forceinline__ void stretch_window(const KvView& kv, Stretch<FP8>& c
   }
 }
 template <bool FP8>
-__device__ __forceinline__ Stretch<FP8> open_stretch(const KvView& kv, int rq, int g, int L, int t0, int lane) {
+__device__ __forceinline__ Stretch<FP8> open_stretch(const KvView& kv, int rq, int g, int L, int t0, int first_ids, int lane) {
   Stretch<FP8> c;
   c.rq = rq;
   c.g = g;
@@ -910,7 +947,9 @@ __device__ __forceinline__ Stretch<FP8> open_stretch(const KvView& kv, int rq, i
   c.tile = t0;
   c.win = ((t0 * kTileTokens) >> kv.page_shift) / kWindowPages;
   c.ks = c.vs = 1.f;
-  const int ids = stretch_ids(kv, c, c.win, lane);
+  // lane j of first_ids: page j of the request where it has one
+  int ids = lane <= c.last_page ? first_ids : __builtin_amdgcn_readfirstlane(first_ids);
+  if (c.win > 0) ids = stretch_ids(kv, c, c.win, lane);
   c.next = stretch_ids(kv, c, c.win + 1, lane);
   stretch_window(kv, c, ids);
   return c;
@@ -1054,7 +1093,7 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const int r = 16 * rb + n;
-      const int last = c.L - rg.nq_b + (r < rg.Rb ? r / rg.G : rg.nq_b - 1);
+      const int last = c.L - rg.nq_b + (r < rg.Rb ? rg.query(r) : rg.nq_b - 1);
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
@@ -1112,36 +1151,192 @@ template <int RB, int W> struct TeamLds {
   static constexpr int kORow = kHeadDim * 4 + 16;            // a row of O on its way between wavefronts
   static_assert(16 * kORow <= kVTileBytes, "a block of O fits a tile buffer");
   __attribute__((aligned(16))) uint8_t tile[W * kVTileBytes];
-  __attribute__((aligned(16))) uint8_t q[(RB * 16 + 1) * kKRow];
+  static constexpr int kQBytes = (RB * 16 + 1) * kKRow;
+  static constexpr int kSolo = RB >= 3 ? 3 : W;              // wavefronts that take short segments (two workgroups share 160 KB)
+  __attribute__((aligned(16))) uint8_t q[kQBytes];
   float m[W * RB * 16], l[W * RB * 16];
+  __attribute__((aligned(16))) uint8_t solo_q[(kSolo - 1) * kQBytes];        // last: what the team uses stays below 64 KB, in reach of an offset
 };
+
+// A value of which the compiler knows nothing: what is worked out from it stays where it is written.  Addresses of the parts that run
+// once per segment, hoisted out of the loop over segments, would hold registers through the loop over tiles and spill.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// ------------------------------------------ segments of a range -----------
+// The segments of a range one after the other.  The lengths of 64 requests wait in a register, one per lane, and the first 64 page
+// ids of this request and of the next one in two more, so that entering a segment waits for no table.
+struct Walk {
+  int unit, end, w;        // first unit of the segment, end of the range, index of the range
+  Segment sg;
+  int lens, len0;          // lane j: length of request len0 + j of the launch
+  int ids, ids_next;       // lane j: page j of the segment's request / of the request after it
+  bool live;
+};
+
+__device__ __forceinline__ int load_lengths(const KvView& kv, int b, int lane) { return kv.seq_lens[request_of(kv, min(b + lane, kv.batch - 1))]; }
+
+__device__ __forceinline__ Walk open_walk(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
+  const RangeStart start = open_range(kv, ws, w, lane, publish);
+  Walk c;
+  c.w = w;
+  c.unit = start.unit;
+  c.end = start.end;
+  c.sg = uniform(start.sg);
+  c.live = start.live;
+  c.len0 = c.sg.b;
+  c.ids = load_window(kv, c.sg.b, 0, lane);
+  c.lens = load_lengths(kv, c.sg.b, lane);
+  c.ids_next = load_window(kv, min(c.sg.b + 1, kv.batch - 1), 0, lane);
+  return c;
+}
+
+__device__ __forceinline__ void next_segment(const KvView& kv, Walk& c, int lane) {
+  Segment& sg = c.sg;
+  c.unit += sg.tile1 - sg.tile0;
+  c.live = c.unit < c.end;
+  if (!c.live) return;
+  sg.g += 1;
+  if (sg.g == kv.num_kv_heads) {
+    sg.g = 0;
+    int skipped = -1;
+    do {                                       // (an empty context has no tile; units are left, so there is one that has)
+      sg.b += 1;
+      skipped += 1;
+      if (sg.b - c.len0 >= kWave) {
+        c.len0 = sg.b;
+        c.lens = load_lengths(kv, sg.b, lane);
+      }
+      sg.L = __builtin_amdgcn_readlane(c.lens, sg.b - c.len0);
+    } while (sg.L <= 0 && sg.b + 1 < kv.batch);
+    sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
+    sg.tiles = tiles_of_len(sg.L);
+    c.ids = c.ids_next;
+    if (__builtin_expect(skipped > 0, 0)) c.ids = load_window(kv, sg.b, 0, lane);
+    c.ids_next = load_window(kv, min(sg.b + 1, kv.batch - 1), 0, lane);
+  }
+  sg.tile0 = 0;
+  sg.tile1 = min(sg.tiles, c.end - c.unit);
+  sg.pair = sg.b * kv.num_kv_heads + sg.g;
+  sg.slot = sg.pair + c.w;
+}
+
+// (m, l) and O of a segment that one wavefront went through alone: final when it is the whole pair, else a partial.
+template <int RB>
+__device__ __forceinline__ void store_solo(const RangeWs& ws, const RowGeom& rg, const Segment& cs, const FlashRows<RB>& st,
+                                           uint16_t* out, int lane) {
+  const int n = lane & 15, g4 = lane >> 4;
+  const bool whole = cs.tile0 == 0 && cs.tile1 == cs.tiles;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float l = sum_over_groups(st.l[rb]);
+    const int r = 16 * rb + n;
+    if (g4 == 0) {
+      ws.part_m[static_cast<int64_t>(cs.slot) * (RB * 16) + r] = st.m[rb];
+      ws.part_l[static_cast<int64_t>(cs.slot) * (RB * 16) + r] = l;
+    }
+    if (r >= rg.Rb) continue;                  // rows of query slots the request does not use are left alone
+    if (whole) {
+      const float inv = l > 0.f ? 1.0f / l : 0.f;            // a row that sees no token: zeros
+      uint16_t* dst = out + rg.first_row(cs.rq, cs.g) + rg.row(r) + 4 * g4;
+#pragma unroll
+      for (int db = 0; db < 8; ++db) {
+        u32x2 pk;
+        pk.x = pack2(st.o[rb][db][0] * inv, st.o[rb][db][1] * inv);
+        pk.y = pack2(st.o[rb][db][2] * inv, st.o[rb][db][3] * inv);
+        *reinterpret_cast<u32x2*>(dst + 16 * db) = pk;
+      }
+    } else {
+      float* dst = ws.part_o + (static_cast<int64_t>(cs.slot) * rg.R + r) * kHeadDim + 4 * g4;
+#pragma unroll
+      for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = st.o[rb][db];
+    }
+  }
+}
+
+// Short segments: shared by the wavefronts, one leaves them with a tile or two each, or none, and all wait at the barriers of its
+// merge.  Where as many units are left in the range as that many segments alike would have, the wavefronts take the segments in
+// turn instead, each with Q rows of its own, as long as the next one is short too.  Shared / up to 3, 6, 12, 24, 48 tiles: 300
+// requests of 20-8000 tokens, their logarithms spread evenly, fp8 and 40 rows 553 / 423, 399, 385, 402, 419 us, with bf16, 20 rows
+// and no statistic 373 / 307, 295, 292, 278, 286; 1000 requests of 32-64 tokens 223 / 175 with all, of 256-512 498 / 502, 503, 485,
+// 479, 479; 128 of 1-8 K tokens 519 up to 24, 537 with 48.  (A range per wavefront, before the teams: 452, 354, 266, 553, 551.)
+constexpr int kSoloTiles = 12;
+__device__ __forceinline__ bool solo_segment(const Walk& c, int alike) {
+  const int nt = c.sg.tile1 - c.sg.tile0;
+  return nt <= kSoloTiles && c.end - c.unit >= alike * nt;
+}
+
+template <int RB, bool FP8, int W, bool STASH>
+__device__ __forceinline__ void flash_solo_run(const KvView& kv, const uint16_t* q, RowGeom rg, const RangeWs& ws, uint16_t* out, float c2,
+                                               TeamLds<RB, W>& lds, Walk& walk, int wave, int lane0) {
+  uint8_t* s_tile = lds.tile + wave * kVTileBytes;
+  uint8_t* s_q = wave == 0 ? lds.q : lds.solo_q + (wave - 1) * TeamLds<RB, W>::kQBytes;
+  int turn = 0;
+  do {
+    if (turn == wave) {
+      const int lane = opaque(lane0);
+      const LaneGeom<FP8> geo = lane_geom<FP8>(kv, lane);
+      const Segment cs = walk.sg;
+      const int64_t u0 = walk.unit - cs.tile0;               // unit of the pair's first tile
+      rg.nq_b = __builtin_amdgcn_readfirstlane(queries_of(kv, ws, cs.b, rg.n_q));
+      rg.Rb = rg.nq_b * rg.G;
+      Stretch<FP8> cur = open_stretch<FP8>(kv, cs.rq, cs.g, cs.L, cs.tile0, walk.ids, lane);
+      StretchTile<FP8> tl;
+      stretch_k<FP8>(kv, cur, tl, geo, lane);
+      stretch_v<FP8>(kv, cur, tl, geo);
+      q_to_lds<RB, kWave>(q, rg, cs.rq, cs.g, s_q, lane);
+      FlashRows<RB> st;
+      st.clear();
+      auto tile = [&](int t, auto last) {
+        stretch_tile<RB, FP8, STASH, decltype(last)::value>(
+            kv, cur, tl, geo, rg, t * kTileTokens, c2, st, s_tile, s_q,
+            __builtin_amdgcn_make_buffer_rsrc(ws.stash + (u0 + t) * rg.tile_lanes * 16, 0, rg.tile_lanes * 16, kRawBuffer),
+            __builtin_amdgcn_make_buffer_rsrc(ws.m_ref + (u0 + t) * RB * 16, 0, RB * 16 * 4, kRawBuffer), lane);
+      };
+      for (int t = cs.tile0; t + 1 < cs.tile1; ++t) tile(t, std::false_type{});
+      tile(cs.tile1 - 1, std::true_type{});
+      store_solo<RB>(ws, rg, cs, st, out, lane);
+    }
+    turn = turn + 1 == TeamLds<RB, W>::kSolo ? 0 : turn + 1;
+    next_segment(kv, walk, lane0);
+  } while (walk.live && solo_segment(walk, 1));
+}
 
 template <int RB, bool FP8, int W, bool STASH>
 __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
                                                 TeamLds<RB, W>& lds, int w) {
   constexpr int THREADS = W * kWave, rows = RB * 16, kORow = TeamLds<RB, W>::kORow;
-  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int n = lane & 15, g4 = lane >> 4;
+  const int lane0 = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   RowGeom rg = row_geom(kv, n_q, RB);
   const float c2 = kv.sm_scale * kLog2e;
-  const LaneGeom<FP8> geo = lane_geom<FP8>(kv, lane);
   uint8_t* s_tile = lds.tile + wave * kVTileBytes;
-  Cursor team = open_cursor(kv, ws, w, lane, wave == 0);     // the segments of the range, the same for all wavefronts
+  Walk team = open_walk(kv, ws, w, lane0, wave == 0);        // the segments of the range, the same for all wavefronts
   if (!team.live) return;
-  FlashRows<RB> st;
   while (team.live) {
+    if (__builtin_expect(solo_segment(team, TeamLds<RB, W>::kSolo), 0)) {
+      flash_solo_run<RB, FP8, W, STASH>(kv, q, rg, ws, out, c2, lds, team, wave, lane0);
+      __syncthreads();                                       // their Q rows have been read
+      continue;
+    }
+    const int lane = opaque(lane0);
+    const LaneGeom<FP8> geo = lane_geom<FP8>(kv, lane);
     const Segment cs = team.sg;
     rg.nq_b = __builtin_amdgcn_readfirstlane(queries_of(kv, ws, cs.b, n_q));
     rg.Rb = rg.nq_b * rg.G;
     const int nt = cs.tile1 - cs.tile0;
     const int t0 = cs.tile0 + wave * nt / W, t1 = cs.tile0 + (wave + 1) * nt / W;
-    Stretch<FP8> cur = open_stretch<FP8>(kv, cs.rq, cs.g, cs.L, t0, lane);
+    Stretch<FP8> cur = open_stretch<FP8>(kv, cs.rq, cs.g, cs.L, t0, team.ids, lane);
     StretchTile<FP8> tl;
     if (t0 < t1) {
       stretch_k<FP8>(kv, cur, tl, geo, lane);
       stretch_v<FP8>(kv, cur, tl, geo);
+    } else {
+      tl.leave();
     }
-    q_to_lds<RB, THREADS>(kv, q, rg, cs.rq, cs.g, lds.q, threadIdx.x);
+    q_to_lds<RB, THREADS>(q, rg, cs.rq, cs.g, lds.q, opaque(threadIdx.x));
+    FlashRows<RB> st;
     st.clear();
     __syncthreads();
     const int64_t u0 = team.unit - cs.tile0;                 // unit of the pair's first tile
@@ -1154,6 +1349,7 @@ __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t
     for (int t = t0; t + 1 < t1; ++t) tile(t, std::false_type{});
     if (t0 < t1) tile(t1 - 1, std::true_type{});
     // the team's (m, l) per row
+    const int tid = opaque(threadIdx.x), n = tid & 15, g4 = (tid & (kWave - 1)) >> 4;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const float l = sum_over_groups(st.l[rb]);
@@ -1187,18 +1383,17 @@ __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t
 #pragma unroll
       for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(s_tile + n * kORow + 64 * db + 16 * g4) = st.o[rb][db] * wgt[rb];
       __syncthreads();
-      for (int idx = threadIdx.x; idx < 16 * (kHeadDim / 4); idx += THREADS) {
+      for (int idx = tid; idx < 16 * (kHeadDim / 4); idx += THREADS) {
         const int rr = idx / (kHeadDim / 4), d4 = idx - rr * (kHeadDim / 4), r = 16 * rb + rr;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < W; ++i) acc += *reinterpret_cast<const f32x4*>(lds.tile + i * kVTileBytes + rr * kORow + 16 * d4);
         if (r < rg.Rb) {                                     // rows of query slots the request does not use are left alone
           if (whole) {
-            const int i = r / rg.G, hg = r - i * rg.G;
             u32x2 pk;
             pk.x = pack2(acc.x, acc.y);
             pk.y = pack2(acc.z, acc.w);
-            *reinterpret_cast<u32x2*>(out + ((static_cast<int64_t>(cs.rq) * n_q + i) * kv.num_q_heads + cs.g * rg.G + hg) * kHeadDim + 4 * d4) = pk;
+            *reinterpret_cast<u32x2*>(out + rg.first_row(cs.rq, cs.g) + rg.row(r) + 4 * d4) = pk;
           } else {
             *reinterpret_cast<f32x4*>(ws.part_o + (static_cast<int64_t>(cs.slot) * rg.R + r) * kHeadDim + 4 * d4) = acc;
           }
@@ -1206,10 +1401,7 @@ __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t
       }
       __syncthreads();
     }
-    // on to the next segment: advance_cursor steps by one unit, so step by the rest first
-    team.unit = team.unit + nt - 1;
-    team.tile = cs.tile1 - 1;
-    advance_cursor(kv, team, lane);
+    next_segment(kv, team, lane0);
   }
 }
 

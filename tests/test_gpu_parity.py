@@ -471,6 +471,44 @@ def test_stretches_at_their_edges(kv_dtype, page, heads, k):
             pa.pillar_set_option("verify_waves", 0)
 
 
+@pytest.mark.parametrize("kv_dtype,heads,k,page", [("bf16", 4, 2, 16), ("bf16", 16, 3, 64), ("fp8_e4m3", 4, 2, 32), ("fp8_e4m3", 16, 3, 16),
+                                                   ("fp8_e4m3", 16, 5, 16)])
+def test_short_segments_among_long_ones(kv_dtype, heads, k, page):
+    """Few wide ranges over contexts of 1 to 40 tiles: the wavefronts take runs of up to 12 tiles in turn (1 to 3 row blocks) and share
+    longer ones, in every order; range boundaries cut both kinds.  With selection, without the statistic, and with speculative
+    lengths of their own."""
+    rng = np.random.default_rng(31 + k)
+    lens = [int(t) for t in np.concatenate([rng.integers(k + 1, 90, size=30), rng.integers(300, 460, size=30), rng.integers(k + 1, 1300, size=30)])]
+    lens[30:60] = [n if i % 4 else 1280 for i, n in enumerate(lens[30:60])]
+    w = small(260 + k, kv_dtype=kv_dtype, P=page, B=len(lens), Hq=heads, Hkv=2, spec_k=k, seq_lens=lens, budgets=[min(n, 24) for n in lens])
+    pa.pillar_set_option("verify_waves", 1)
+    try:
+        run, _ = round_trip(w, what=f"short and long segments, {kv_dtype}, {heads} heads", fused_select=True)
+        bare = GpuRun(w)
+        bare.verify(with_scores=False)
+        torch.cuda.synchronize()
+        assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
+        _hetero_case(w, rng.integers(0, k + 1, size=w.B), "short and long segments, hetero k", with_select=True)
+    finally:
+        pa.pillar_set_option("verify_waves", 0)
+
+
+def test_ranges_over_more_requests_than_lanes():
+    """4500 requests of one tile in 64 ranges: a range's lengths come 64 requests at a time; every seventh is empty."""
+    rng = np.random.default_rng(41)
+    B = 4500
+    w = small(265, B=B, Hq=2, Hkv=1, spec_k=1, seq_lens=rng.integers(2, 30, size=B).tolist(), budgets=[4] * B)
+    run = GpuRun(w)
+    _emptied(w, run, list(range(0, B, 7)))
+    pa.pillar_set_option("verify_waves", 1)
+    try:
+        run.verify_select()
+        torch.cuda.synchronize()
+    finally:
+        pa.pillar_set_option("verify_waves", 0)
+    _check_with_empty_contexts(w, run, "4500 requests")
+
+
 @pytest.mark.parametrize("kv_dtype,heads,k", [("fp8_e4m3", 8, 2), ("fp8_e4m3", 16, 4), ("fp8_e4m3", 16, 7), ("bf16", 16, 4), ("bf16", 8, 8)])
 def test_output_does_not_depend_on_the_statistic(kv_dtype, heads, k):
     """With and without the score statistic the pass does the same arithmetic, so the outputs agree bit for bit: page scales that
