@@ -1257,15 +1257,16 @@ __device__ __forceinline__ void store_solo(const RangeWs& ws, const RowGeom& rg,
 }
 
 // Short segments: shared by the wavefronts, one leaves them with a tile or two each, or none, and all wait at the barriers of its
-// merge.  Where as many units are left in the range as that many segments alike would have, the wavefronts take the segments in
-// turn instead, each with Q rows of its own, as long as the next one is short too.  Shared / up to 3, 6, 12, 24, 48 tiles: 300
-// requests of 20-8000 tokens, their logarithms spread evenly, fp8 and 40 rows 553 / 423, 399, 385, 402, 419 us, with bf16, 20 rows
-// and no statistic 373 / 307, 295, 292, 278, 286; 1000 requests of 32-64 tokens 223 / 175 with all, of 256-512 498 / 502, 503, 485,
-// 479, 479; 128 of 1-8 K tokens 519 up to 24, 537 with 48.  (A range per wavefront, before the teams: 452, 354, 266, 553, 551.)
+// merge.  Where as many units are left in the range as that many pairs alike have, the wavefronts take the segments of pairs of up to
+// kSoloTiles tiles in turn instead, each with Q rows of its own.  Shared / in turn (before the teams, with a range per wavefront):
+// 300 requests of 20-8000 tokens, their logarithms spread evenly, fp8 and 40 rows 540 / 383 (452) us, with bf16, 20 rows and no
+// statistic 380 / 299 (354); 1000 of 32-64 tokens 223 / 185 (266), of 256-512 497 / 487 (554).  Up to 6 tiles the first takes
+// 4 % longer, up to 24 as well, and with 48 so do 128 requests of 1-8 K tokens.
 constexpr int kSoloTiles = 12;
+// A segment of a short pair, with units left for the `alike` wavefronts that wait for one (the rest of a long pair is shared: what follows
+// it is long as well).
 __device__ __forceinline__ bool solo_segment(const Walk& c, int alike) {
-  const int nt = c.sg.tile1 - c.sg.tile0;
-  return nt <= kSoloTiles && c.end - c.unit >= alike * nt;
+  return c.sg.tiles <= kSoloTiles && c.end - c.unit >= alike * c.sg.tiles;
 }
 
 template <int RB, bool FP8, int W, bool STASH>
@@ -1301,7 +1302,7 @@ __device__ __forceinline__ void flash_solo_run(const KvView& kv, const uint16_t*
     }
     turn = turn + 1 == TeamLds<RB, W>::kSolo ? 0 : turn + 1;
     next_segment(kv, walk, lane0);
-  } while (walk.live && solo_segment(walk, 1));
+  } while (walk.live && solo_segment(walk, TeamLds<RB, W>::kSolo - turn));
 }
 
 template <int RB, bool FP8, int W, bool STASH>
