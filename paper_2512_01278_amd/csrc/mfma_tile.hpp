@@ -147,12 +147,6 @@ __device__ __forceinline__ void rows_to_lds(const u32x4 (&regs)[TileRegs<FP8>::k
   }
 }
 
-template <bool FP8>
-__device__ __forceinline__ void tile_to_lds(const TileRegs<FP8>& t, uint8_t* ktile, uint8_t* vtile, int lane) {
-  rows_to_lds<FP8, false>(t.k, ktile, lane);
-  rows_to_lds<FP8, true>(t.v, vtile, lane);
-}
-
 // S^T of the tile: acc[sub][rb] (sub = 16-token half, rb = 16-row block of Q).
 // qf[rb][s] holds, for lane (n, g), Q[16rb+n][32s+8g .. 32s+8g+7].
 template <int RB>

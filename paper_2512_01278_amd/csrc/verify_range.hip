@@ -1139,13 +1139,14 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 // Up to two row blocks (three with fp8): range w belongs to a workgroup of kTeamWaves wavefronts that share the Q rows.  Each
 // takes an equal stretch of every segment's tiles, and the segment's state is put together in LDS, so that it leaves one
 // partial.  Bound by the memory system at 128 requests of 1-8 K tokens (bf16, 20 rows: 2.29 GB of K and V in 383 us without
-// the stash, 6.0 of 6.7 TB/s; the 200 MB of stash written cost 75 us more), by its vector instructions with 40 rows and fp8
-// (258 us without, 360 with; no memory traffic at all would leave 246).  One range per wavefront, each with its own Q rows and
-// partials and a cursor that ran on across pairs without draining, spilled 22 registers, needed four times the segments
-// and waited for V where it needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish)
-// where this takes 466 + 63; 32 requests of 4096 tokens 112 + 19, now 104 + 18; without the statistic 414, now 386.
-// Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the statistic and the selection in the same
-// launch: 523 / 545 us in all at the first, but a long row then waits for one compute unit.
+// the stash, 6.0 of 6.7 TB/s; the 200 MB of stash written cost 80 us more), by its vector instructions with 40 rows and fp8
+// (245 us without, 343 with, at 64 requests of 512-32 K tokens).  One range per wavefront, each with its own Q rows and
+// partials and a cursor that ran on across pairs without draining, needed four times the segments and waited for V where it
+// needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish) where this takes 463 + 60; 32
+// requests of 4096 tokens 112 + 19, now 104 + 18.  Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the
+// statistic and the selection in the same launch: 523 / 545 us in all at the first, but a long row then waits for one compute
+// unit.  Three row blocks of bf16 stay with two wavefronts per range: here they would need more registers than there are
+// (46 spilled).  Registers spilled here: 3 with three row blocks and the statistic (5 in the unified batch), else none.
 constexpr int kTeamWaves = 4;                  // two such workgroups fill a compute unit (registers)
 template <int RB, int W> struct TeamLds {
   static constexpr int kORow = kHeadDim * 4 + 16;            // a row of O on its way between wavefronts
@@ -1553,8 +1554,8 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
   Cursor cur = open_cursor(kv, ws, blockIdx.x, lane);
   if (!cur.live) return;                       // the same for both wavefronts
   int unit = cur.unit;
-  // Half tiles in flight per wavefront: two where the registers allow it.  Three row blocks of bf16: 402 against
-  // 414 us at 16 requests of 24-32 K tokens (four row blocks would spill).  fp8: the dequantisation scales of a
+  // Half tiles in flight per wavefront: two.  Three row blocks of bf16: 402 against 414 us at 16 requests of 24-32 K tokens, with
+  // 4 registers spilled; four row blocks of bf16 have one in flight (243 registers).  fp8: the dequantisation scales of a
   // tile must then be fetched along with its rows (issue_next_half), or their load at the tile's turn keeps a
   // round trip to memory in every tile.
   constexpr int DEPTH = (FP8 || RB == 3) ? 2 : 1;
@@ -1705,10 +1706,8 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
 }
 
 template <int RB, bool FP8, bool STASH>
-__global__ __launch_bounds__(2 * kThreads, RB >= 3 ? 2 : 3) void verify_flash_pair(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
-  static_assert(RB >= 2, "two wavefronts need two row blocks");
-  // (with 2 row blocks, one each at 3 wavefronts per SIMD, the pass took as long as the one-wavefront kernel:
-  // 518 against 523 us at batch 128, so that case keeps the simpler kernel)
+__global__ __launch_bounds__(2 * kThreads, 2) void verify_flash_pair(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
+  static_assert(RB >= 3, "up to two row blocks run verify_flash_team");
   constexpr int kFirst = (RB + 1) / 2;         // row blocks of the first wavefront
   __shared__ __attribute__((aligned(16))) uint8_t s_tile[kVTileBytes];
   __shared__ __attribute__((aligned(16))) uint8_t s_q[(RB * 16 + 1) * kKRow];
@@ -2082,10 +2081,10 @@ int num_cus() {
   return cus;
 }
 
-// Ranges per compute unit: as many wavefronts as it holds at once (registers: 2 per SIMD up to 32 rows, else 1;
-// LDS allows as many).  Small workloads take fewer, down to half: below about 24 tiles per range the pass gains
-// nothing from more wavefronts, and every further cut of a pair is one more segment for the finish kernel to
-// merge (32 requests of 4096 tokens: finish 27 us with 8 per compute unit, 23 with 5, pass unchanged).
+// Ranges of the passes with a range per wavefront or per two (fp32 probabilities; more than 32 rows, 48 with fp8), and the partial
+// slots of every pass: per compute unit as many wavefronts as it holds at once (registers: 2 per SIMD up to 32 rows, else 1).
+// Small workloads take fewer, down to half: below about 24 tiles per range a pass gains nothing from more wavefronts, and every
+// further cut of a pair is one more segment to merge.
 int ranges_for(const KvView& kv, int rb) {
   int per_cu = rb >= 3 ? 4 : 8;
   const int opt = options().verify_waves;
@@ -2096,10 +2095,11 @@ int ranges_for(const KvView& kv, int rb) {
   return per_cu * num_cus();
 }
 
-// ranges of the passes with a workgroup per range: as many as the chip holds at once
-int team_ranges() {
+// Ranges of the passes with a workgroup per range: as many as the chip holds at once, and no more than the `slots` that the
+// workspace has been carved for (it has enough for every verify_waves: a team is several wavefronts).
+int team_ranges(int slots) {
   const int opt = options().verify_waves;
-  return std::max(1, (opt > 0 ? opt : 8) * num_cus() / kTeamWaves);
+  return std::min(slots, std::max(1, (opt > 0 ? opt : 8) * num_cus() / kTeamWaves));
 }
 
 int row_blocks(const KvView& kv, int n_q) { return (n_q * (kv.num_q_heads / kv.num_kv_heads) + 15) / 16; }
@@ -2164,7 +2164,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
       n_draft = nspan * draft->kv.num_kv_heads * draft->kv.batch;
     }
     if constexpr (RB <= 2 || (FP8 && RB == 3)) {     // a range per workgroup
-      ws.n_ranges = team_ranges();
+      ws.n_ranges = team_ranges(ws.n_ranges);
       if (fused) {
         KernelTimer t("mixed_flash_team", st);
         hipLaunchKernelGGL((mixed_flash_team<RB, FP8>), dim3(ws.n_ranges + n_draft), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out,
@@ -2206,7 +2206,9 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     split_select = CH;                                                                                                            \
   }
       // few pairs (a unified batch with a handful of verifying requests): every pair gets 16 wavefronts, the
-      // kernel then lasts as long as its longest pair; rows beyond 8192 tokens are shared by several workgroups
+      // kernel then lasts as long as its longest pair; rows beyond 8192 tokens are shared by several workgroups.  Up to two pairs
+      // per compute unit, though only one such workgroup is resident: 512 pairs of 4-8 K tokens 42 us (57 when two were
+      // resident and merged their segments one by one)
       const bool few = pairs <= 2 * num_cus();
       if (!a.select && a.scores && kv.max_seq_len > 8192 && pairs <= num_cus()) PILLAR_FINISH_SPLIT(0)   // (statistic only)
       else if (!a.select) PILLAR_FINISH(512, 1, false);
