@@ -51,6 +51,21 @@ __device__ __forceinline__ void issue_rows(const KvView& kv, const Rows& r, int 
   }
 }
 
+// S^T of a tile of fp8 rows
+__device__ __forceinline__ void tile_qk8(const uint8_t* ktile, const bf16x8 (&qf)[4], f32x4 (&acc)[2][1], int lane) {
+  const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+    acc[sub][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; s += 2) {
+      const u32x4 raw = *reinterpret_cast<const u32x4*>(ktile + (16 * sub + n) * kF8Row + ((2 * s + g) << 4));
+      acc[sub][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_fp8x8(raw.x, raw.y), qf[s], acc[sub][0], 0, 0, 0);
+      acc[sub][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_fp8x8(raw.z, raw.w), qf[s + 1], acc[sub][0], 0, 0, 0);
+    }
+  }
+}
+
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return f32_to_bf16(a) | (static_cast<uint32_t>(f32_to_bf16(b)) << 16);
 }
@@ -100,13 +115,14 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
   for (int d = 0; d < 8; ++d) o[0][d] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   if (wave < ntiles) {
-    // B operand: lane (n, g4) holds Q[row n][32s + 8 g4 .. +7]
+    // B operand: lane (n, g4) holds Q[row n][32s + 8 g4 .. +7]; for fp8, whose K rows bring 16 dims per read, half s % 2 of
+    // dims 64 (s / 2) + 16 g4 .. + 15
     bf16x8 qf[1][4];
     const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + (static_cast<int64_t>(b) * kv.num_q_heads + g * G + n) * kHeadDim;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (n < G) v = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g4);
+      if (n < G) v = *reinterpret_cast<const u32x4*>(qrow + (FP8 ? 64 * (s >> 1) + 16 * g4 + 8 * (s & 1) : 32 * s + 8 * g4));
       qf[0][s] = as_bf16x8(v);
     }
     TileRegs<FP8> regs;
@@ -135,11 +151,17 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
         const Rows& cur = (k & 2) ? rr[1] : rr[0];
         const int half = k & 1;
         const bool more = k < 3 && ti + WAVES < ntiles;
-        rows_to_lds<FP8, false, true>(regs.k, s_tile, lane);
         f32x4 s[2][1];
-        tile_qk<1>(s_tile, qf, s, lane);
-        rows_to_lds<FP8, true, true>(regs.v, s_tile, lane);
+        if constexpr (FP8) {                     // both tiles have room, as they are
+          rows8_to_lds(regs.k, s_tile, lane);
+          rows8_to_lds(regs.v, s_tile + kF8TileBytes, lane);
+        } else {
+          rows_to_lds<false, false>(regs.k, s_tile, lane);
+          tile_qk<1>(s_tile, qf, s, lane);
+          rows_to_lds<false, true>(regs.v, s_tile, lane);
+        }
         if (more) issue_rows<FP8>(kv, ((k + 1) & 2) ? rr[1] : rr[0], (k + 1) & 1, regs, lane);
+        if constexpr (FP8) tile_qk8(s_tile, qf[0], s, lane);
         f32x4 vsc[2];
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
@@ -161,13 +183,13 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
                          fmaxf(fmaxf(s[1][0][0], s[1][0][1]), fmaxf(s[1][0][2], s[1][0][3])));
         mx = max_over_groups(mx);
         const float m_new = fmaxf(m_run, mx);              // finite: every tile has a valid row
-        const float alpha = exp2f(m_run - m_new);
+        const float alpha = fast_exp2(m_run - m_new);
         f32x4 p0, p1;
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          p0[i] = exp2f(s[0][0][i] - m_new);
-          p1[i] = exp2f(s[1][0][i] - m_new);
+          p0[i] = fast_exp2(s[0][0][i] - m_new);
+          p1[i] = fast_exp2(s[1][0][i] - m_new);
           sum += p0[i] + p1[i];
         }
         l_run = l_run * alpha + sum;
@@ -180,7 +202,8 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
         if constexpr (FP8) { p0 *= vsc[0]; p1 *= vsc[1]; }
         bf16x8 p[1];
         p[0] = pack_p(p0, p1);
-        tile_pv<1>(s_tile, p, o, lane);
+        if constexpr (FP8) tile_pv8<1>(s_tile + kF8TileBytes, p, o, lane);
+        else tile_pv<1>(s_tile, p, o, lane);
       }
     }
     l_run = sum_over_groups(l_run);
@@ -205,7 +228,7 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
       const float* pw = reinterpret_cast<const float*>(s_tiles[w]);
-      const float wgt = exp2f(pw[16 * kHeadDim + r] - m);        // m is finite: the first wavefront always has a tile
+      const float wgt = fast_exp2(pw[16 * kHeadDim + r] - m);        // m is finite: the first wavefront always has a tile
       l = fmaf(pw[16 * kHeadDim + 16 + r], wgt, l);
       acc += *reinterpret_cast<const f32x4*>(pw + r * kHeadDim + 4 * d4) * wgt;
     }

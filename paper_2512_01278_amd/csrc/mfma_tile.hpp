@@ -56,6 +56,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast
 __device__ __forceinline__ int k_lds_addr(int r, int c) { return r * kKRow + (c << 4); }
 __device__ __forceinline__ int v_lds_addr(int r, int c) { return r * kVRow + ((c ^ (r & 1)) << 4); }
 
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 __device__ __forceinline__ float xor16(float v) { return __shfl_xor(v, 16, 64); }
 __device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
 
@@ -98,34 +100,25 @@ template <bool FP8> struct TileRegs {
   u32x4 v[kLoads];
 };
 
-// two packed fp8 e4m3 -> two packed bf16 (exact: e4m3 is a subset of bf16).  One instruction where instructions count: a
-// verification of 64 requests with 40 query rows 494 us through fp32, 478 directly.  VIA_F32, two conversions and two bit
-// operations, where latency does: the draft step of those requests 21.5 us directly, 21.3 through fp32.
-template <bool VIA_F32 = false>
+// two packed fp8 e4m3 -> two packed bf16 (exact: e4m3 is a subset of bf16) in one instruction: a verification of 64 requests with 40
+// query rows 494 us through fp32 (two conversions, two bit operations), 478 directly
 __device__ __forceinline__ uint32_t fp8x2_to_bf16x2(uint32_t src, bool hi) {
-  if constexpr (VIA_F32) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const f32x2 f = hi ? __builtin_amdgcn_cvt_pk_f32_fp8(src, true) : __builtin_amdgcn_cvt_pk_f32_fp8(src, false);
-    return (__float_as_uint(f.x) >> 16) | (__float_as_uint(f.y) & 0xffff0000u);      // truncation is exact
-  } else {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 v = hi ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(src, 1.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(src, 1.0f, false);
-    return __builtin_bit_cast(uint32_t, v);
-  }
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = hi ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(src, 1.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(src, 1.0f, false);
+  return __builtin_bit_cast(uint32_t, v);
 }
 
 // sixteen fp8 -> two 16-byte chunks of bf16
-template <bool VIA_F32 = false>
 __device__ __forceinline__ void widen_fp8x16(const u32x4& src, u32x4& lo, u32x4& hi) {
-  lo.x = fp8x2_to_bf16x2<VIA_F32>(src.x, false); lo.y = fp8x2_to_bf16x2<VIA_F32>(src.x, true);
-  lo.z = fp8x2_to_bf16x2<VIA_F32>(src.y, false); lo.w = fp8x2_to_bf16x2<VIA_F32>(src.y, true);
-  hi.x = fp8x2_to_bf16x2<VIA_F32>(src.z, false); hi.y = fp8x2_to_bf16x2<VIA_F32>(src.z, true);
-  hi.z = fp8x2_to_bf16x2<VIA_F32>(src.w, false); hi.w = fp8x2_to_bf16x2<VIA_F32>(src.w, true);
+  lo.x = fp8x2_to_bf16x2(src.x, false); lo.y = fp8x2_to_bf16x2(src.x, true);
+  lo.z = fp8x2_to_bf16x2(src.y, false); lo.w = fp8x2_to_bf16x2(src.y, true);
+  hi.x = fp8x2_to_bf16x2(src.z, false); hi.y = fp8x2_to_bf16x2(src.z, true);
+  hi.z = fp8x2_to_bf16x2(src.w, false); hi.w = fp8x2_to_bf16x2(src.w, true);
 }
 
 // Parks the K (IS_V = false) or V rows of a tile in LDS as bf16 rows (fp8 rows
 // are widened here, exactly).
-template <bool FP8, bool IS_V, bool VIA_F32 = false>
+template <bool FP8, bool IS_V>
 __device__ __forceinline__ void rows_to_lds(const u32x4 (&regs)[TileRegs<FP8>::kLoads], uint8_t* tile, int lane) {
   if constexpr (!FP8) {
     const int c = lane & 15;
@@ -140,7 +133,7 @@ __device__ __forceinline__ void rows_to_lds(const u32x4 (&regs)[TileRegs<FP8>::k
     for (int u = 0; u < 4; ++u) {
       const int r = 8 * u + (lane >> 3);
       u32x4 lo, hi;
-      widen_fp8x16<VIA_F32>(regs[u], lo, hi);
+      widen_fp8x16(regs[u], lo, hi);
       *reinterpret_cast<u32x4*>(tile + (IS_V ? v_lds_addr(r, c) : k_lds_addr(r, c))) = lo;
       *reinterpret_cast<u32x4*>(tile + (IS_V ? v_lds_addr(r, c + 1) : k_lds_addr(r, c + 1))) = hi;
     }
@@ -190,6 +183,47 @@ __device__ __forceinline__ void tile_pv(const uint8_t* vtile, const bf16x8 (&p)[
 #pragma unroll
   for (int db = 0; db < 8; ++db) {
     const bf16x8 av = operand(db);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) o[rb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, p[rb], o[rb][db], 0, 0, 0);
+    if (RB > 1 && (db & 1)) __builtin_amdgcn_sched_barrier(0);     // keeps the operand reads from piling up in registers
+  }
+}
+
+// ---- fp8 rows left as they are: widened on the way out of LDS ----
+// Half the LDS traffic, and room for K and V side by side, so that both register sets are free for the next tile at once: a tile of the
+// draft step (K, products, probabilities, V) 2.1 -> 1.2 us at two wavefronts per SIMD, and three row blocks of the streaming pass
+// spill no register (3 when V was widened on the way in).  Rows of 128 bytes, 144 apart: the 16 bytes that 16 rows hold at one
+// place cover all banks.
+constexpr int kF8Row = 144;
+constexpr int kF8TileBytes = kTileTokens * kF8Row;
+
+__device__ __forceinline__ void rows8_to_lds(const u32x4 (&regs)[TileRegs<true>::kLoads], uint8_t* tile, int lane) {
+#pragma unroll
+  for (int u = 0; u < TileRegs<true>::kLoads; ++u) *reinterpret_cast<u32x4*>(tile + (8 * u + (lane >> 3)) * kF8Row + ((lane & 7) << 4)) = regs[u];
+}
+
+// eight fp8 -> a bf16 operand
+__device__ __forceinline__ bf16x8 widen_fp8x8(uint32_t x, uint32_t y) {
+  u32x4 w;
+  w.x = fp8x2_to_bf16x2(x, false); w.y = fp8x2_to_bf16x2(x, true);
+  w.z = fp8x2_to_bf16x2(y, false); w.w = fp8x2_to_bf16x2(y, true);
+  return as_bf16x8(w);
+}
+
+// tile_pv of a V tile of rows8_to_lds.  ds_read_b64_tr_b8: within each group of 16 lanes, lane 2k+a supplies the address of 8 dims
+// (16db+8a..+7) of token k of the group's eight, and lane m receives dim 16db+m of the eight tokens.
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef i32x2 __attribute__((address_space(3))) * lds_i32x2_ptr;
+
+template <int RB>
+__device__ __forceinline__ void tile_pv8(const uint8_t* vtile, const bf16x8 (&p)[RB], f32x4 (&o)[RB][8], int lane) {
+  const int k = (lane >> 1) & 7, g = lane >> 4;
+  const int row = 4 * g + (k & 3) + 16 * (k >> 2);           // the tokens of p's elements, in order
+  const uint8_t* src = vtile + row * kF8Row + (lane & 1) * 8;
+#pragma unroll
+  for (int db = 0; db < 8; ++db) {
+    const i32x2 raw = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2_ptr)(src + 16 * db));
+    const bf16x8 av = widen_fp8x8(static_cast<uint32_t>(raw.x), static_cast<uint32_t>(raw.y));
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) o[rb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, p[rb], o[rb][db], 0, 0, 0);
     if (RB > 1 && (db & 1)) __builtin_amdgcn_sched_barrier(0);     // keeps the operand reads from piling up in registers

@@ -999,20 +999,12 @@ __device__ __forceinline__ void stretch_v(const KvView& kv, Stretch<FP8>& c, Str
   c.tile += 1;
 }
 
-// K rows of a tile in LDS.  bf16: the padded rows of mfma_tile.hpp.  fp8 stays fp8 (half the LDS traffic; it is widened on the
-// way into the matrix cores): rows of 128 bytes, 16-byte chunk c of row r at place c ^ (r / 2 % 8), so that two rows written
-// and 16 rows read at one chunk both cover all banks.
-template <bool FP8>
-__device__ __forceinline__ void stretch_park_k(const u32x4 (&rk)[TileRegs<FP8>::kLoads], uint8_t* tile, int lane) {
-  if constexpr (FP8) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int r = 8 * u + (lane >> 3);
-      *reinterpret_cast<u32x4*>(tile + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4)) = rk[u];
-    }
-  } else {
-    rows_to_lds<false, false>(rk, tile, lane);
-  }
+// K or V rows of a tile in LDS.  fp8 stays fp8 (half the LDS traffic; it is widened on the way into the matrix cores), and K and V
+// have room side by side.
+template <bool FP8, bool IS_V>
+__device__ __forceinline__ void stretch_park(const u32x4 (&rows)[TileRegs<FP8>::kLoads], uint8_t* tile, int lane) {
+  if constexpr (FP8) rows8_to_lds(rows, tile + (IS_V ? kF8TileBytes : 0), lane);
+  else rows_to_lds<false, IS_V>(rows, tile, lane);
 }
 
 // S^T of the tile, Q rows from LDS too (row R is the zero row that padded rows read).  The contraction over the head
@@ -1036,7 +1028,7 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
   auto k_of = [&](int s, u32x4 (&k)[2]) {                    // of the two 16-token groups
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
-      k[sub] = FP8 ? *reinterpret_cast<const u32x4*>(tile + (16 * sub + n) * 128 + (((4 * (s >> 1) + g4) ^ ((n >> 1) & 7)) << 4))
+      k[sub] = FP8 ? *reinterpret_cast<const u32x4*>(tile + (16 * sub + n) * kF8Row + ((4 * (s >> 1) + g4) << 4))
                    : *reinterpret_cast<const u32x4*>(tile + k_lds_addr(16 * sub + n, 4 * s + g4));
   };
   u32x4 k[2];
@@ -1048,12 +1040,7 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       if constexpr (FP8) {
-        const u32x4& raw = k[sub];
-        const uint32_t x = (s & 1) ? raw.z : raw.x, y = (s & 1) ? raw.w : raw.y;
-        u32x4 w;
-        w.x = fp8x2_to_bf16x2(x, false); w.y = fp8x2_to_bf16x2(x, true);
-        w.z = fp8x2_to_bf16x2(y, false); w.w = fp8x2_to_bf16x2(y, true);
-        a[sub] = as_bf16x8(w);
+        a[sub] = (s & 1) ? widen_fp8x8(k[sub].z, k[sub].w) : widen_fp8x8(k[sub].x, k[sub].y);
       } else {
         a[sub] = as_bf16x8(k[sub]);
       }
@@ -1080,14 +1067,14 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
                                              int tb, float c2, FlashRows<RB>& st, uint8_t* s_tile, const uint8_t* s_q, __amdgpu_buffer_rsrc_t stash, __amdgpu_buffer_rsrc_t m_ref, int lane) {
   const int n = lane & 15, g4 = lane >> 4;
   f32x4 s[2][RB];
-  stretch_park_k<FP8>(t.rows.k, s_tile, lane);
+  stretch_park<FP8, false>(t.rows.k, s_tile, lane);
   const float sc[2] = {c2 * t.ks[0], c2 * t.ks[1]}, vs[2] = {t.vs[0], t.vs[1]};
   if constexpr (!LAST) stretch_k<FP8>(kv, c, t, geo, lane);        // the K registers are free: next tile's K rows leave now
   stretch_qk<RB, FP8>(s_tile, s_q, rg.R, s, lane);
   if constexpr (LAST) {
     if (tb + kTileTokens > c.L) zero_tail_rows<FP8>(t.rows.v, tb, c.L, geo);
   }
-  rows_to_lds<FP8, true>(t.rows.v, s_tile, lane);
+  stretch_park<FP8, true>(t.rows.v, s_tile, lane);
   if constexpr (!LAST) stretch_v<FP8>(kv, c, t, geo);              // and its V rows once the V registers are
   if (tb + kTileTokens > c.L - rg.n_q) {
 #pragma unroll
@@ -1132,7 +1119,8 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
     if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
     p[rb] = pack_p(pr[0], pr[1]);
   }
-  tile_pv<RB>(s_tile, p, st.o, lane);
+  if constexpr (FP8) tile_pv8<RB>(s_tile + kF8TileBytes, p, st.o, lane);
+  else tile_pv<RB>(s_tile, p, st.o, lane);
 }
 
 // ------------------------------------------ a range per workgroup ----------
@@ -1147,7 +1135,7 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 // requests of 4096 tokens 112 + 19, now 104 + 18.  Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the
 // statistic and the selection in the same launch: 523 / 545 us in all at the first, but a long row then waits for one compute
 // unit.  Three row blocks of bf16 stay with two wavefronts per range: here they would need more registers than there are
-// (46 spilled).  Registers spilled here: 3 with three row blocks and the statistic (5 in the unified batch), else none.
+// (46 spilled).  No register is spilled here.
 constexpr int kTeamWaves = 4;                  // two such workgroups fill a compute unit (registers)
 template <int RB, int W> struct TeamLds {
   static constexpr int kORow = kHeadDim * 4 + 16;            // a row of O on its way between wavefronts

@@ -37,8 +37,6 @@ __device__ __forceinline__ void zero_tail_rows(u32x4 (&rv)[TileRegs<FP8>::kLoads
     if (tb + kRowsPerLoad * u + geo.row >= L) rv[u] = u32x4{0u, 0u, 0u, 0u};
 }
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   bf16x2 v;
