@@ -1413,9 +1413,8 @@ __global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView
   if (static_cast<int>(blockIdx.x) < ws.n_ranges) {
     flash_team_body<RB, FP8, kTeamWaves, true>(kv, q, n_q, ws, out, lds, blockIdx.x);
   } else {
-    const int i = blockIdx.x - ws.n_ranges;
-    const int sp = i % nspan, pg = i / nspan;
-    decode_span_body<FP8, kTeamWaves>(da, dws, span_rows, nspan, pg / da.kv.num_kv_heads, pg % da.kv.num_kv_heads, sp,
+    const DecPlace at = decode_place<FP8>(blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
+    decode_span_body<FP8, kTeamWaves>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
                                       reinterpret_cast<uint8_t (*)[kVTileBytes]>(lds.tile));
   }
 }
@@ -1718,9 +1717,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, c
     if (threadIdx.x < kThreads) flash_pair_wave<RB, FP8, true, kFirst, 0>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 0);
     else flash_pair_wave<RB, FP8, true, RB - kFirst, kFirst>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 1);
   } else {
-    const int i = blockIdx.x - ws.n_ranges;
-    const int sp = i % nspan, pg = i / nspan;
-    decode_span_body<FP8, 2>(da, dws, span_rows, nspan, pg / da.kv.num_kv_heads, pg % da.kv.num_kv_heads, sp,
+    const DecPlace at = decode_place<FP8>(blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
+    decode_span_body<FP8, 2>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
                              reinterpret_cast<uint8_t (*)[kVTileBytes]>(smem));
   }
 }

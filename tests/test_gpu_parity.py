@@ -58,6 +58,15 @@ def test_small_shapes(seed, kw):
     round_trip(small(seed, **kw))
 
 
+@pytest.mark.parametrize("batch", [1, 7, 8, 9, 17])
+def test_fp8_draft_around_turns_of_eight_requests(batch):
+    """The draft step gives fp8 requests to the XCDs eight at a time and spreads the rest: every request, head and span once, with
+    lists of one and of two spans."""
+    lens = [1100 if b % 3 == 0 else 60 + 7 * b for b in range(batch)]
+    round_trip(small(180 + batch, kv_dtype="fp8_e4m3", B=batch, Hq=6, Hkv=3, seq_lens=lens, budgets=[600 if n > 1000 else 33 for n in lens]),
+               what=f"fp8 draft, {batch} requests")
+
+
 def test_random_shapes_both_call_styles():
     """24 seeded random shapes of the matrix-core paths (1 to 64 query rows per KV head, bf16 and fp8 KV, pages of
     16 to 64 tokens, contexts from the queries' own tokens up to 30 K), as three calls and as the fused call."""
