@@ -90,6 +90,17 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// sum over groups of 4 or 8 neighbouring lanes (all of a group receive the total)
+template <int LANES>
+__device__ __forceinline__ float lanes_sum(float v) {
+  static_assert(LANES == 4 || LANES == 8, "");
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));   // quad_perm [2,3,0,1]
+  if constexpr (LANES == 8)
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));  // row_half_mirror
+  return v;
+}
+
 // Registers of one 32-token tile in flight from HBM.
 //   bf16: 8 loads of 16 B for K and 8 for V per lane; load u covers token rows
 //         4u..4u+3, 16 lanes per 256-byte row.

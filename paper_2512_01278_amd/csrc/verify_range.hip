@@ -821,10 +821,28 @@ __device__ __forceinline__ u32x4 stash_pack8(const f32x4 (&pr)[2]) {
   packed.w = stash_pack(pr[1][2], pr[1][3]);
   return packed;
 }
-// The stashed value times 2^-64: a plain shift into float position (0 stays 0).  Readers fold the 2^64 into
-// the per-row weight, see kStashBias.
-__device__ __forceinline__ float stash_decode_scaled(uint32_t c) { return __uint_as_float(c << 13); }
+// The two values of a word times 2^-64: a shift of either half into float position (0 stays 0), one instruction each.  (From a shift and
+// a mask the compiler makes two of the lower one.)  Readers fold the 2^64 into the per-row weight, see kStashBias.
+__device__ __forceinline__ float stash_lo_scaled(uint32_t w) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(r) : "v"(13), "v"(w));
+  return __uint_as_float(r);
+}
+__device__ __forceinline__ float stash_hi_scaled(uint32_t w) {
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(r) : "v"(13), "v"(w));
+  return __uint_as_float(r);
+}
 constexpr float kStashBias = 64.f;
+
+// How the stash is read back: kLanes lanes per (tile, token group g4) take the rows in turn, kRows of every block each, so that a row
+// sum is kRows * blocks additions within a lane and two or three across; kRows tiles fill a wavefront.  m_ref keeps the rows
+// of one lane next to each other.
+template <int RB> struct StashRead {
+  static constexpr int kLanes = RB <= 2 ? 4 : 8, kRows = 16 / kLanes;
+  static constexpr int kTiles = kRows;                       // tiles a wavefront takes at a time
+  __device__ static int m_place(int n) { return (n % kLanes) * kRows + n / kLanes; }      // place of row n of a block in m_ref
+};
 
 __device__ __forceinline__ int stash_lane(int rb, int nblocks, int nv, int n, int g4, int lane) {
   return rb < nblocks - 1 ? rb * 64 + lane : (n < nv ? (nblocks - 1) * 64 + g4 * nv + n : -1);
@@ -1114,7 +1132,7 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
       // could not count the stores and would wait for them, and for V, where the next tile needs K.
       const int sl = stash_lane(rb, RB, rg.nv, n, g4, lane);
       __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_use), m_ref, g4 == 0 ? 4 * (16 * rb + n) : kDropped, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_use), m_ref, g4 == 0 ? 4 * (16 * rb + StashRead<RB>::m_place(n)) : kDropped, 0, 0);
     }
     if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
     p[rb] = pack_p(pr[0], pr[1]);
@@ -1675,7 +1693,7 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
       if (sl >= 0) {
         *reinterpret_cast<u32x4*>(st_base + sl * 16) = stash_pack8(pr);
       }
-      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * (RB0 + rb) + n] = m_use;
+      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * (RB0 + rb) + StashRead<RB>::m_place(n)] = m_use;
       if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
       p[rb] = pack_p(pr[0], pr[1]);
     }
@@ -1736,9 +1754,12 @@ __device__ __forceinline__ uint32_t score_key(float f) { return __float_as_uint(
 //   2. O of a pair that was cut into several segments: sum over segments of exp2(m_seg - lse) O_seg
 //      (a pair inside one range was finished by the pass itself);
 //   3. the score statistic from the stash, scores = mean over rows of e * exp2(m_tile - lse): wavefronts take
-//      the pair's tiles in turn, two in flight each, and leave the scores of one chunk of tokens at a time in
+//      groups of two or four tiles in turn, one on its way, and leave the scores of one chunk of tokens at a time in
 //      LDS, from where every thread takes 8 consecutive ones as sort keys into registers (and writes them out
-//      if the caller wants the statistic itself);
+//      if the caller wants the statistic itself).  What this costs is instructions as much as memory: with a lane per row, a
+//      row sum across 16 lanes and a third of the lanes on rows that are not there (20 of 32), a tile took three times as many,
+//      and the kernel 66 us where it takes 60 (128 requests of 1-8 K tokens, 249 MB), 127 and 117 (64 of 512-32 K, 40 rows,
+//      412 MB), 27 and 23 (26 of 1-8 K);
 //   4. SELECT: Top-K of the keys in registers (topk_core.hpp) -- the statistic makes no round trip through
 //      memory between two launches (paper Section 4.1: identification from the verification's own
 //      intermediates).
@@ -1796,34 +1817,62 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   const int n_used = ranges_used(ws, total);
   const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
 
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int n = lane & 15, g4 = lane >> 4;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nv = R - 16 * (RB - 1);
   const int tile_lanes = (RB - 1) * 64 + 4 * nv;
   const bool want_scores = SELECT || SPLIT || scores;
 
-  // The stash stream: wavefronts take the tiles of a chunk in turn, kBufs tiles in flight each.
-  constexpr int kBufs = THREADS >= 1024 ? 2 : 4;       // (a 1024-thread workgroup has 128 registers per lane)
-  int sl[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) sl[rb] = stash_lane(rb, RB, nv, n, g4, lane);
-  u32x4 st[kBufs][RB];
-  float mref[kBufs][RB];
-  auto fetch = [&](int tile, int buf) {
-    const int64_t u = u0 + tile;
+  // The stash stream: wavefronts take groups of kGroup tiles in turn, through range-checked buffers of one chunk that read as zero
+  // where there is no tile or row.  A register is sent for again as soon as it has been used, so a group is always on its way.
+  using Read = StashRead<RB>;
+  constexpr int kRows = Read::kRows, kGroup = Read::kTiles;
+  const int my_r = lane % Read::kLanes, my_g4 = lane / Read::kLanes % 4, my_tile = lane / (4 * Read::kLanes);
+  const int rows_there = (nv + Read::kLanes - 1) / Read::kLanes;         // of the last block, per lane
+  u32x4 st[RB][kRows];
+  float mref[RB][kRows];
+  struct Chunk {
+    __amdgpu_buffer_rsrc_t stash, m_ref;
+    int groups;
+  };
+  auto open_chunk = [&](int c) {
+    const int t_begin = c * kChunkTiles, n = min(tiles, t_begin + kChunkTiles) - t_begin;
+    Chunk ch;
+    ch.stash = __builtin_amdgcn_make_buffer_rsrc(ws.stash + (static_cast<int64_t>(u0) + t_begin) * tile_lanes * 16, 0, n * tile_lanes * 16, kRawBuffer);
+    ch.m_ref = __builtin_amdgcn_make_buffer_rsrc(ws.m_ref + (static_cast<int64_t>(u0) + t_begin) * rows, 0, n * rows * 4, kRawBuffer);
+    ch.groups = (n + kGroup - 1) / kGroup;
+    return ch;
+  };
+  constexpr int kStream = 2;                             // nt: read once
+  auto fetch_row = [&](const Chunk& ch, int group, int rb, int j) {
+    const int tile0 = (group * kGroup + my_tile) * tile_lanes * 16;
+    const bool last = rb == RB - 1;
+    const int off = last ? ((RB - 1) * 64 + my_g4 * nv + my_r + Read::kLanes * j) * 16 : rb * 1024 + (my_g4 * 16 + my_r + Read::kLanes * j) * 16;
+    const bool there = !last || my_r + Read::kLanes * j < nv;
+    st[rb][j] = __builtin_amdgcn_raw_buffer_load_b128(ch.stash, there ? tile0 + off : kDropped, 0, kStream);
+  };
+  auto fetch_m = [&](const Chunk& ch, int group) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      st[buf][rb] = u32x4{0u, 0u, 0u, 0u};
-      if (sl[rb] >= 0)
-        st[buf][rb] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ws.stash + (u * tile_lanes + sl[rb]) * 16));
-      mref[buf][rb] = __builtin_nontemporal_load(ws.m_ref + u * rows + 16 * rb + n);
+      const int off = ((group * kGroup + my_tile) * rows + 16 * rb + my_r * kRows) * 4;
+      if constexpr (kRows == 4) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ch.m_ref, off, 0, kStream);
+        mref[rb][0] = __uint_as_float(v.x); mref[rb][1] = __uint_as_float(v.y); mref[rb][2] = __uint_as_float(v.z); mref[rb][3] = __uint_as_float(v.w);
+      } else {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(ch.m_ref, off, 0, kStream);
+        mref[rb][0] = __uint_as_float(v.x); mref[rb][1] = __uint_as_float(v.y);
+      }
     }
   };
+  auto row_there = [&](int rb, int j) { return rb < RB - 1 || j < rows_there; };         // uniform over the launch
+  Chunk ch;
   auto prime = [&](int c) {                              // first tiles of chunk c on their way
-    const int t_begin = c * kChunkTiles, t_end = min(tiles, t_begin + kChunkTiles);
+    ch = open_chunk(c);
+    fetch_m(ch, wave);
 #pragma unroll
-    for (int i = 0; i < kBufs; ++i)
-      if (t_begin + wave + i * kWaves < t_end) fetch(t_begin + wave + i * kWaves, i);
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (row_there(rb, j)) fetch_row(ch, wave, rb, j);
   };
   if (want_scores) prime(my_chunk);                    // needs nothing of steps 1 and 2: in flight meanwhile
 
@@ -1942,42 +1991,47 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
 
   // 3. scores of the pair, chunk by chunk
   const float log2_inv_r = -log2f(static_cast<float>(Rb));
-  float bias[RB];                                      // per row: -lse + the stash's 2^64 + log2(1 / rows)
+  float bias[RB][kRows];                               // per row: -lse + the stash's 2^64 + log2(1 / rows)
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) bias[rb] = kStashBias + log2_inv_r - s_lse[16 * rb + n];   // -inf for rows that carry no weight
-  auto tile_out = [&](int slot, int buf) {             // slot = tile within the chunk
-    f32x4 tot[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const float w = fast_exp2(mref[buf][rb] + bias[rb]);
-      const uint32_t h[4] = {st[buf][rb].x, st[buf][rb].y, st[buf][rb].z, st[buf][rb].w};
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t c = (k & 1) ? (h[k >> 1] >> 16) : (h[k >> 1] & 0xffffu);
-        tot[k >> 2][k & 3] = fmaf(stash_decode_scaled(c), w, tot[k >> 2][k & 3]);
-      }
-    }
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) tot[sub][i] = row16_sum(tot[sub][i]);
-      if (n == 0) *reinterpret_cast<f32x4*>(s_scores + slot * kTileTokens + 16 * sub + 4 * g4) = tot[sub];
-    }
-  };
+    for (int j = 0; j < kRows; ++j) bias[rb][j] = kStashBias + log2_inv_r - s_lse[16 * rb + my_r + Read::kLanes * j];   // -inf for rows that carry no weight
   float* sdst = scores ? scores + (static_cast<int64_t>(rq) * kv.num_kv_heads + g) * score_stride : nullptr;
   if (SPLIT && !sdst) sdst = ws.scratch_scores + static_cast<int64_t>(pair) * ws.scratch_stride;
   uint32_t key[CH][KPC];
   auto chunk = [&](int c, uint32_t (&keys)[KPC]) {
-    const int t_begin = c * kChunkTiles, t_end = min(tiles, t_begin + kChunkTiles);
-    for (int tile = t_begin + wave; tile < t_end;) {
+    const int t_end = min(tiles, (c + 1) * kChunkTiles);
+    for (int group = wave; group < ch.groups; group += kWaves) {
+      float w[RB][kRows];
 #pragma unroll
-      for (int i = 0; i < kBufs; ++i) {
-        if (tile < t_end) {
-          tile_out(tile - t_begin, i);
-          if (tile + kBufs * kWaves < t_end) fetch(tile + kBufs * kWaves, i);      // buffer i is free again
-          tile += kWaves;
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) w[rb][j] = fast_exp2(mref[rb][j] + bias[rb][j]);
+      fetch_m(ch, group + kWaves);
+      float tot[2][4] = {};
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          if (!row_there(rb, j)) continue;
+          const u32x4 v = st[rb][j];
+          const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            tot[k >> 1][(2 * k) & 3] = fmaf(stash_lo_scaled(h[k]), w[rb][j], tot[k >> 1][(2 * k) & 3]);
+            tot[k >> 1][(2 * k + 1) & 3] = fmaf(stash_hi_scaled(h[k]), w[rb][j], tot[k >> 1][(2 * k + 1) & 3]);
+          }
+          fetch_row(ch, group + kWaves, rb, j);
         }
       }
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[sub][i] = lanes_sum<Read::kLanes>(tot[sub][i]);
+      f32x4 mine;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mine[i] = my_r == 0 ? tot[0][i] : tot[1][i];
+      if (my_r < 2) *reinterpret_cast<f32x4*>(s_scores + (group * kGroup + my_tile) * kTileTokens + 16 * my_r + 4 * my_g4) = mine;
     }
     if (!SPLIT && (c + 1) * kChunk < L) prime(c + 1);   // the next chunk's first tiles leave before the barriers
     __syncthreads();

@@ -67,6 +67,17 @@ def test_fp8_draft_around_turns_of_eight_requests(batch):
                what=f"fp8 draft, {batch} requests")
 
 
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("group,k", [(1, 0), (1, 2), (4, 0), (1, 4), (1, 14), (8, 1), (1, 15), (3, 5), (8, 2), (5, 4), (7, 3), (4, 7), (11, 2), (3, 12),
+                                     (10, 3), (16, 2), (7, 6), (9, 6), (16, 3)])
+def test_statistic_at_every_kind_of_row_count(group, k, kv_dtype):
+    """The stash is read back by 4 or 8 lanes that take the rows of a block in turn: 1 to 64 rows, last blocks of every kind, contexts
+    that end within a tile, within a group of tiles and within a chunk."""
+    for fused in (True, False):
+        round_trip(small(900 + 16 * group + k, kv_dtype=kv_dtype, Hq=2 * group, Hkv=2, spec_k=k, seq_lens=[k + 1, 97, 1500], budgets=[1, 33, 64]),
+                   what=f"{group * (k + 1)} rows", fused_select=fused)
+
+
 def test_random_shapes_both_call_styles():
     """24 seeded random shapes of the matrix-core paths (1 to 64 query rows per KV head, bf16 and fp8 KV, pages of
     16 to 64 tokens, contexts from the queries' own tokens up to 30 K), as three calls and as the fused call."""
