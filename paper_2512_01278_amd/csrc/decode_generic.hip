@@ -13,7 +13,7 @@
 namespace pillar {
 namespace {
 
-constexpr int kTile = 128;                     // (what softmax128 takes)
+constexpr int kTile = 128;
 constexpr int kThreads = kGenThreads;
 constexpr int kMaxG = 16;
 
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kThreads) void decode_generic(DecodeArgs a) {
       }
     }
     __syncthreads();
-    softmax128(s, G, [&](int r) { return row_m[r]; }, [&](int r, float m, float l) {      // nj >= 1, so m is finite
+    softmax_rows<kTile>(s, G, [&](int r) { return row_m[r]; }, [&](int r, float m, float l) {      // nj >= 1, so m is finite
       const float alpha = (row_m[r] == -INFINITY) ? 0.f : __expf(row_m[r] - m);
       row_alpha[r] = alpha;
       row_l[r] = row_l[r] * alpha + l;

@@ -4,8 +4,8 @@
 //
 // Before, a thread walked a K row by itself (neighbouring lanes a whole row apart) and looked every V row's page up again
 // for every element: two requests of 300 and 512 tokens with 16 rows (fp32, head_dim 64)
-// took 98 us to verify in three launches (split 70, merge 8, scores 20) and 22.6 to draft from 64 of them, now 24 + 17
-// and 9.8: what is left is the chain length -> page -> row -> LDS of one workgroup per 128 tokens.
+// took 98 us to verify in three launches (split 70, merge 8, scores 20) and 22.6 to draft from 64 of them, then 24 + 17
+// and 9.8, and 9 + 11 with a workgroup per 32 tokens: what is left is the chain length -> page -> row -> LDS.
 #pragma once
 
 #include "common.hpp"
@@ -107,22 +107,34 @@ __device__ __forceinline__ float lanes16_sum(float v) {
   return v;
 }
 
-// Softmax of `rows` rows of 128 logits in place, relative to the larger of a row's own maximum and floor_of(r): 16 lanes per
+// Softmax of `rows` rows of N logits in place, relative to the larger of a row's own maximum and floor_of(r): 16 lanes per
 // row, 16 rows at a time.  done(r, m, l) is called by one lane per row with the maximum used and the row's sum.
-template <typename Floor, typename Done>
-__device__ __forceinline__ void softmax128(float* s, int rows, Floor floor_of, Done done) {
+template <int N, typename Floor, typename Done>
+__device__ __forceinline__ void softmax_rows(float* s, int rows, Floor floor_of, Done done) {
+  constexpr int kWide = N >= 64 ? 4 : 2, kVecs = N / (16 * kWide);
+  typedef float vec __attribute__((ext_vector_type(kWide)));
   const int e = threadIdx.x & 15;
   for (int r = threadIdx.x / 16; r < rows; r += kGenThreads / 16) {
-    float4* sr = reinterpret_cast<float4*>(s + r * 128);
-    float4 a = sr[e], b = sr[16 + e];
-    float m = fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
+    vec* sr = reinterpret_cast<vec*>(s + r * N);
+    vec x[kVecs];
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) x[i] = sr[16 * i + e];
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i)
+#pragma unroll
+      for (int j = 0; j < kWide; ++j) m = fmaxf(m, x[i][j]);
     m = fmaxf(lanes16_max(m), floor_of(r));
     const float mu = (m == -INFINITY) ? 0.f : m;           // a row that sees no token: exp(-inf) = 0 throughout
-    a.x = __expf(a.x - mu); a.y = __expf(a.y - mu); a.z = __expf(a.z - mu); a.w = __expf(a.w - mu);
-    b.x = __expf(b.x - mu); b.y = __expf(b.y - mu); b.z = __expf(b.z - mu); b.w = __expf(b.w - mu);
-    sr[e] = a;
-    sr[16 + e] = b;
-    const float l = lanes16_sum(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+    float l = 0.f;
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+#pragma unroll
+      for (int j = 0; j < kWide; ++j) x[i][j] = __expf(x[i][j] - mu);
+      sr[16 * i + e] = x[i];
+      l += kWide == 2 ? x[i][0] + x[i][1] : (x[i][0] + x[i][1]) + (x[i][kWide - 2] + x[i][kWide - 1]);
+    }
+    l = lanes16_sum(l);
     if (e == 0) done(r, m, l);
   }
 }

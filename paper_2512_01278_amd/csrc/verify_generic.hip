@@ -8,7 +8,7 @@
 // one GQA group, are the score statistic that Top-K later reads.
 //
 // Two or three launches:
-//   split   one workgroup per (request, KV head, chunk of kChunk tokens):
+//   split   one workgroup per (request, KV head, chunk of 128 or 32 tokens):
 //           logits of all R=(k+1)*G rows against the chunk, chunk-local
 //           softmax, partial output -> workspace
 //   merge   (contexts of more than kInlineChunks chunks) one workgroup per
@@ -17,13 +17,22 @@
 //           every row from the partials, and a share of the output; then
 //           logits again, now against the final lse: exp(s - lse) is the exact
 //           softmax probability; mean over rows
+#include <algorithm>
+
 #include "generic_rows.hpp"
 #include "launch.hpp"
 
 namespace pillar {
 namespace {
 
-constexpr int kChunk = 128;     // tokens per workgroup
+// Tokens per workgroup.  The pieces of 32 tokens of a chunk follow each other through LDS, with two barriers and a walk over the
+// rows each, so a launch is as long as its longest chunk until the chip is full: where all its pieces fit on the chip side by side (4
+// workgroups per compute unit), every piece is a chunk.  Chunks of 128 / of 32 tokens, fp32, 4 heads, head_dim 64, verification and
+// selection and draft: 2 requests of 300 to 512 tokens 55.5 / 34.6 us, 4 of 1 K 56.5 / 36.9, 64 of 512 57.4 / 41.9 (1024 pieces),
+// 16 of 2 K 59.0 / 40.3, 32 of 1 K 58.9 / 46.3; 64 rows and head_dim 128, 16 of 2 K 223 / 163.  Beyond, chunks of 128 fetch the query
+// rows and leave partial outputs a quarter as often.
+constexpr int kChunk = 128, kFineChunk = kPiece;
+constexpr int kFineChunks = 1024;              // 256 compute units
 constexpr int kThreads = kGenThreads;
 
 // Without a merge launch every workgroup of the finish kernel reads the (m, l) of all chunks: quadratic in the context.  With
@@ -36,22 +45,23 @@ struct GenericWs {
   float* part_l;   // [B][Hkv][NC][R]     (merged: the rows' log-sum-exp in chunk 0's place)
   float* part_o;   // [B][Hkv][NC][R][D]
   int nc;
+  bool fine;       // chunks of kFineChunk tokens
   bool merged;     // a launch of its own merges (NC > kInlineChunks)
 };
 
 __host__ __device__ inline int num_chunks(int max_seq_len) { return (max_seq_len + kChunk - 1) / kChunk; }
 
-struct GenericLds {
+template <int CHUNK> struct GenericLds {
   __attribute__((aligned(16))) float q[kPieceRows * kGenMaxD];       // query rows at work
-  __attribute__((aligned(16))) float s[kPieceRows * kChunk];         // their logits, then probabilities
+  __attribute__((aligned(16))) float s[kPieceRows * CHUNK];          // their logits, then probabilities
   __attribute__((aligned(16))) float rows[kPiece * kPieceStride];    // K or V rows of a piece
-  int64_t off[kChunk];                                               // element offset of every token's row
-  float ks[kChunk], vs[kChunk];                                      // fp8: scales of its page
+  int64_t off[CHUNK];                                                // element offset of every token's row
+  float ks[CHUNK], vs[CHUNK];                                        // fp8: scales of its page
   float lse[kMaxRows];
 };
 
-template <int KVDT>
-__device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, int t0, int nt, GenericLds& lds) {
+template <int KVDT, int CHUNK>
+__device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, int t0, int nt, GenericLds<CHUNK>& lds) {
   for (int tt = threadIdx.x; tt < nt; tt += kThreads) {
     int page;
     lds.off[tt] = row_offset(kv, b, g, t0 + tt, &page);
@@ -64,16 +74,12 @@ __device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, in
 
 // Logits of query rows row0 .. row0+rows-1 against the chunk's tokens into lds.s[r][tt] (sm_scale applied, -inf where masked or
 // beyond the sequence).  Every thread of the workgroup calls this; lds.off is complete (a barrier ago).
-// All K rows are sent for before the first is needed, and `ahead` is called right after (to send for V rows).
-constexpr int kPieces = kChunk / kPiece;
-template <int QDT, int KVDT, int D, typename Ahead>
+// piece: the chunk's K rows, sent for.
+template <int QDT, int KVDT, int D, int CHUNK>
 __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int nt, int L, int row0, int rows,
-                                             GenericLds& lds, Ahead ahead) {
+                                             GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&piece)[CHUNK / kPiece]) {
+  constexpr int kPieces = CHUNK / kPiece;
   const int G = kv.num_q_heads / kv.num_kv_heads;
-  StagedPiece<KVDT, D> piece[kPieces];
-#pragma unroll
-  for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
-  ahead();
   for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
     const int r = row0 + idx / D, d = idx & (D - 1);
     const int i = r / G, hg = r - i * G;
@@ -100,34 +106,41 @@ __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, in
           if (KVDT == PILLAR_FP8_E4M3) v *= lds.ks[tt];
           v *= kv.sm_scale;
         }
-        lds.s[r * kChunk + tt] = v;
+        lds.s[r * CHUNK + tt] = v;
       }
     }
   }
   __syncthreads();
 }
 
-template <int QDT, int KVDT, int D>
+// sends for the chunk's rows, all before the first is needed
+template <int KVDT, int D, int PIECES>
+__device__ __forceinline__ void fetch_chunk(const void* pool, const int64_t* s_off, int nt, StagedPiece<KVDT, D> (&piece)[PIECES]) {
+#pragma unroll
+  for (int p = 0; p < PIECES; ++p) piece[p].fetch(pool, s_off, p * kPiece, nt);
+}
+
+template <int QDT, int KVDT, int D, int CHUNK>
 __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
-  __shared__ GenericLds lds;
+  constexpr int kPieces = CHUNK / kPiece;
+  __shared__ GenericLds<CHUNK> lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
-  const int t0 = c * kChunk;
+  const int t0 = c * CHUNK;
   if (t0 >= L) return;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int nt = min(kChunk, L - t0);
+  const int nt = min(CHUNK, L - t0);
   const int64_t slot = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc + c;
   resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
   __syncthreads();
   for (int row0 = 0; row0 < R; row0 += kPieceRows) {
     const int rows = min(kPieceRows, R - row0);
-    StagedPiece<KVDT, D> piece[kPieces];
-    chunk_logits<QDT, KVDT, D>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, [&]() {
-#pragma unroll
-      for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.v_pool, lds.off, p * kPiece, nt);
-    });
-    softmax128(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
+    StagedPiece<KVDT, D> k_piece[kPieces], piece[kPieces];
+    fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);
+    fetch_chunk<KVDT, D>(kv.v_pool, lds.off, nt, piece);
+    chunk_logits<QDT, KVDT, D, CHUNK>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece);
+    softmax_rows<CHUNK>(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
       ws.part_m[slot * R + row0 + r] = m;
       ws.part_l[slot * R + row0 + r] = l;
     });
@@ -142,7 +155,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
         if (KVDT == PILLAR_FP8_E4M3) piece[p].scale(lds.vs, p * kPiece, nt);
         piece[p].store(lds.rows);
         __syncthreads();
-        piece_pv<kPieceRows, D>(lds.rows, lds.s, kChunk, p * kPiece, rows, acc);
+        piece_pv<kPieceRows, D>(lds.rows, lds.s, CHUNK, p * kPiece, rows, acc);
       }
     }
     const int d = threadIdx.x & (D - 1);
@@ -169,7 +182,7 @@ __global__ __launch_bounds__(kMergeThreads) void verify_merge_generic(KvView kv,
   const int b = blockIdx.z, g = blockIdx.y, r = blockIdx.x;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
-  const int nc = (max(kv.seq_lens[b], 0) + kChunk - 1) / kChunk;
+  const int chunk = ws.fine ? kFineChunk : kChunk, nc = (max(kv.seq_lens[b], 0) + chunk - 1) / chunk;
   const int64_t base = ((static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc) * R + r;      // (m, l) of chunk 0; R floats from chunk to chunk
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   float m = -INFINITY;
@@ -211,13 +224,13 @@ __global__ __launch_bounds__(kMergeThreads) void verify_merge_generic(KvView kv,
   }
 }
 
-template <int QDT, int KVDT, int D, bool MERGED>
+template <int QDT, int KVDT, int D, int CHUNK, bool MERGED>
 __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, const void* q, int n_q, GenericWs ws, void* out, float* lse_out,
                                                                    float* scores, int64_t score_stride) {
-  __shared__ GenericLds lds;
+  __shared__ GenericLds<CHUNK> lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
-  const int t0 = c * kChunk;
+  const int t0 = c * CHUNK;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
   if (t0 >= L) {
@@ -231,26 +244,37 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
     }
     return;
   }
-  const int nc = (L + kChunk - 1) / kChunk;
-  const int nt = min(kChunk, L - t0);
+  const int nc = (L + CHUNK - 1) / CHUNK;
+  const int nt = min(CHUNK, L - t0);
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
-  if (scores) resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
+  StagedPiece<KVDT, D> k_piece[CHUNK / kPiece];
+  if (scores) {                                // uniform
+    resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
+    __syncthreads();
+    fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);               // on their way while the partials are merged
+  }
   if constexpr (MERGED) {
     if (threadIdx.x < R) lds.lse[threadIdx.x] = ws.part_l[base * R + threadIdx.x];
   } else {                                     // log-sum-exp of every row: four threads per row take the chunks in turn
     const int r = threadIdx.x / 4, part = threadIdx.x & 3;
-    float m = -INFINITY, l = 0.f;
-    if (r < R)
-#pragma unroll 4
-      for (int i = part; i < nc; i += 4) m = fmaxf(m, ws.part_m[(base + i) * R + r]);
+    constexpr int kMine = kInlineChunks * (kChunk / CHUNK) / 4;          // chunks of a thread, sent for side by side
+    float mc[kMine], lc[kMine], m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      const int64_t at = (base + min(part + 4 * i, nc - 1)) * R + min(r, R - 1);
+      mc[i] = ws.part_m[at];
+      lc[i] = ws.part_l[at];
+    }
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      if (part + 4 * i >= nc) mc[i] = -INFINITY;
+      m = fmaxf(m, mc[i]);
+    }
     m = fmaxf(m, __shfl_xor(m, 1, kWave));
     m = fmaxf(m, __shfl_xor(m, 2, kWave));
-    if (r < R)
-#pragma unroll 4
-      for (int i = part; i < nc; i += 4) {
-        const float mc = ws.part_m[(base + i) * R + r];
-        if (mc != -INFINITY) l = fmaf(ws.part_l[(base + i) * R + r], __expf(mc - m), l);
-      }
+#pragma unroll
+    for (int i = 0; i < kMine; ++i)
+      if (mc[i] != -INFINITY) l = fmaf(lc[i], __expf(mc[i] - m), l);
     l += __shfl_xor(l, 1, kWave);
     l += __shfl_xor(l, 2, kWave);
     if (r < R && part == 0) {
@@ -265,10 +289,10 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
     }
     __syncthreads();
     // this workgroup's share of the output
-    for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {      // (c < kInlineChunks)
+    for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {      // (few chunks: 32 bits are enough)
       const int r = idx / D, d = idx & (D - 1);
       float o = 0.f;
-#pragma unroll 4
+#pragma unroll 8
       for (int i = 0; i < nc; ++i) {
         const float mc = ws.part_m[(base + i) * R + r];
         const float w = (mc == -INFINITY) ? 0.f : __expf(mc - lds.q[r]);
@@ -282,35 +306,46 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   if (!scores) return;
   __syncthreads();                             // the query rows take the place of the weights
   const float inv_r = 1.0f / static_cast<float>(R);
+  constexpr int kPer = kThreads / CHUNK;
   float sum = 0.f;                             // of this thread's token
   for (int row0 = 0; row0 < R; row0 += kPieceRows) {
     const int rows = min(kPieceRows, R - row0);
-    chunk_logits<QDT, KVDT, D>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, []() {});
-    // two threads per token: even rows, odd rows
-    const int tt = threadIdx.x >> 1;
+    if (row0 > 0) fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);
+    chunk_logits<QDT, KVDT, D, CHUNK>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece);
+    // kPer threads per token take the rows in turn
+    const int tt = threadIdx.x / kPer;
 #pragma unroll 4
-    for (int r = threadIdx.x & 1; r < rows; r += 2) {
-      const float v = lds.s[r * kChunk + tt];
+    for (int r = threadIdx.x % kPer; r < rows; r += kPer) {
+      const float v = lds.s[r * CHUNK + tt];
       sum += (v == -INFINITY) ? 0.f : __expf(v - lds.lse[row0 + r]);
     }
     __syncthreads();
   }
-  sum += __shfl_xor(sum, 1, kWave);
-  const int tt = threadIdx.x >> 1;
-  if ((threadIdx.x & 1) == 0 && tt < nt) scores[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * score_stride + t0 + tt] = sum * inv_r;
+#pragma unroll
+  for (int o = 1; o < kPer; o <<= 1) sum += __shfl_xor(sum, o, kWave);
+  const int tt = threadIdx.x / kPer;
+  if (threadIdx.x % kPer == 0 && tt < nt) scores[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * score_stride + t0 + tt] = sum * inv_r;
+}
+
+// (request, KV head, chunk) slots of the workspace: as many as either chunk size takes, so that a smaller batch or a shorter
+// context never needs more.
+size_t chunk_slots(const KvView& kv) {
+  const size_t n = static_cast<size_t>(kv.batch) * kv.num_kv_heads * num_chunks(kv.max_seq_len);
+  return std::max<size_t>(n, kChunk / kFineChunk * std::min<size_t>(n, kFineChunks * kFineChunk / kChunk));
 }
 
 GenericWs carve(const KvView& kv, int n_q, void* workspace) {
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const size_t R = static_cast<size_t>(n_q) * G;
   const size_t nc = num_chunks(kv.max_seq_len);
-  const size_t pairs = static_cast<size_t>(kv.batch) * kv.num_kv_heads;
+  const size_t slots = chunk_slots(kv);
   char* p = static_cast<char*>(workspace);
   GenericWs w;
-  w.nc = static_cast<int>(nc);
   w.merged = nc > kInlineChunks;
-  w.part_m = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
-  w.part_l = reinterpret_cast<float*>(p); p += align_up(pairs * nc * R * 4, 256);
+  w.fine = static_cast<size_t>(kv.batch) * kv.num_kv_heads * nc * (kChunk / kFineChunk) <= kFineChunks;
+  w.nc = w.fine ? (kv.max_seq_len + kFineChunk - 1) / kFineChunk : static_cast<int>(nc);
+  w.part_m = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);
+  w.part_l = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);
   w.part_o = reinterpret_cast<float*>(p);
   return w;
 }
@@ -322,7 +357,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
   const dim3 grid(ws.nc, kv.num_kv_heads, kv.batch);
   {
     KernelTimer t("verify_split_generic", st);
-    hipLaunchKernelGGL((verify_split_generic<QDT, KVDT, D>), grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws);
+    const auto kernel = ws.fine ? verify_split_generic<QDT, KVDT, D, kFineChunk> : verify_split_generic<QDT, KVDT, D, kChunk>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws);
   }
   if (ws.merged) {
     KernelTimer t("verify_merge_generic", st);
@@ -331,7 +367,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
   }
   if (!ws.merged || a.scores) {
     KernelTimer t("verify_finish_generic", st);
-    const auto kernel = ws.merged ? verify_finish_generic<QDT, KVDT, D, true> : verify_finish_generic<QDT, KVDT, D, false>;
+    const auto kernel = ws.merged ? (ws.fine ? verify_finish_generic<QDT, KVDT, D, kFineChunk, true> : verify_finish_generic<QDT, KVDT, D, kChunk, true>)
+                                  : (ws.fine ? verify_finish_generic<QDT, KVDT, D, kFineChunk, false> : verify_finish_generic<QDT, KVDT, D, kChunk, false>);
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws, a.out, a.lse, a.scores, a.score_stride);
   }
   return hipGetLastError();
@@ -340,11 +377,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
 }  // namespace
 
 size_t verify_generic_workspace(const KvView& kv, int n_q) {
-  const int G = kv.num_q_heads / kv.num_kv_heads;
-  const size_t R = static_cast<size_t>(n_q) * G;
-  const size_t nc = num_chunks(kv.max_seq_len);
-  const size_t pairs = static_cast<size_t>(kv.batch) * kv.num_kv_heads;
-  return 2 * align_up(pairs * nc * R * 4, 256) + align_up(pairs * nc * R * kv.head_dim * 4, 256);
+  const size_t R = static_cast<size_t>(n_q) * (kv.num_q_heads / kv.num_kv_heads);
+  return 2 * align_up(chunk_slots(kv) * R * 4, 256) + align_up(chunk_slots(kv) * R * kv.head_dim * 4, 256);
 }
 
 hipError_t launch_verify_generic(const VerifyArgs& a, hipStream_t s) {

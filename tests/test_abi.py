@@ -68,6 +68,18 @@ def test_workspace_query(lib):
     assert lib.pillar_workspace_bytes(C.byref(s), 16, 256) == 0
 
 
+def test_workspace_of_a_batch_holds_any_smaller_one(lib):
+    """The kernels for any shape take smaller chunks where they are few: a workspace that was asked for once must do for fewer
+    requests and shorter contexts."""
+    need = lambda batch, top: lib.pillar_workspace_bytes(C.byref(good_kv(batch=batch, num_q_heads=4, num_kv_heads=1, head_dim=64, max_seq_len=top)), 3, 64)
+    for top in (31, 32, 128, 129, 1024):
+        sizes = [need(batch, top) for batch in range(1, 300)]
+        assert sizes == sorted(sizes)
+    for batch in (1, 2, 29, 300):
+        sizes = [need(batch, top) for top in range(1, 1025)]
+        assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(batch=0), pb.PILLAR_EINVAL), (dict(num_kv_heads=5), pb.PILLAR_EINVAL),
     (dict(k_pool=None), pb.PILLAR_EINVAL), (dict(seq_lens=None), pb.PILLAR_EINVAL),

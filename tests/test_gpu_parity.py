@@ -188,6 +188,16 @@ def test_generic_kernels_at_their_edges(q_dtype, kv_dtype, D, heads, k):
     round_trip(w, what="generic kernels, edges", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
 
 
+@pytest.mark.parametrize("q_dtype,kv_dtype,D", [("f32", "f32", 64), ("bf16", "fp8_e4m3", 128)])
+@pytest.mark.parametrize("batch,top", [(85, 257), (86, 257), (28, 1100), (29, 1100)])
+def test_generic_kernels_on_both_sides_of_the_chunk_rule(batch, top, q_dtype, kv_dtype, D):
+    """Up to 1024 pieces of 32 tokens in the launch (85 and 28 requests here) a workgroup takes one, beyond (86 and 29) four: both with
+    contexts around pieces and chunks, merged by the finish kernel and by a launch of its own."""
+    lens = [top] + [(3, 31, 32, 33, 96, 127, 128, 129, 160, 257)[b % 10] for b in range(1, batch)]
+    w = small(260 + batch, q_dtype=q_dtype, kv_dtype=kv_dtype, D=D, P=8, B=batch, Hq=4, Hkv=1, spec_k=2, seq_lens=lens, budgets=[min(n, 33) for n in lens])
+    round_trip(w, what="generic kernels, chunk rule", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
+
+
 @pytest.mark.parametrize("q_dtype,kv_dtype,D,heads,k", [("f32", "f32", 64, 4, 4), ("bf16", "fp8_e4m3", 128, 4, 15), ("f32", "bf16", 128, 2, 0)])
 @pytest.mark.parametrize("top", [1024, 1025, 2500])
 def test_generic_kernels_around_the_merge_launch(q_dtype, kv_dtype, D, heads, k, top):
