@@ -304,16 +304,17 @@ __device__ __forceinline__ Segment uniform(const Segment& s) {
 // single pass reads all lengths (lane l, register j: request 64 j + l) and scans them into the unit prefix, which
 // costs one round trip to memory where reading a finished plan costs three dependent ones.
 constexpr int kPlanRegs = 16;
-struct WavePlan {
-  int len[kPlanRegs];
-  int first[kPlanRegs];   // units before the request
+template <int REGS> struct WavePlan {
+  int len[REGS];
+  int first[REGS];        // units before the request
   int total;
 };
 
-__device__ __forceinline__ WavePlan wave_plan(const KvView& kv, int lane) {
-  WavePlan p;
+template <int REGS>
+__device__ __forceinline__ WavePlan<REGS> wave_plan(const KvView& kv, int lane) {
+  WavePlan<REGS> p;
 #pragma unroll
-  for (int j = 0; j < kPlanRegs; ++j) {
+  for (int j = 0; j < REGS; ++j) {
     p.len[j] = 0;
     if (kWave * j < kv.batch) {                // wave-uniform
       const int b = kWave * j + lane;
@@ -322,7 +323,7 @@ __device__ __forceinline__ WavePlan wave_plan(const KvView& kv, int lane) {
   }
   int carry = 0;
 #pragma unroll
-  for (int j = 0; j < kPlanRegs; ++j) {
+  for (int j = 0; j < REGS; ++j) {
     p.first[j] = carry;
     if (kWave * j < kv.batch) {
       const int mine = tiles_of_len(p.len[j]) * kv.num_kv_heads;         // 0 beyond the batch
@@ -336,10 +337,11 @@ __device__ __forceinline__ WavePlan wave_plan(const KvView& kv, int lane) {
 }
 
 // value of register set v for request b (wave-uniform)
-__device__ __forceinline__ int plan_get(const int (&v)[kPlanRegs], int b) {
+template <int REGS>
+__device__ __forceinline__ int plan_get(const int (&v)[REGS], int b) {
   int r = 0;
 #pragma unroll
-  for (int j = 0; j < kPlanRegs; ++j)
+  for (int j = 0; j < REGS; ++j)
     if (j == (b >> 6)) r = __builtin_amdgcn_readlane(v[j], b & (kWave - 1));
   return r;
 }
@@ -347,12 +349,13 @@ __device__ __forceinline__ int plan_get(const int (&v)[kPlanRegs], int b) {
 // What range_plan leaves in memory for the kernels after the pass, written by the pass itself: wavefront w ranks
 // requests w, w + N, ... by length (the order of the finish kernel: longest first, ties by index), wavefront 0
 // also writes the prefix.
-__device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws, const WavePlan& p, int w, int lane) {
+template <int REGS>
+__device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int w, int lane) {
   for (int r = w; r < kv.batch; r += ws.n_ranges) {
     const int len_r = plan_get(p.len, r);
     int rank = 0;
 #pragma unroll
-    for (int j = 0; j < kPlanRegs; ++j) {
+    for (int j = 0; j < REGS; ++j) {
       if (kWave * j < kv.batch) {
         const int b = kWave * j + lane;
         const bool ahead = b < kv.batch && (p.len[j] > len_r || (p.len[j] == len_r && b < r));
@@ -363,7 +366,7 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
   }
   if (w == 0) {
 #pragma unroll
-    for (int j = 0; j < kPlanRegs; ++j) {
+    for (int j = 0; j < REGS; ++j) {
       const int b = kWave * j + lane;
       if (b < kv.batch) ws.ureq[b] = p.first[j];
     }
@@ -382,28 +385,37 @@ struct RangeStart {
   bool live;
 };
 
+// The range's units and, if it has any, the request it begins in and that request's first unit, from lengths in registers.  Batches of up
+// to 128 have a copy with two registers: stepping over the parts of the other fourteen, in every scan and every look-up, is
+// some 500 instructions in a row, 1 us of each pass (one request of 2100 tokens, verification and draft, 30.4 -> 29.8 us, 24 of 5 to
+// 3000 31.7 -> 30.8, 128 of 1-8 K 516.8 -> 514.5).
+template <int REGS>
+__device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish, RangeStart& c, int& first_unit) {
+  const WavePlan<REGS> p = wave_plan<REGS>(kv, lane);
+  if (publish) publish_plan(kv, ws, p, w, lane);
+  const int n = ranges_used(ws, p.total);
+  c.unit = range_begin(w, p.total, n);
+  c.end = range_begin(w + 1, p.total, n);
+  c.live = w < n && c.unit < c.end;            // (a batch of empty contexts has one range of nothing)
+  if (!c.live) return;
+  int upto = 0;                                // requests that begin at or before the unit
+#pragma unroll
+  for (int j = 0; j < REGS; ++j) {
+    if (kWave * j < kv.batch) upto += __popcll(__ballot(kWave * j + lane < kv.batch && p.first[j] <= c.unit));
+  }
+  c.sg.b = upto - 1;
+  c.sg.L = plan_get(p.len, c.sg.b);
+  first_unit = plan_get(p.first, c.sg.b);
+}
+
 __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
   RangeStart c;
   c.sg = Segment{};
-  Segment sg;
-  int first_unit;                              // of the request the range begins in
+  int first_unit = 0;                          // of the request the range begins in
   if (ws.plan_in_wave) {                       // the same for the whole grid
-    const WavePlan p = wave_plan(kv, lane);
-    if (publish) publish_plan(kv, ws, p, w, lane);
-    const int n = ranges_used(ws, p.total);
-    c.unit = range_begin(w, p.total, n);
-    c.end = range_begin(w + 1, p.total, n);
-    c.live = w < n && c.unit < c.end;          // (a batch of empty contexts has one range of nothing)
+    if (kv.batch <= 2 * kWave) plan_range<2>(kv, ws, w, lane, publish, c, first_unit);
+    else plan_range<kPlanRegs>(kv, ws, w, lane, publish, c, first_unit);
     if (!c.live) return c;
-    int upto = 0;                              // requests that begin at or before the unit
-#pragma unroll
-    for (int j = 0; j < kPlanRegs; ++j) {
-      if (kWave * j < kv.batch) upto += __popcll(__ballot(kWave * j + lane < kv.batch && p.first[j] <= c.unit));
-    }
-    sg.b = upto - 1;
-    sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
-    sg.L = plan_get(p.len, sg.b);
-    first_unit = plan_get(p.first, sg.b);
   } else {
     const int total = ws.ctrl[0];
     const int n = ranges_used(ws, total);
@@ -411,11 +423,12 @@ __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs
     c.end = range_begin(w + 1, total, n);
     c.live = w < n && c.unit < c.end;
     if (!c.live) return c;
-    sg.b = find_request(ws, kv.batch, c.unit, lane);
-    sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
-    sg.L = __builtin_amdgcn_readfirstlane(kv.seq_lens[sg.rq]);
-    first_unit = __builtin_amdgcn_readfirstlane(ws.ureq[sg.b]);
+    c.sg.b = find_request(ws, kv.batch, c.unit, lane);
+    c.sg.L = __builtin_amdgcn_readfirstlane(kv.seq_lens[request_of(kv, c.sg.b)]);
+    first_unit = __builtin_amdgcn_readfirstlane(ws.ureq[c.sg.b]);
   }
+  Segment& sg = c.sg;
+  sg.rq = __builtin_amdgcn_readfirstlane(request_of(kv, sg.b));
   sg.tiles = tiles_of_len(sg.L);
   const int rel = c.unit - first_unit;
   sg.g = rel / sg.tiles;
@@ -423,7 +436,6 @@ __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs
   sg.tile1 = min(sg.tiles, sg.tile0 + (c.end - c.unit));
   sg.pair = sg.b * kv.num_kv_heads + sg.g;
   sg.slot = sg.pair + w;
-  c.sg = sg;
   return c;
 }
 

@@ -108,6 +108,14 @@ def test_many_tiny_requests_span_ranges():
     round_trip(w, what="300 tiny requests")
 
 
+@pytest.mark.parametrize("batch", [63, 64, 65, 127, 128, 129])
+def test_batches_around_the_registers_of_the_plan(batch):
+    """The pass keeps the lengths of 64 requests per register, in two registers up to 128 requests and in sixteen beyond; empty
+    contexts would hide a wrong look-up, so every request has a length of its own."""
+    w = small(300 + batch, B=batch, Hq=4, Hkv=2, spec_k=2, seq_lens=[5 + 3 * b for b in range(batch)], budgets=[5] * batch)
+    round_trip(w, what=f"{batch} requests", fused_select=True)
+
+
 def test_batch_larger_than_one_planning_pass():
     """1100 requests: the unit prefix is built in two passes of 1024 and a range's first request is found
     through a prefix longer than one wavefront-wide search step."""
