@@ -75,6 +75,15 @@ template <int THREADS, int CH> struct SelectLds {
   uint32_t cand[kWave];                    // those keys, where one wavefront's lanes hold them all
 };
 
+// Clears the histogram.  Called by every thread some time before the selection, with a barrier in between that the caller has anyway:
+// the stores and the barrier then cost nothing of their own (with one barrier less after the last scores, 32 requests of 4096 tokens
+// 132.2 -> 131.3 us, unified batch of 128 149.7 -> 148.2).
+template <int THREADS, int CH>
+__device__ __forceinline__ void select_clear(SelectLds<THREADS, CH>& lds) {
+  for (int i = threadIdx.x; i < 4096; i += THREADS) lds.hist[i] = 0;
+  if (threadIdx.x == 0) lds.n_cand = 0;
+}
+
 // The workgroup holds CH * THREADS * KPC keys: key[c][j] of thread t belongs to position
 // c * (THREADS * KPC) + t * KPC + j; positions >= L are ignored.  Writes the K selected positions in
 // ascending order to out[0..K).  A histogram of the upper 12 bits (sign, exponent and three or more mantissa
@@ -82,7 +91,7 @@ template <int THREADS, int CH> struct SelectLds {
 // serialising) finds the first digit of the K-th largest key.  Usually few keys share it: up to 64 of them are
 // collected and every wavefront ranks them by itself, so that two barriers follow where two further histogram
 // passes (12 and 8 bits: the path for more keys) take six; and if all of them are taken there is nothing to rank.
-// Equal keys go to the lower position.  Every thread of the workgroup must call this.
+// Equal keys go to the lower position.  Every thread of the workgroup must call this, after select_clear and a barrier.
 // What it costs is latency (barriers, LDS round trips): the stand-alone kernel on two rows of 512 scores 9.3 -> 5.3 us,
 // 128 rows of 28 K 30.5 -> 20.7 us with the candidates and with the scans over wavefronts done by lanes instead of loops.
 template <int THREADS, int KPC, int CH>
@@ -106,11 +115,7 @@ __device__ __forceinline__ void select_topk_in_registers(const uint32_t (&key)[C
       const int bins = pass == 2 ? 256 : 4096;
       const uint32_t digit_mask = bins - 1;
       const uint32_t mask = pass == 0 ? 0u : pass == 1 ? 0xfff00000u : 0xffffff00u;
-      if (pass == 0) {                           // later passes find the bins zeroed by their last readers
-        for (int i = threadIdx.x; i < 4096; i += THREADS) hist[i] = 0;
-        if (threadIdx.x == 0) lds.n_cand = 0;
-        __syncthreads();
-      }
+      // (every pass finds the bins zeroed: by select_clear, or by the last pass's readers)
       // A wavefront whose active keys all fall into one bin (constant or zero scores, or the few keys left in a late
       // pass) adds their number once instead of queueing up on one LDS address; otherwise every key adds itself.
       uint32_t lo = 0xffffffffu, hi = 0u, mine = 0u;

@@ -1813,6 +1813,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     out_idx = sel.indices + (static_cast<int64_t>(rq) * kv.num_kv_heads + g) * sel.max_budget;
     if (g == 0 && threadIdx.x == 0) sel.counts[rq] = K;
     for (int j = K + threadIdx.x; j < sel.max_budget; j += THREADS) out_idx[j] = -1;
+    select_clear(lds);
   }
 
   if (L <= 0) {                                          // an empty context: no unit, no segment; no query sees a token
@@ -2014,11 +2015,17 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   auto chunk = [&](int c, uint32_t (&keys)[KPC]) {
     const int t_end = min(tiles, (c + 1) * kChunkTiles);
     for (int group = wave; group < ch.groups; group += kWaves) {
+      // (the weights are there before the next maxima are sent for: else those get other registers, are moved at the loop's end and
+      // waited for there; 128 requests of 1-8 K tokens 517 -> 515.5 us, 16 of 24-32 K 492 -> 489)
       float w[RB][kRows];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int j = 0; j < kRows; ++j) w[rb][j] = fast_exp2(mref[rb][j] + bias[rb][j]);
+        for (int j = 0; j < kRows; ++j) {
+          w[rb][j] = fast_exp2(mref[rb][j] + bias[rb][j]);
+          asm volatile("" : "+v"(w[rb][j]));
+        }
+      __builtin_amdgcn_sched_barrier(0);
       fetch_m(ch, group + kWaves);
       float tot[2][4] = {};
 #pragma unroll
@@ -2064,7 +2071,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
         }
       }
     }
-    __syncthreads();                                   // the next chunk overwrites the scores
+    if (!SPLIT && (c + 1) * kChunk < L) __syncthreads();                 // the next chunk overwrites the scores
   };
   if constexpr (SPLIT) {
     chunk(my_chunk, key[0]);                           // the scores of this chunk go to memory
@@ -2102,6 +2109,7 @@ __global__ __launch_bounds__(1024) void verify_select_rows(KvView kv, RangeWs ws
   if (K == 0) return;
   const float* src = scores ? scores + (static_cast<int64_t>(rq) * kv.num_kv_heads + g) * score_stride
                             : ws.scratch_scores + static_cast<int64_t>(pair) * ws.scratch_stride;
+  select_clear(lds);
   uint32_t key[CH][KPC];
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -2120,6 +2128,7 @@ __global__ __launch_bounds__(1024) void verify_select_rows(KvView kv, RangeWs ws
       for (int i = 0; i < 4; ++i) key[c][j + i] = score_key(v[i]);
     }
   }
+  __syncthreads();
   select_topk_in_registers<THREADS, KPC, CH>(key, L, K, out_idx, lds);
 }
 
