@@ -1159,7 +1159,7 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 // partial.  Bound by the memory system at 128 requests of 1-8 K tokens (bf16, 20 rows: 2.29 GB of K and V in 383 us without
 // the stash, 6.0 of 6.7 TB/s; the 200 MB of stash written cost 80 us more), by the chain of a tile (products, exponentials,
 // products) at two wavefronts per SIMD with 40 rows and fp8: vector ALU busy 35 % of the time, matrix cores 15 % (245 us without
-// the stash, 343 with, at 64 requests of 512-32 K tokens).  One range per wavefront, each with its own Q rows and
+// the stash, 338 with, at 64 requests of 512-32 K tokens).  One range per wavefront, each with its own Q rows and
 // partials and a cursor that ran on across pairs without draining, needed four times the segments and waited for V where it
 // needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish) where this takes 463 + 60; 32
 // requests of 4096 tokens 112 + 19, now 104 + 18.  Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the
