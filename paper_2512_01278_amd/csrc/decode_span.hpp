@@ -73,17 +73,17 @@ __device__ __forceinline__ void issue_rows(const KvView& kv, uint32_t off16, int
   }
 }
 
-// S^T of a tile of fp8 rows
+// S^T of a tile of fp8 rows, the dims in the order of tile_qk (8 bytes of a row per step), so that a cache of either type that holds the
+// same values gives the same bits.  (16 bytes per read would serve two steps, but of other dims: sums in another order.)
 __device__ __forceinline__ void tile_qk8(const uint8_t* ktile, const bf16x8 (&qf)[4], f32x4 (&acc)[2][1], int lane) {
   const int n = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int sub = 0; sub < 2; ++sub) {
     acc[sub][0] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 4; s += 2) {
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(ktile + (16 * sub + n) * kF8Row + ((2 * s + g) << 4));
+    for (int s = 0; s < 4; ++s) {
+      const u32x2 raw = *reinterpret_cast<const u32x2*>(ktile + (16 * sub + n) * kF8Row + 32 * s + 8 * g);
       acc[sub][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_fp8x8(raw.x, raw.y), qf[s], acc[sub][0], 0, 0, 0);
-      acc[sub][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen_fp8x8(raw.z, raw.w), qf[s + 1], acc[sub][0], 0, 0, 0);
     }
   }
 }
@@ -137,14 +137,13 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
   for (int d = 0; d < 8; ++d) o[0][d] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   if (wave < ntiles) {
-    // B operand: lane (n, g4) holds Q[row n][32s + 8 g4 .. +7]; for fp8, whose K rows bring 16 dims per read, half s % 2 of
-    // dims 64 (s / 2) + 16 g4 .. + 15
+    // B operand: lane (n, g4) holds Q[row n][32s + 8 g4 .. +7]
     bf16x8 qf[1][4];
     const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + (static_cast<int64_t>(b) * kv.num_q_heads + g * G + n) * kHeadDim;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (n < G) v = *reinterpret_cast<const u32x4*>(qrow + (FP8 ? 64 * (s >> 1) + 16 * g4 + 8 * (s & 1) : 32 * s + 8 * g4));
+      if (n < G) v = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g4);
       qf[0][s] = as_bf16x8(v);
     }
     TileRegs<FP8> regs;

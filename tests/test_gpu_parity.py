@@ -78,6 +78,31 @@ def test_statistic_at_every_kind_of_row_count(group, k, kv_dtype):
                    what=f"{group * (k + 1)} rows", fused_select=fused)
 
 
+@pytest.mark.parametrize("G", [1, 3, 8])
+def test_fp8_draft_gives_the_bits_of_a_bf16_cache_of_the_same_values(G):
+    """Every e4m3 value is a bf16 value: with page scales of one the two caches hold the same numbers, and the draft step adds them in
+    one order.  Lists of one and of several tiles, wavefronts, rounds and spans."""
+    gen_ = torch.Generator(device="cuda:0").manual_seed(77 + G)
+    B, Hkv, P, n = 5, 2, 16, 1504
+    pages = B * n // P
+    k8, v8 = (torch.randn(pages, Hkv, P, 128, generator=gen_, device="cuda:0").to(torch.float8_e4m3fn) for _ in range(2))
+    table = torch.arange(pages, dtype=torch.int32, device="cuda:0").reshape(B, -1)
+    counts = torch.tensor([7, 33, 512, 513, 1500], dtype=torch.int32, device="cuda:0")
+    lists = torch.rand(B, Hkv, n, generator=gen_, device="cuda:0").topk(1500, dim=2).indices.to(torch.int32)
+    q = torch.randn(B, G * Hkv, 128, generator=gen_, device="cuda:0").to(torch.bfloat16)
+    one = torch.ones(pages, Hkv, device="cuda:0")
+    got = []
+    for kw in (dict(k_pool=k8.view(torch.uint8), v_pool=v8.view(torch.uint8), kv_dtype="fp8_e4m3", k_scale=one, v_scale=one),
+               dict(k_pool=k8.to(torch.bfloat16), v_pool=v8.to(torch.bfloat16), kv_dtype="bf16")):
+        kv = pa.KvCache(block_table=table, seq_lens=torch.full((B,), n, dtype=torch.int32, device="cuda:0"), num_q_heads=G * Hkv, q_dtype="bf16",
+                        sm_scale=128 ** -0.5, max_seq_len=n, **kw)
+        out, lse = torch.zeros_like(q), torch.zeros(B, G * Hkv, device="cuda:0")
+        ws = torch.empty(pa.pillar_workspace_bytes(kv, 0, 1500), dtype=torch.uint8, device="cuda:0")
+        pa.pillar_sparse_decode(kv, q, lists, counts, 1500, out, lse, ws)
+        got.append((out, lse))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 def test_random_shapes_both_call_styles():
     """24 seeded random shapes of the matrix-core paths (1 to 64 query rows per KV head, bf16 and fp8 KV, pages of
     16 to 64 tokens, contexts from the queries' own tokens up to 30 K), as three calls and as the fused call."""
