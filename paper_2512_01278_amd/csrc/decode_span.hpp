@@ -212,13 +212,15 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
                          fmaxf(fmaxf(s[1][0][0], s[1][0][1]), fmaxf(s[1][0][2], s[1][0][3])));
         mx = max_over_groups(mx);
         const float m_new = fmaxf(m_run, mx);              // finite: every tile has a valid row
-        const float alpha = fast_exp2(m_run - m_new);
+        // (exp2f, not the bare instruction, which takes weights below 2^-126 for zero: the values they weigh may be large.  Costs 0.2 us
+        // of 19.5 at 64 requests with fp8 lists of 512, 0.3 of 32.0 at 128 with bf16 lists of 64 to 448.)
+        const float alpha = exp2f(m_run - m_new);
         f32x4 p0, p1;
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          p0[i] = fast_exp2(s[0][0][i] - m_new);
-          p1[i] = fast_exp2(s[1][0][i] - m_new);
+          p0[i] = exp2f(s[0][0][i] - m_new);
+          p1[i] = exp2f(s[1][0][i] - m_new);
           sum += p0[i] + p1[i];
         }
         l_run = l_run * alpha + sum;
@@ -257,7 +259,7 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
       const float* pw = reinterpret_cast<const float*>(s_tiles[w]);
-      const float wgt = fast_exp2(pw[16 * kHeadDim + r] - m);        // m is finite: the first wavefront always has a tile
+      const float wgt = exp2f(pw[16 * kHeadDim + r] - m);        // m is finite: the first wavefront always has a tile
       l = fmaf(pw[16 * kHeadDim + 16 + r], wgt, l);
       acc += *reinterpret_cast<const f32x4*>(pw + r * kHeadDim + 4 * d4) * wgt;
     }

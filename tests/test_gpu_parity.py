@@ -103,6 +103,40 @@ def test_fp8_draft_gives_the_bits_of_a_bf16_cache_of_the_same_values(G):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("where", ["one tile", "two wavefronts", "two tiles of a wavefront"])
+def test_draft_keeps_weights_below_the_normal_range(kv_dtype, where):
+    """Values of 2^122 whose weight is 2^-128 beside values of zero: the result is of ordinary size, if weights below 2^-126 are not taken
+    for zero -- a probability, the weight of a wavefront's partial, the factor that rescales the sum of the tiles before."""
+    n, dev = 256, "cuda:0"
+    low, high = {"one tile": (range(0, 16), range(16, 32)), "two wavefronts": (range(0, 32), range(32, 64)),
+                 "two tiles of a wavefront": (range(0, 32), range(128, 160))}[where]
+    count = high[-1] + 1
+    mid = [t for t in range(count) if t not in low and t not in high]        # as low as `low`, values of zero
+    k, v = torch.zeros(n, 128, device=dev), torch.zeros(n, 128, device=dev)
+    q = torch.zeros(1, 4, 128, device=dev)
+    q[..., 0] = 16.0
+    k[list(high), 0] = 8.0                               # 128 in base 2, with the scale below
+    v[list(low)] = 1.0
+    scale = 2.0 ** 122
+    k, v = (x.reshape(16, 1, 16, 128) for x in (k, v))   # pages of 16
+    if kv_dtype == "bf16":
+        kw = dict(k_pool=k.to(torch.bfloat16), v_pool=(v * scale).to(torch.bfloat16))
+    else:
+        kw = dict(k_pool=k.to(torch.float8_e4m3fn).view(torch.uint8), v_pool=v.to(torch.float8_e4m3fn).view(torch.uint8),
+                  k_scale=torch.ones(16, 1, device=dev), v_scale=torch.full((16, 1), scale, device=dev))
+    as_int = lambda x: torch.tensor(x, dtype=torch.int32, device=dev)
+    kv = pa.KvCache(block_table=as_int([list(range(16))]), seq_lens=as_int([n]), num_q_heads=4, q_dtype="bf16", kv_dtype=kv_dtype,
+                    sm_scale=float(np.log(2.0)), max_seq_len=n, **kw)
+    out, lse = torch.zeros(1, 4, 128, dtype=torch.bfloat16, device=dev), torch.zeros(1, 4, device=dev)
+    ws = torch.empty(pa.pillar_workspace_bytes(kv, 0, n), dtype=torch.uint8, device=dev)
+    pa.pillar_sparse_decode(kv, q.to(torch.bfloat16), as_int([[list(range(n))]]), as_int([count]), n, out, lse, ws)
+    want = len(low) * 2.0 ** -128 * scale / len(high)
+    assert len(mid) == 0 or where == "two tiles of a wavefront"
+    # the product of 128 with log2(e) and its inverse is off by 2^-16 at most, the exponential by 2^-23, the output by 2^-9
+    assert np.abs(to_f64(out) / want - 1.0).max() <= 2.0 ** -8
+
+
 def test_random_shapes_both_call_styles():
     """24 seeded random shapes of the matrix-core paths (1 to 64 query rows per KV head, bf16 and fp8 KV, pages of
     16 to 64 tokens, contexts from the queries' own tokens up to 30 K), as three calls and as the fused call."""
