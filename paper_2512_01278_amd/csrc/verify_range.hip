@@ -70,7 +70,7 @@ struct RangeWs {
   float* part_o;        // [pairs + N][R][128]
   float* lse2;          // [pairs][rows_pad]      log2 domain
   uint8_t* stash;       // single-pass variant: [units][tile lanes][16 bytes]
-  float* m_ref;         //                      [units][rows_pad] running maximum the stash of a tile refers to
+  float* m_ref;         //                      [units][rows_pad] running maximum the stash of a tile refers to (-inf: the row sees nothing yet)
   const int32_t* spec_lens;   // [B] speculative length of each request, or null: all use the call's k
   int32_t rows_pad;     // 16 * row blocks
   int32_t n_ranges;     // N
@@ -1140,11 +1140,13 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
       for (int i = 0; i < 4; ++i) pr[sub][i] = fast_exp2(fmaf(s[sub][rb][i], sc[sub], -m_use));
     st.l[rb] += ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
     if constexpr (STASH) {                                   // the exponentials, 16 bits each, and the maximum they refer to
+      // (-inf, not m_use, for a row that sees none of the tokens so far: its weight in the finish kernel is then zero.  With 0, exp2(0 - lse)
+      // overflows below an lse of about -70 in base 2, and the score of a token such a row does not see is 0 * inf.)
       // Stores past a buffer's end are dropped: lanes with nothing to store need no branch, behind which the compiler
       // could not count the stores and would wait for them, and for V, where the next tile needs K.
       const int sl = stash_lane(rb, RB, rg.nv, n, g4, lane);
       __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_use), m_ref, g4 == 0 ? 4 * (16 * rb + StashRead<RB>::m_place(n)) : kDropped, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(st.m[rb]), m_ref, g4 == 0 ? 4 * (16 * rb + StashRead<RB>::m_place(n)) : kDropped, 0, 0);
     }
     if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
     p[rb] = pack_p(pr[0], pr[1]);
@@ -1705,7 +1707,7 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
       if (sl >= 0) {
         *reinterpret_cast<u32x4*>(st_base + sl * 16) = stash_pack8(pr);
       }
-      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * (RB0 + rb) + StashRead<RB>::m_place(n)] = m_use;
+      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * (RB0 + rb) + StashRead<RB>::m_place(n)] = m_new;
       if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
       p[rb] = pack_p(pr[0], pr[1]);
     }

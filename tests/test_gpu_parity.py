@@ -222,6 +222,22 @@ def test_peaked_attention_wide_logit_range():
     assert rep["scores"] < 1e-3
 
 
+@pytest.mark.parametrize("kv_dtype,heads", [("bf16", 8), ("bf16", 16), ("fp8_e4m3", 8), ("fp8_e4m3", 16), ("fp8_e4m3", 24)])
+def test_low_logits_and_rows_that_see_nothing_of_a_tile(kv_dtype, heads):
+    """All logits around -90 and contexts whose last tile holds one to four tokens, so that the first queries see none of it: with 20 rows
+    (a team of wavefronts per range), 40 and 60 (two wavefronts)."""
+    lens = [5, 33, 34, 35, 36, 66, 98, 130, 1506]
+    w = small(190, kv_dtype=kv_dtype, B=len(lens), Hq=heads, Hkv=2, spec_k=4, seq_lens=lens, budgets=[min(n, 16) for n in lens])
+    if kv_dtype == "bf16":
+        w.q[..., 0], w.q_draft[..., 0], w.k_pool[..., 0] = 0x4400, 0x4400, 0xc000          # 512, -2
+    else:
+        w.k_scale[...] = 2.0 ** -7
+        w.q[..., 0], w.q_draft[..., 0], w.k_pool[..., 0] = 0x4400, 0x4400, 0xf8            # 512, -256 / 128
+    for fused in (False, True):
+        run, _ = round_trip(w, what=f"low logits, {5 * heads // 2} rows", fused_select=fused)
+        assert to_f64(run.lse).max() < -60
+
+
 def test_two_pass_variant_with_fp32_probabilities():
     """PILLAR_FLAG_EXACT_SCORES reads K twice and never rounds a probability below fp32: same results, and
     the score statistic then agrees with the oracle to fp32 accuracy."""
