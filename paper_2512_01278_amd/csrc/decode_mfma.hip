@@ -33,7 +33,7 @@ constexpr int kSpanRows = 512;                 // rows of an index list one work
 template <bool FP8>
 __global__ __launch_bounds__(kDecThreads, 3) void decode_span_mfma(DecodeArgs a, DecWs ws, int span_rows, int nspan_max) {
   __shared__ __attribute__((aligned(16))) uint8_t s_tiles[kDecWaves][kVTileBytes];
-  const DecPlace at = decode_place<FP8>(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), a.kv.batch, a.kv.num_kv_heads, nspan_max);
+  const DecPlace at = decode_place(FP8, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), a.kv.batch, a.kv.num_kv_heads, nspan_max);
   decode_span_body<FP8, kDecWaves>(a, ws, span_rows, nspan_max, at.slot_b, at.g, at.sp, s_tiles);
 }
 

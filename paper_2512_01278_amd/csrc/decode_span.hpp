@@ -2,6 +2,7 @@
 // kernel and by the kernel that runs a unified draft / verify batch in one grid (paper Sections 1 and 4.2).
 #pragma once
 
+#include "decode_place.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
 
@@ -10,33 +11,6 @@ namespace {
 
 constexpr int kDecWaves = 4;                      // wavefronts per workgroup of the draft kernel
 constexpr int kDecThreads = kDecWaves * kWave;
-
-// Which (request slot, KV head, span) workgroup i takes.  Consecutive workgroups run on different XCDs, each with an L2 of its own.
-// With fp8 the workgroups of one request share the lines its page scales lie in, as many as it has rows of its own to fetch, so
-// they are given to one XCD: eight requests at a time, one per XCD (requests beyond the last multiple of eight are spread as they
-// come).  64 requests with lists of 512: 21.15 -> 19.67 us; with bf16 there is little to share (lists of 2048 32.4 -> 32.9 us).
-constexpr uint32_t kXcds = 8;
-struct DecPlace {
-  int slot_b, g, sp;
-};
-template <bool FP8>
-__device__ __forceinline__ DecPlace decode_place(uint32_t i, int batch, int heads, int nspan) {
-  const uint32_t per = static_cast<uint32_t>(heads) * static_cast<uint32_t>(nspan), turn = i / (kXcds * per);
-  uint32_t b, r;
-  if (FP8 && (turn + 1) * kXcds <= static_cast<uint32_t>(batch)) {
-    const uint32_t j = i - turn * kXcds * per;
-    b = turn * kXcds + j % kXcds;
-    r = j / kXcds;
-  } else {
-    b = i / per;
-    r = i - b * per;
-  }
-  DecPlace p;
-  p.slot_b = static_cast<int>(b);
-  p.g = static_cast<int>(r / static_cast<uint32_t>(nspan));
-  p.sp = static_cast<int>(r - static_cast<uint32_t>(p.g) * static_cast<uint32_t>(nspan));
-  return p;
-}
 
 // Resolved rows of two tiles: lane j < 32 holds row j of one tile, lane 32 + j row j of another.
 struct Rows {

@@ -1445,7 +1445,7 @@ __global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView
   if (static_cast<int>(blockIdx.x) < ws.n_ranges) {
     flash_team_body<RB, FP8, kTeamWaves, true>(kv, q, n_q, ws, out, lds, blockIdx.x);
   } else {
-    const DecPlace at = decode_place<FP8>(blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
+    const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
     decode_span_body<FP8, kTeamWaves>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
                                       reinterpret_cast<uint8_t (*)[kVTileBytes]>(lds.tile));
   }
@@ -1749,7 +1749,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, c
     if (threadIdx.x < kThreads) flash_pair_wave<RB, FP8, true, kFirst, 0>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 0);
     else flash_pair_wave<RB, FP8, true, RB - kFirst, kFirst>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 1);
   } else {
-    const DecPlace at = decode_place<FP8>(blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
+    const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
     decode_span_body<FP8, 2>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
                              reinterpret_cast<uint8_t (*)[kVTileBytes]>(smem));
   }

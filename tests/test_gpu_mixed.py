@@ -99,6 +99,17 @@ def test_mixed_batch_long_lists_and_wide_groups():
     _case(w8, [1, 2], [0, 3], "mixed batch, fp8, 40 rows", draft_bits=False)
 
 
+@pytest.mark.parametrize("heads,k", [(8, 4), (16, 7)])
+@pytest.mark.parametrize("n_draft", [8, 9, 17])
+def test_mixed_batch_fp8_drafts_in_turns_of_eight(n_draft, heads, k):
+    """The draft workgroups of fp8 requests are placed eight requests at a time, also inside the grid of the verification: 20 query rows
+    (a team of wavefronts per range) and 64 (two), lists of one and of two spans."""
+    B = n_draft + 2
+    w8 = gen.make_custom(name="mixed-fp8-turns", seed=410 + n_draft, B=B, Hq=heads, Hkv=2, D=128, P=16, spec_k=k, q_dtype="bf16", kv_dtype="fp8_e4m3",
+                         seq_lens=[900 if b % 3 == 0 else 40 + 7 * b for b in range(B)], budgets=[600 if b % 3 == 0 else 33 for b in range(B)])
+    _case(w8, [1, 3], [b for b in range(B) if b not in (1, 3)], f"mixed batch, fp8, {n_draft} drafts", draft_bits=(k + 1) * heads // 2 <= 32)
+
+
 def test_mixed_batch_config3_reduced():
     w = gen.make_workload(3, batch=10)
     _case(w, [0, 5], [1, 2, 3, 4, 6, 7, 8, 9], "config3[:10], every fifth request verifies")
