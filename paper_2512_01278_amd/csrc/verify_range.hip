@@ -1900,7 +1900,8 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   // A loop over the segments by one thread per row was a round trip to memory per segment: one request of 2100 tokens
   // (66 segments of one tile) 96 -> 20 us, 32 of 4096 tokens (5) 25 -> 19 us, 26 of up to 8 K tokens (10) 47 -> 30 us.
   constexpr int kPar = 512 / rows;                       // (the same for every THREADS: the order of the sums is, too)
-  constexpr int kSegs = THREADS >= 1024 ? 4 : 5;
+  // (with 5, two row blocks of a 512-thread workgroup spill up to five registers beside the stash that is on its way)
+  constexpr int kSegs = THREADS >= 1024 || RB == 2 ? 4 : 5;
   constexpr int kOuts = (rows * (kHeadDim / 4) + THREADS - 1) / THREADS;
   static_assert(2 * kPar * rows <= kChunk, "the (m, l) of the segments wait where the scores will be");
   const int nseg = w1 - w0 + 1;
@@ -2025,9 +2026,9 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
 #pragma unroll
         for (int j = 0; j < kRows; ++j) {
           w[rb][j] = fast_exp2(mref[rb][j] + bias[rb][j]);
-          asm volatile("" : "+v"(w[rb][j]));
+          if constexpr (CH < 4) asm volatile("" : "+v"(w[rb][j]));      // (with the keys of four chunks there is no room: a register spills)
         }
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (CH < 4) __builtin_amdgcn_sched_barrier(0);
       fetch_m(ch, group + kWaves);
       float tot[2][4] = {};
 #pragma unroll
