@@ -1815,7 +1815,6 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     out_idx = sel.indices + (static_cast<int64_t>(rq) * kv.num_kv_heads + g) * sel.max_budget;
     if (g == 0 && threadIdx.x == 0) sel.counts[rq] = K;
     for (int j = K + threadIdx.x; j < sel.max_budget; j += THREADS) out_idx[j] = -1;
-    select_clear(lds);
   }
 
   if (L <= 0) {                                          // an empty context: no unit, no segment; no query sees a token
@@ -1900,8 +1899,9 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   // A loop over the segments by one thread per row was a round trip to memory per segment: one request of 2100 tokens
   // (66 segments of one tile) 96 -> 20 us, 32 of 4096 tokens (5) 25 -> 19 us, 26 of up to 8 K tokens (10) 47 -> 30 us.
   constexpr int kPar = 512 / rows;                       // (the same for every THREADS: the order of the sums is, too)
-  // (with 5, two row blocks of a 512-thread workgroup spill up to five registers beside the stash that is on its way)
-  constexpr int kSegs = THREADS >= 1024 || RB == 2 ? 4 : 5;
+  // (as many as the registers hold beside the stash that is on its way: with 5, two row blocks of a 512-thread workgroup spill up to
+  // five; the keys of four chunks leave room for 3)
+  constexpr int kSegs = CH == 4 ? 3 : THREADS >= 1024 || RB == 2 ? 4 : 5;
   constexpr int kOuts = (rows * (kHeadDim / 4) + THREADS - 1) / THREADS;
   static_assert(2 * kPar * rows <= kChunk, "the (m, l) of the segments wait where the scores will be");
   const int nseg = w1 - w0 + 1;
@@ -2079,6 +2079,9 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   if constexpr (SPLIT) {
     chunk(my_chunk, key[0]);                           // the scores of this chunk go to memory
   } else if constexpr (SELECT) {
+    // (here and not at the start of the kernel, where the stores hold up the loads of short pairs: 1000 requests of up to 300 tokens
+    // 300 -> 306 us)
+    select_clear(lds);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       if (c * kChunk < L) {                            // uniform over the workgroup
