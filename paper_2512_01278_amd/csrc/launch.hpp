@@ -38,6 +38,7 @@ struct VerifyArgs {
   int32_t n_q;           // k+1
   int32_t q_dtype, kv_dtype;
   void* workspace;
+  bool fine_room = true;               // the generic kernels' part of the workspace has room for their fine chunks
   const SelectOut* select = nullptr;   // non-null: also select the Top-K of every (request, KV head)
   bool exact_scores = false;           // PILLAR_FLAG_EXACT_SCORES: K read twice, fp32 probabilities
   const int32_t* spec_lens = nullptr;  // non-null: device [B], request b speculates spec_lens[b] <= n_q - 1 tokens
@@ -75,7 +76,8 @@ struct TopkArgs {
 };
 
 // generic (any supported shape, fp32 arithmetic on the vector ALUs)
-size_t verify_generic_workspace(const KvView& kv, int n_q);
+// fine_room: what small launches make use of; without it, the least the kernels run with
+size_t verify_generic_workspace(const KvView& kv, int n_q, bool fine_room);
 hipError_t launch_verify_generic(const VerifyArgs& a, hipStream_t s);
 hipError_t launch_decode_generic(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_topk(const TopkArgs& a, hipStream_t s);

@@ -125,8 +125,10 @@ int check_workspace(const void* ws, size_t have, size_t need) {
   return PILLAR_OK;
 }
 
-size_t verify_workspace(const KvView& v, int n_q) {
-  const size_t a = verify_generic_workspace(v, n_q);
+// The size that is reported has room for the generic kernels' fine chunks; without it (a size that a build before those chunks
+// reported), calls run all the same.
+size_t verify_workspace(const KvView& v, int n_q, bool fine_room) {
+  const size_t a = verify_generic_workspace(v, n_q, fine_room);
   size_t b = 0;
   if (v.head_dim == 128 && v.page_size >= 16) {
     b = verify_range_workspace(v, n_q);
@@ -153,8 +155,8 @@ size_t scratch_scores_bytes(const KvView& v) {
   return static_cast<size_t>(v.batch) * v.num_kv_heads * scratch_score_stride(v) * sizeof(float);
 }
 
-size_t draft_region_offset(const KvView& v, int n_q) {
-  return align_up(align_up(verify_workspace(v, n_q), 256) + scratch_scores_bytes(v), 256);
+size_t draft_region_offset(const KvView& v, int n_q, bool fine_room) {
+  return align_up(align_up(verify_workspace(v, n_q, fine_room), 256) + scratch_scores_bytes(v), 256);
 }
 
 // req_ids / n_req (optional): the call covers only these requests (device list of request indices); draft (optional): one
@@ -189,8 +191,11 @@ int verify_common(const pillar_kv_t* kv, const void* q, int32_t spec_len_k, cons
   const bool generic = (kv->flags & PILLAR_FLAG_GENERIC_KERNELS) != 0;
   // per-request speculative lengths exist in the matrix-core single-pass kernels only
   if (spec_lens && (generic || !verify_range_supported(a))) return PILLAR_EUNSUPPORTED;
-  const size_t stage_ws = verify_workspace(a.kv, a.n_q);
-  rc = check_workspace(workspace, workspace_bytes, stage_ws + (select ? scratch_scores_bytes(a.kv) : 0));
+  const size_t score_ws = select ? scratch_scores_bytes(a.kv) : 0;
+  size_t stage_ws = verify_workspace(a.kv, a.n_q, true);
+  a.fine_room = workspace_bytes >= stage_ws + score_ws;
+  if (!a.fine_room) stage_ws = verify_workspace(a.kv, a.n_q, false);
+  rc = check_workspace(workspace, workspace_bytes, stage_ws + score_ws);
   if (rc != PILLAR_OK) return rc;
   const hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (select) {                                  // long rows pass the statistic between workgroups through memory
@@ -255,7 +260,7 @@ size_t pillar_workspace_bytes(const pillar_kv_t* kv, int32_t spec_len_k, int32_t
   const KvView v = make_view(kv);
   // [verification | scores of pillar_verify_select's two-step fallback | draft partials]: the draft region is its
   // own so that a unified batch (pillar_mixed_step) can run both at once
-  const size_t need = draft_region_offset(v, spec_len_k + 1) + ((v.head_dim == 128) ? decode_mfma_workspace(v, max_budget) : 0);
+  const size_t need = draft_region_offset(v, spec_len_k + 1, true) + ((v.head_dim == 128) ? decode_mfma_workspace(v, max_budget) : 0);
   return need < 256 ? 256 : need;
 }
 
@@ -359,7 +364,7 @@ int pillar_mixed_step(const pillar_kv_t* kv, const int32_t* verify_ids, int32_t 
   if (!budgets || !indices || !counts || max_budget < 1) return PILLAR_EINVAL;
   if (kv->flags != 0) return PILLAR_EUNSUPPORTED;            // matrix-core kernels, default statistic only
   const KvView full = make_view(kv);
-  const size_t dec_off = draft_region_offset(full, spec_len_k + 1);
+  const size_t dec_off = draft_region_offset(full, spec_len_k + 1, false);         // (no generic kernel runs here)
   rc = check_workspace(workspace, workspace_bytes, dec_off + decode_mfma_workspace(full, max_budget));
   if (rc != PILLAR_OK) return rc;
   const hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -401,7 +406,7 @@ int pillar_mixed_step(const pillar_kv_t* kv, const int32_t* verify_ids, int32_t 
   sel.indices = indices;
   sel.counts = counts;
   return verify_common(kv, q_verify, spec_len_k, nullptr, out_verify, lse_verify, scores, score_stride, &sel, workspace,
-                       workspace_bytes, hip_stream, verify_ids, n_verify, n_draft > 0 ? &d : nullptr);
+                       dec_off, hip_stream, verify_ids, n_verify, n_draft > 0 ? &d : nullptr);
 }
 
 int pillar_sparse_decode_static(const pillar_kv_t* kv, const void* q, const int32_t* indices, const int32_t* counts,

@@ -327,22 +327,22 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   if (threadIdx.x % kPer == 0 && tt < nt) scores[(static_cast<int64_t>(b) * kv.num_kv_heads + g) * score_stride + t0 + tt] = sum * inv_r;
 }
 
-// (request, KV head, chunk) slots of the workspace: as many as either chunk size takes, so that a smaller batch or a shorter
-// context never needs more.
-size_t chunk_slots(const KvView& kv) {
+// (request, KV head, chunk) slots of the workspace.  With room for fine chunks: as many as either chunk size takes, so that a smaller
+// batch or a shorter context never needs more.
+size_t chunk_slots(const KvView& kv, bool fine_room) {
   const size_t n = static_cast<size_t>(kv.batch) * kv.num_kv_heads * num_chunks(kv.max_seq_len);
-  return std::max<size_t>(n, kChunk / kFineChunk * std::min<size_t>(n, kFineChunks * kFineChunk / kChunk));
+  return fine_room ? std::max<size_t>(n, kChunk / kFineChunk * std::min<size_t>(n, kFineChunks * kFineChunk / kChunk)) : n;
 }
 
-GenericWs carve(const KvView& kv, int n_q, void* workspace) {
+GenericWs carve(const KvView& kv, int n_q, void* workspace, bool fine_room) {
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const size_t R = static_cast<size_t>(n_q) * G;
   const size_t nc = num_chunks(kv.max_seq_len);
-  const size_t slots = chunk_slots(kv);
+  const size_t slots = chunk_slots(kv, fine_room);
   char* p = static_cast<char*>(workspace);
   GenericWs w;
   w.merged = nc > kInlineChunks;
-  w.fine = static_cast<size_t>(kv.batch) * kv.num_kv_heads * nc * (kChunk / kFineChunk) <= kFineChunks;
+  w.fine = fine_room && static_cast<size_t>(kv.batch) * kv.num_kv_heads * nc * (kChunk / kFineChunk) <= kFineChunks;
   w.nc = w.fine ? (kv.max_seq_len + kFineChunk - 1) / kFineChunk : static_cast<int>(nc);
   w.part_m = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);
   w.part_l = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);
@@ -353,7 +353,7 @@ GenericWs carve(const KvView& kv, int n_q, void* workspace) {
 template <int QDT, int KVDT, int D>
 hipError_t run(const VerifyArgs& a, hipStream_t st) {
   const KvView& kv = a.kv;
-  const GenericWs ws = carve(kv, a.n_q, a.workspace);
+  const GenericWs ws = carve(kv, a.n_q, a.workspace, a.fine_room);
   const dim3 grid(ws.nc, kv.num_kv_heads, kv.batch);
   {
     KernelTimer t("verify_split_generic", st);
@@ -376,9 +376,9 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
 
 }  // namespace
 
-size_t verify_generic_workspace(const KvView& kv, int n_q) {
-  const size_t R = static_cast<size_t>(n_q) * (kv.num_q_heads / kv.num_kv_heads);
-  return 2 * align_up(chunk_slots(kv) * R * 4, 256) + align_up(chunk_slots(kv) * R * kv.head_dim * 4, 256);
+size_t verify_generic_workspace(const KvView& kv, int n_q, bool fine_room) {
+  const size_t R = static_cast<size_t>(n_q) * (kv.num_q_heads / kv.num_kv_heads), slots = chunk_slots(kv, fine_room);
+  return 2 * align_up(slots * R * 4, 256) + align_up(slots * R * kv.head_dim * 4, 256);
 }
 
 hipError_t launch_verify_generic(const VerifyArgs& a, hipStream_t s) {

@@ -281,6 +281,30 @@ def test_generic_kernels_on_both_sides_of_the_chunk_rule(batch, top, q_dtype, kv
     round_trip(w, what="generic kernels, chunk rule", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
 
 
+@pytest.mark.parametrize("top", [512, 1500])
+def test_generic_kernels_without_room_for_fine_chunks(top):
+    """A workspace with a slot per 128 tokens, less than is reported for small shapes, is enough, as it was before there were chunks of 32;
+    nothing behind it is written, and less is refused."""
+    w = small(270, q_dtype="f32", kv_dtype="f32", D=64, B=2, Hq=4, Hkv=1, spec_k=3, seq_lens=[300, top], budgets=[64, 64])
+    run = GpuRun(w)
+    slots, rows = 2 * -(-top // 128), 16
+    up = lambda n: (n + 255) // 256 * 256
+    least = {False: 2 * up(slots * rows * 4) + up(slots * rows * 64 * 4)}
+    least[True] = least[False] + 2 * -(-top // 4) * 4 * 4                  # and the scores of the selection
+    assert least[True] < run.workspace.numel()
+    room = torch.full((least[True] + 4096,), 0x5a, dtype=torch.uint8, device=run.dev)
+    for fused in (False, True):
+        room.fill_(0x5a)
+        run.workspace = room[:least[fused]]
+        run.run_all(fused_select=fused)
+        compare_with_oracle(w, run, None, "least workspace")
+        assert bool((room[least[fused]:] == 0x5a).all())
+        run.workspace = room[:least[fused] - 1]
+        with pytest.raises(pa.PillarError) as e:
+            run.run_all(fused_select=fused)
+        assert e.value.status == pa.binding.PILLAR_EWORKSPACE
+
+
 @pytest.mark.parametrize("q_dtype,kv_dtype,D,heads,k", [("f32", "f32", 64, 4, 4), ("bf16", "fp8_e4m3", 128, 4, 15), ("f32", "bf16", 128, 2, 0)])
 @pytest.mark.parametrize("top", [1024, 1025, 2500])
 def test_generic_kernels_around_the_merge_launch(q_dtype, kv_dtype, D, heads, k, top):
