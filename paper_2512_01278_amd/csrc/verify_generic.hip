@@ -74,11 +74,19 @@ __device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, in
 
 // Logits of query rows row0 .. row0+rows-1 against the chunk's tokens into lds.s[r][tt] (sm_scale applied, -inf where masked or
 // beyond the sequence).  Every thread of the workgroup calls this; lds.off is complete (a barrier ago).
-// piece: the chunk's K rows, sent for.
-template <int QDT, int KVDT, int D, int CHUNK>
+// All K rows are sent for before the first is needed (SENT: they have been, into `sent`), and `ahead` is called right after (to send for
+// V rows).
+template <int QDT, int KVDT, int D, int CHUNK, bool SENT, typename Ahead>
 __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int nt, int L, int row0, int rows,
-                                             GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&piece)[CHUNK / kPiece]) {
+                                             GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&sent)[CHUNK / kPiece], Ahead ahead) {
   constexpr int kPieces = CHUNK / kPiece;
+  StagedPiece<KVDT, D> piece[kPieces];
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p) {
+    if constexpr (SENT) piece[p] = sent[p];
+    else piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
+  }
+  ahead();
   const int G = kv.num_q_heads / kv.num_kv_heads;
   for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
     const int r = row0 + idx / D, d = idx & (D - 1);
@@ -113,13 +121,6 @@ __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, in
   __syncthreads();
 }
 
-// sends for the chunk's rows, all before the first is needed
-template <int KVDT, int D, int PIECES>
-__device__ __forceinline__ void fetch_chunk(const void* pool, const int64_t* s_off, int nt, StagedPiece<KVDT, D> (&piece)[PIECES]) {
-#pragma unroll
-  for (int p = 0; p < PIECES; ++p) piece[p].fetch(pool, s_off, p * kPiece, nt);
-}
-
 template <int QDT, int KVDT, int D, int CHUNK>
 __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
   constexpr int kPieces = CHUNK / kPiece;
@@ -136,10 +137,11 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
   __syncthreads();
   for (int row0 = 0; row0 < R; row0 += kPieceRows) {
     const int rows = min(kPieceRows, R - row0);
-    StagedPiece<KVDT, D> k_piece[kPieces], piece[kPieces];
-    fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);
-    fetch_chunk<KVDT, D>(kv.v_pool, lds.off, nt, piece);
-    chunk_logits<QDT, KVDT, D, CHUNK>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece);
+    StagedPiece<KVDT, D> piece[kPieces];
+    chunk_logits<QDT, KVDT, D, CHUNK, false>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, piece, [&]() {
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.v_pool, lds.off, p * kPiece, nt);
+    });
     softmax_rows<CHUNK>(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
       ws.part_m[slot * R + row0 + r] = m;
       ws.part_l[slot * R + row0 + r] = l;
@@ -247,11 +249,17 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   const int nc = (L + CHUNK - 1) / CHUNK;
   const int nt = min(CHUNK, L - t0);
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
+  // A fine chunk's K rows are on their way while the partials are merged.  (Where the chip is full there is nothing to wait for, and
+  // rows held that long cost: 64 requests of 1 to 2 K tokens, 64 rows, head_dim 128, this kernel 136 -> 148 us.)
+  constexpr bool kSent = CHUNK == kFineChunk;
   StagedPiece<KVDT, D> k_piece[CHUNK / kPiece];
   if (scores) {                                // uniform
     resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
-    __syncthreads();
-    fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);               // on their way while the partials are merged
+    if constexpr (kSent) {
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < CHUNK / kPiece; ++p) k_piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
+    }
   }
   if constexpr (MERGED) {
     if (threadIdx.x < R) lds.lse[threadIdx.x] = ws.part_l[base * R + threadIdx.x];
@@ -310,8 +318,13 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   float sum = 0.f;                             // of this thread's token
   for (int row0 = 0; row0 < R; row0 += kPieceRows) {
     const int rows = min(kPieceRows, R - row0);
-    if (row0 > 0) fetch_chunk<KVDT, D>(kv.k_pool, lds.off, nt, k_piece);
-    chunk_logits<QDT, KVDT, D, CHUNK>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece);
+    if constexpr (kSent) {
+      if (row0 > 0) {
+#pragma unroll
+        for (int p = 0; p < CHUNK / kPiece; ++p) k_piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
+      }
+    }
+    chunk_logits<QDT, KVDT, D, CHUNK, kSent>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece, []() {});
     // kPer threads per token take the rows in turn
     const int tt = threadIdx.x / kPer;
 #pragma unroll 4
