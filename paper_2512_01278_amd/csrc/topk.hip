@@ -141,7 +141,6 @@ __global__ __launch_bounds__(kThreads) void topk_select(TopkArgs a) {
   for (int j = K + threadIdx.x; j < a.max_budget; j += kThreads) out[j] = -1;
   if (K == 0) return;
   const float* row = a.scores + (static_cast<int64_t>(b) * a.num_kv_heads + g) * a.score_stride;
-  select_clear(lds);
 
   // thread t holds positions t*KPT .. t*KPT+KPT-1
   const int t0 = threadIdx.x * KPT;
@@ -163,6 +162,7 @@ __global__ __launch_bounds__(kThreads) void topk_select(TopkArgs a) {
 #pragma unroll
     for (int j = 0; j < KPT; ++j) key[0][j] = order_key(t0 + j < L ? row[t0 + j] : 0.f);
   }
+  select_clear(lds);                                        // (behind the loads, which it would hold up)
   __syncthreads();
   select_topk_in_registers<kThreads, KPT, 1>(key, L, K, out, lds);
 }
