@@ -110,5 +110,6 @@ struct Options {
   int decode_rows = 0;    // rows of the index list per workgroup of the draft kernel
 };
 Options& options();
+int num_cus();               // compute units of the device (256 where there is none to ask)
 
 }  // namespace pillar

@@ -30,9 +30,10 @@ namespace {
 // workgroups per compute unit), every piece is a chunk.  Chunks of 128 / of 32 tokens, fp32, 4 heads, head_dim 64, verification and
 // selection and draft: 2 requests of 300 to 512 tokens 55.5 / 34.6 us, 4 of 1 K 56.5 / 36.9, 64 of 512 57.4 / 41.9 (1024 pieces),
 // 16 of 2 K 59.0 / 40.3, 32 of 1 K 58.9 / 46.3; 64 rows and head_dim 128, 16 of 2 K 223 / 163.  Beyond, chunks of 128 fetch the query
-// rows and leave partial outputs a quarter as often.
+// rows and leave partial outputs a quarter as often.  (The host knows no lengths: it counts with max_seq_len, so a caller whose contexts
+// are short does well to say so.)
 constexpr int kChunk = 128, kFineChunk = kPiece;
-constexpr int kFineChunks = 1024;              // 256 compute units
+size_t fine_chunks() { return 4 * static_cast<size_t>(num_cus()); }
 constexpr int kThreads = kGenThreads;
 
 // Without a merge launch every workgroup of the finish kernel reads the (m, l) of all chunks: quadratic in the context.  With
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
 // batch or a shorter context never needs more.
 size_t chunk_slots(const KvView& kv, bool fine_room) {
   const size_t n = static_cast<size_t>(kv.batch) * kv.num_kv_heads * num_chunks(kv.max_seq_len);
-  return fine_room ? std::max<size_t>(n, kChunk / kFineChunk * std::min<size_t>(n, kFineChunks * kFineChunk / kChunk)) : n;
+  return fine_room ? std::max<size_t>(n, kChunk / kFineChunk * std::min<size_t>(n, fine_chunks() * kFineChunk / kChunk)) : n;
 }
 
 GenericWs carve(const KvView& kv, int n_q, void* workspace, bool fine_room) {
@@ -355,7 +356,7 @@ GenericWs carve(const KvView& kv, int n_q, void* workspace, bool fine_room) {
   char* p = static_cast<char*>(workspace);
   GenericWs w;
   w.merged = nc > kInlineChunks;
-  w.fine = fine_room && static_cast<size_t>(kv.batch) * kv.num_kv_heads * nc * (kChunk / kFineChunk) <= kFineChunks;
+  w.fine = fine_room && static_cast<size_t>(kv.batch) * kv.num_kv_heads * nc * (kChunk / kFineChunk) <= fine_chunks();
   w.nc = w.fine ? (kv.max_seq_len + kFineChunk - 1) / kFineChunk : static_cast<int>(nc);
   w.part_m = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);
   w.part_l = reinterpret_cast<float*>(p); p += align_up(slots * R * 4, 256);

@@ -2139,16 +2139,6 @@ __global__ __launch_bounds__(1024) void verify_select_rows(KvView kv, RangeWs ws
 }
 
 // ---------------------------------------------------------------- host ------
-int num_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    cus = v;
-  }
-  return cus;
-}
-
 // Ranges of the passes with a range per wavefront or per two (fp32 probabilities; more than 32 rows, 48 with fp8), and the partial
 // slots of every pass: per compute unit as many wavefronts as it holds at once (registers: 2 per SIMD up to 32 rows, else 1).
 // Small workloads take fewer, down to half: below about 24 tiles per range a pass gains nothing from more wavefronts, and every
