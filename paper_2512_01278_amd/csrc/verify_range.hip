@@ -1160,11 +1160,11 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 // takes an equal stretch of every segment's tiles, and the segment's state is put together in LDS, so that it leaves one
 // partial.  Bound by the memory system at 128 requests of 1-8 K tokens (bf16, 20 rows: 2.29 GB of K and V in 383 us without
 // the stash, 6.0 of 6.7 TB/s; the 200 MB of stash written cost 80 us more), by the chain of a tile (products, exponentials,
-// products) at two wavefronts per SIMD with 40 rows and fp8: vector ALU busy 35 % of the time, matrix cores 15 % (245 us without
-// the stash, 338 with, at 64 requests of 512-32 K tokens).  One range per wavefront, each with its own Q rows and
+// products) at two wavefronts per SIMD with 40 rows and fp8: vector ALU busy 36 % of the time, matrix cores 15 % (245 us without
+// the stash, 342 with, at 64 requests of 512-32 K tokens).  One range per wavefront, each with its own Q rows and
 // partials and a cursor that ran on across pairs without draining, needed four times the segments and waited for V where it
-// needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish) where this takes 463 + 60; 32
-// requests of 4096 tokens 112 + 19, now 104 + 18.  Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the
+// needed K (the compiler cannot count loads behind a branch): 484 + 72 us (pass and finish) where this takes 464 + 57; 32
+// requests of 4096 tokens 112 + 19, now 103 + 17.  Whole pairs given to workgroups of 4 or 8 wavefronts, longest first, with the
 // statistic and the selection in the same launch: 523 / 545 us in all at the first, but a long row then waits for one compute
 // unit.  Three row blocks of bf16 stay with two wavefronts per range: here they would need more registers than there are
 // (46 spilled).  No register is spilled here.
@@ -1771,9 +1771,9 @@ __device__ __forceinline__ uint32_t score_key(float f) { return __float_as_uint(
 //      groups of two or four tiles in turn, one on its way, and leave the scores of one chunk of tokens at a time in
 //      LDS, from where every thread takes 8 consecutive ones as sort keys into registers (and writes them out
 //      if the caller wants the statistic itself).  What this costs is instructions as much as memory: with a lane per row, a
-//      row sum across 16 lanes and a third of the lanes on rows that are not there (20 of 32), a tile took three times as many,
-//      and the kernel 66 us where it takes 60 (128 requests of 1-8 K tokens, 249 MB), 127 and 117 (64 of 512-32 K, 40 rows,
-//      412 MB), 27 and 23 (26 of 1-8 K);
+//      row sum across 16 lanes and a third of the lanes on rows that are not there (20 of 32), the kernel issued 1.76 times as
+//      many vector instructions and took 66 us where it takes 57 (128 requests of 1-8 K tokens, 231 MB read), 1.42 times and 127
+//      where it takes 117 (64 of 512-32 K, 40 rows, 432 MB), 27 where it takes 23 (26 of 1-8 K);
 //   4. SELECT: Top-K of the keys in registers (topk_core.hpp) -- the statistic makes no round trip through
 //      memory between two launches (paper Section 4.1: identification from the verification's own
 //      intermediates).
