@@ -60,7 +60,7 @@ constexpr int kWindowPages = 64;               // page ids held per register: on
 constexpr int kFinishMaxTokens = 32768;        // longest row whose Top-K the finish kernel selects itself
 
 struct RangeWs {
-  int32_t* ctrl;        // [0] total units T
+  int32_t* ctrl;        // [0] total units T  [1] 0: equal ranges; else a range is a piece of one pair, 2^(ctrl[1] - 1) tiles
   int32_t* ureq;        // [B+1] first unit of request b (its heads follow each other)
   int32_t* order;       // [pairs] (request, head) pairs in the order the finish kernel takes them: longest rows first
   float* scratch_scores;  // [pairs][scratch_stride] statistic of the split finish kernel when the caller wants none
@@ -97,6 +97,27 @@ __device__ __forceinline__ int range_of(int unit, int total, int n) {
   return static_cast<int>(((static_cast<int64_t>(unit) + 1) * n - 1) / total);
 }
 
+// Small batches: pieces of one pair instead of equal ranges.  A range of a few tiles that crosses from pair to pair takes as long as its
+// stretches together (each a chain of loads and a merge), and the grid as long as that.  So a batch whose pairs make no more pieces
+// of 4, 8, 16 or 32 tiles than there are ranges is cut that way, into the shortest such pieces, one per range: a team has a tile per
+// wavefront in the shortest, and shorter ones would only leave more partials.  Equal ranges / pieces, pass + finish: 24 requests of 5-3000
+// tokens, 4 heads 15.5 + 14.9 / 11.4 + 12.4 us, one of 2100 11.0 + 15.2 / 10.0 + 12.5, 2 of 6-8 K 43.3 / 36.8 in all, fp8 with 40
+// rows 8 of 1-4 K 42.7 / 38.1 and 12 of 3-7 K 61.6 / 57.7, 24 of 10-3000 with 64 rows 47.6 / 35.0.  Pieces of 2 tiles for the pass
+// with two wavefronts per range: one request of 2100 tokens with 36 rows 34.4 us, of 4 tiles 29.5.  Beyond 32 tiles a range has few
+// boundaries anyway and equal ranges drain all at once (40 requests of 300-4000 tokens, 8 heads, no difference).
+constexpr int kMinPieceShift = 2, kMaxPieceShift = 5;
+__device__ __forceinline__ int pieces_of(int tiles, int shift) { return (tiles + (1 << shift) - 1) >> shift; }
+
+// Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or, with pieces, pair + (first unit >> shift), which
+// is distinct for the same reason (both indices grow along the layout).
+struct PairSegs { int slot0, n; };
+__device__ __forceinline__ PairSegs segs_of_pair(const RangeWs& ws, int pair, int u0, int tiles) {
+  const int total = ws.ctrl[0], cut = ws.ctrl[1];
+  if (cut > 0) return PairSegs{pair + (u0 >> (cut - 1)), pieces_of(tiles, cut - 1)};
+  const int n = ranges_used(ws, total), w0 = range_of(u0, total, n);
+  return PairSegs{pair + w0, range_of(u0 + tiles - 1, total, n) - w0 + 1};
+}
+
 // ---------------------------------------------------------------- plan ------
 // Unit prefix per request, and the order in which the finish kernel takes the (request, head) pairs:
 // longest requests first, so that the workgroups still running when the grid drains are short ones.
@@ -127,6 +148,7 @@ __global__ __launch_bounds__(1024) void range_plan(KvView kv, RangeWs ws) {
   if (threadIdx.x == 0) {
     ws.ureq[kv.batch] = carry;
     ws.ctrl[0] = carry;
+    ws.ctrl[1] = 0;
   }
   // rank of every request by length (ties by index); batches beyond one workgroup keep their own order
   if (kv.batch <= 1024) {
@@ -350,7 +372,7 @@ __device__ __forceinline__ int plan_get(const int (&v)[REGS], int b) {
 // requests w, w + N, ... by length (the order of the finish kernel: longest first, ties by index), wavefront 0
 // also writes the prefix.
 template <int REGS>
-__device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int w, int lane) {
+__device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int cut, int w, int lane) {
   for (int r = w; r < kv.batch; r += ws.n_ranges) {
     const int len_r = plan_get(p.len, r);
     int rank = 0;
@@ -373,6 +395,7 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
     if (lane == 0) {
       ws.ureq[kv.batch] = p.total;
       ws.ctrl[0] = p.total;
+      ws.ctrl[1] = cut;
     }
   }
 }
@@ -381,9 +404,24 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
 // memory (one of those that share a range).
 struct RangeStart {
   int unit, end;
+  int cut;                 // as ctrl[1]
   Segment sg;
   bool live;
 };
+
+// The shortest pieces with which the batch makes no more of them than there are ranges (log2 of their tiles plus one), or 0: equal ranges.
+template <int REGS>
+__device__ __forceinline__ int plan_pieces(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int lane) {
+  if (p.total > (ws.n_ranges << kMaxPieceShift)) return 0;
+  for (int shift = kMinPieceShift; shift <= kMaxPieceShift; ++shift) {
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < REGS; ++j) mine += pieces_of(tiles_of_len(p.len[j]), shift);         // 0 beyond the batch
+    const int pieces = __builtin_amdgcn_readlane(static_cast<int>(wave_inclusive_sum(static_cast<uint32_t>(mine))), kWave - 1);
+    if (pieces * kv.num_kv_heads <= ws.n_ranges) return shift + 1;
+  }
+  return 0;
+}
 
 // The range's units and, if it has any, the request it begins in and that request's first unit, from lengths in registers.  Batches of up
 // to 128 have a copy with two registers: stepping over the parts of the other fourteen, in every scan and every look-up, is
@@ -392,7 +430,34 @@ struct RangeStart {
 template <int REGS>
 __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish, RangeStart& c, int& first_unit) {
   const WavePlan<REGS> p = wave_plan<REGS>(kv, lane);
-  if (publish) publish_plan(kv, ws, p, w, lane);
+  const int cut = plan_pieces<REGS>(kv, ws, p, lane);
+  if (publish) publish_plan(kv, ws, p, cut, w, lane);
+  c.cut = cut;
+  if (cut > 0) {
+    const int shift = cut - 1;
+    int carry = 0, upto = 0, before[REGS];                   // pieces before a request; requests that begin at or before piece w
+#pragma unroll
+    for (int j = 0; j < REGS; ++j) {
+      before[j] = carry;
+      if (kWave * j < kv.batch) {
+        const int mine = pieces_of(tiles_of_len(p.len[j]), shift) * kv.num_kv_heads;
+        const int incl = static_cast<int>(wave_inclusive_sum(static_cast<uint32_t>(mine)));
+        before[j] = carry + incl - mine;
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+        upto += __popcll(__ballot(kWave * j + lane < kv.batch && before[j] <= w));
+      }
+    }
+    c.live = w < carry;
+    if (!c.live) return;
+    c.sg.b = upto - 1;
+    c.sg.L = plan_get(p.len, c.sg.b);
+    first_unit = plan_get(p.first, c.sg.b);
+    const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift);
+    const int rel = w - plan_get(before, c.sg.b), head = rel / per_head, tile0 = (rel - head * per_head) << shift;
+    c.unit = first_unit + head * tiles + tile0;
+    c.end = c.unit + min(tiles - tile0, 1 << shift);
+    return;
+  }
   const int n = ranges_used(ws, p.total);
   c.unit = range_begin(w, p.total, n);
   c.end = range_begin(w + 1, p.total, n);
@@ -411,6 +476,7 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
 __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
   RangeStart c;
   c.sg = Segment{};
+  c.cut = 0;
   int first_unit = 0;                          // of the request the range begins in
   if (ws.plan_in_wave) {                       // the same for the whole grid
     if (kv.batch <= 2 * kWave) plan_range<2>(kv, ws, w, lane, publish, c, first_unit);
@@ -435,7 +501,7 @@ __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs
   sg.tile0 = rel - sg.g * sg.tiles;
   sg.tile1 = min(sg.tiles, sg.tile0 + (c.end - c.unit));
   sg.pair = sg.b * kv.num_kv_heads + sg.g;
-  sg.slot = sg.pair + w;
+  sg.slot = sg.pair + (c.cut > 0 ? c.unit >> (c.cut - 1) : w);
   return c;
 }
 
@@ -1826,10 +1892,8 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     }
     return;
   }
-  const int total = ws.ctrl[0];
   const int u0 = ws.ureq[b] + g * tiles;
-  const int n_used = ranges_used(ws, total);
-  const int w0 = range_of(u0, total, n_used), w1 = range_of(u0 + tiles - 1, total, n_used);
+  const PairSegs segs = segs_of_pair(ws, pair, u0, tiles);
 
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nv = R - 16 * (RB - 1);
@@ -1904,8 +1968,8 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   constexpr int kSegs = CH == 4 ? 3 : THREADS >= 1024 || RB == 2 ? 4 : 5;
   constexpr int kOuts = (rows * (kHeadDim / 4) + THREADS - 1) / THREADS;
   static_assert(2 * kPar * rows <= kChunk, "the (m, l) of the segments wait where the scores will be");
-  const int nseg = w1 - w0 + 1;
-  const bool split = w1 > w0;
+  const int nseg = segs.n;
+  const bool split = nseg > 1;
   const int n_share = SPLIT ? (L + kChunk - 1) / kChunk : 1;             // workgroups of this pair
   const int pieces = Rb * (kHeadDim / 4);
   const int my_first = my_chunk * pieces / n_share, my_end = (my_chunk + 1) * pieces / n_share;
@@ -1918,7 +1982,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
       for (int sg = 0; sg < kSegs; ++sg) {
         po[o][sg] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (idx < my_end && sg < nseg)
-          po[o][sg] = *reinterpret_cast<const f32x4*>(ws.part_o + static_cast<int64_t>(pair + w0 + sg) * R * kHeadDim + 4 * idx);
+          po[o][sg] = *reinterpret_cast<const f32x4*>(ws.part_o + static_cast<int64_t>(segs.slot0 + sg) * R * kHeadDim + 4 * idx);
       }
     }
   }
@@ -1931,8 +1995,8 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     float m = -INFINITY, l = 0.f;
     if (merging) {
       for (int sg = my_sg; sg < nseg; sg += kPar) {
-        const float mc = ws.part_m[static_cast<int64_t>(pair + w0 + sg) * rows + my_row];
-        const float lc = ws.part_l[static_cast<int64_t>(pair + w0 + sg) * rows + my_row];
+        const float mc = ws.part_m[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
+        const float lc = ws.part_l[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
         if (sg == my_sg) m_seg = mc;
         const float mn = fmaxf(m, mc);
         const float mu = (mn == -INFINITY) ? 0.f : mn;
@@ -1967,7 +2031,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     for (int c0 = 0; c0 < nseg; c0 += kPar) {            // (one turn unless a pair spans very many ranges)
       if (c0 > 0) __syncthreads();                       // the weights of the previous turn have been read
       if (merging && c0 + my_sg < nseg) {
-        const float m = c0 == 0 ? m_seg : ws.part_m[static_cast<int64_t>(pair + w0 + c0 + my_sg) * rows + my_row];
+        const float m = c0 == 0 ? m_seg : ws.part_m[static_cast<int64_t>(segs.slot0 + c0 + my_sg) * rows + my_row];
         s_m[threadIdx.x] = fast_exp2(m - s_lse[my_row]);
       }
       __syncthreads();
@@ -1977,7 +2041,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
         const int idx = my_first + static_cast<int>(threadIdx.x) + o * THREADS;
         if (idx >= my_end) continue;
         const float* wgt = s_m + idx / (kHeadDim / 4);
-        const float* src = ws.part_o + static_cast<int64_t>(pair + w0 + c0) * R * kHeadDim + 4 * idx;
+        const float* src = ws.part_o + static_cast<int64_t>(segs.slot0 + c0) * R * kHeadDim + 4 * idx;
         int sg = 0;
         if (c0 == 0) {
 #pragma unroll

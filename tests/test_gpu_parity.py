@@ -630,6 +630,26 @@ def test_short_segments_among_long_ones(kv_dtype, heads, k, page):
         pa.pillar_set_option("verify_waves", 0)
 
 
+@pytest.mark.parametrize("copies", [1, 14])
+@pytest.mark.parametrize("kv_dtype,page,heads,k", [("bf16", 16, 4, 2), ("bf16", 64, 16, 3), ("fp8_e4m3", 16, 16, 4), ("bf16", 32, 16, 4), ("fp8_e4m3", 16, 16, 7)])
+def test_pieces_of_small_batches_and_ranges_of_larger_ones(kv_dtype, page, heads, k, copies):
+    """A batch whose pairs make no more pieces of 4 to 32 tiles than there are ranges (64, or 256 with more than 32 rows) has a range per
+    piece, a larger one equal ranges: contexts of whole pieces and a token more or less, either side of that line, with and without
+    the statistic."""
+    one = [k + 1, 127, 128, 129, 257, 384, 32 * 16 + 5, 32 * 32, 32 * 32 + 1, 32 * 33 - 1]
+    lens = one * copies
+    w = small(290 + k, kv_dtype=kv_dtype, P=page, B=len(lens), Hq=heads, Hkv=2, spec_k=k, seq_lens=lens, budgets=[min(n, 40) for n in lens])
+    pa.pillar_set_option("verify_waves", 1)
+    try:
+        run, _ = round_trip(w, what=f"pieces, {copies} times", fused_select=True)
+        bare = GpuRun(w)
+        bare.verify(with_scores=False)
+        torch.cuda.synchronize()
+        assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
+    finally:
+        pa.pillar_set_option("verify_waves", 0)
+
+
 def test_ranges_over_more_requests_than_lanes():
     """4500 requests of one tile in 64 ranges: a range's lengths come 64 requests at a time; every seventh is empty."""
     rng = np.random.default_rng(41)
