@@ -112,7 +112,7 @@ __device__ __forceinline__ int pieces_of(int tiles, int shift) { return (tiles +
 // is distinct for the same reason (both indices grow along the layout).
 struct PairSegs { int slot0, n; };
 __device__ __forceinline__ PairSegs segs_of_pair(const RangeWs& ws, int pair, int u0, int tiles) {
-  const int total = ws.ctrl[0], cut = ws.ctrl[1];
+  const int total = max(ws.ctrl[0], 1), cut = ws.ctrl[1];
   if (cut > 0) return PairSegs{pair + (u0 >> (cut - 1)), pieces_of(tiles, cut - 1)};
   const int n = ranges_used(ws, total), w0 = range_of(u0, total, n);
   return PairSegs{pair + w0, range_of(u0 + tiles - 1, total, n) - w0 + 1};
@@ -1827,6 +1827,106 @@ __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, c
 // few exponents queue up on far fewer LDS addresses.
 __device__ __forceinline__ uint32_t score_key(float f) { return __float_as_uint(f) << 2; }
 
+// Log-sum-exp of every row of a pair (log2 domain) into s_lse, by the first 512 threads: kParSegs threads per row take the segments in turn,
+// so that the (m, l) of all segments leave together, and combine through LDS (s_m: 2 * 512 floats; the number of threads per row is the
+// same for every workgroup size, so the order of the sums is, too).  Rows beyond the request's own, and rows that see no token at
+// all, get +inf: their probabilities vanish wherever the log-sum-exp is applied.  Returns the maximum of this thread's first segment.
+template <int RB> constexpr int kParSegs = 512 / (RB * 16);
+template <int RB>
+__device__ __forceinline__ float pair_lse(const KvView& kv, const RangeWs& ws, int n_q, int G, int Rb, int rq, int g, const PairSegs& segs,
+                                          float* lse_out, float* s_m, float* s_lse) {
+  constexpr int rows = RB * 16, kPar = kParSegs<RB>;
+  float* s_l = s_m + kPar * rows;
+  const int my_row = static_cast<int>(threadIdx.x) % rows, my_sg = static_cast<int>(threadIdx.x) / rows;
+  float m_seg = -INFINITY;
+  if (my_sg < kPar) {
+    float m = -INFINITY, l = 0.f;
+    for (int sg = my_sg; sg < segs.n; sg += kPar) {
+      const float mc = ws.part_m[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
+      const float lc = ws.part_l[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
+      if (sg == my_sg) m_seg = mc;
+      const float mn = fmaxf(m, mc);
+      const float mu = (mn == -INFINITY) ? 0.f : mn;
+      l = l * fast_exp2(m - mu) + lc * fast_exp2(mc - mu);
+      m = mn;
+    }
+    s_m[threadIdx.x] = m;
+    s_l[threadIdx.x] = l;
+  }
+  __syncthreads();
+  if (threadIdx.x < rows) {
+    const int row = threadIdx.x;
+    float m = -INFINITY, l = 0.f;
+    // (every place has been written, -inf and 0 where there is no segment, so all reads leave together)
+#pragma unroll
+    for (int sg = 0; sg < kPar; ++sg) m = fmaxf(m, s_m[sg * rows + row]);
+    const float mu = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+    for (int sg = 0; sg < kPar; ++sg) l += s_l[sg * rows + row] * fast_exp2(s_m[sg * rows + row] - mu);
+    const bool live = row < Rb && l > 0.f;
+    const float v = live ? m + log2f(l) : INFINITY;
+    s_lse[row] = v;
+    if (lse_out && row < Rb) {
+      const int i = row / G, hg = row - i * G;
+      lse_out[(static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg] = live ? v * kLn2 : -INFINITY;
+    }
+  }
+  __syncthreads();
+  return m_seg;
+}
+
+// O of a pair cut into several segments, by `mergers` workgroups of its own: 512 threads take four rows (a piece of four dims of one each)
+// by four groups that take the segments in turn.  What it costs one workgroup is the rate at which a compute unit reads what others have
+// written: 17 to 33 segments of 10 KB each took 3 to 5 us between the log-sum-exp and the scores.
+template <int RB, int THREADS>
+__device__ __forceinline__ void merge_pair(const KvView& kv, int n_q, const RangeWs& ws, uint16_t* out, int share, int mergers, float* s_o, float* s_lse) {
+  const int pair = ws.order ? ws.order[blockIdx.x] : static_cast<int>(blockIdx.x);
+  const int b = pair / kv.num_kv_heads, g = pair - b * kv.num_kv_heads, rq = request_of(kv, b);
+  const int G = kv.num_q_heads / kv.num_kv_heads, R = n_q * G, Rb = queries_of(kv, ws, b, n_q) * G, tiles = tiles_of_len(kv.seq_lens[rq]);
+  constexpr int rows = RB * 16;
+  const PairSegs segs = segs_of_pair(ws, pair, ws.ureq[b] + g * tiles, tiles);
+  if (tiles <= 0 || segs.n <= 1) return;       // (one segment: the pass has written O)
+  pair_lse<RB>(kv, ws, n_q, G, Rb, rq, g, segs, nullptr, s_o, s_lse);
+  constexpr int kQuads = THREADS / 512, kGroups = 4, kAtOnce = 8;        // quads of rows at work; segments of a thread sent for together
+  const int sub = static_cast<int>(threadIdx.x) / 512, grp = static_cast<int>(threadIdx.x) % 512 / 128, piece = static_cast<int>(threadIdx.x) % 128;
+  f32x4* mine = reinterpret_cast<f32x4*>(s_o) + threadIdx.x;
+  for (int q0 = share * kQuads; 4 * q0 < Rb; q0 += mergers * kQuads) {
+    const int row = 4 * (q0 + sub) + piece / 32, d4 = piece % 32;
+    const bool there = row < Rb;
+    const float* src = ws.part_o + static_cast<int64_t>(segs.slot0) * R * kHeadDim + row * kHeadDim + 4 * d4;
+    const float* pm = ws.part_m + static_cast<int64_t>(segs.slot0) * rows + row;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (there) {
+      const float lse = s_lse[row];
+      for (int sg0 = grp; sg0 < segs.n; sg0 += kGroups * kAtOnce) {
+        f32x4 po[kAtOnce];
+        float m[kAtOnce];
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {
+          const int sg = min(sg0 + kGroups * j, segs.n - 1);
+          po[j] = *reinterpret_cast<const f32x4*>(src + static_cast<int64_t>(sg) * R * kHeadDim);
+          m[j] = pm[static_cast<int64_t>(sg) * rows];
+        }
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j)
+          if (sg0 + kGroups * j < segs.n) acc += po[j] * fast_exp2(m[j] - lse);
+      }
+    }
+    *mine = acc;
+    __syncthreads();
+    if (there && grp == 0) {
+#pragma unroll
+      for (int i = 1; i < kGroups; ++i) acc += mine[128 * i];
+      const int i = row / G, hg = row - i * G;
+      u32x2 pk;
+      pk.x = pack2(acc.x, acc.y);
+      pk.y = pack2(acc.z, acc.w);
+      *reinterpret_cast<u32x2*>(out + ((static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg) * kHeadDim + 4 * d4) = pk;
+    }
+    __syncthreads();                           // the next rows take their place
+  }
+}
+
 // ------------------------------------------------ finish ---------------------
 // Everything that needs the whole pair, in one kernel: one workgroup per (request, KV head), longest
 // rows first.
@@ -1849,11 +1949,12 @@ __device__ __forceinline__ uint32_t score_key(float f) { return __float_as_uint(
 // next launch, selects from it.  The first chunk's workgroup also does step 1's output and step 2.  (Handing the
 // chunks to the last workgroup to arrive inside one launch was measured: the device-wide release every workgroup
 // then needs writes back the whole L2 behind it, 3 to 5 times the cost of the extra launch.)
+// With `mergers` (few pairs), workgroups 1 .. mergers of a pair, by blockIdx.y, do step 2 and nothing else, the others no step 2.
 // Up to two row blocks, two workgroups of 512 threads share a compute unit, which takes 128 registers at most: with 129, 128 requests of
 // 1-8 K tokens took 539 us instead of 518 (pass and finish).
 template <int RB, int THREADS, int CH, bool SELECT, bool SPLIT>
 __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void verify_finish(KvView kv, int n_q, RangeWs ws, uint16_t* out, float* lse_out,
-                                                         float* scores, int64_t score_stride, SelectOut sel) {
+                                                         float* scores, int64_t score_stride, SelectOut sel, int mergers) {
   static_assert(!SPLIT || !SELECT, "a split pair is selected by verify_select_rows");
   constexpr int KPC = 8;
   constexpr int kChunk = THREADS * KPC;                      // tokens whose scores LDS holds at a time
@@ -1862,7 +1963,11 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   __shared__ __attribute__((aligned(16))) float s_scores[kChunk];
   __shared__ float s_lse[RB * 16];
   __shared__ SelectLds<THREADS, CH> lds;
-  const int pair = ws.order[blockIdx.x];
+  if (static_cast<int>(blockIdx.y) - 1 < mergers && blockIdx.y > 0) {
+    merge_pair<RB, THREADS>(kv, n_q, ws, out, static_cast<int>(blockIdx.y) - 1, mergers, s_scores, s_lse);
+    return;
+  }
+  const int pair = ws.order ? ws.order[blockIdx.x] : static_cast<int>(blockIdx.x);
   const int b = pair / kv.num_kv_heads, g = pair - b * kv.num_kv_heads;
   const int rq = request_of(kv, b);
   const int L = kv.seq_lens[rq];
@@ -1871,7 +1976,11 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   const int R = n_q * G;
   const int Rb = queries_of(kv, ws, b, n_q) * G;
   constexpr int rows = RB * 16;
-  const int my_chunk = SPLIT ? static_cast<int>(blockIdx.y) : 0;
+  const int u0 = ws.ureq[b] + g * tiles;
+  const PairSegs segs = segs_of_pair(ws, pair, u0, tiles);
+  const int nseg = segs.n;
+  const bool split = nseg > 1;
+  const int my_chunk = SPLIT && blockIdx.y > 0 ? static_cast<int>(blockIdx.y) - mergers : 0;
   if (SPLIT && my_chunk > 0 && my_chunk * kChunk >= L) return;      // this pair has fewer chunks (uniform over the workgroup)
   const bool lead = my_chunk == 0;                       // the workgroup that writes what exists once per pair
   int K = 0;
@@ -1892,8 +2001,6 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     }
     return;
   }
-  const int u0 = ws.ureq[b] + g * tiles;
-  const PairSegs segs = segs_of_pair(ws, pair, u0, tiles);
 
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nv = R - 16 * (RB - 1);
@@ -1954,27 +2061,24 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   };
   if (want_scores) prime(my_chunk);                    // needs nothing of steps 1 and 2: in flight meanwhile
 
-  // 1. log-sum-exp per row (log2 domain).  kPar threads per row take the segments in turn, so that the (m, l) of all
-  // segments leave together, and combine through LDS.  Rows beyond the request's own, and rows that see no token at
-  // all, get +inf: their probabilities vanish wherever the log-sum-exp is applied.
+  // 1. log-sum-exp per row (log2 domain).
   // 2. O of a pair cut into several segments.  The partials of the first kSegs segments are fetched before the
   // log-sum-exp is known (every thread owns up to kOuts pieces of 4 dims), so both waits overlap; the weights of kPar
   // segments at a time wait in LDS.  The workgroups that share a pair (SPLIT) share its pieces too.
   // A loop over the segments by one thread per row was a round trip to memory per segment: one request of 2100 tokens
   // (66 segments of one tile) 96 -> 20 us, 32 of 4096 tokens (5) 25 -> 19 us, 26 of up to 8 K tokens (10) 47 -> 30 us.
-  constexpr int kPar = 512 / rows;                       // (the same for every THREADS: the order of the sums is, too)
+  constexpr int kPar = kParSegs<RB>;
   // (as many as the registers hold beside the stash that is on its way: with 5, two row blocks of a 512-thread workgroup spill up to
-  // five; the keys of four chunks leave room for 3)
-  constexpr int kSegs = CH == 4 ? 3 : THREADS >= 1024 || RB == 2 ? 4 : 5;
+  // five; the keys of four chunks leave room for 2 or 3)
+  constexpr int kSegs = CH == 4 ? (RB == 4 ? 2 : 3) : THREADS >= 1024 || RB == 2 ? 4 : 5;
   constexpr int kOuts = (rows * (kHeadDim / 4) + THREADS - 1) / THREADS;
   static_assert(2 * kPar * rows <= kChunk, "the (m, l) of the segments wait where the scores will be");
-  const int nseg = segs.n;
-  const bool split = nseg > 1;
+  const bool merge_here = split && mergers == 0;
   const int n_share = SPLIT ? (L + kChunk - 1) / kChunk : 1;             // workgroups of this pair
   const int pieces = Rb * (kHeadDim / 4);
   const int my_first = my_chunk * pieces / n_share, my_end = (my_chunk + 1) * pieces / n_share;
   f32x4 po[kOuts][kSegs];
-  if (split) {
+  if (merge_here) {
 #pragma unroll
     for (int o = 0; o < kOuts; ++o) {
       const int idx = my_first + static_cast<int>(threadIdx.x) + o * THREADS;
@@ -1987,44 +2091,10 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     }
   }
   float* s_m = s_scores;                                 // [kPar][rows] maximum, then weight, of a segment's rows
-  float* s_l = s_scores + kPar * rows;
   const int my_row = static_cast<int>(threadIdx.x) % rows, my_sg = static_cast<int>(threadIdx.x) / rows;
   const bool merging = my_sg < kPar;
-  float m_seg = -INFINITY;                               // of this thread's first segment
-  {
-    float m = -INFINITY, l = 0.f;
-    if (merging) {
-      for (int sg = my_sg; sg < nseg; sg += kPar) {
-        const float mc = ws.part_m[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
-        const float lc = ws.part_l[static_cast<int64_t>(segs.slot0 + sg) * rows + my_row];
-        if (sg == my_sg) m_seg = mc;
-        const float mn = fmaxf(m, mc);
-        const float mu = (mn == -INFINITY) ? 0.f : mn;
-        l = l * fast_exp2(m - mu) + lc * fast_exp2(mc - mu);
-        m = mn;
-      }
-      s_m[threadIdx.x] = m;
-      s_l[threadIdx.x] = l;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < rows) {
-    const int row = threadIdx.x;
-    const int live_sg = min(nseg, kPar);
-    float m = -INFINITY, l = 0.f;
-    for (int sg = 0; sg < live_sg; ++sg) m = fmaxf(m, s_m[sg * rows + row]);
-    const float mu = (m == -INFINITY) ? 0.f : m;
-    for (int sg = 0; sg < live_sg; ++sg) l += s_l[sg * rows + row] * fast_exp2(s_m[sg * rows + row] - mu);
-    const bool live = row < Rb && l > 0.f;
-    const float v = live ? m + log2f(l) : INFINITY;
-    s_lse[row] = v;
-    if (lse_out && row < Rb && lead) {
-      const int i = row / G, hg = row - i * G;
-      lse_out[(static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg] = live ? v * kLn2 : -INFINITY;
-    }
-  }
-  __syncthreads();
-  if (split) {
+  const float m_seg = pair_lse<RB>(kv, ws, n_q, G, Rb, rq, g, segs, lead ? lse_out : nullptr, s_m, s_lse);       // of this thread's first segment
+  if (merge_here) {
     f32x4 acc[kOuts];
 #pragma unroll
     for (int o = 0; o < kOuts; ++o) acc[o] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -2224,6 +2294,18 @@ int team_ranges(int slots) {
   return std::min(slots, std::max(1, (opt > 0 ? opt : 8) * num_cus() / kTeamWaves));
 }
 
+// Workgroups of the finish kernel that put O of one pair together and do nothing else: where half the chip would idle, as many as it holds
+// beside the others (one per pair and 8192 tokens) in two rounds.  The rule must not ask for the statistic: with and without it, O has
+// the same bits.  Without / with them, whole call: one request of 2100 tokens 26.4 / 23.5 us, 24 of 5-3000 24.1 / 20.4, 16 of 2-4 K with 8
+// heads 60.7 / 57.0, 24 of 10-3000 with 64 rows 35.0 / 27.0, one of 32 K 64.4 / 56.0, one of 8 K without the statistic 41.1 / 30.3.
+// With every compute unit taken by the statistic they only get in its way: 16 requests of 24-32 K tokens 494 / 496.
+int merger_groups(const KvView& kv, int n_q, int threads) {
+  const int64_t pairs = static_cast<int64_t>(kv.batch) * kv.num_kv_heads, others = pairs * ((kv.max_seq_len + 8191) / 8192);
+  if (2 * others > num_cus()) return 0;
+  const int at_once = 4 * (threads / 512), rows = n_q * (kv.num_q_heads / kv.num_kv_heads);       // rows of a turn
+  return std::min(static_cast<int>(2 * (num_cus() - others) / pairs), (rows + at_once - 1) / at_once);
+}
+
 int row_blocks(const KvView& kv, int n_q) { return (n_q * (kv.num_q_heads / kv.num_kv_heads) + 15) / 16; }
 
 RangeWs carve(const KvView& kv, int n_q, void* workspace, size_t* total_bytes) {
@@ -2317,14 +2399,19 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
       // one workgroup per pair: log-sum-exp, O of split pairs, scores, selection
       KernelTimer t("verify_finish", st);
       sel = a.select ? *a.select : SelectOut{};
-#define PILLAR_FINISH(THREADS, CH, SELECT)                                                                                           \
-  hipLaunchKernelGGL((verify_finish<RB, THREADS, CH, SELECT, false>), dim3(pairs), dim3(THREADS), 0, st, kv, a.n_q, ws, out, a.lse, \
-                     a.scores, a.score_stride, sel)
+#define PILLAR_FINISH(THREADS, CH, SELECT)                                                                                          \
+  {                                                                                                                                 \
+    const int mergers = merger_groups(kv, a.n_q, THREADS);                                                                          \
+    if (pairs <= num_cus()) ws.order = nullptr;                                                                                     \
+    hipLaunchKernelGGL((verify_finish<RB, THREADS, CH, SELECT, false>), dim3(pairs, mergers + 1), dim3(THREADS), 0, st, kv, a.n_q,  \
+                       ws, out, a.lse, a.scores, a.score_stride, sel, mergers);                                                     \
+  }
 #define PILLAR_FINISH_SPLIT(CH)                                                                                                   \
   {                                                                                                                               \
     const int nchunks = (kv.max_seq_len + 8191) / 8192;                                                                           \
-    hipLaunchKernelGGL((verify_finish<RB, 1024, 1, false, true>), dim3(pairs, nchunks), dim3(1024), 0, st, kv, a.n_q, ws, out,    \
-                       a.lse, a.scores, a.score_stride, sel);                                                                     \
+    const int mergers = merger_groups(kv, a.n_q, 1024);                                                                           \
+    hipLaunchKernelGGL((verify_finish<RB, 1024, 1, false, true>), dim3(pairs, mergers + nchunks), dim3(1024), 0, st, kv, a.n_q,   \
+                       ws, out, a.lse, a.scores, a.score_stride, sel, mergers);                                                   \
     split_select = CH;                                                                                                            \
   }
       // few pairs (a unified batch with a handful of verifying requests): every pair gets 16 wavefronts, the
@@ -2333,17 +2420,17 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
       // resident and merged their segments one by one)
       const bool few = pairs <= 2 * num_cus();
       if (!a.select && a.scores && kv.max_seq_len > 8192 && pairs <= num_cus()) PILLAR_FINISH_SPLIT(0)   // (statistic only)
-      else if (!a.select) PILLAR_FINISH(512, 1, false);
-      else if (kv.max_seq_len <= 4096 && !few) PILLAR_FINISH(512, 1, true);
-      else if (kv.max_seq_len <= 8192 && few) PILLAR_FINISH(1024, 1, true);
-      else if (kv.max_seq_len <= 8192) PILLAR_FINISH(512, 2, true);
+      else if (!a.select) PILLAR_FINISH(512, 1, false)
+      else if (kv.max_seq_len <= 4096 && !few) PILLAR_FINISH(512, 1, true)
+      else if (kv.max_seq_len <= 8192 && few) PILLAR_FINISH(1024, 1, true)
+      else if (kv.max_seq_len <= 8192) PILLAR_FINISH(512, 2, true)
       // long rows: with fewer pairs than compute units a pair is shared by several workgroups (measured at 128 pairs
       // of 28 K tokens: 121 against 142 us); with more pairs one workgroup per pair keeps everything in one launch
       // (512 pairs of up to 32 K tokens: 149 against 163 us)
       else if (kv.max_seq_len <= 16384 && pairs <= num_cus()) PILLAR_FINISH_SPLIT(2)
-      else if (kv.max_seq_len <= 16384) PILLAR_FINISH(1024, 2, true);
+      else if (kv.max_seq_len <= 16384) PILLAR_FINISH(1024, 2, true)
       else if (pairs <= num_cus()) PILLAR_FINISH_SPLIT(4)
-      else PILLAR_FINISH(1024, 4, true);
+      else PILLAR_FINISH(1024, 4, true)
 #undef PILLAR_FINISH_SPLIT
 #undef PILLAR_FINISH
     }

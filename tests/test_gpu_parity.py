@@ -650,6 +650,23 @@ def test_pieces_of_small_batches_and_ranges_of_larger_ones(kv_dtype, page, heads
         pa.pillar_set_option("verify_waves", 0)
 
 
+@pytest.mark.parametrize("batch", [64, 65])
+@pytest.mark.parametrize("kv_dtype,heads,k", [("bf16", 4, 0), ("bf16", 8, 4), ("bf16", 16, 4), ("fp8_e4m3", 16, 7)])
+def test_output_put_together_by_workgroups_of_its_own(kv_dtype, heads, k, batch):
+    """With up to 128 pairs (two KV heads here), O of a pair of several segments is put together by workgroups that do nothing else, with
+    more by the one that rebuilds the statistic: rows in every number of fours, contexts of one segment to ten,
+    speculative lengths of their own, and the same bits without the statistic."""
+    rng = np.random.default_rng(43 + k)
+    lens = [k + 1, 100, 128, 129, 1290] + rng.integers(k + 1, 700, size=batch - 5).tolist()
+    w = small(300 + k, kv_dtype=kv_dtype, Hq=heads, B=batch, Hkv=2, spec_k=k, seq_lens=lens, budgets=[min(n, 24) for n in lens])
+    run, _ = round_trip(w, what=f"{batch} requests, {kv_dtype}, {heads} heads", fused_select=True)
+    bare = GpuRun(w)
+    bare.verify(with_scores=False)
+    torch.cuda.synchronize()
+    assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
+    _hetero_case(w, rng.integers(0, k + 1, size=w.B), "hetero k", with_select=True)
+
+
 def test_ranges_over_more_requests_than_lanes():
     """4500 requests of one tile in 64 ranges: a range's lengths come 64 requests at a time; every seventh is empty."""
     rng = np.random.default_rng(41)
