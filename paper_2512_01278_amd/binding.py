@@ -129,8 +129,9 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
+    # (the handle alone: a torch.cuda.Stream object around it takes 2.8 us, a third of a whole draft call on the host; this 0.2)
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     return stream.cuda_stream or None
 
 
@@ -152,27 +153,12 @@ class KvCache:
 
     def c_struct(self) -> pillar_kv_t:
         kp = self.k_pool
-        s = pillar_kv_t()
-        s.batch = self.block_table.shape[0]
-        s.num_q_heads = self.num_q_heads
-        s.num_kv_heads = kp.shape[1]
-        s.head_dim = kp.shape[3]
-        s.page_size = kp.shape[2]
-        s.q_dtype = DTYPE_CODE[self.q_dtype]
-        s.kv_dtype = DTYPE_CODE[self.kv_dtype]
-        s.sm_scale = self.sm_scale
-        s.k_pool = kp.data_ptr()
-        s.v_pool = self.v_pool.data_ptr()
-        s.stride_page, s.stride_head, s.stride_slot = kp.stride(0), kp.stride(1), kp.stride(2)
-        s.k_scale = _ptr(self.k_scale)
-        s.v_scale = _ptr(self.v_scale)
-        s.num_pages = kp.shape[0]
-        s.block_table_stride = self.block_table.stride(0)
-        s.block_table = self.block_table.data_ptr()
-        s.seq_lens = self.seq_lens.data_ptr()
-        s.max_seq_len = self.max_seq_len
-        s.flags = self.flags
-        return s
+        shape, strides = kp.shape, kp.stride()
+        # in the order of the fields (one by one they take 1.7 us)
+        return pillar_kv_t(self.block_table.shape[0], self.num_q_heads, shape[1], shape[3], shape[2], DTYPE_CODE[self.q_dtype],
+                           DTYPE_CODE[self.kv_dtype], self.sm_scale, kp.data_ptr(), self.v_pool.data_ptr(), strides[0], strides[1], strides[2],
+                           _ptr(self.k_scale), _ptr(self.v_scale), shape[0], self.block_table.stride(0),
+                           self.block_table.data_ptr(), self.seq_lens.data_ptr(), self.max_seq_len, self.flags)
 
 
 def pillar_workspace_bytes(kv: KvCache, spec_len_k: int, max_budget: int) -> int:
