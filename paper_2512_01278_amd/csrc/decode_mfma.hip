@@ -30,33 +30,56 @@ constexpr int kMergeThreads = 256;
 constexpr int kSpanRows = 512;                 // rows of an index list one workgroup takes
 
 
-template <bool FP8>
+template <bool FP8, bool BYPASS>
 __global__ __launch_bounds__(kDecThreads, 3) void decode_span_mfma(DecodeArgs a, DecWs ws, int span_rows, int nspan_max) {
   __shared__ __attribute__((aligned(16))) uint8_t s_tiles[kDecWaves][kVTileBytes];
   const DecPlace at = decode_place(FP8, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), a.kv.batch, a.kv.num_kv_heads, nspan_max);
-  decode_span_body<FP8, kDecWaves>(a, ws, span_rows, nspan_max, at.slot_b, at.g, at.sp, s_tiles);
+  decode_span_body<FP8, kDecWaves, BYPASS>(a, ws, span_rows, nspan_max, at.slot_b, at.g, at.sp, s_tiles);
 }
 
+// Everything a thread needs of up to kAtOnce spans is sent for at once, before the count says how many there are (spans that the list does
+// not have are room in the workspace all the same, and are left out by selection).  A loop over them waits for memory twice per span.
 __global__ __launch_bounds__(kMergeThreads) void decode_merge_mfma(DecodeArgs a, DecWs ws, int split_rows, int nsplit_max) {
+  constexpr int kAtOnce = 4;
   const KvView& kv = a.kv;
   const int slot_b = blockIdx.y, g = blockIdx.x;
   const int b = request_of(kv, slot_b);
   const int G = kv.num_q_heads / kv.num_kv_heads;
-  const int count = min(max(a.counts[b], 0), a.max_budget);
-  const int nsplit = (count + split_rows - 1) / split_rows;
-  if (nsplit <= 1) return;
   uint16_t* out = static_cast<uint16_t*>(a.out);
   const int64_t base = (static_cast<int64_t>(slot_b) * kv.num_kv_heads + g) * nsplit_max;
   for (int idx = threadIdx.x; idx < G * (kHeadDim / 4); idx += kMergeThreads) {
     const int r = idx / (kHeadDim / 4), d4 = idx - r * (kHeadDim / 4);
-    float m = -INFINITY;
-    for (int s = 0; s < nsplit; ++s) m = fmaxf(m, ws.part_m[(base + s) * 16 + r]);
-    float l = 0.f;
+    float m = -INFINITY, l = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < nsplit; ++s) {
-      const float w = exp2f(ws.part_m[(base + s) * 16 + r] - m);
-      l = fmaf(ws.part_l[(base + s) * 16 + r], w, l);
-      acc += *reinterpret_cast<const f32x4*>(ws.part_o + ((base + s) * G + r) * kHeadDim + 4 * d4) * w;
+    int nsplit = nsplit_max;
+    for (int s0 = 0; s0 < nsplit; s0 += kAtOnce) {
+      float ms[kAtOnce], ls[kAtOnce];
+      f32x4 os[kAtOnce];
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        const int64_t slot = base + min(s0 + j, nsplit_max - 1);
+        ms[j] = ws.part_m[slot * 16 + r];
+        ls[j] = ws.part_l[slot * 16 + r];
+        os[j] = *reinterpret_cast<const f32x4*>(ws.part_o + (slot * G + r) * kHeadDim + 4 * d4);
+      }
+      nsplit = (min(max(a.counts[b], 0), a.max_budget) + split_rows - 1) / split_rows;
+      if (nsplit <= 1) return;                     // the same for the workgroup: the list's only span has written the output
+      float m_new = m;
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j)
+        if (s0 + j < nsplit) m_new = fmaxf(m_new, ms[j]);
+      const float keep = exp2f(m - m_new);
+      l *= keep;
+      acc *= keep;
+      m = m_new;
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        if (s0 + j < nsplit) {
+          const float w = exp2f(ms[j] - m);
+          l = fmaf(ls[j], w, l);
+          acc += os[j] * w;
+        }
+      }
     }
     const float inv = 1.0f / l;
     const int64_t row = static_cast<int64_t>(b) * kv.num_q_heads + g * G + r;
@@ -100,8 +123,8 @@ hipError_t run(const DecodeArgs& a, hipStream_t st) {
   const DecWs ws = carve(kv, a.max_budget, a.workspace, nullptr);
   {
     KernelTimer t("decode_span_mfma", st);
-    hipLaunchKernelGGL((decode_span_mfma<FP8>), dim3(nsplit, kv.num_kv_heads, kv.batch), dim3(kDecThreads), 0, st, a, ws, split_rows,
-                       nsplit);
+    const auto kernel = draft_bypasses(static_cast<int64_t>(kv.batch) * kv.num_kv_heads * a.max_budget, FP8) ? decode_span_mfma<FP8, true> : decode_span_mfma<FP8, false>;
+    hipLaunchKernelGGL(kernel, dim3(nsplit, kv.num_kv_heads, kv.batch), dim3(kDecThreads), 0, st, a, ws, split_rows, nsplit);
   }
   if (nsplit > 1) {
     KernelTimer t("decode_merge_mfma", st);

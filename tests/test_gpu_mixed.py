@@ -110,6 +110,14 @@ def test_mixed_batch_fp8_drafts_in_turns_of_eight(n_draft, heads, k):
     _case(w8, [1, 3], [b for b in range(B) if b not in (1, 3)], f"mixed batch, fp8, {n_draft} drafts", draft_bits=(k + 1) * heads // 2 <= 32)
 
 
+@pytest.mark.parametrize("kv_dtype,heads,k,widest", [("bf16", 8, 4, 60000), ("fp8_e4m3", 8, 4, 120000), ("bf16", 16, 4, 60000), ("fp8_e4m3", 16, 7, 120000)])
+def test_mixed_batch_whose_draft_rows_bypass_the_cache(kv_dtype, heads, k, widest):
+    """Index buffers with room for more than 96 MB of the drafting requests' rows: other loads in either grid."""
+    w = gen.make_custom(name="bypass", seed=330 + k, B=3, Hq=heads, Hkv=2, D=128, P=16, spec_k=k, q_dtype="bf16", kv_dtype=kv_dtype,
+                        seq_lens=[40, 700, 2100], budgets=[8, 600, widest])
+    _case(w, [0], [1, 2], f"bypass, {kv_dtype}, {heads} heads", draft_bits=(k + 1) * heads // 2 <= (48 if kv_dtype == "fp8_e4m3" else 32))
+
+
 def test_mixed_batch_config3_reduced():
     w = gen.make_workload(3, batch=10)
     _case(w, [0, 5], [1, 2, 3, 4, 6, 7, 8, 9], "config3[:10], every fifth request verifies")

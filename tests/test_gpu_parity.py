@@ -667,6 +667,14 @@ def test_output_put_together_by_workgroups_of_its_own(kv_dtype, heads, k, batch)
     _hetero_case(w, rng.integers(0, k + 1, size=w.B), "hetero k", with_select=True)
 
 
+@pytest.mark.parametrize("kv_dtype,widest", [("bf16", 40000), ("fp8_e4m3", 80000)])
+def test_draft_rows_that_bypass_the_cache(kv_dtype, widest):
+    """Index buffers with room for more than 96 MB of rows: other loads, and lists of one, two and five spans of 512 under a merge with room
+    for 79 or 157."""
+    w = small(320, kv_dtype=kv_dtype, Hq=16, seq_lens=[3, 700, 2100], budgets=[2, 600, widest])
+    round_trip(w, what=f"room for {widest}", fused_select=True)
+
+
 def test_ranges_over_more_requests_than_lanes():
     """4500 requests of one tile in 64 ranges: a range's lengths come 64 requests at a time; every seventh is empty."""
     rng = np.random.default_rng(41)
