@@ -1150,6 +1150,14 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
   }
 }
 
+// What a pass does with the stash: nothing, leaves it in the L2 to be written back, or writes it through.  A stash that the L2s (32 MB) cannot
+// hold leaves them line by line while the pass reads, and costs it less when it does so at once: 128 requests of 1-8 K tokens (200
+// MB) 517.5 -> 512.5 us, fp8 with 40 rows 64 of 512-32 K (412 MB) 455.5 -> 450.3, 16 of 24-32 K with 36 rows (293 MB) 490.6 ->
+// 485.6; but the finish kernel finds less of a small one: 32 requests of 4096 tokens (42 MB) 130.8 -> 132.0.  The host chooses, by what
+// max_seq_len allows (a choice per tile on the chip costs as much as it gives).
+enum { kNoStash = 0, kStashKept = 1, kStashThrough = 2 };
+constexpr int64_t kThroughBytes = int64_t{192} << 20;
+
 // One tile of the single pass.  Nothing crosses lanes unless a logit exceeds its row's running maximum.  (A maximum that may lag by
 // 2^8 spares most of the rescaling, but the probability of a row's largest logit is then rounded to bf16 instead of being 1: with
 // page scales that bf16 holds exactly, the error of fp8 outputs grew from 1.72e-3 to 1.79e-3, of the worst row from 2.6e-3 to 4.1e-3.)
@@ -1157,8 +1165,9 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
 // LAST: the last tile of the stretch, after which nothing is sent for, and the only one that may reach past the sequence.
 // (A branch around the loads instead makes the compiler wait for all of them where it needs the first.)
 constexpr int kRawBuffer = 0x00020000;          // third word of a raw buffer descriptor: no stride, no swizzle, range checked
+constexpr int kWriteThrough = 16;               // sc1: a store does not stay in the L2 to be written back later
 constexpr int kDropped = 0x7ffffff0;            // an offset past the end of every buffer here
-template <int RB, bool FP8, bool STASH, bool LAST>
+template <int RB, bool FP8, int STASH, bool LAST>
 __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, StretchTile<FP8>& t, const LaneGeom<FP8>& geo, const RowGeom& rg,
                                              int tb, float c2, FlashRows<RB>& st, uint8_t* s_tile, const uint8_t* s_q, __amdgpu_buffer_rsrc_t stash, __amdgpu_buffer_rsrc_t m_ref, int lane) {
   const int n = lane & 15, g4 = lane >> 4;
@@ -1205,13 +1214,13 @@ __device__ __forceinline__ void stretch_tile(const KvView& kv, Stretch<FP8>& c, 
 #pragma unroll
       for (int i = 0; i < 4; ++i) pr[sub][i] = fast_exp2(fmaf(s[sub][rb][i], sc[sub], -m_use));
     st.l[rb] += ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
-    if constexpr (STASH) {                                   // the exponentials, 16 bits each, and the maximum they refer to
+    if constexpr (STASH != kNoStash) {                                   // the exponentials, 16 bits each, and the maximum they refer to
       // (-inf, not m_use, for a row that sees none of the tokens so far: its weight in the finish kernel is then zero.  With 0, exp2(0 - lse)
       // overflows below an lse of about -70 in base 2, and the score of a token such a row does not see is 0 * inf.)
       // Stores past a buffer's end are dropped: lanes with nothing to store need no branch, behind which the compiler
       // could not count the stores and would wait for them, and for V, where the next tile needs K.
       const int sl = stash_lane(rb, RB, rg.nv, n, g4, lane);
-      __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, STASH == kStashThrough ? kWriteThrough : 0);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(st.m[rb]), m_ref, g4 == 0 ? 4 * (16 * rb + StashRead<RB>::m_place(n)) : kDropped, 0, 0);
     }
     if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
@@ -1357,7 +1366,7 @@ __device__ __forceinline__ bool solo_segment(const Walk& c, int alike) {
   return c.sg.tiles <= kSoloTiles && c.end - c.unit >= alike * c.sg.tiles;
 }
 
-template <int RB, bool FP8, int W, bool STASH>
+template <int RB, bool FP8, int W, int STASH>
 __device__ __forceinline__ void flash_solo_run(const KvView& kv, const uint16_t* q, RowGeom rg, const RangeWs& ws, uint16_t* out, float c2,
                                                TeamLds<RB, W>& lds, Walk& walk, int wave, int lane0) {
   uint8_t* s_tile = lds.tile + wave * kVTileBytes;
@@ -1393,7 +1402,7 @@ __device__ __forceinline__ void flash_solo_run(const KvView& kv, const uint16_t*
   } while (walk.live && solo_segment(walk, TeamLds<RB, W>::kSolo - turn));
 }
 
-template <int RB, bool FP8, int W, bool STASH>
+template <int RB, bool FP8, int W, int STASH>
 __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
                                                 TeamLds<RB, W>& lds, int w) {
   constexpr int THREADS = W * kWave, rows = RB * 16, kORow = TeamLds<RB, W>::kORow;
@@ -1494,7 +1503,7 @@ __device__ __forceinline__ void flash_team_body(const KvView& kv, const uint16_t
   }
 }
 
-template <int RB, bool FP8, bool STASH>
+template <int RB, bool FP8, int STASH>
 __global__ __launch_bounds__(kTeamWaves * kWave, 2) void verify_flash_team(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
   __shared__ TeamLds<RB, kTeamWaves> lds;
   flash_team_body<RB, FP8, kTeamWaves, STASH>(kv, q, n_q, ws, out, lds, blockIdx.x);
@@ -1509,7 +1518,7 @@ __global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView
                                                                           DecodeArgs da, DecWs dws, int span_rows, int nspan) {
   __shared__ TeamLds<RB, kTeamWaves> lds;      // its tile buffers serve the draft path too
   if (static_cast<int>(blockIdx.x) < ws.n_ranges) {
-    flash_team_body<RB, FP8, kTeamWaves, true>(kv, q, n_q, ws, out, lds, blockIdx.x);
+    flash_team_body<RB, FP8, kTeamWaves, kStashKept>(kv, q, n_q, ws, out, lds, blockIdx.x);
   } else {
     const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
     decode_span_body<FP8, kTeamWaves, BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
@@ -1622,7 +1631,7 @@ __device__ __forceinline__ void tile_qk_ldsq_at(const uint8_t* ktile, const uint
 }
 
 // one of the two wavefronts: `half` = which 16 tokens of every tile it fetches, RB0 / RBW = its row blocks
-template <int RB, bool FP8, bool STASH, int RBW, int RB0>
+template <int RB, bool FP8, int STASH, int RBW, int RB0>
 __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t* q, int n_q, const RangeWs& ws, uint16_t* out,
                                                 uint8_t* s_tile, uint8_t* s_q, int half) {
   constexpr int kPairThreads = 2 * kThreads;
@@ -1734,7 +1743,6 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
     f = issue_next_half<FP8>(kv, cur, half, geo, lane, rk, rv);
     const bool edge = tb + kTileTokens > cs.L - n_q;
     bf16x8 p[RBW];
-    uint8_t* st_base = ws.stash + static_cast<int64_t>(unit) * tile_lanes * 16;
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb) {
       f32x4 pr[2] = {s[0][rb], s[1][rb]};
@@ -1769,11 +1777,13 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
           sum += pr[sub][i];
         }
       l_run[rb] += sum;
-      const int sl = STASH ? stash_lane(RB0 + rb, RB, nv, n, g4, lane) : -1;
-      if (sl >= 0) {
-        *reinterpret_cast<u32x4*>(st_base + sl * 16) = stash_pack8(pr);
+      const int sl = stash_lane(RB0 + rb, RB, nv, n, g4, lane);
+      if constexpr (STASH != kNoStash) {
+        const auto stash = __builtin_amdgcn_make_buffer_rsrc(ws.stash + static_cast<int64_t>(unit) * tile_lanes * 16, 0, tile_lanes * 16, kRawBuffer);
+        const auto m_ref = __builtin_amdgcn_make_buffer_rsrc(ws.m_ref + static_cast<int64_t>(unit) * (RB * 16), 0, RB * 16 * 4, kRawBuffer);
+        __builtin_amdgcn_raw_buffer_store_b128(stash_pack8(pr), stash, sl >= 0 ? sl * 16 : kDropped, 0, STASH == kStashThrough ? kWriteThrough : 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_new), m_ref, g4 == 0 ? 4 * (16 * (RB0 + rb) + StashRead<RB>::m_place(n)) : kDropped, 0, 0);
       }
-      if (STASH && g4 == 0) ws.m_ref[static_cast<int64_t>(unit) * (RB * 16) + 16 * (RB0 + rb) + StashRead<RB>::m_place(n)] = m_new;
       if constexpr (FP8) { pr[0] *= vs[0]; pr[1] *= vs[1]; }
       p[rb] = pack_p(pr[0], pr[1]);
     }
@@ -1791,7 +1801,7 @@ __device__ __forceinline__ void flash_pair_wave(const KvView& kv, const uint16_t
   finish();
 }
 
-template <int RB, bool FP8, bool STASH>
+template <int RB, bool FP8, int STASH>
 __global__ __launch_bounds__(2 * kThreads, 2) void verify_flash_pair(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out) {
   static_assert(RB >= 3, "up to two row blocks run verify_flash_team");
   constexpr int kFirst = (RB + 1) / 2;         // row blocks of the first wavefront
@@ -1812,8 +1822,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, c
   static_assert(kPassLds >= 2 * kVTileBytes, "the draft path uses the same memory as two tile buffers");
   __shared__ __attribute__((aligned(16))) uint8_t smem[kPassLds];
   if (static_cast<int>(blockIdx.x) < ws.n_ranges) {
-    if (threadIdx.x < kThreads) flash_pair_wave<RB, FP8, true, kFirst, 0>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 0);
-    else flash_pair_wave<RB, FP8, true, RB - kFirst, kFirst>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 1);
+    if (threadIdx.x < kThreads) flash_pair_wave<RB, FP8, kStashKept, kFirst, 0>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 0);
+    else flash_pair_wave<RB, FP8, kStashKept, RB - kFirst, kFirst>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 1);
   } else {
     const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
     decode_span_body<FP8, 2, BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
@@ -2358,6 +2368,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
   }
   if (single_pass) {
     const bool stats = a.scores || a.select;
+    const int rows = a.n_q * (kv.num_q_heads / kv.num_kv_heads);
+    const bool through = static_cast<int64_t>(pairs) * tiles_of_len(kv.max_seq_len) * kTileTokens * rows * 2 > kThroughBytes;
     const bool fused = draft != nullptr;       // a unified batch: the draft step of other requests rides in the same grid
     DecWs dws{};
     int span_rows = 0, nspan = 0, n_draft = 0;
@@ -2378,10 +2390,9 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
                            *draft, dws, span_rows, nspan);
       } else {
         KernelTimer t("verify_flash_team", st);
-        if (stats)
-          hipLaunchKernelGGL((verify_flash_team<RB, FP8, true>), dim3(ws.n_ranges), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out);
-        else                                   // plain multi-query decode: nothing is stashed, nothing rebuilt
-          hipLaunchKernelGGL((verify_flash_team<RB, FP8, false>), dim3(ws.n_ranges), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out);
+        // (without the statistic, plain multi-query decode: nothing is stashed, nothing rebuilt)
+        const auto kernel = !stats ? verify_flash_team<RB, FP8, kNoStash> : through ? verify_flash_team<RB, FP8, kStashThrough> : verify_flash_team<RB, FP8, kStashKept>;
+        hipLaunchKernelGGL(kernel, dim3(ws.n_ranges), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out);
       }
     } else {                                         // two wavefronts per range and per draft workgroup
       if (fused) {
@@ -2391,10 +2402,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
                            *draft, dws, span_rows, nspan);
       } else {
         KernelTimer t("verify_flash_pair", st);
-        if (stats)
-          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, true>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
-        else
-          hipLaunchKernelGGL((verify_flash_pair<RB, FP8, false>), dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
+        const auto kernel = !stats ? verify_flash_pair<RB, FP8, kNoStash> : through ? verify_flash_pair<RB, FP8, kStashThrough> : verify_flash_pair<RB, FP8, kStashKept>;
+        hipLaunchKernelGGL(kernel, dim3(ws.n_ranges), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out);
       }
     }
     int split_select = 0;                      // chunks per row when the selection is a launch of its own

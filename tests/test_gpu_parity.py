@@ -7,7 +7,7 @@ import torch
 import gen
 import oracle
 import paper_2512_01278_amd as pa
-from tests.harness import (GpuRun, check_out, check_topk_exact, compare_with_oracle, to_f64, LSE_ABS)
+from tests.harness import (GpuRun, check_out, check_scores, check_topk_exact, compare_with_oracle, to_f64, LSE_ABS)
 
 pytestmark = pytest.mark.gpu
 
@@ -665,6 +665,25 @@ def test_output_put_together_by_workgroups_of_its_own(kv_dtype, heads, k, batch)
     torch.cuda.synchronize()
     assert torch.equal(bare.out.view(torch.int16), run.out.view(torch.int16)) and torch.equal(bare.lse, run.lse)
     _hetero_case(w, rng.integers(0, k + 1, size=w.B), "hetero k", with_select=True)
+
+
+@pytest.mark.parametrize("kv_dtype,heads,k", [("bf16", 8, 0), ("bf16", 8, 4), ("bf16", 16, 4), ("bf16", 16, 7), ("fp8_e4m3", 8, 0), ("fp8_e4m3", 8, 4),
+                                              ("fp8_e4m3", 16, 4), ("fp8_e4m3", 16, 7)])
+def test_statistic_written_through_the_cache(kv_dtype, heads, k):
+    """Calls whose max_seq_len allows for more than 192 MB of exponentials store them another way (1 to 4 row blocks)."""
+    rows = (k + 1) * heads // 2
+    longest = (192 << 20) // (6 * 2 * rows) + 33
+    w = small(310 + k, kv_dtype=kv_dtype, Hq=heads, spec_k=k, seq_lens=[k + 1, 300, 1100], budgets=[1, 40, 64], extra_table_cols=longest // 16 + 1)
+    run = GpuRun(w)
+    run.dw.kv.max_seq_len = longest
+    run.workspace = torch.empty(pa.pillar_workspace_bytes(run.dw.kv, w.spec_k, run.max_budget), dtype=torch.uint8, device=run.dev)
+    run.scores = torch.full((w.B, w.Hkv, (longest + 3) // 4 * 4), float("nan"), device=run.dev)
+    run.verify()
+    torch.cuda.synchronize()
+    want, want_lse, want_scores = oracle.verify_attn(w)
+    check_out(to_f64(run.out), want, w.kv_dtype, "written through: out")
+    assert np.abs(to_f64(run.lse) - want_lse).max() <= LSE_ABS
+    check_scores(run.scores[:, :, :1100].cpu().numpy().astype(np.float64), want_scores, w.seq_lens, range(w.B), "written through")
 
 
 @pytest.mark.parametrize("kv_dtype,widest", [("bf16", 40000), ("fp8_e4m3", 80000)])
