@@ -5,7 +5,8 @@
 // Before, a thread walked a K row by itself (neighbouring lanes a whole row apart) and looked every V row's page up again
 // for every element: two requests of 300 and 512 tokens with 16 rows (fp32, head_dim 64)
 // took 98 us to verify in three launches (split 70, merge 8, scores 20) and 22.6 to draft from 64 of them, then 24 + 17
-// and 9.8, and 9 + 11 with a workgroup per 32 tokens: what is left is the chain length -> page -> row -> LDS.
+// and 9.8, and 9 + 11 with a workgroup per 32 tokens, and 5 + 7 and 6.4 with the contractions on the matrix cores: what is left is the
+// chain length -> page -> row -> LDS.
 #pragma once
 
 #include "common.hpp"
@@ -42,53 +43,45 @@ template <int DT, int D> struct StagedPiece {
   }
 };
 
-// Dot products of the thread's token (threadIdx.x % 32) with query rows threadIdx.x / 32 + 8 j, j < ROWS / 8 (rows past
-// `rows` give garbage that nobody reads), summed over the dimensions in ascending order.
-template <int ROWS, int D>
-__device__ __forceinline__ void piece_dots(const float* s_rows, const float* s_q, int rows, float (&dot)[ROWS / 8]) {
-  const float* kr = s_rows + (threadIdx.x & (kPiece - 1)) * kPieceStride;
-  const int r0 = threadIdx.x / kPiece;
+// The contractions of a piece on the matrix cores, in fp32 (v_mfma_f32_16x16x4_f32: 16 rows, 16 columns, 4 terms).  With a dot product per
+// thread the LDS was what bounded a piece: four multiply-adds of a wavefront took a 16-byte read of K and one of Q, where here 64 do.
+// Two fp32 requests of 300 and 512 tokens with 16 rows: split 9.1 -> 5.3 us, finish 10.3 -> 7.0 (query rows and partials are sent for
+// earlier as well), draft 9.8 -> 6.4; 16 of 2 K with 64 rows and head_dim 128, whole round 174 -> 83; 256 of 1 K, 2 heads 566 -> 327; 8 of
+// 32 K 248 -> 138.  Errors against float64 as before (outputs 1.1e-6, scores 4e-7).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kQStride = kGenMaxD + 4;         // floats between staged query rows, as for kPieceStride
+
+// Logits of 16 tokens (block tb of the piece) against 16 query rows (block rb): element i of lane (n, g) is token 16 tb + 4 g + i, row
+// 16 rb + n (n = lane % 16, g = lane / 16).  A lane reads four dims at a time and the products take one of each lane group: dims 16 u +
+// 4 g + j, g < 4.  Rows past the last give garbage in columns that nobody reads.
+template <int D>
+__device__ __forceinline__ f32x4 piece_qk(const float* s_rows, const float* s_q, int tb, int rb, int lane) {
+  const float* k = s_rows + (16 * tb + (lane & 15)) * kPieceStride + 4 * (lane >> 4);
+  const float* q = s_q + (16 * rb + (lane & 15)) * kQStride + 4 * (lane >> 4);
+  f32x4 acc[4] = {};                           // four short sums: less rounding than one long one, and no product waits for the last
 #pragma unroll
-  for (int j = 0; j < ROWS / 8; ++j) dot[j] = 0.f;
-#pragma unroll 4
-  for (int d = 0; d < D; d += 4) {
-    const float4 k = *reinterpret_cast<const float4*>(kr + d);
+  for (int u = 0; u < D; u += 16) {
+    const f32x4 kv = *reinterpret_cast<const f32x4*>(k + u), qv = *reinterpret_cast<const f32x4*>(q + u);
 #pragma unroll
-    for (int j = 0; j < ROWS / 8; ++j) {
-      if (8 * j < rows) {                      // uniform
-        const float4 q = *reinterpret_cast<const float4*>(s_q + min(r0 + 8 * j, rows - 1) * D + d);
-        dot[j] = fmaf(q.x, k.x, dot[j]);
-        dot[j] = fmaf(q.y, k.y, dot[j]);
-        dot[j] = fmaf(q.z, k.z, dot[j]);
-        dot[j] = fmaf(q.w, k.w, dot[j]);
-      }
-    }
+    for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j], qv[j], acc[j], 0, 0, 0);
   }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
-// acc[j] += sum over the piece's tokens of p[row][t0 + t] * v[t][d] for the thread's dimension d = threadIdx.x % D and rows
-// threadIdx.x / D + (256 / D) j, in ascending order; p has `p_stride` floats per row.  Rows of tokens past the end are staged as
-// zeros and their probabilities are zero, so the piece is always walked whole.
-template <int ROWS, int D>
-__device__ __forceinline__ void piece_pv(const float* s_rows, const float* s_p, int p_stride, int t0, int rows, float (&acc)[ROWS * D / kGenThreads]) {
-  constexpr int step = kGenThreads / D;
-  const int d = threadIdx.x & (D - 1), r0 = threadIdx.x / D;
-#pragma unroll 2
-  for (int t = 0; t < kPiece; t += 4) {
-    float v[4];
+// acc += P V of a piece for 16 rows (block rb) and 16 dims (block db): element i of lane (n, g) is row 16 rb + 4 g + i, dim 16 db + n.  p has
+// `p_stride` floats per row (a multiple of 4; 4 more than a multiple of 64 or 32 spreads the rows over the banks).  Rows of tokens past
+// the end are staged as zeros and their probabilities are zero, so the piece is always walked whole.
+__device__ __forceinline__ void piece_pv(const float* s_rows, const float* s_p, int p_stride, int t0, int rb, int db, f32x4& acc, int lane) {
+  const float* p = s_p + (16 * rb + (lane & 15)) * p_stride + t0 + 4 * (lane >> 4);
+  const float* v = s_rows + 4 * (lane >> 4) * kPieceStride + 16 * db + (lane & 15);
+  f32x4 sum[2] = {};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = s_rows[(t + i) * kPieceStride + d];
+  for (int u = 0; u < kPiece; u += 16) {
+    const f32x4 pv = *reinterpret_cast<const f32x4*>(p + u);
 #pragma unroll
-    for (int j = 0; j < ROWS / step; ++j) {
-      if (step * j < rows) {                   // uniform
-        const float4 p = *reinterpret_cast<const float4*>(s_p + min(r0 + step * j, rows - 1) * p_stride + t0 + t);
-        acc[j] = fmaf(p.x, v[0], acc[j]);
-        acc[j] = fmaf(p.y, v[1], acc[j]);
-        acc[j] = fmaf(p.z, v[2], acc[j]);
-        acc[j] = fmaf(p.w, v[3], acc[j]);
-      }
-    }
+    for (int j = 0; j < 4; ++j) sum[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[j], v[(u + j) * kPieceStride], sum[j & 1], 0, 0, 0);
   }
+  acc += sum[0] + sum[1];
 }
 
 // maximum / sum over the 16 lanes of a DPP row, in all of them
@@ -107,15 +100,15 @@ __device__ __forceinline__ float lanes16_sum(float v) {
   return v;
 }
 
-// Softmax of `rows` rows of N logits in place, relative to the larger of a row's own maximum and floor_of(r): 16 lanes per
+// Softmax of `rows` rows of N logits, `stride` floats apart, in place, relative to the larger of a row's own maximum and floor_of(r): 16 lanes per
 // row, 16 rows at a time.  done(r, m, l) is called by one lane per row with the maximum used and the row's sum.
-template <int N, typename Floor, typename Done>
+template <int N, int stride, typename Floor, typename Done>
 __device__ __forceinline__ void softmax_rows(float* s, int rows, Floor floor_of, Done done) {
   constexpr int kWide = N >= 64 ? 4 : 2, kVecs = N / (16 * kWide);
   typedef float vec __attribute__((ext_vector_type(kWide)));
   const int e = threadIdx.x & 15;
   for (int r = threadIdx.x / 16; r < rows; r += kGenThreads / 16) {
-    vec* sr = reinterpret_cast<vec*>(s + r * N);
+    vec* sr = reinterpret_cast<vec*>(s + r * stride);
     vec x[kVecs];
 #pragma unroll
     for (int i = 0; i < kVecs; ++i) x[i] = sr[16 * i + e];

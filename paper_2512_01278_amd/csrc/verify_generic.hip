@@ -1,7 +1,7 @@
 // Verification attention, generic path: any supported shape and dtype, fp32
-// arithmetic on the vector ALUs.  Correct everywhere, fast nowhere: it serves
-// the shapes the MFMA path does not cover (fp32 tensors, head_dim 64) and is
-// the in-library cross-check of that path.
+// arithmetic throughout (vector ALUs, and fp32 matrix instructions for the
+// contractions).  It serves the shapes the bf16 matrix-core path does not
+// cover (fp32 tensors, head_dim 64) and is the in-library cross-check of it.
 //
 // Paper Section 4.1: the k+1 verification rows attend to the whole KV-Cache;
 // the softmax probabilities, averaged over those rows and the query heads of
@@ -28,8 +28,8 @@ namespace {
 // Tokens per workgroup.  The pieces of 32 tokens of a chunk follow each other through LDS, with two barriers and a walk over the
 // rows each, so a launch is as long as its longest chunk until the chip is full: where all its pieces fit on the chip side by side (4
 // workgroups per compute unit), every piece is a chunk.  Chunks of 128 / of 32 tokens, fp32, 4 heads, head_dim 64, verification and
-// selection and draft: 2 requests of 300 to 512 tokens 55.5 / 34.6 us, 4 of 1 K 56.5 / 36.9, 64 of 512 57.4 / 41.9 (1024 pieces),
-// 16 of 2 K 59.0 / 40.3, 32 of 1 K 58.9 / 46.3; 64 rows and head_dim 128, 16 of 2 K 223 / 163.  Beyond, chunks of 128 fetch the query
+// selection and draft: 2 requests of 300 to 512 tokens 32.2 / 25.0 us, 4 of 2 K and 2 heads 35.9 / 30.0, 64 of 512 33.7 / 31.9 (1024
+// pieces), 16 of 2 K 37.8 / 33.5; 64 rows and head_dim 128, 16 of 2 K 97 / 83.  Beyond, chunks of 128 fetch the query
 // rows and leave partial outputs a quarter as often.  (The host knows no lengths: it counts with max_seq_len, so a caller whose contexts
 // are short does well to say so.)
 constexpr int kChunk = 128, kFineChunk = kPiece;
@@ -37,8 +37,9 @@ size_t fine_chunks() { return 4 * static_cast<size_t>(num_cus()); }
 constexpr int kThreads = kGenThreads;
 
 // Without a merge launch every workgroup of the finish kernel reads the (m, l) of all chunks: quadratic in the context.  With
-// one of its own / without, fp32: 64 requests of 512 tokens 372 / 339 us, 8 of 1024 96.8 / 95.2, 8 of 2048 179 / 184, 8 of 32 K
-// 2416 / 4666, one of 2 M tokens 2.7 / 139 ms (with one workgroup per (request, KV head) instead of one per row: 101).
+// one of its own / without, fp32, whole round: 2 requests of 300 to 512 tokens 27.7 / 25.0 us, 64 of 512 34.7 / 31.9, 256 of 1 K with 2 heads
+// 348 / 327.  Before the matrix cores: 8 of 2048 179 / 184, 8 of 32 K 2416 / 4666, one of 2 M tokens 2.7 / 139 ms (with one
+// workgroup per (request, KV head) instead of one per row: 101).
 constexpr int kInlineChunks = 8;
 
 struct GenericWs {
@@ -53,8 +54,9 @@ struct GenericWs {
 __host__ __device__ inline int num_chunks(int max_seq_len) { return (max_seq_len + kChunk - 1) / kChunk; }
 
 template <int CHUNK> struct GenericLds {
-  __attribute__((aligned(16))) float q[kPieceRows * kGenMaxD];       // query rows at work
-  __attribute__((aligned(16))) float s[kPieceRows * CHUNK];          // their logits, then probabilities
+  static constexpr int kStride = CHUNK + 4;
+  __attribute__((aligned(16))) float q[kPieceRows * kQStride];       // query rows at work
+  __attribute__((aligned(16))) float s[kPieceRows * kStride];        // their logits, then probabilities
   __attribute__((aligned(16))) float rows[kPiece * kPieceStride];    // K or V rows of a piece
   int64_t off[CHUNK];                                                // element offset of every token's row
   float ks[CHUNK], vs[CHUNK];                                        // fp8: scales of its page
@@ -73,13 +75,36 @@ __device__ __forceinline__ void resolve_chunk(const KvView& kv, int b, int g, in
   }
 }
 
+// Up to kPieceRows query rows on their way to LDS, all sent for at once (a loop of loads and stores waits for memory in every turn: of the
+// 9 us that two requests of 300 to 512 tokens took to split, 3; so did the last half of the finish kernel).
+template <int QDT, int D> struct StagedQueries {
+  static constexpr int kPerThread = kPieceRows * D / kThreads;
+  float v[kPerThread];
+  __device__ __forceinline__ void fetch(const KvView& kv, const void* q, int n_q, int b, int g, int row0, int rows) {
+    const int G = kv.num_q_heads / kv.num_kv_heads, inv_g = ((1 << 16) + G - 1) / G;         // r / G: exact for r < 64, G <= 16
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+      const int idx = static_cast<int>(threadIdx.x) + j * kThreads, r = row0 + idx / D, i = (r * inv_g) >> 16;
+      v[j] = idx < rows * D ? Storage<QDT>::load(q, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + r - i * G) * D + (idx & (D - 1))) : 0.f;
+    }
+  }
+  __device__ __forceinline__ void store(float* s_q, int rows) const {
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+      const int idx = static_cast<int>(threadIdx.x) + j * kThreads;
+      if (idx < rows * D) s_q[idx / D * kQStride + (idx & (D - 1))] = v[j];
+    }
+  }
+};
+
 // Logits of query rows row0 .. row0+rows-1 against the chunk's tokens into lds.s[r][tt] (sm_scale applied, -inf where masked or
 // beyond the sequence).  Every thread of the workgroup calls this; lds.off is complete (a barrier ago).
 // All K rows are sent for before the first is needed (SENT: they have been, into `sent`), and `ahead` is called right after (to send for
-// V rows).
+// V rows).  Fine chunks have sent for the query rows as well (`queries`); a full chip has nothing to gain from that, nor the registers.
 template <int QDT, int KVDT, int D, int CHUNK, bool SENT, typename Ahead>
 __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int nt, int L, int row0, int rows,
-                                             GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&sent)[CHUNK / kPiece], Ahead ahead) {
+                                             GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&sent)[CHUNK / kPiece],
+                                             const StagedQueries<QDT, D>& queries, Ahead ahead) {
   constexpr int kPieces = CHUNK / kPiece;
   StagedPiece<KVDT, D> piece[kPieces];
 #pragma unroll
@@ -89,35 +114,36 @@ __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, in
   }
   ahead();
   const int G = kv.num_q_heads / kv.num_kv_heads;
-  for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
-    const int r = row0 + idx / D, d = idx & (D - 1);
-    const int i = r / G, hg = r - i * G;
-    lds.q[idx] = Storage<QDT>::load(q, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d);
+  if constexpr (CHUNK == kFineChunk) {
+    queries.store(lds.q, rows);
+  } else {
+    for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
+      const int r = row0 + idx / D, d = idx & (D - 1);
+      const int i = r / G, hg = r - i * G;
+      lds.q[(r - row0) * kQStride + d] = Storage<QDT>::load(q, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d);
+    }
   }
+  // a wavefront takes 16 tokens of a piece against 16 rows
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), tb = wave & 1, rb = wave >> 1;
+  const int r = 16 * rb + (lane & 15), inv_g = ((1 << 16) + G - 1) / G;
+  const int last = L - n_q + (((row0 + r) * inv_g) >> 16);             // the row's last token
 #pragma unroll
   for (int p = 0; p < kPieces; ++p) {
     const int p0 = p * kPiece;
-    float dot[kPieceRows / 8];
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
     if (p0 < nt) {                             // uniform
       __syncthreads();                         // the previous piece has been read
       piece[p].store(lds.rows);
       __syncthreads();
-      piece_dots<kPieceRows, D>(lds.rows, lds.q, rows, dot);
+      if (16 * rb < rows) x = piece_qk<D>(lds.rows, lds.q, tb, rb, lane);
     }
-    const int tt = p0 + (threadIdx.x & (kPiece - 1)), t = t0 + tt;
+    const int tt = p0 + 16 * tb + 4 * (lane >> 4);
 #pragma unroll
-    for (int j = 0; j < kPieceRows / 8; ++j) {
-      const int r = threadIdx.x / kPiece + 8 * j;
-      if (r < rows) {
-        float v = -INFINITY;
-        if (t < L && t <= L - n_q + (row0 + r) / G) {
-          v = dot[j];
-          if (KVDT == PILLAR_FP8_E4M3) v *= lds.ks[tt];
-          v *= kv.sm_scale;
-        }
-        lds.s[r * CHUNK + tt] = v;
-      }
+    for (int i = 0; i < 4; ++i) {
+      if (KVDT == PILLAR_FP8_E4M3 && tt + i < nt) x[i] *= lds.ks[tt + i];
+      x[i] = t0 + tt + i < L && t0 + tt + i <= last ? x[i] * kv.sm_scale : -INFINITY;
     }
+    if (r < rows) *reinterpret_cast<f32x4*>(lds.s + r * GenericLds<CHUNK>::kStride + tt) = x;
   }
   __syncthreads();
 }
@@ -129,28 +155,37 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
   const int t0 = c * CHUNK;
-  if (t0 >= L) return;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   const int R = n_q * G;
+  StagedQueries<QDT, D> queries;
+  if constexpr (CHUNK == kFineChunk) queries.fetch(kv, q, n_q, b, g, 0, min(kPieceRows, R));
+  if (t0 >= L) return;
   const int nt = min(CHUNK, L - t0);
   const int64_t slot = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc + c;
   resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
   __syncthreads();
   for (int row0 = 0; row0 < R; row0 += kPieceRows) {
     const int rows = min(kPieceRows, R - row0);
+    if constexpr (CHUNK == kFineChunk) {
+      if (row0 > 0) queries.fetch(kv, q, n_q, b, g, row0, rows);
+    }
     StagedPiece<KVDT, D> piece[kPieces];
-    chunk_logits<QDT, KVDT, D, CHUNK, false>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, piece, [&]() {
+    chunk_logits<QDT, KVDT, D, CHUNK, false>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, piece, queries, [&]() {
 #pragma unroll
       for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.v_pool, lds.off, p * kPiece, nt);
     });
-    softmax_rows<CHUNK>(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
+    softmax_rows<CHUNK, GenericLds<CHUNK>::kStride>(lds.s, rows, [](int) { return -INFINITY; }, [&](int r, float m, float l) {
       ws.part_m[slot * R + row0 + r] = m;
       ws.part_l[slot * R + row0 + r] = l;
     });
-    constexpr int step = kThreads / D;
-    float acc[kPieceRows / step];
+    // a wavefront takes every fourth block of 16 dims
+    constexpr int kRowBlocks = kPieceRows / 16, kDimBlocks = D / 64;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    f32x4 acc[kRowBlocks][kDimBlocks];
 #pragma unroll
-    for (int j = 0; j < kPieceRows / step; ++j) acc[j] = 0.f;
+    for (int rb = 0; rb < kRowBlocks; ++rb)
+#pragma unroll
+      for (int j = 0; j < kDimBlocks; ++j) acc[rb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < kPieces; ++p) {
       if (p * kPiece < nt) {                   // uniform
@@ -158,14 +193,25 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
         if (KVDT == PILLAR_FP8_E4M3) piece[p].scale(lds.vs, p * kPiece, nt);
         piece[p].store(lds.rows);
         __syncthreads();
-        piece_pv<kPieceRows, D>(lds.rows, lds.s, CHUNK, p * kPiece, rows, acc);
+#pragma unroll
+        for (int rb = 0; rb < kRowBlocks; ++rb) {
+          if (16 * rb < rows) {                // uniform
+#pragma unroll
+            for (int j = 0; j < kDimBlocks; ++j) piece_pv(lds.rows, lds.s, GenericLds<CHUNK>::kStride, p * kPiece, rb, wave + 4 * j, acc[rb][j], lane);
+          }
+        }
       }
     }
-    const int d = threadIdx.x & (D - 1);
 #pragma unroll
-    for (int j = 0; j < kPieceRows / step; ++j) {
-      const int r = threadIdx.x / D + step * j;
-      if (r < rows) ws.part_o[(slot * R + row0 + r) * D + d] = acc[j];
+    for (int rb = 0; rb < kRowBlocks; ++rb) {
+#pragma unroll
+      for (int j = 0; j < kDimBlocks; ++j) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = 16 * rb + 4 * (lane >> 4) + i;
+          if (r < rows) ws.part_o[(slot * R + row0 + r) * D + 16 * (wave + 4 * j) + (lane & 15)] = acc[rb][j][i];
+        }
+      }
     }
     __syncthreads();                           // before the next rows' logits
   }
@@ -251,8 +297,24 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   const int nt = min(CHUNK, L - t0);
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
   // A fine chunk's K rows are on their way while the partials are merged.  (Where the chip is full there is nothing to wait for, and
-  // rows held that long cost: 64 requests of 1 to 2 K tokens, 64 rows, head_dim 128, this kernel 136 -> 148 us.)
+  // rows held that long cost: 64 requests of 1 to 2 K tokens, 64 rows, head_dim 128, this kernel 136 -> 148 us before the matrix cores.)
   constexpr bool kSent = CHUNK == kFineChunk;
+  StagedQueries<QDT, D> queries;
+  if constexpr (kSent) {
+    if (scores) queries.fetch(kv, q, n_q, b, g, 0, min(kPieceRows, R));
+  }
+  // and so are the partials of this thread's first element of the output
+  constexpr int kAhead = kSent && !MERGED ? 16 : 1;
+  float m_ahead[kAhead], o_ahead[kAhead];
+  if constexpr (kAhead > 1) {
+    const int idx = min(c * R * D / nc + static_cast<int>(threadIdx.x), R * D - 1);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int64_t at = (base + min(i, nc - 1)) * R + idx / D;
+      m_ahead[i] = ws.part_m[at];
+      o_ahead[i] = ws.part_o[at * D + (idx & (D - 1))];
+    }
+  }
   StagedPiece<KVDT, D> k_piece[CHUNK / kPiece];
   if (scores) {                                // uniform
     resolve_chunk<KVDT>(kv, b, g, t0, nt, lds);
@@ -301,12 +363,21 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
     for (int idx = c * R * D / nc + threadIdx.x; idx < (c + 1) * R * D / nc; idx += kThreads) {      // (few chunks: 32 bits are enough)
       const int r = idx / D, d = idx & (D - 1);
       float o = 0.f;
-#pragma unroll 8
-      for (int i = 0; i < nc; ++i) {
-        const float mc = ws.part_m[(base + i) * R + r];
+      auto add = [&](float mc, float po) {
         const float w = (mc == -INFINITY) ? 0.f : __expf(mc - lds.q[r]);
-        o = fmaf(ws.part_o[((base + i) * R + r) * D + d], w, o);
+        o = fmaf(po, w, o);
+      };
+      int i0 = 0;
+      if constexpr (kAhead > 1) {
+        if (idx < c * R * D / nc + kThreads) {               // the thread's first
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i)
+            if (i < nc) add(m_ahead[i], o_ahead[i]);
+          i0 = kAhead;
+        }
       }
+#pragma unroll 8
+      for (int i = i0; i < nc; ++i) add(ws.part_m[(base + i) * R + r], ws.part_o[((base + i) * R + r) * D + d]);
       const int i = r / G, hg = r - i * G;
       Storage<QDT>::store(out, ((static_cast<int64_t>(b) * n_q + i) * kv.num_q_heads + g * G + hg) * D + d,
                           lds.q[kMaxRows + r] > 0.f ? o / lds.q[kMaxRows + r] : 0.f);
@@ -323,14 +394,15 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
       if (row0 > 0) {
 #pragma unroll
         for (int p = 0; p < CHUNK / kPiece; ++p) k_piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
+        queries.fetch(kv, q, n_q, b, g, row0, rows);
       }
     }
-    chunk_logits<QDT, KVDT, D, CHUNK, kSent>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece, []() {});
+    chunk_logits<QDT, KVDT, D, CHUNK, kSent>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece, queries, []() {});
     // kPer threads per token take the rows in turn
     const int tt = threadIdx.x / kPer;
 #pragma unroll 4
     for (int r = threadIdx.x % kPer; r < rows; r += kPer) {
-      const float v = lds.s[r * CHUNK + tt];
+      const float v = lds.s[r * GenericLds<CHUNK>::kStride + tt];
       sum += (v == -INFINITY) ? 0.f : __expf(v - lds.lse[row0 + r]);
     }
     __syncthreads();

@@ -694,6 +694,14 @@ def test_draft_rows_that_bypass_the_cache(kv_dtype, widest):
     round_trip(w, what=f"room for {widest}", fused_select=True)
 
 
+@pytest.mark.parametrize("q_dtype,kv_dtype,D,G", [("f32", "f32", 64, 1), ("f32", "f32", 128, 16), ("bf16", "fp8_e4m3", 64, 4), ("f32", "bf16", 128, 5)])
+def test_generic_draft_around_its_tiles(q_dtype, kv_dtype, D, G):
+    """Lists around blocks of 16 and pieces of 32 rows, half a tile (64 rows, a path of its own) and a tile of 128."""
+    lens = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 191, 192, 193, 400]
+    w = small(340 + G, q_dtype=q_dtype, kv_dtype=kv_dtype, D=D, Hq=2 * G, B=len(lens), spec_k=0, seq_lens=[n + 3 for n in lens], budgets=lens)
+    round_trip(w, what=f"generic draft, {q_dtype}/{kv_dtype}, D={D}, G={G}", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
+
+
 def test_ranges_over_more_requests_than_lanes():
     """4500 requests of one tile in 64 ranges: a range's lengths come 64 requests at a time; every seventh is empty."""
     rng = np.random.default_rng(41)
