@@ -74,6 +74,7 @@ struct RangeWs {
   const int32_t* spec_lens;   // [B] speculative length of each request, or null: all use the call's k
   int32_t rows_pad;     // 16 * row blocks
   int32_t n_ranges;     // N
+  int32_t max_piece_shift;  // log2 of the longest pieces the pass may be cut into
   int32_t plan_in_wave; // ctrl / ureq / order are not there yet: the wavefronts of the single pass work them out (wave_plan)
 };
 
@@ -103,9 +104,12 @@ __device__ __forceinline__ int range_of(int unit, int total, int n) {
 // wavefront in the shortest, and shorter ones would only leave more partials.  Equal ranges / pieces, pass + finish: 24 requests of 5-3000
 // tokens, 4 heads 15.5 + 14.9 / 11.4 + 12.4 us, one of 2100 11.0 + 15.2 / 10.0 + 12.5, 2 of 6-8 K 43.3 / 36.8 in all, fp8 with 40
 // rows 8 of 1-4 K 42.7 / 38.1 and 12 of 3-7 K 61.6 / 57.7, 24 of 10-3000 with 64 rows 47.6 / 35.0.  Pieces of 2 tiles for the pass
-// with two wavefronts per range: one request of 2100 tokens with 36 rows 34.4 us, of 4 tiles 29.5.  Beyond 32 tiles a range has few
-// boundaries anyway and equal ranges drain all at once (40 requests of 300-4000 tokens, 8 heads, no difference).
-constexpr int kMinPieceShift = 2, kMaxPieceShift = 5;
+// with two wavefronts per range: one request of 2100 tokens with 36 rows 34.4 us, of 4 tiles 29.5.
+// A piece may be longer than an equal range by what a boundary costs, some 8 tiles: 64 pairs of 17 x 256 tokens (pieces of 32 tiles,
+// ranges of 17) 48.8 / 50.5 us, of 14 x 256 (16 against 14) 43.6 / 37.9.  The pass with two wavefronts per range goes through a tile with
+// both, so that a longer range costs it more than a boundary: pieces of 4 tiles only (128 pairs, 36 rows, pieces of 16 against ranges
+// of 9 62.5 / 73.7, 64 rows, of 8 against 6 49.5 / 55.9).
+constexpr int kMinPieceShift = 2, kMaxPieceShift = 5, kPieceSlack = 8;
 __device__ __forceinline__ int pieces_of(int tiles, int shift) { return (tiles + (1 << shift) - 1) >> shift; }
 
 // Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or, with pieces, pair + (first unit >> shift), which
@@ -412,8 +416,9 @@ struct RangeStart {
 // The shortest pieces with which the batch makes no more of them than there are ranges (log2 of their tiles plus one), or 0: equal ranges.
 template <int REGS>
 __device__ __forceinline__ int plan_pieces(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int lane) {
-  if (p.total > (ws.n_ranges << kMaxPieceShift)) return 0;
-  for (int shift = kMinPieceShift; shift <= kMaxPieceShift; ++shift) {
+  if (p.total > (ws.n_ranges << ws.max_piece_shift)) return 0;
+  for (int shift = kMinPieceShift; shift <= ws.max_piece_shift; ++shift) {
+    if (shift > kMinPieceShift && (ws.n_ranges << shift) > p.total + kPieceSlack * ws.n_ranges) return 0;
     int mine = 0;
 #pragma unroll
     for (int j = 0; j < REGS; ++j) mine += pieces_of(tiles_of_len(p.len[j]), shift);         // 0 beyond the batch
@@ -2308,12 +2313,15 @@ int team_ranges(int slots) {
 // beside the others (one per pair and 8192 tokens) in two rounds.  The rule must not ask for the statistic: with and without it, O has
 // the same bits.  Without / with them, whole call: one request of 2100 tokens 26.4 / 23.5 us, 24 of 5-3000 24.1 / 20.4, 16 of 2-4 K with 8
 // heads 60.7 / 57.0, 24 of 10-3000 with 64 rows 35.0 / 27.0, one of 32 K 64.4 / 56.0, one of 8 K without the statistic 41.1 / 30.3.
-// With every compute unit taken by the statistic they only get in its way: 16 requests of 24-32 K tokens 494 / 496.
+// With every compute unit taken by the statistic they only get in its way: 16 requests of 24-32 K tokens 494 / 496; and with more than 96
+// pairs where they take more than two turns: 128 pairs of 768 tokens with 36 rows 36.4 / 38.7 (with 20, 64 to 2048 tokens 23.5 / 21.9).
 int merger_groups(const KvView& kv, int n_q, int threads) {
   const int64_t pairs = static_cast<int64_t>(kv.batch) * kv.num_kv_heads, others = pairs * ((kv.max_seq_len + 8191) / 8192);
   if (2 * others > num_cus()) return 0;
   const int at_once = 4 * (threads / 512), rows = n_q * (kv.num_q_heads / kv.num_kv_heads);       // rows of a turn
-  return std::min(static_cast<int>(2 * (num_cus() - others) / pairs), (rows + at_once - 1) / at_once);
+  const int room = static_cast<int>(2 * (num_cus() - others) / pairs);
+  if (8 * others > 3 * num_cus() && rows > 16 * room) return 0;          // (two turns of 1024 threads)
+  return std::min(room, (rows + at_once - 1) / at_once);
 }
 
 int row_blocks(const KvView& kv, int n_q) { return (n_q * (kv.num_q_heads / kv.num_kv_heads) + 15) / 16; }
@@ -2345,6 +2353,7 @@ RangeWs carve(const KvView& kv, int n_q, void* workspace, size_t* total_bytes) {
   w.spec_lens = nullptr;
   w.rows_pad = static_cast<int32_t>(rpad);
   w.n_ranges = static_cast<int32_t>(n);
+  w.max_piece_shift = kMinPieceShift;
   w.plan_in_wave = 0;
   if (total_bytes) *total_bytes = off;
   return w;
@@ -2383,6 +2392,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     }
     if constexpr (RB <= 2 || (FP8 && RB == 3)) {     // a range per workgroup
       ws.n_ranges = team_ranges(ws.n_ranges);
+      ws.max_piece_shift = kMaxPieceShift;
       if (fused) {
         KernelTimer t("mixed_flash_team", st);
         const auto kernel = bypass ? mixed_flash_team<RB, FP8, true> : mixed_flash_team<RB, FP8, false>;
