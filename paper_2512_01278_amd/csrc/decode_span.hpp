@@ -35,7 +35,9 @@ __device__ __forceinline__ Rows resolve_rows(const KvView& kv, int b, int g, int
 // 64 of 512 22.2 / 20.7, each over so many pools that nothing stays cached; and the unified batch of 128 of 1-8 K tokens takes 154 / 144.
 // But a layer that is verified or drafted from again before 256 MB have been read loses what is still there: one draft step and
 // one verification of 32 requests of 4096 tokens in turn (34 MB of rows) 131 / 135.5, fp8 lists of 512 over three pools (67 MB each) 20.1 /
-// 20.9.  So the line lies where two calls' rows no longer fit beside what the pass leaves: 96 MB.
+// 20.9.  So the line lies where two calls' rows no longer fit beside what the pass leaves: 96 MB.  (Above it, too, a single layer stepped
+// over and over on the same pools reads less from memory without: 128 requests of 1-8 K tokens, verification and draft 586.5 / 593.5,
+// unified batch 151 / 161.  A model has many layers between two steps of one.)
 __host__ __device__ inline bool draft_bypasses(int64_t list_rows, bool fp8) { return list_rows * 2 * kHeadDim * (fp8 ? 1 : 2) > (int64_t{96} << 20); }
 
 // sends the row loads of the tile whose row offsets half `half` of the lanes (0: lanes 0..31, 1: lanes 32..63) holds
