@@ -587,6 +587,15 @@ def test_many_segments_per_pair(k, segments):
     _same_as_two_calls(small(190 + k, B=2, Hq=8, Hkv=2, spec_k=k, seq_lens=[17000, 8200], budgets=[300, 64]), "segments of long rows")
 
 
+@pytest.mark.parametrize("batch", [5, 140])
+@pytest.mark.parametrize("k,segments", [(2, 32), (4, 16), (8, 10), (15, 8)])
+def test_many_pieces_per_pair(k, segments, batch):
+    """Small batches are cut into pieces of four tiles, so a pair of 128 n tokens has n segments: around the number whose log-sum-exp one
+    turn takes and several times that, with O put together by workgroups of its own (few pairs) and by the finish kernel's own."""
+    lens = [128 * (segments - 1), 128 * segments, 128 * (segments + 1), 128 * 3 * segments + 5] + [17] * (batch - 4)
+    _same_as_two_calls(small(350 + k, B=batch, Hq=4, Hkv=1, spec_k=k, seq_lens=lens, budgets=[64, 64, 64, 200] + [5] * (batch - 4)), f"{segments} pieces")
+
+
 @pytest.mark.parametrize("kv_dtype,page,heads,k", [("bf16", 16, 8, 2), ("bf16", 64, 16, 4), ("fp8_e4m3", 16, 8, 2), ("fp8_e4m3", 32, 16, 4),
                                                    ("fp8_e4m3", 16, 16, 5)])
 def test_stretches_at_their_edges(kv_dtype, page, heads, k):
