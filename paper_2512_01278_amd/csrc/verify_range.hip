@@ -1872,18 +1872,22 @@ __device__ __forceinline__ float pair_lse(const KvView& kv, const RangeWs& ws, i
   if (threadIdx.x < rows) {
     const int row = threadIdx.x;
     float m = -INFINITY, l = 0.f;
-    // (every place has been written, -inf and 0 where there is no segment, so all reads leave together)
+    // (every place has been written, -inf and 0 where there is no segment, so eight reads leave together)
+    constexpr int kStep = kPar % 8 == 0 ? 8 : kPar;
+    const int live = min(segs.n, kPar);
+    for (int s0 = 0; s0 < live; s0 += kStep)
 #pragma unroll
-    for (int sg = 0; sg < kPar; ++sg) m = fmaxf(m, s_m[sg * rows + row]);
+      for (int j = 0; j < kStep; ++j) m = fmaxf(m, s_m[(s0 + j) * rows + row]);
     const float mu = (m == -INFINITY) ? 0.f : m;
+    for (int s0 = 0; s0 < live; s0 += kStep)
 #pragma unroll
-    for (int sg = 0; sg < kPar; ++sg) l += s_l[sg * rows + row] * fast_exp2(s_m[sg * rows + row] - mu);
-    const bool live = row < Rb && l > 0.f;
-    const float v = live ? m + log2f(l) : INFINITY;
+      for (int j = 0; j < kStep; ++j) l += s_l[(s0 + j) * rows + row] * fast_exp2(s_m[(s0 + j) * rows + row] - mu);
+    const bool sees = row < Rb && l > 0.f;
+    const float v = sees ? m + log2f(l) : INFINITY;
     s_lse[row] = v;
     if (lse_out && row < Rb) {
       const int i = row / G, hg = row - i * G;
-      lse_out[(static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg] = live ? v * kLn2 : -INFINITY;
+      lse_out[(static_cast<int64_t>(rq) * n_q + i) * kv.num_q_heads + g * G + hg] = sees ? v * kLn2 : -INFINITY;
     }
   }
   __syncthreads();
