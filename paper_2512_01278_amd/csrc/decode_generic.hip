@@ -19,8 +19,14 @@ constexpr int kTile = 128, kStride = kTile + 4;
 constexpr int kThreads = kGenThreads;
 constexpr int kMaxG = 16;
 
+// Workgroups that a compute unit has to hold; what bounds that are the registers of the rows on their way.  The compiler, left to itself, takes
+// more for their addresses in the two forms of a tile and holds one workgroup less: 600 (request, head) pairs with lists of 64, head_dim
+// 64 and fp32 14.8 us (two per compute unit, 12.8 before the matrix cores) / 10.7 here, bf16 rows 26.9 (19.9) / 16.7, their lists of 1024
+// rows 335 (317) / 188; head_dim 128 and fp32, 300 pairs, lists of 64 19.1 (19.6) / 12.2.  The other types do not fit closer without spilling.
+constexpr int decode_per_cu(int kvdt, int d) { return d == 64 ? (kvdt == PILLAR_FP8_E4M3 ? 2 : 3) : kvdt == PILLAR_F32 ? 2 : 1; }
+
 template <int QDT, int KVDT, int D>
-__global__ __launch_bounds__(kThreads) void decode_generic(DecodeArgs a) {
+__global__ __launch_bounds__(kThreads, decode_per_cu(KVDT, D)) void decode_generic(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) float s_q[kMaxG * kQStride];
   __shared__ __attribute__((aligned(16))) float s[kMaxG * kStride];
   __shared__ __attribute__((aligned(16))) float s_k[kPiece * kPieceStride];

@@ -1,5 +1,6 @@
 """Register use of the built kernels, from the notes the compiler leaves in the library's code objects."""
 import os
+import re
 import struct
 
 import msgpack
@@ -40,3 +41,30 @@ def test_finish_kernels_spill_no_registers():
         pytest.fail(f"no finish kernel among {len(all_)} kernels")
     bad = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in finish.items() if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert len(finish) == 28 and not bad, bad
+
+
+def workgroups(metadata):
+    """Workgroups that a compute unit has registers for: 512 per lane and SIMD, given out in eights."""
+    return 512 // (-(-metadata[".vgpr_count"] // 8) * 8)
+
+
+def generic(kernel):
+    """Template arguments -> metadata of the generic kernels of that name (256 threads: a wavefront per SIMD)."""
+    found = {}
+    for name, k in kernels().items():
+        m = re.search(rf"\d{kernel}I((?:L[ib]\d+E)+)E", name)
+        if m:
+            found[tuple(map(int, re.findall(r"L[ib](\d+)E", m.group(1))))] = k
+    assert found, f"no {kernel}"
+    return found
+
+
+F32, BF16, FP8 = (pb.DTYPE_CODE[t] for t in ("f32", "bf16", "fp8_e4m3"))
+
+
+def test_generic_draft_keeps_its_workgroups_per_compute_unit():
+    """With a workgroup fewer per compute unit, 600 (request, head) pairs took up to a third longer than before the contractions went to
+    the matrix cores."""
+    for (_, kv, d), k in generic("decode_generic").items():
+        least = (2 if kv == FP8 else 3) if d == 64 else 2 if kv == F32 else 1
+        assert workgroups(k) >= least and k[".vgpr_spill_count"] == 0, (kv, d, k[".vgpr_count"], k[".vgpr_spill_count"])
