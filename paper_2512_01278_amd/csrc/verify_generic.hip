@@ -18,6 +18,7 @@
 //           logits again, now against the final lse: exp(s - lse) is the exact
 //           softmax probability; mean over rows
 #include <algorithm>
+#include <type_traits>
 
 #include "generic_rows.hpp"
 #include "launch.hpp"
@@ -26,12 +27,12 @@ namespace pillar {
 namespace {
 
 // Tokens per workgroup.  The pieces of 32 tokens of a chunk follow each other through LDS, with two barriers and a walk over the
-// rows each, so a launch is as long as its longest chunk until the chip is full: where all its pieces fit on the chip side by side (4
-// workgroups per compute unit), every piece is a chunk.  Chunks of 128 / of 32 tokens, fp32, 4 heads, head_dim 64, verification and
-// selection and draft: 2 requests of 300 to 512 tokens 32.2 / 25.0 us, 4 of 2 K and 2 heads 35.9 / 30.0, 64 of 512 33.7 / 31.9 (1024
-// pieces), 16 of 2 K 37.8 / 33.5; 64 rows and head_dim 128, 16 of 2 K 97 / 83.  Beyond, chunks of 128 fetch the query
-// rows and leave partial outputs a quarter as often.  (The host knows no lengths: it counts with max_seq_len, so a caller whose contexts
-// are short does well to say so.)
+// rows each, so a launch is as long as its longest chunk until the chip is full: up to 4 pieces per compute unit, what the LDS is room for
+// (head_dim 128: the split kernel has registers for 3), every piece is a chunk.  Chunks of 128 / of 32 tokens, verification and
+// selection and draft, fp32, 4 heads, head_dim 64: 2 requests of 300 to 512 tokens 32.2 / 25.0 us, 4 of 2 K and 2 heads 35.9 / 30.0; 1024
+// pieces: 64 of 512 33.5 / 31.7, 16 of 2 K 38.1 / 33.9, 32 of 1 K 34.1 / 35.4; with head_dim 128 49.9 / 48.2, 53.3 / 50.1, 49.5 / 52.0, with fp8
+// 116 / 88, 128 / 108, 113 / 92.  Beyond, chunks of 128 fetch the query rows and leave partial outputs a quarter as often.  (The host knows no
+// lengths: it counts with max_seq_len, so a caller whose contexts are short does well to say so.)
 constexpr int kChunk = 128, kFineChunk = kPiece;
 size_t fine_chunks() { return 4 * static_cast<size_t>(num_cus()); }
 constexpr int kThreads = kGenThreads;
@@ -100,8 +101,8 @@ template <int QDT, int D> struct StagedQueries {
 // Logits of query rows row0 .. row0+rows-1 against the chunk's tokens into lds.s[r][tt] (sm_scale applied, -inf where masked or
 // beyond the sequence).  Every thread of the workgroup calls this; lds.off is complete (a barrier ago).
 // All K rows are sent for before the first is needed (SENT: they have been, into `sent`), and `ahead` is called right after (to send for
-// V rows).  Fine chunks have sent for the query rows as well (`queries`); a full chip has nothing to gain from that, nor the registers.
-template <int QDT, int KVDT, int D, int CHUNK, bool SENT, typename Ahead>
+// V rows).  QUERIES_SENT: the query rows are on their way as well (`queries`); a full chip has nothing to gain from that, nor the registers.
+template <int QDT, int KVDT, int D, int CHUNK, bool SENT, bool QUERIES_SENT, typename Ahead>
 __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, int n_q, int b, int g, int t0, int nt, int L, int row0, int rows,
                                              GenericLds<CHUNK>& lds, const StagedPiece<KVDT, D> (&sent)[CHUNK / kPiece],
                                              const StagedQueries<QDT, D>& queries, Ahead ahead) {
@@ -114,7 +115,7 @@ __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, in
   }
   ahead();
   const int G = kv.num_q_heads / kv.num_kv_heads;
-  if constexpr (CHUNK == kFineChunk) {
+  if constexpr (QUERIES_SENT) {
     queries.store(lds.q, rows);
   } else {
     for (int idx = threadIdx.x; idx < rows * D; idx += kThreads) {
@@ -148,8 +149,10 @@ __device__ __forceinline__ void chunk_logits(const KvView& kv, const void* q, in
   __syncthreads();
 }
 
+// (Fine chunks with head_dim 128: the query rows that are sent for early leave registers for three workgroups per compute unit.  With fp8 the
+// compiler, left to itself, took enough for two: 48 requests of 512 tokens, this kernel 37.3 us, 23.4 with three, 31.4 before the matrix cores.)
 template <int QDT, int KVDT, int D, int CHUNK>
-__global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
+__global__ __launch_bounds__(kThreads, CHUNK == kFineChunk ? (D == 64 ? 4 : 3) : 2) void verify_split_generic(KvView kv, const void* q, int n_q, GenericWs ws) {
   constexpr int kPieces = CHUNK / kPiece;
   __shared__ GenericLds<CHUNK> lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void verify_split_generic(KvView kv, c
       if (row0 > 0) queries.fetch(kv, q, n_q, b, g, row0, rows);
     }
     StagedPiece<KVDT, D> piece[kPieces];
-    chunk_logits<QDT, KVDT, D, CHUNK, false>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, piece, queries, [&]() {
+    chunk_logits<QDT, KVDT, D, CHUNK, false, CHUNK == kFineChunk>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, piece, queries, [&]() {
 #pragma unroll
       for (int p = 0; p < kPieces; ++p) piece[p].fetch(kv.v_pool, lds.off, p * kPiece, nt);
     });
@@ -273,9 +276,17 @@ __global__ __launch_bounds__(kMergeThreads) void verify_merge_generic(KvView kv,
   }
 }
 
-template <int QDT, int KVDT, int D, int CHUNK, bool MERGED>
-__global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, const void* q, int n_q, GenericWs ws, void* out, float* lse_out,
-                                                                   float* scores, int64_t score_stride) {
+// Workgroups of the finish kernel of fine chunks that a compute unit holds (registers; the LDS is room for four).  EARLY: what is needed
+// after the log-sum-exp, the query rows and the partials of 16 chunks instead of 8, is sent for before it.  With head_dim 128 that takes 165
+// registers, with fp8 199, so it is for launches that fit on the chip that way.  Whole rounds without / with it, fp32, 4 heads, head_dim
+// 128: 2 requests of 300 to 512 tokens and 32 rows 36.7 / 34.7 us, 8 of 2 K and 64 rows 57.4 / 52.5, 48 of 512 41.3 / 39.1; 64 of 512, which do
+// not fit, 48.3 / 50.3, with fp8 88.3 / 98.7, 32 of 1 K 92.5 / 106.  (8: of a pair's up to 32 chunks as many as four workgroups leave
+// registers for.  16: of two requests of 512 tokens all.)
+constexpr int finish_per_cu(int kvdt, int d, bool early) { return d == 64 || !early ? 4 : kvdt == PILLAR_FP8_E4M3 ? 2 : 3; }
+
+template <int QDT, int KVDT, int D, int CHUNK, bool MERGED, bool EARLY>
+__global__ __launch_bounds__(kThreads, CHUNK == kFineChunk ? finish_per_cu(KVDT, D, EARLY) : 2) void verify_finish_generic(
+    KvView kv, const void* q, int n_q, GenericWs ws, void* out, float* lse_out, float* scores, int64_t score_stride) {
   __shared__ GenericLds<CHUNK> lds;
   const int b = blockIdx.z, g = blockIdx.y, c = blockIdx.x;
   const int L = kv.seq_lens[b];
@@ -298,13 +309,13 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
   const int64_t base = (static_cast<int64_t>(b) * kv.num_kv_heads + g) * ws.nc;
   // A fine chunk's K rows are on their way while the partials are merged.  (Where the chip is full there is nothing to wait for, and
   // rows held that long cost: 64 requests of 1 to 2 K tokens, 64 rows, head_dim 128, this kernel 136 -> 148 us before the matrix cores.)
-  constexpr bool kSent = CHUNK == kFineChunk;
+  constexpr bool kSent = CHUNK == kFineChunk, kQueriesSent = kSent && EARLY;
   StagedQueries<QDT, D> queries;
-  if constexpr (kSent) {
+  if constexpr (kQueriesSent) {
     if (scores) queries.fetch(kv, q, n_q, b, g, 0, min(kPieceRows, R));
   }
   // and so are the partials of this thread's first element of the output
-  constexpr int kAhead = kSent && !MERGED ? 16 : 1;
+  constexpr int kAhead = kSent && !MERGED ? (EARLY ? 16 : 8) : 1;
   float m_ahead[kAhead], o_ahead[kAhead];
   if constexpr (kAhead > 1) {
     const int idx = min(c * R * D / nc + static_cast<int>(threadIdx.x), R * D - 1);
@@ -394,10 +405,10 @@ __global__ __launch_bounds__(kThreads, 2) void verify_finish_generic(KvView kv, 
       if (row0 > 0) {
 #pragma unroll
         for (int p = 0; p < CHUNK / kPiece; ++p) k_piece[p].fetch(kv.k_pool, lds.off, p * kPiece, nt);
-        queries.fetch(kv, q, n_q, b, g, row0, rows);
+        if constexpr (kQueriesSent) queries.fetch(kv, q, n_q, b, g, row0, rows);
       }
     }
-    chunk_logits<QDT, KVDT, D, CHUNK, kSent>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece, queries, []() {});
+    chunk_logits<QDT, KVDT, D, CHUNK, kSent, kQueriesSent>(kv, q, n_q, b, g, t0, nt, L, row0, rows, lds, k_piece, queries, []() {});
     // kPer threads per token take the rows in turn
     const int tt = threadIdx.x / kPer;
 #pragma unroll 4
@@ -453,8 +464,16 @@ hipError_t run(const VerifyArgs& a, hipStream_t st) {
   }
   if (!ws.merged || a.scores) {
     KernelTimer t("verify_finish_generic", st);
-    const auto kernel = ws.merged ? (ws.fine ? verify_finish_generic<QDT, KVDT, D, kFineChunk, true> : verify_finish_generic<QDT, KVDT, D, kChunk, true>)
-                                  : (ws.fine ? verify_finish_generic<QDT, KVDT, D, kFineChunk, false> : verify_finish_generic<QDT, KVDT, D, kChunk, false>);
+    const bool early = static_cast<size_t>(grid.x) * grid.y * grid.z <= finish_per_cu(KVDT, D, true) * static_cast<size_t>(num_cus());
+    const auto form = [&](auto chunk, auto sent) {
+      constexpr int CHUNK = decltype(chunk)::value;
+      constexpr bool EARLY = decltype(sent)::value;
+      return ws.merged ? verify_finish_generic<QDT, KVDT, D, CHUNK, true, EARLY> : verify_finish_generic<QDT, KVDT, D, CHUNK, false, EARLY>;
+    };
+    const std::integral_constant<int, kFineChunk> fine{};
+    // (head_dim 64: any fine launch fits)
+    const auto kernel = !ws.fine ? form(std::integral_constant<int, kChunk>{}, std::false_type{})
+                        : early ? form(fine, std::true_type{}) : form(fine, std::bool_constant<D == 64>{});
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, kv, a.q, a.n_q, ws, a.out, a.lse, a.scores, a.score_stride);
   }
   return hipGetLastError();

@@ -281,6 +281,18 @@ def test_generic_kernels_on_both_sides_of_the_chunk_rule(batch, top, q_dtype, kv
     round_trip(w, what="generic kernels, chunk rule", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
 
 
+@pytest.mark.parametrize("top", [1000, 1100])
+@pytest.mark.parametrize("q_dtype,kv_dtype,pieces", [("f32", "f32", 768), ("bf16", "fp8_e4m3", 512)])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_generic_kernels_on_both_sides_of_the_early_form(q_dtype, kv_dtype, pieces, beyond, top):
+    """head_dim 128: while a compute unit holds all pieces that way the finish kernel sends for queries and partials early, beyond it sends
+    for half the partials only.  64 query rows (two turns), contexts of 1 to 32 pieces (merged by that kernel) and of more."""
+    batch = pieces // -(-top // 32) + beyond
+    lens = [top] + [(4, 33, 256, 257, 511, 513, 900)[b % 7] for b in range(1, batch)]
+    w = small(360, q_dtype=q_dtype, kv_dtype=kv_dtype, D=128, P=8, B=batch, Hq=16, Hkv=1, spec_k=3, seq_lens=lens, budgets=[min(n, 33) for n in lens])
+    round_trip(w, what="generic kernels, early form", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
+
+
 @pytest.mark.parametrize("top", [512, 1500])
 def test_generic_kernels_without_room_for_fine_chunks(top):
     """A workspace with a slot per 128 tokens, less than is reported for small shapes, is enough, as it was before there were chunks of 32;

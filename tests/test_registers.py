@@ -68,3 +68,17 @@ def test_generic_draft_keeps_its_workgroups_per_compute_unit():
     for (_, kv, d), k in generic("decode_generic").items():
         least = (2 if kv == FP8 else 3) if d == 64 else 2 if kv == F32 else 1
         assert workgroups(k) >= least and k[".vgpr_spill_count"] == 0, (kv, d, k[".vgpr_count"], k[".vgpr_spill_count"])
+
+
+def test_generic_verification_keeps_its_workgroups_per_compute_unit():
+    """Chunks of 32 tokens run with up to four workgroups per compute unit.  With head_dim 128 the split kernel holds three, and so does the
+    form of the finish kernel that sends for queries and partials early (fp8 two): the host takes that form only for launches that fit so."""
+    fine = 32
+    for (_, kv, d, chunk), k in generic("verify_split_generic").items():
+        assert workgroups(k) >= (2 if chunk != fine else 4 if d == 64 else 3) and k[".vgpr_spill_count"] == 0, (kv, d, chunk, k[".vgpr_count"])
+    early_forms = 0
+    for (_, kv, d, chunk, merged, early), k in generic("verify_finish_generic").items():
+        least = 2 if chunk != fine else 4 if d == 64 or not early else 2 if kv == FP8 else 3
+        early_forms += chunk == fine and early
+        assert workgroups(k) >= least and k[".vgpr_spill_count"] == 0, (kv, d, chunk, merged, early, k[".vgpr_count"])
+    assert early_forms == 24
