@@ -46,6 +46,7 @@
 // 1024 requests, worked out by the wavefronts of the pass themselves (wave_plan).
 #include <type_traits>
 
+#include "host_rules.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
 #include "topk_core.hpp"
@@ -2313,21 +2314,6 @@ int team_ranges(int slots) {
   return std::min(slots, std::max(1, (opt > 0 ? opt : 8) * num_cus() / kTeamWaves));
 }
 
-// Workgroups of the finish kernel that put O of one pair together and do nothing else: where half the chip would idle, as many as it holds
-// beside the others (one per pair and 8192 tokens) in two rounds.  The rule must not ask for the statistic: with and without it, O has
-// the same bits.  Without / with them, whole call: one request of 2100 tokens 26.4 / 23.5 us, 24 of 5-3000 24.1 / 20.4, 16 of 2-4 K with 8
-// heads 60.7 / 57.0, 24 of 10-3000 with 64 rows 35.0 / 27.0, one of 32 K 64.4 / 56.0, one of 8 K without the statistic 41.1 / 30.3.
-// With every compute unit taken by the statistic they only get in its way: 16 requests of 24-32 K tokens 494 / 496; and with more than 96
-// pairs where they take more than two turns: 128 pairs of 768 tokens with 36 rows 36.4 / 38.7 (with 20, 64 to 2048 tokens 23.5 / 21.9).
-int merger_groups(const KvView& kv, int n_q, int threads) {
-  const int64_t pairs = static_cast<int64_t>(kv.batch) * kv.num_kv_heads, others = pairs * ((kv.max_seq_len + 8191) / 8192);
-  if (2 * others > num_cus()) return 0;
-  const int at_once = 4 * (threads / 512), rows = n_q * (kv.num_q_heads / kv.num_kv_heads);       // rows of a turn
-  const int room = static_cast<int>(2 * (num_cus() - others) / pairs);
-  if (8 * others > 3 * num_cus() && rows > 16 * room) return 0;          // (two turns of 1024 threads)
-  return std::min(room, (rows + at_once - 1) / at_once);
-}
-
 int row_blocks(const KvView& kv, int n_q) { return (n_q * (kv.num_q_heads / kv.num_kv_heads) + 15) / 16; }
 
 RangeWs carve(const KvView& kv, int n_q, void* workspace, size_t* total_bytes) {
@@ -2428,7 +2414,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
       sel = a.select ? *a.select : SelectOut{};
 #define PILLAR_FINISH(THREADS, CH, SELECT)                                                                                          \
   {                                                                                                                                 \
-    const int mergers = merger_groups(kv, a.n_q, THREADS);                                                                          \
+    const int mergers = merger_groups(pairs, kv.max_seq_len, rows, THREADS, num_cus());                                             \
     if (pairs <= num_cus()) ws.order = nullptr;                                                                                     \
     hipLaunchKernelGGL((verify_finish<RB, THREADS, CH, SELECT, false>), dim3(pairs, mergers + 1), dim3(THREADS), 0, st, kv, a.n_q,  \
                        ws, out, a.lse, a.scores, a.score_stride, sel, mergers);                                                     \
@@ -2436,7 +2422,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
 #define PILLAR_FINISH_SPLIT(CH)                                                                                                   \
   {                                                                                                                               \
     const int nchunks = (kv.max_seq_len + 8191) / 8192;                                                                           \
-    const int mergers = merger_groups(kv, a.n_q, 1024);                                                                           \
+    const int mergers = merger_groups(pairs, kv.max_seq_len, rows, 1024, num_cus());                                              \
     hipLaunchKernelGGL((verify_finish<RB, 1024, 1, false, true>), dim3(pairs, mergers + nchunks), dim3(1024), 0, st, kv, a.n_q,   \
                        ws, out, a.lse, a.scores, a.score_stride, sel, mergers);                                                   \
     split_select = CH;                                                                                                            \
