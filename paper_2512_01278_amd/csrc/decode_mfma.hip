@@ -30,11 +30,11 @@ constexpr int kMergeThreads = 256;
 constexpr int kSpanRows = 512;                 // rows of an index list one workgroup takes
 
 
-template <bool FP8, bool BYPASS>
+template <bool FP8, bool MAY_BYPASS>
 __global__ __launch_bounds__(kDecThreads, 3) void decode_span_mfma(DecodeArgs a, DecWs ws, int span_rows, int nspan_max) {
   __shared__ __attribute__((aligned(16))) uint8_t s_tiles[kDecWaves][kVTileBytes];
   const DecPlace at = decode_place(FP8, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), a.kv.batch, a.kv.num_kv_heads, nspan_max);
-  decode_span_body<FP8, kDecWaves, BYPASS>(a, ws, span_rows, nspan_max, at.slot_b, at.g, at.sp, s_tiles);
+  decode_span_body<FP8, kDecWaves, MAY_BYPASS>(a, ws, span_rows, nspan_max, at.slot_b, at.g, at.sp, s_tiles);
 }
 
 // Everything a thread needs of up to kAtOnce spans is sent for at once, before the count says how many there are (spans that the list does

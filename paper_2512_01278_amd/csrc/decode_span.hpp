@@ -3,6 +3,7 @@
 #pragma once
 
 #include "decode_place.hpp"
+#include "host_rules.hpp"
 #include "launch.hpp"
 #include "mfma_tile.hpp"
 
@@ -30,17 +31,8 @@ __device__ __forceinline__ Rows resolve_rows(const KvView& kv, int b, int g, int
   return r;
 }
 
-// Whether the rows of a draft step bypass the Infinity Cache (non-temporal loads).  Rows that are there no more when they are next
-// needed are read 7 to 14 % faster that way: 128 requests with lists of 256 31.3 / 27.1 us, 32 12.1 / 11.0, 16 of 1024 rows 21.3 / 19.4, fp8
-// 64 of 512 22.2 / 20.7, each over so many pools that nothing stays cached; and the unified batch of 128 of 1-8 K tokens takes 154 / 144.
-// But a layer that is verified or drafted from again before 256 MB have been read loses what is still there: one draft step and
-// one verification of 32 requests of 4096 tokens in turn (34 MB of rows) 131 / 135.5, fp8 lists of 512 over three pools (67 MB each) 20.1 /
-// 20.9.  So the line lies where two calls' rows no longer fit beside what the pass leaves: 96 MB.  (Above it, too, a single layer stepped
-// over and over on the same pools reads less from memory without: 128 requests of 1-8 K tokens, verification and draft 586.5 / 593.5,
-// unified batch 151 / 161.  A model has many layers between two steps of one.)
-__host__ __device__ inline bool draft_bypasses(int64_t list_rows, bool fp8) { return list_rows * 2 * kHeadDim * (fp8 ? 1 : 2) > (int64_t{96} << 20); }
-
-// sends the row loads of the tile whose row offsets half `half` of the lanes (0: lanes 0..31, 1: lanes 32..63) holds
+// sends the row loads of the tile whose row offsets half `half` of the lanes (0: lanes 0..31, 1: lanes 32..63) holds; BYPASS: past the Infinity
+// Cache
 template <bool FP8, bool BYPASS>
 __device__ __forceinline__ void issue_rows(const KvView& kv, uint32_t off16, int half, TileRegs<FP8>& t, int lane) {
   constexpr int kRowsPerLoad = FP8 ? 8 : 4;
@@ -77,41 +69,23 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return f32_to_bf16(a) | (static_cast<uint32_t>(f32_to_bf16(b)) << 16);
 }
 
-// One (request slot, KV head, span) of the draft step by a workgroup of WAVES wavefronts.  s_tiles: per
-// wavefront one tile buffer (the K rows, then, once S^T is done, the V rows of the same tile; at the end its
-// (max, sum, O) for the combine).  Every thread of the workgroup must call this.
+// The rest of decode_span_body, once the count is known; tok: the index entries of the first round.  (Whole copies for either kind of loads: with
+// a branch at the loads 128 requests with lists of 64 to 448 take 34 us, with one around the rounds 29.0, so 28.0.)
 template <bool FP8, int WAVES, bool BYPASS>
-__device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecWs& ws, int span_rows, int nspan_max, int slot_b, int g,
-                                                 int sp, uint8_t (*s_tiles)[kVTileBytes]) {
+__device__ __forceinline__ void decode_span_rest(const DecodeArgs& a, const DecWs& ws, int span_rows, int nspan_max, int slot_b, int b, int g, int sp,
+                                                 int count, int (&tok)[2], uint8_t (*s_tiles)[kVTileBytes]) {
   const KvView& kv = a.kv;
-  const int b = request_of(kv, slot_b);          // everything the request owns is indexed by its id
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int n = lane & 15, g4 = lane >> 4;
   const int G = kv.num_q_heads / kv.num_kv_heads;
   uint8_t* s_tile = s_tiles[wave];
   const int32_t* list = a.indices + (static_cast<int64_t>(b) * kv.num_kv_heads + g) * a.max_budget;
   const int j_begin = sp * span_rows;
-  // The index entries of the first four tiles of this wavefront (tiles wave, wave + WAVES, ...; register q holds
-  // tile 2q in lanes 0..31 and tile 2q + 1 in lanes 32..63) leave together with the count: entries up to
-  // max_budget exist, which of them count is decided when both are here.
+  uint16_t* out = static_cast<uint16_t*>(a.out);
   auto entry_of = [&](int round, int q) {
     const int tile = wave + WAVES * (4 * round + 2 * q + (lane >> 5));
     return j_begin + tile * kTileTokens + (lane & 31);
   };
-  int tok[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) tok[q] = list[min(entry_of(0, q), a.max_budget - 1)];
-  const int count = min(max(a.counts[b], 0), a.max_budget);
-  uint16_t* out = static_cast<uint16_t*>(a.out);
-  if (count == 0) {
-    if (sp == 0) {
-      for (int idx = threadIdx.x; idx < G * kHeadDim; idx += (WAVES * kWave))
-        out[(static_cast<int64_t>(b) * kv.num_q_heads + g * G) * kHeadDim + idx] = 0;
-      if (a.lse && threadIdx.x < G) a.lse[static_cast<int64_t>(b) * kv.num_q_heads + g * G + threadIdx.x] = -INFINITY;
-    }
-    return;
-  }
-  if (j_begin >= count) return;
   const int j_end = min(count, j_begin + span_rows);
   const int nspan = (count + span_rows - 1) / span_rows;
   const int ntiles = (j_end - j_begin + kTileTokens - 1) / kTileTokens;       // of the span
@@ -262,6 +236,46 @@ __device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecW
       *reinterpret_cast<f32x4*>(ws.part_o + (slot * G + r) * kHeadDim + 4 * d4) = acc;
     }
   }
+}
+
+// One (request slot, KV head, span) of the draft step by a workgroup of WAVES wavefronts.  s_tiles: per
+// wavefront one tile buffer (the K rows, then, once S^T is done, the V rows of the same tile; at the end its
+// (max, sum, O) for the combine).  MAY_BYPASS: the index buffers have room for so many rows that they might bypass the Infinity Cache; a
+// workgroup decides by its own list.  Every thread of the workgroup must call this.
+template <bool FP8, int WAVES, bool MAY_BYPASS>
+__device__ __forceinline__ void decode_span_body(const DecodeArgs& a, const DecWs& ws, int span_rows, int nspan_max, int slot_b, int g,
+                                                 int sp, uint8_t (*s_tiles)[kVTileBytes]) {
+  const KvView& kv = a.kv;
+  const int b = request_of(kv, slot_b);          // everything the request owns is indexed by its id
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int G = kv.num_q_heads / kv.num_kv_heads;
+  const int32_t* list = a.indices + (static_cast<int64_t>(b) * kv.num_kv_heads + g) * a.max_budget;
+  const int j_begin = sp * span_rows;
+  // The index entries of the first four tiles of this wavefront (tiles wave, wave + WAVES, ...; register q holds
+  // tile 2q in lanes 0..31 and tile 2q + 1 in lanes 32..63) leave together with the count: entries up to
+  // max_budget exist, which of them count is decided when both are here.
+  auto entry_of = [&](int round, int q) {
+    const int tile = wave + WAVES * (4 * round + 2 * q + (lane >> 5));
+    return j_begin + tile * kTileTokens + (lane & 31);
+  };
+  int tok[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) tok[q] = list[min(entry_of(0, q), a.max_budget - 1)];
+  const int count = min(max(a.counts[b], 0), a.max_budget);
+  uint16_t* out = static_cast<uint16_t*>(a.out);
+  if (count == 0) {
+    if (sp == 0) {
+      for (int idx = threadIdx.x; idx < G * kHeadDim; idx += (WAVES * kWave))
+        out[(static_cast<int64_t>(b) * kv.num_q_heads + g * G) * kHeadDim + idx] = 0;
+      if (a.lse && threadIdx.x < G) a.lse[static_cast<int64_t>(b) * kv.num_q_heads + g * G + threadIdx.x] = -INFINITY;
+    }
+    return;
+  }
+  if (j_begin >= count) return;
+  if (MAY_BYPASS && draft_bypasses(static_cast<int64_t>(count) * kv.batch * kv.num_kv_heads, FP8))
+    decode_span_rest<FP8, WAVES, true>(a, ws, span_rows, nspan_max, slot_b, b, g, sp, count, tok, s_tiles);
+  else
+    decode_span_rest<FP8, WAVES, false>(a, ws, span_rows, nspan_max, slot_b, b, g, sp, count, tok, s_tiles);
 }
 
 }  // namespace

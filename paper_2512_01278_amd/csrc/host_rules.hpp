@@ -1,4 +1,4 @@
-// Rules by which a launch is chosen, as plain arithmetic, also for a host compiler.
+// Rules by which a kernel, or a path within one, is chosen: plain arithmetic, also for a host compiler.
 #pragma once
 
 #include <algorithm>
@@ -23,5 +23,19 @@ inline int merger_groups(int64_t pairs, int max_seq_len, int rows, int threads, 
   if (rows > 16 * room) return 0;
   return std::min(room, (rows + at_once - 1) / at_once);
 }
+
+// Whether the rows of a draft step bypass the Infinity Cache (non-temporal loads).  Rows that are there no more when they are next
+// needed are read 7 to 14 % faster that way: 128 requests with lists of 256 31.3 / 27.1 us, 32 12.1 / 11.0, 16 of 1024 rows 21.3 / 19.4, fp8
+// 64 of 512 22.2 / 20.7, each over so many pools that nothing stays cached; and the unified batch of 128 of 1-8 K tokens takes 154 / 144.
+// But a layer that is verified or drafted from again before 256 MB have been read loses what is still there: one draft step and
+// one verification of 32 requests of 4096 tokens in turn (34 MB of rows) 131 / 135.5, fp8 lists of 512 over three pools (67 MB each) 20.1 /
+// 20.9.  So the line lies where two calls' rows no longer fit beside what the pass leaves: 96 MB.  (Above it, too, a single layer stepped
+// over and over on the same pools reads less from memory without: 128 requests of 1-8 K tokens, verification and draft 586.5 / 593.5,
+// unified batch 151 / 161.  A model has many layers between two steps of one.)
+// list_rows: the host knows only what the index buffers have room for; where that is beyond the line, each workgroup asks again as if all lists
+// were as long as its own.  (With lists of 256 and room for 2048, one draft step and one verification of 32 requests of 4096 tokens took
+// 145 us when the room decided, 142 so, 140 without bypass.  All counts added up by every workgroup: 128 requests 30.6 us instead of 28.0,
+// 300 with lists of 64 27 instead of 22.)
+__host__ __device__ inline bool draft_bypasses(int64_t list_rows, bool fp8) { return list_rows * (fp8 ? 256 : 512) > (int64_t{96} << 20); }
 
 }  // namespace pillar

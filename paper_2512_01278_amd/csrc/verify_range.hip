@@ -1519,7 +1519,7 @@ __global__ __launch_bounds__(kTeamWaves * kWave, 2) void verify_flash_team(KvVie
 // range of the verification pass each, as in their own kernel, the workgroups after them one (request, KV head, span) of
 // the draft step each.  Which path a workgroup takes is decided on the chip from its index; the draft workgroups come last
 // in dispatch order, so they fill the compute units as the ranges drain.
-template <int RB, bool FP8, bool BYPASS>
+template <int RB, bool FP8, bool MAY_BYPASS>
 __global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out,
                                                                           DecodeArgs da, DecWs dws, int span_rows, int nspan) {
   __shared__ TeamLds<RB, kTeamWaves> lds;      // its tile buffers serve the draft path too
@@ -1527,8 +1527,8 @@ __global__ __launch_bounds__(kTeamWaves * kWave, 2) void mixed_flash_team(KvView
     flash_team_body<RB, FP8, kTeamWaves, kStashKept>(kv, q, n_q, ws, out, lds, blockIdx.x);
   } else {
     const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
-    decode_span_body<FP8, kTeamWaves, BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
-                                      reinterpret_cast<uint8_t (*)[kVTileBytes]>(lds.tile));
+    decode_span_body<FP8, kTeamWaves, MAY_BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
+                                                  reinterpret_cast<uint8_t (*)[kVTileBytes]>(lds.tile));
   }
 }
 
@@ -1819,7 +1819,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void verify_flash_pair(KvView kv, 
 
 // A unified batch with more than 32 query rows per KV head: the first n_ranges workgroups are those of
 // verify_flash_pair, the others carry one (request, KV head, span) of the draft step each, with two wavefronts.
-template <int RB, bool FP8, bool BYPASS>
+template <int RB, bool FP8, bool MAY_BYPASS>
 __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, const uint16_t* q, int n_q, RangeWs ws, uint16_t* out,
                                                                     DecodeArgs da, DecWs dws, int span_rows, int nspan) {
   static_assert(RB >= 3, "up to two row blocks run mixed_flash_team");
@@ -1832,8 +1832,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void mixed_flash_pair(KvView kv, c
     else flash_pair_wave<RB, FP8, kStashKept, RB - kFirst, kFirst>(kv, q, n_q, ws, out, smem, smem + kVTileBytes, 1);
   } else {
     const DecPlace at = decode_place(FP8, blockIdx.x - ws.n_ranges, da.kv.batch, da.kv.num_kv_heads, nspan);
-    decode_span_body<FP8, 2, BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
-                             reinterpret_cast<uint8_t (*)[kVTileBytes]>(smem));
+    decode_span_body<FP8, 2, MAY_BYPASS>(da, dws, span_rows, nspan, at.slot_b, at.g, at.sp,
+                                         reinterpret_cast<uint8_t (*)[kVTileBytes]>(smem));
   }
 }
 
@@ -2372,9 +2372,9 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     const bool fused = draft != nullptr;       // a unified batch: the draft step of other requests rides in the same grid
     DecWs dws{};
     int span_rows = 0, nspan = 0, n_draft = 0;
-    bool bypass = false;
+    bool may_bypass = false;
     if (fused) {
-      bypass = draft_bypasses(static_cast<int64_t>(draft->kv.batch) * draft->kv.num_kv_heads * draft->max_budget, FP8);
+      may_bypass = draft_bypasses(static_cast<int64_t>(draft->kv.batch) * draft->kv.num_kv_heads * draft->max_budget, FP8);
       span_rows = decode_span_rows(draft->kv, draft->max_budget);
       nspan = (draft->max_budget + span_rows - 1) / span_rows;
       dws = decode_carve(draft->kv, draft->max_budget, draft->workspace);
@@ -2385,7 +2385,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
       ws.max_piece_shift = kMaxPieceShift;
       if (fused) {
         KernelTimer t("mixed_flash_team", st);
-        const auto kernel = bypass ? mixed_flash_team<RB, FP8, true> : mixed_flash_team<RB, FP8, false>;
+        const auto kernel = may_bypass ? mixed_flash_team<RB, FP8, true> : mixed_flash_team<RB, FP8, false>;
         hipLaunchKernelGGL(kernel, dim3(ws.n_ranges + n_draft), dim3(kTeamWaves * kWave), 0, st, kv, q, a.n_q, ws, out,
                            *draft, dws, span_rows, nspan);
       } else {
@@ -2397,7 +2397,7 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     } else {                                         // two wavefronts per range and per draft workgroup
       if (fused) {
         KernelTimer t("mixed_flash_pair", st);
-        const auto kernel = bypass ? mixed_flash_pair<RB, FP8, true> : mixed_flash_pair<RB, FP8, false>;
+        const auto kernel = may_bypass ? mixed_flash_pair<RB, FP8, true> : mixed_flash_pair<RB, FP8, false>;
         hipLaunchKernelGGL(kernel, dim3(ws.n_ranges + n_draft), dim3(2 * kThreads), 0, st, kv, q, a.n_q, ws, out,
                            *draft, dws, span_rows, nspan);
       } else {

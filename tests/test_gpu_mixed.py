@@ -118,6 +118,15 @@ def test_mixed_batch_whose_draft_rows_bypass_the_cache(kv_dtype, heads, k, wides
     _case(w, [0], [1, 2], f"bypass, {kv_dtype}, {heads} heads", draft_bits=(k + 1) * heads // 2 <= (48 if kv_dtype == "fp8_e4m3" else 32))
 
 
+@pytest.mark.parametrize("kv_dtype,heads,k,rows", [("bf16", 8, 2, 1030), ("fp8_e4m3", 64, 7, 2060)])
+def test_mixed_batch_whose_draft_lists_bypass_the_cache(kv_dtype, heads, k, rows):
+    """Lists of the drafting requests that name more than 96 MB of rows, in either grid."""
+    B = 26
+    w = gen.make_custom(name="bypass", seed=335 + k, B=B, Hq=heads, Hkv=8, D=128, P=16, spec_k=k, q_dtype="bf16", kv_dtype=kv_dtype,
+                        seq_lens=[40, 300] + [rows + 5] * (B - 2), budgets=[8, 40] + [rows] * (B - 2))
+    _case(w, [0, 1], list(range(2, B)), f"lists that bypass, {kv_dtype}, {heads} heads", draft_bits=(k + 1) * heads // 8 <= (48 if kv_dtype == "fp8_e4m3" else 32))
+
+
 def test_mixed_batch_config3_reduced():
     w = gen.make_workload(3, batch=10)
     _case(w, [0, 5], [1, 2, 3, 4, 6, 7, 8, 9], "config3[:10], every fifth request verifies")

@@ -709,10 +709,17 @@ def test_statistic_written_through_the_cache(kv_dtype, heads, k):
 
 @pytest.mark.parametrize("kv_dtype,widest", [("bf16", 40000), ("fp8_e4m3", 80000)])
 def test_draft_rows_that_bypass_the_cache(kv_dtype, widest):
-    """Index buffers with room for more than 96 MB of rows: other loads, and lists of one, two and five spans of 512 under a merge with room
-    for 79 or 157."""
+    """Index buffers with room for more than 96 MB of rows, where each workgroup asks its own list (and finds that it names less): lists of one, two and five spans of 512 under a merge with room for 79 or 157."""
     w = small(320, kv_dtype=kv_dtype, Hq=16, seq_lens=[3, 700, 2100], budgets=[2, 600, widest])
     round_trip(w, what=f"room for {widest}", fused_select=True)
+
+
+@pytest.mark.parametrize("kv_dtype,batch,rows", [("bf16", 48, 520), ("fp8_e4m3", 24, 2060), ("bf16", 300, 90)])
+def test_draft_rows_that_bypass_the_cache_by_their_lists(kv_dtype, batch, rows):
+    """Lists that name more than 96 MB of rows: of two spans, of five, and of a batch of which some counts are asked."""
+    w = small(325, kv_dtype=kv_dtype, B=batch, Hq=8, Hkv=8, spec_k=0, seq_lens=[rows + 7] * batch, budgets=[rows] * batch)
+    assert batch * 8 * rows * 256 * (1 if kv_dtype == "fp8_e4m3" else 2) > 96 << 20
+    round_trip(w, what=f"{batch} lists of {rows}", fused_select=True)
 
 
 @pytest.mark.parametrize("q_dtype,kv_dtype,D,G", [("f32", "f32", 64, 1), ("f32", "f32", 128, 16), ("bf16", "fp8_e4m3", 64, 4), ("f32", "bf16", 128, 5)])

@@ -11,18 +11,24 @@ MAIN = r"""
 #include <cstdlib>
 #include "host_rules.hpp"
 int main(int, char** v) {
-  printf("%d\n", pillar::merger_groups(atoll(v[1]), atoi(v[2]), atoi(v[3]), atoi(v[4]), 256));
+  if (v[1][0] == 'm') printf("%d\n", pillar::merger_groups(atoll(v[2]), atoi(v[3]), atoi(v[4]), atoi(v[5]), 256));
+  if (v[1][0] == 'b') printf("%d\n", pillar::draft_bypasses(atoll(v[2]), atoi(v[3]) != 0));
 }
 """
 
 
 @pytest.fixture(scope="module")
-def mergers(tmp_path_factory):
+def rule(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "main.cpp").write_text(MAIN)
     exe = str(d / "rules")
-    subprocess.run([shutil.which("g++") or "c++", "-std=c++17", "-I", CSRC, str(d / "main.cpp"), "-o", exe], check=True)
+    subprocess.run([shutil.which("g++") or "c++", "-std=c++17", "-D__host__=", "-D__device__=", "-I", CSRC, str(d / "main.cpp"), "-o", exe], check=True)
     return lambda *args: int(subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True).stdout)
+
+
+@pytest.fixture(scope="module")
+def mergers(rule):
+    return lambda *args: rule("m", *args)
 
 
 def test_mergers_only_where_they_take_two_turns_at_most(mergers):
@@ -38,3 +44,10 @@ def test_mergers_only_where_they_take_two_turns_at_most(mergers):
     assert mergers(96, 4096, 48, 1024) == 3 and mergers(102, 4096, 48, 1024) == 3 and mergers(103, 4096, 48, 1024) == 0
     # contexts of up to n chunks of 8192 tokens take n workgroups per pair
     assert mergers(8, 16 * 8192, 20, 1024) > 0 and mergers(8, 16 * 8192 + 1, 20, 1024) == 0
+
+
+def test_draft_rows_bypass_beyond_96_mb(rule):
+    bypass = lambda list_rows, fp8: bool(rule("b", list_rows, int(fp8)))
+    line = (96 << 20) // 512
+    assert not bypass(line, False) and bypass(line + 1, False) and not bypass(2 * line, True) and bypass(2 * line + 1, True)
+    assert bypass(1 << 40, False) and not bypass(0, False)
