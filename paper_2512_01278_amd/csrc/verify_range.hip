@@ -116,8 +116,7 @@ __device__ __forceinline__ int pieces_of(int tiles, int shift) { return (tiles +
 // Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or, with pieces, pair + (first unit >> shift), which
 // is distinct for the same reason (both indices grow along the layout).
 struct PairSegs { int slot0, n; };
-__device__ __forceinline__ PairSegs segs_of_pair(const RangeWs& ws, int pair, int u0, int tiles) {
-  const int total = max(ws.ctrl[0], 1), cut = ws.ctrl[1];
+__device__ __forceinline__ PairSegs segs_of_pair(const RangeWs& ws, int total, int cut, int pair, int u0, int tiles) {
   if (cut > 0) return PairSegs{pair + (u0 >> (cut - 1)), pieces_of(tiles, cut - 1)};
   const int n = ranges_used(ws, total), w0 = range_of(u0, total, n);
   return PairSegs{pair + w0, range_of(u0 + tiles - 1, total, n) - w0 + 1};
@@ -1904,8 +1903,10 @@ __device__ __forceinline__ void merge_pair(const KvView& kv, int n_q, const Rang
   const int b = pair / kv.num_kv_heads, g = pair - b * kv.num_kv_heads, rq = request_of(kv, b);
   const int G = kv.num_q_heads / kv.num_kv_heads, R = n_q * G, Rb = queries_of(kv, ws, b, n_q) * G, tiles = tiles_of_len(kv.seq_lens[rq]);
   constexpr int rows = RB * 16;
-  const PairSegs segs = segs_of_pair(ws, pair, ws.ureq[b] + g * tiles, tiles);
-  if (tiles <= 0 || segs.n <= 1) return;       // (one segment: the pass has written O)
+  const int u0 = ws.ureq[b] + g * tiles, total = ws.ctrl[0], cut = ws.ctrl[1];
+  if (tiles <= 0) return;
+  const PairSegs segs = segs_of_pair(ws, total, cut, pair, u0, tiles);
+  if (segs.n <= 1) return;                     // (the pass has written O)
   pair_lse<RB>(kv, ws, n_q, G, Rb, rq, g, segs, nullptr, s_o, s_lse);
   constexpr int kQuads = THREADS / 512, kGroups = 4, kAtOnce = 8;        // quads of rows at work; segments of a thread sent for together
   const int sub = static_cast<int>(threadIdx.x) / 512, grp = static_cast<int>(threadIdx.x) % 512 / 128, piece = static_cast<int>(threadIdx.x) % 128;
@@ -1996,10 +1997,7 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
   const int R = n_q * G;
   const int Rb = queries_of(kv, ws, b, n_q) * G;
   constexpr int rows = RB * 16;
-  const int u0 = ws.ureq[b] + g * tiles;
-  const PairSegs segs = segs_of_pair(ws, pair, u0, tiles);
-  const int nseg = segs.n;
-  const bool split = nseg > 1;
+  const int u0 = ws.ureq[b] + g * tiles, total = ws.ctrl[0], cut = ws.ctrl[1];             // (sent for beside the length)
   const int my_chunk = SPLIT && blockIdx.y > 0 ? static_cast<int>(blockIdx.y) - mergers : 0;
   if (SPLIT && my_chunk > 0 && my_chunk * kChunk >= L) return;      // this pair has fewer chunks (uniform over the workgroup)
   const bool lead = my_chunk == 0;                       // the workgroup that writes what exists once per pair
@@ -2022,6 +2020,11 @@ __global__ __launch_bounds__(THREADS, THREADS >= 1024 || RB <= 2 ? 4 : 2) void v
     return;
   }
 
+  // (its divisions come after the workgroups with nothing to do have left: where max_seq_len allows for more chunks than there are, they run
+  // when the others have finished, and 32 requests of 1.5 K tokens under a max_seq_len of 32 K took 66.9 us instead of 64.7)
+  const PairSegs segs = segs_of_pair(ws, total, cut, pair, u0, tiles);
+  const int nseg = segs.n;
+  const bool split = nseg > 1;
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int nv = R - 16 * (RB - 1);
   const int tile_lanes = (RB - 1) * 64 + 4 * nv;
