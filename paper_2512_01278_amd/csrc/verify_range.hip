@@ -416,8 +416,8 @@ struct RangeStart {
 // The shortest pieces with which the batch makes no more of them than there are ranges (log2 of their tiles plus one), or 0: equal ranges.
 template <int REGS>
 __device__ __forceinline__ int plan_pieces(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int lane) {
-  if (p.total > (ws.n_ranges << ws.max_piece_shift)) return 0;
   for (int shift = kMinPieceShift; shift <= ws.max_piece_shift; ++shift) {
+    if (p.total > (ws.n_ranges << shift)) continue;                    // too many whatever the lengths are
     if (shift > kMinPieceShift && (ws.n_ranges << shift) > p.total + kPieceSlack * ws.n_ranges) return 0;
     int mine = 0;
 #pragma unroll
