@@ -24,6 +24,16 @@ inline int merger_groups(int64_t pairs, int max_seq_len, int rows, int threads, 
   return std::min(room, (rows + at_once - 1) / at_once);
 }
 
+// Pieces of one pair that the streaming pass is cut into where a batch is small: as few as have at most 2^shift tiles, all alike to a tile.
+// (Pieces of 2^shift tiles and a rest were long and short in turn where the contexts are alike, and with two per pair the long ones went to
+// every other workgroup, that is to half the XCDs: 32 requests of 575-600 tokens, 8 heads, 34.6 us where equal ranges take 31.4 and
+// these 31.4, of 730-760 36.7 / 38.4 / 34.7, of 1500-1560 58.1 / 60.4 / 55.9; fp8 with 40 rows 36.7 / 33.6 / 34.0.)
+__host__ __device__ inline int pieces_of(int tiles, int shift) { return (tiles + (1 << shift) - 1) >> shift; }
+__host__ __device__ inline int piece_begin(int tiles, int pieces, int i) { return static_cast<int>(static_cast<int64_t>(i) * tiles / pieces); }
+// Partial slots: piece i of the pair that begins at unit u0 has pair + first_slot + i.  Distinct: a pair has at most (tiles >> shift) + 1 pieces,
+// and the next one, tiles units on, begins at least (tiles >> shift) + 1 slots later.
+__host__ __device__ inline int first_slot(int u0, int shift) { return u0 >> shift; }
+
 // Whether the rows of a draft step bypass the Infinity Cache (non-temporal loads).  Rows that are there no more when they are next
 // needed are read 7 to 14 % faster that way: 128 requests with lists of 256 31.3 / 27.1 us, 32 12.1 / 11.0, 16 of 1024 rows 21.3 / 19.4, fp8
 // 64 of 512 22.2 / 20.7, each over so many pools that nothing stays cached; and the unified batch of 128 of 1-8 K tokens takes 154 / 144.

@@ -61,7 +61,7 @@ constexpr int kWindowPages = 64;               // page ids held per register: on
 constexpr int kFinishMaxTokens = 32768;        // longest row whose Top-K the finish kernel selects itself
 
 struct RangeWs {
-  int32_t* ctrl;        // [0] total units T  [1] 0: equal ranges; else a range is a piece of one pair, 2^(ctrl[1] - 1) tiles
+  int32_t* ctrl;        // [0] total units T  [1] 0: equal ranges; else a range is a piece of one pair, at most 2^(ctrl[1] - 1) tiles
   int32_t* ureq;        // [B+1] first unit of request b (its heads follow each other)
   int32_t* order;       // [pairs] (request, head) pairs in the order the finish kernel takes them: longest rows first
   float* scratch_scores;  // [pairs][scratch_stride] statistic of the split finish kernel when the caller wants none
@@ -101,7 +101,7 @@ __device__ __forceinline__ int range_of(int unit, int total, int n) {
 
 // Small batches: pieces of one pair instead of equal ranges.  A range of a few tiles that crosses from pair to pair takes as long as its
 // stretches together (each a chain of loads and a merge), and the grid as long as that.  So a batch whose pairs make no more pieces
-// of 4, 8, 16 or 32 tiles than there are ranges is cut that way, into the shortest such pieces, one per range: a team has a tile per
+// of at most 4, 8, 16 or 32 tiles than there are ranges is cut that way, into the shortest such pieces, one per range: a team has a tile per
 // wavefront in the shortest, and shorter ones would only leave more partials.  Equal ranges / pieces, pass + finish: 24 requests of 5-3000
 // tokens, 4 heads 15.5 + 14.9 / 11.4 + 12.4 us, one of 2100 11.0 + 15.2 / 10.0 + 12.5, 2 of 6-8 K 43.3 / 36.8 in all, fp8 with 40
 // rows 8 of 1-4 K 42.7 / 38.1 and 12 of 3-7 K 61.6 / 57.7, 24 of 10-3000 with 64 rows 47.6 / 35.0.  Pieces of 2 tiles for the pass
@@ -109,15 +109,13 @@ __device__ __forceinline__ int range_of(int unit, int total, int n) {
 // A piece may be longer than an equal range by what a boundary costs, some 8 tiles: 64 pairs of 17 x 256 tokens (pieces of 32 tiles,
 // ranges of 17) 48.8 / 50.5 us, of 14 x 256 (16 against 14) 43.6 / 37.9.  The pass with two wavefronts per range goes through a tile with
 // both, so that a longer range costs it more than a boundary: pieces of 4 tiles only (128 pairs, 36 rows, pieces of 16 against ranges
-// of 9 62.5 / 73.7, 64 rows, of 8 against 6 49.5 / 55.9).
+// of 9 62.5 / 73.7, 64 rows, of 8 against 6 49.5 / 55.9).  (These two lines with pieces of 16, 8 or 32 tiles and a rest.)
 constexpr int kMinPieceShift = 2, kMaxPieceShift = 5, kPieceSlack = 8;
-__device__ __forceinline__ int pieces_of(int tiles, int shift) { return (tiles + (1 << shift) - 1) >> shift; }
 
-// Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or, with pieces, pair + (first unit >> shift), which
-// is distinct for the same reason (both indices grow along the layout).
+// Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or that of its first piece.
 struct PairSegs { int slot0, n; };
 __device__ __forceinline__ PairSegs segs_of_pair(const RangeWs& ws, int total, int cut, int pair, int u0, int tiles) {
-  if (cut > 0) return PairSegs{pair + (u0 >> (cut - 1)), pieces_of(tiles, cut - 1)};
+  if (cut > 0) return PairSegs{pair + first_slot(u0, cut - 1), pieces_of(tiles, cut - 1)};
   const int n = ranges_used(ws, total), w0 = range_of(u0, total, n);
   return PairSegs{pair + w0, range_of(u0 + tiles - 1, total, n) - w0 + 1};
 }
@@ -408,7 +406,7 @@ __device__ __forceinline__ void publish_plan(const KvView& kv, const RangeWs& ws
 // memory (one of those that share a range).
 struct RangeStart {
   int unit, end;
-  int cut;                 // as ctrl[1]
+  int slot;                // partial slot of the first segment, less its pair
   Segment sg;
   bool live;
 };
@@ -437,7 +435,6 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
   const WavePlan<REGS> p = wave_plan<REGS>(kv, lane);
   const int cut = plan_pieces<REGS>(kv, ws, p, lane);
   if (publish) publish_plan(kv, ws, p, cut, w, lane);
-  c.cut = cut;
   if (cut > 0) {
     const int shift = cut - 1;
     int carry = 0, upto = 0, before[REGS];                   // pieces before a request; requests that begin at or before piece w
@@ -458,11 +455,13 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
     c.sg.L = plan_get(p.len, c.sg.b);
     first_unit = plan_get(p.first, c.sg.b);
     const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift);
-    const int rel = w - plan_get(before, c.sg.b), head = rel / per_head, tile0 = (rel - head * per_head) << shift;
-    c.unit = first_unit + head * tiles + tile0;
-    c.end = c.unit + min(tiles - tile0, 1 << shift);
+    const int rel = w - plan_get(before, c.sg.b), head = rel / per_head, piece = rel - head * per_head, u0 = first_unit + head * tiles;
+    c.unit = u0 + piece_begin(tiles, per_head, piece);
+    c.end = u0 + piece_begin(tiles, per_head, piece + 1);
+    c.slot = first_slot(u0, shift) + piece;
     return;
   }
+  c.slot = w;
   const int n = ranges_used(ws, p.total);
   c.unit = range_begin(w, p.total, n);
   c.end = range_begin(w + 1, p.total, n);
@@ -481,7 +480,7 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
 __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
   RangeStart c;
   c.sg = Segment{};
-  c.cut = 0;
+  c.slot = w;
   int first_unit = 0;                          // of the request the range begins in
   if (ws.plan_in_wave) {                       // the same for the whole grid
     if (kv.batch <= 2 * kWave) plan_range<2>(kv, ws, w, lane, publish, c, first_unit);
@@ -506,7 +505,7 @@ __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs
   sg.tile0 = rel - sg.g * sg.tiles;
   sg.tile1 = min(sg.tiles, sg.tile0 + (c.end - c.unit));
   sg.pair = sg.b * kv.num_kv_heads + sg.g;
-  sg.slot = sg.pair + (c.cut > 0 ? c.unit >> (c.cut - 1) : w);
+  sg.slot = sg.pair + c.slot;
   return c;
 }
 
