@@ -3,6 +3,7 @@ declares, and rejects bad arguments on the host before any launch."""
 import ctypes as C
 import os
 import re
+import sys
 
 import pytest
 
@@ -198,3 +199,29 @@ def test_streaming_kernels_take_slot_strides_whose_rows_of_one_load_fit_32_bits(
     below = limit // 16 * 16
     assert hetero(below) == pb.PILLAR_EWORKSPACE
     assert hetero(below + 16) == pb.PILLAR_EUNSUPPORTED
+
+
+def test_current_stream_with_and_without_torchs_private_name(monkeypatch):
+    """The handle comes from a name that torch does not promise; without it the public call gives the same."""
+    import importlib.util
+    import types
+
+    import torch
+
+    def stream_of(raw):
+        spec = importlib.util.spec_from_file_location("binding_alone", pb.__file__)
+        module = importlib.util.module_from_spec(spec)
+        monkeypatch.setitem(sys.modules, "binding_alone", module)      # (its dataclass looks itself up)
+        if raw is None:
+            monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+        else:
+            monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", raw, raising=False)
+        spec.loader.exec_module(module)
+        return module._stream
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x500))
+    assert stream_of(lambda device: 0x400 + device)(None) == 0x403
+    assert stream_of(lambda device: 0)(None) is None                   # the default stream
+    assert stream_of(None)(None) == 0x500
+    assert stream_of(None)(types.SimpleNamespace(cuda_stream=0x600)) == 0x600
