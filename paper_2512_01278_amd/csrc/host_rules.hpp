@@ -29,7 +29,11 @@ inline int merger_groups(int64_t pairs, int max_seq_len, int rows, int threads, 
 // every other workgroup, that is to half the XCDs: 32 requests of 575-600 tokens, 8 heads, 34.6 us where equal ranges take 31.4 and
 // these 31.4, of 730-760 36.7 / 38.4 / 34.7, of 1500-1560 58.1 / 60.4 / 55.9; fp8 with 40 rows 36.7 / 33.6 / 34.0.)
 __host__ __device__ inline int pieces_of(int tiles, int shift) { return (tiles + (1 << shift) - 1) >> shift; }
-__host__ __device__ inline int piece_begin(int tiles, int pieces, int i) { return static_cast<int>(static_cast<int64_t>(i) * tiles / pieces); }
+// first tile of piece i; least = tiles / pieces (the first ones have a tile more)
+__host__ __device__ inline int piece_begin(int tiles, int pieces, int least, int i) {
+  const int longer = tiles - least * pieces;
+  return i * least + (i < longer ? i : longer);
+}
 // Partial slots: piece i of the pair that begins at unit u0 has pair + first_slot + i.  Distinct: a pair has at most (tiles >> shift) + 1 pieces,
 // and the next one, tiles units on, begins at least (tiles >> shift) + 1 slots later.
 __host__ __device__ inline int first_slot(int u0, int shift) { return u0 >> shift; }

@@ -75,7 +75,7 @@ struct RangeWs {
   const int32_t* spec_lens;   // [B] speculative length of each request, or null: all use the call's k
   int32_t rows_pad;     // 16 * row blocks
   int32_t n_ranges;     // N
-  int32_t max_piece_shift;  // log2 of the longest pieces the pass may be cut into
+  int32_t min_piece_shift, max_piece_shift;  // log2 of the shortest and the longest pieces the pass may be cut into
   int32_t plan_in_wave; // ctrl / ureq / order are not there yet: the wavefronts of the single pass work them out (wave_plan)
 };
 
@@ -104,13 +104,15 @@ __device__ __forceinline__ int range_of(int unit, int total, int n) {
 // of at most 4, 8, 16 or 32 tiles than there are ranges is cut that way, into the shortest such pieces, one per range: a team has a tile per
 // wavefront in the shortest, and shorter ones would only leave more partials.  Equal ranges / pieces, pass + finish: 24 requests of 5-3000
 // tokens, 4 heads 15.5 + 14.9 / 11.4 + 12.4 us, one of 2100 11.0 + 15.2 / 10.0 + 12.5, 2 of 6-8 K 43.3 / 36.8 in all, fp8 with 40
-// rows 8 of 1-4 K 42.7 / 38.1 and 12 of 3-7 K 61.6 / 57.7, 24 of 10-3000 with 64 rows 47.6 / 35.0.  Pieces of 2 tiles for the pass
-// with two wavefronts per range: one request of 2100 tokens with 36 rows 34.4 us, of 4 tiles 29.5.
+// rows 8 of 1-4 K 42.7 / 38.1 and 12 of 3-7 K 61.6 / 57.7, 24 of 10-3000 with 64 rows 47.6 / 35.0.
 // A piece may be longer than an equal range by what a boundary costs, some 8 tiles: 64 pairs of 17 x 256 tokens (pieces of 32 tiles,
 // ranges of 17) 48.8 / 50.5 us, of 14 x 256 (16 against 14) 43.6 / 37.9.  The pass with two wavefronts per range goes through a tile with
-// both, so that a longer range costs it more than a boundary: pieces of 4 tiles only (128 pairs, 36 rows, pieces of 16 against ranges
-// of 9 62.5 / 73.7, 64 rows, of 8 against 6 49.5 / 55.9).  (These two lines with pieces of 16, 8 or 32 tiles and a rest.)
-constexpr int kMinPieceShift = 2, kMaxPieceShift = 5, kPieceSlack = 8;
+// both, so that a longer range costs it more than a boundary: pieces of 2 and of 4 tiles only (128 pairs, 36 rows, pieces of 16 against
+// ranges of 9 62.5 / 73.7, 64 rows, of 8 against 6 49.5 / 55.9).  (These with pieces of 2^n tiles and a rest.)
+// Pieces of 2 for that pass, up to half as many as there are ranges, beyond which their partials cost as much.  8 heads, equal ranges / pieces
+// of 4 / of 2: one request of 100 tokens, 64 rows 19.4 / 20.5 / 17.6 us, of 1000 33.2 / 22.4 / 20.4, of 2000 47.1 / 25.5 / 22.5; 4 of 256
+// 22.0 / 21.8 / 19.6; 8 of 270-300 with 36 rows 24.2 / 21.7 / 20.1, of 480-720 (640 pieces) 29.1 / 23.2 / 24.1.
+constexpr int kMinTeamPiece = 2, kMaxTeamPiece = 5, kMinPairPiece = 1, kMaxPairPiece = 2, kPieceSlack = 8;
 
 // Segments of a pair that begins at unit u0, and the slot of the first: pair + range, or that of its first piece.
 struct PairSegs { int slot0, n; };
@@ -288,7 +290,7 @@ __device__ __forceinline__ void fetch_scales(const KvView& kv, Flight& f) {
 // tiles in flight and crosses pair boundaries without draining: when it enters a pair it already
 // holds the page ids of the pair after it (they were fetched one pair earlier).
 struct Cursor {
-  int unit, end, w;  // next unit to issue, end of the range, index of the range
+  int unit, end, slot;  // next unit to issue, end of the range, slot of a segment less its pair
   Segment sg;        // the segment that unit belongs to
   int tile;          // next tile of sg
   PageWin pw;
@@ -414,14 +416,15 @@ struct RangeStart {
 // The shortest pieces with which the batch makes no more of them than there are ranges (log2 of their tiles plus one), or 0: equal ranges.
 template <int REGS>
 __device__ __forceinline__ int plan_pieces(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int lane) {
-  for (int shift = kMinPieceShift; shift <= ws.max_piece_shift; ++shift) {
-    if (p.total > (ws.n_ranges << shift)) continue;                    // too many whatever the lengths are
-    if (shift > kMinPieceShift && (ws.n_ranges << shift) > p.total + kPieceSlack * ws.n_ranges) return 0;
+  for (int shift = ws.min_piece_shift; shift <= ws.max_piece_shift; ++shift) {
+    const int most = shift == kMinPairPiece ? ws.n_ranges / 2 : ws.n_ranges;
+    if (p.total > (most << shift)) continue;                           // too many whatever the lengths are
+    if (shift > ws.min_piece_shift && (ws.n_ranges << shift) > p.total + kPieceSlack * ws.n_ranges) return 0;
     int mine = 0;
 #pragma unroll
     for (int j = 0; j < REGS; ++j) mine += pieces_of(tiles_of_len(p.len[j]), shift);         // 0 beyond the batch
     const int pieces = __builtin_amdgcn_readlane(static_cast<int>(wave_inclusive_sum(static_cast<uint32_t>(mine))), kWave - 1);
-    if (pieces * kv.num_kv_heads <= ws.n_ranges) return shift + 1;
+    if (pieces * kv.num_kv_heads <= most) return shift + 1;
   }
   return 0;
 }
@@ -454,10 +457,10 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
     c.sg.b = upto - 1;
     c.sg.L = plan_get(p.len, c.sg.b);
     first_unit = plan_get(p.first, c.sg.b);
-    const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift);
+    const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift), least = tiles / per_head;
     const int rel = w - plan_get(before, c.sg.b), head = rel / per_head, piece = rel - head * per_head, u0 = first_unit + head * tiles;
-    c.unit = u0 + piece_begin(tiles, per_head, piece);
-    c.end = u0 + piece_begin(tiles, per_head, piece + 1);
+    c.unit = u0 + piece_begin(tiles, per_head, least, piece);
+    c.end = u0 + piece_begin(tiles, per_head, least, piece + 1);
     c.slot = first_slot(u0, shift) + piece;
     return;
   }
@@ -512,7 +515,7 @@ __device__ __forceinline__ RangeStart open_range(const KvView& kv, const RangeWs
 __device__ __forceinline__ Cursor open_cursor(const KvView& kv, const RangeWs& ws, int w, int lane) {
   const RangeStart start = open_range(kv, ws, w, lane, true);
   Cursor c;
-  c.w = w;
+  c.slot = start.slot;
   c.unit = start.unit;
   c.end = start.end;
   c.sg = start.sg;
@@ -556,7 +559,7 @@ __device__ __forceinline__ void advance_cursor(const KvView& kv, Cursor& c, int 
     sg.tile0 = 0;
     sg.tile1 = min(sg.tiles, c.end - c.unit);
     sg.pair = sg.b * kv.num_kv_heads + sg.g;
-    sg.slot = sg.pair + c.w;
+    sg.slot = sg.pair + c.slot;
     sg.rq = request_of(kv, sg.b);
     c.sg = uniform(sg);
     c.tile = 0;
@@ -1270,7 +1273,7 @@ __device__ __forceinline__ int opaque(int v) {
 // The segments of a range one after the other.  The lengths of 64 requests wait in a register, one per lane, and the first 64 page
 // ids of this request and of the next one in two more, so that entering a segment waits for no table.
 struct Walk {
-  int unit, end, w;        // first unit of the segment, end of the range, index of the range
+  int unit, end, slot;     // first unit of the segment, end of the range, slot of a segment less its pair
   Segment sg;
   int lens, len0;          // lane j: length of request len0 + j of the launch
   int ids, ids_next;       // lane j: page j of the segment's request / of the request after it
@@ -1282,7 +1285,7 @@ __device__ __forceinline__ int load_lengths(const KvView& kv, int b, int lane) {
 __device__ __forceinline__ Walk open_walk(const KvView& kv, const RangeWs& ws, int w, int lane, bool publish) {
   const RangeStart start = open_range(kv, ws, w, lane, publish);
   Walk c;
-  c.w = w;
+  c.slot = start.slot;
   c.unit = start.unit;
   c.end = start.end;
   c.sg = uniform(start.sg);
@@ -1321,7 +1324,7 @@ __device__ __forceinline__ void next_segment(const KvView& kv, Walk& c, int lane
   sg.tile0 = 0;
   sg.tile1 = min(sg.tiles, c.end - c.unit);
   sg.pair = sg.b * kv.num_kv_heads + sg.g;
-  sg.slot = sg.pair + c.w;
+  sg.slot = sg.pair + c.slot;
 }
 
 // (m, l) and O of a segment that one wavefront went through alone: final when it is the whole pair, else a partial.
@@ -2345,7 +2348,8 @@ RangeWs carve(const KvView& kv, int n_q, void* workspace, size_t* total_bytes) {
   w.spec_lens = nullptr;
   w.rows_pad = static_cast<int32_t>(rpad);
   w.n_ranges = static_cast<int32_t>(n);
-  w.max_piece_shift = kMinPieceShift;
+  w.min_piece_shift = kMinPairPiece;
+  w.max_piece_shift = kMaxPairPiece;
   w.plan_in_wave = 0;
   if (total_bytes) *total_bytes = off;
   return w;
@@ -2384,7 +2388,8 @@ hipError_t run(const VerifyArgs& a, hipStream_t st, const DecodeArgs* draft) {
     }
     if constexpr (RB <= 2 || (FP8 && RB == 3)) {     // a range per workgroup
       ws.n_ranges = team_ranges(ws.n_ranges);
-      ws.max_piece_shift = kMaxPieceShift;
+      ws.min_piece_shift = kMinTeamPiece;
+      ws.max_piece_shift = kMaxTeamPiece;
       if (fused) {
         KernelTimer t("mixed_flash_team", st);
         const auto kernel = may_bypass ? mixed_flash_team<RB, FP8, true> : mixed_flash_team<RB, FP8, false>;

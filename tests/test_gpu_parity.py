@@ -602,9 +602,11 @@ def test_many_segments_per_pair(k, segments):
 @pytest.mark.parametrize("batch", [5, 140])
 @pytest.mark.parametrize("k,segments", [(2, 32), (4, 16), (8, 10), (15, 8)])
 def test_many_pieces_per_pair(k, segments, batch):
-    """Small batches are cut into pieces of four tiles, so a pair of 128 n tokens has n segments: around the number whose log-sum-exp one
-    turn takes and several times that, with O put together by workgroups of its own (few pairs) and by the finish kernel's own."""
-    lens = [128 * (segments - 1), 128 * segments, 128 * (segments + 1), 128 * 3 * segments + 5] + [17] * (batch - 4)
+    """Small batches are cut into pieces of four tiles (two with more than 32 rows), so a pair of 128 n (64 n) tokens has n segments: around
+    the number whose log-sum-exp one turn takes and several times that, with O put together by workgroups of its own (few pairs) and by
+    the finish kernel's own."""
+    piece = 128 if 4 * (k + 1) <= 32 else 64
+    lens = [piece * (segments - 1), piece * segments, piece * (segments + 1), piece * 3 * segments + 5] + [17] * (batch - 4)
     _same_as_two_calls(small(350 + k, B=batch, Hq=4, Hkv=1, spec_k=k, seq_lens=lens, budgets=[64, 64, 64, 200] + [5] * (batch - 4)), f"{segments} pieces")
 
 
