@@ -413,6 +413,13 @@ struct RangeStart {
   bool live;
 };
 
+// a / b, both below 2^22 (a piece has no more than 32 tiles, a range is no more than one), by a reciprocal of b that divisions share: at most one
+// off before it is set right.
+__device__ __forceinline__ int div_near(int a, int b, float rcp_b) {
+  const int q = static_cast<int>(static_cast<float>(a) * rcp_b), r = a - q * b;
+  return __builtin_amdgcn_readfirstlane(q + (r >= b) - (r < 0));
+}
+
 // The shortest pieces with which the batch makes no more of them than there are ranges (log2 of their tiles plus one), or 0: equal ranges.
 template <int REGS>
 __device__ __forceinline__ int plan_pieces(const KvView& kv, const RangeWs& ws, const WavePlan<REGS>& p, int lane) {
@@ -457,8 +464,10 @@ __device__ __forceinline__ void plan_range(const KvView& kv, const RangeWs& ws, 
     c.sg.b = upto - 1;
     c.sg.L = plan_get(p.len, c.sg.b);
     first_unit = plan_get(p.first, c.sg.b);
-    const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift), least = tiles / per_head;
-    const int rel = w - plan_get(before, c.sg.b), head = rel / per_head, piece = rel - head * per_head, u0 = first_unit + head * tiles;
+    const int tiles = tiles_of_len(c.sg.L), per_head = pieces_of(tiles, shift);
+    const float rcp = __builtin_amdgcn_rcpf(static_cast<float>(per_head));       // (whole divisions: 24 requests of 5-3000 tokens 20.75 us, 20.6 so)
+    const int least = div_near(tiles, per_head, rcp);
+    const int rel = w - plan_get(before, c.sg.b), head = div_near(rel, per_head, rcp), piece = rel - head * per_head, u0 = first_unit + head * tiles;
     c.unit = u0 + piece_begin(tiles, per_head, least, piece);
     c.end = u0 + piece_begin(tiles, per_head, least, piece + 1);
     c.slot = first_slot(u0, shift) + piece;
