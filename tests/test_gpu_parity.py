@@ -673,12 +673,12 @@ def test_pieces_of_small_batches_and_ranges_of_larger_ones(kv_dtype, page, heads
         pa.pillar_set_option("verify_waves", 0)
 
 
-@pytest.mark.parametrize("batch", [64, 65])
-@pytest.mark.parametrize("kv_dtype,heads,k", [("bf16", 4, 0), ("bf16", 8, 4), ("bf16", 16, 4), ("fp8_e4m3", 16, 7)])
+@pytest.mark.parametrize("kv_dtype,heads,k,batch", [(*rows, batch) for rows, most in ((("bf16", 4, 0), 64), (("bf16", 8, 4), 64), (("bf16", 16, 4), 51), (("fp8_e4m3", 16, 7), 42))
+                                                     for batch in sorted({most, most + 1, 64, 65})])
 def test_output_put_together_by_workgroups_of_its_own(kv_dtype, heads, k, batch):
-    """With up to 128 pairs (two KV heads here), O of a pair of several segments is put together by workgroups that do nothing else, with
-    more by the one that rebuilds the statistic: rows in every number of fours, contexts of one segment to ten,
-    speculative lengths of their own, and the same bits without the statistic."""
+    """With up to 128 pairs (two KV heads here; 102 with 40 rows and 85 with 64, which take two turns there, four without the statistic), O of a
+    pair of several segments is put together by workgroups that do nothing else, with more by the one that rebuilds the statistic: 2,
+    20, 40 and 64 rows, contexts of one segment to ten, speculative lengths of their own, and the same bits without the statistic."""
     rng = np.random.default_rng(43 + k)
     lens = [k + 1, 100, 128, 129, 1290] + rng.integers(k + 1, 700, size=batch - 5).tolist()
     w = small(300 + k, kv_dtype=kv_dtype, Hq=heads, B=batch, Hkv=2, spec_k=k, seq_lens=lens, budgets=[min(n, 24) for n in lens])

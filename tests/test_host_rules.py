@@ -58,6 +58,7 @@ def test_mergers_only_where_they_take_two_turns_at_most(mergers):
                 assert (n > 0) == (pairs <= 128 and rows <= 16 * (2 * (256 - pairs) // pairs)), (pairs, rows, threads, n)
     assert mergers(96, 4096, 64, 1024) == 0 and mergers(88, 4096, 64, 512) == 0 and mergers(85, 4096, 64, 1024) == 4
     assert mergers(96, 4096, 48, 1024) == 3 and mergers(102, 4096, 48, 1024) == 3 and mergers(103, 4096, 48, 1024) == 0
+    assert mergers(102, 1290, 40, 1024) == 3 and mergers(104, 1290, 40, 1024) == 0 and mergers(84, 1290, 64, 512) == 4 and mergers(86, 1290, 64, 512) == 0
     # contexts of up to n chunks of 8192 tokens take n workgroups per pair
     assert mergers(8, 16 * 8192, 20, 1024) > 0 and mergers(8, 16 * 8192 + 1, 20, 1024) == 0
 
