@@ -87,7 +87,11 @@ typedef struct {
   int32_t block_table_stride;  /* row length of block_table, in entries */
   const int32_t* block_table;  /* device [B][block_table_stride] */
   const int32_t* seq_lens;     /* device [B], 1 <= seq_lens[b] <= max_seq_len */
-  int32_t max_seq_len;         /* host-known bound, <= block_table_stride*page_size */
+  int32_t max_seq_len;         /* host-known bound, <= block_table_stride*page_size.
+                                * Kernels and grids are chosen by it (and by
+                                * max_budget below), lengths being known on the
+                                * device only: any bound is correct, a close one
+                                * is faster */
   int32_t flags;               /* 0 or an OR of pillar_flag values; unknown bits: PILLAR_EINVAL */
 } pillar_kv_t;
 

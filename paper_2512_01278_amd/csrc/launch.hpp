@@ -75,7 +75,7 @@ struct TopkArgs {
   int32_t* counts;
 };
 
-// generic (any supported shape, fp32 arithmetic on the vector ALUs)
+// generic (any supported shape, fp32 arithmetic)
 // fine_room: what small launches make use of; without it, the least the kernels run with
 size_t verify_generic_workspace(const KvView& kv, int n_q, bool fine_room);
 hipError_t launch_verify_generic(const VerifyArgs& a, hipStream_t s);

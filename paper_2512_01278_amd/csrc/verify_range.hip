@@ -63,7 +63,8 @@ constexpr int kFinishMaxTokens = 32768;        // longest row whose Top-K the fi
 struct RangeWs {
   int32_t* ctrl;        // [0] total units T  [1] 0: equal ranges; else a range is a piece of one pair, at most 2^(ctrl[1] - 1) tiles
   int32_t* ureq;        // [B+1] first unit of request b (its heads follow each other)
-  int32_t* order;       // [pairs] (request, head) pairs in the order the finish kernel takes them: longest rows first
+  int32_t* order;       // [pairs] (request, head) pairs in the order the finish kernel takes them: longest rows first.  Null for a finish
+                        // kernel of one workgroup per pair that all run at once; those that share pairs, and verify_select_rows, read it
   float* scratch_scores;  // [pairs][scratch_stride] statistic of the split finish kernel when the caller wants none
   int64_t scratch_stride;
   float* part_m;        // [pairs + N][rows_pad]  log2 domain
@@ -89,7 +90,9 @@ __device__ __forceinline__ int queries_of(const KvView& kv, const RangeWs& ws, i
 // Ranges in use: all that the chip holds at once, but none shorter than kMinTiles tiles.  A segment more to merge costs the
 // finish kernel little, a segment more in a range a workgroup one after the other: pass + finish at one request of 2100
 // tokens 11.3 + 15.2 us with 2 tiles, 13.2 + 14.2 with 4, 14.8 + 12.8 with 8; 24 requests of 5 to 3000 tokens 17.0 + 16.2,
-// 23.0 + 14.2, 39.6 + 12.8.  (With 1, every tile a segment: 12.4 + 20.4 and 14.3 + 20.4 with a range per wavefront.)
+// 23.0 + 14.2, 39.6 + 12.8.  (With 1, every tile a segment: 12.4 + 20.4 and 14.3 + 20.4 with a range per wavefront.  Both of these batches
+// are cut into pieces now, below.  Left to this rule are batches of more short pairs than there are ranges, those of more than 1024
+// requests, and the exact variant.)
 constexpr int kMinTiles = 2;
 __device__ __forceinline__ int ranges_used(const RangeWs& ws, int total) { return max(1, min(ws.n_ranges, total / kMinTiles)); }
 
@@ -1168,9 +1171,14 @@ __device__ __forceinline__ void stretch_qk(const uint8_t* tile, const uint8_t* s
 
 // What a pass does with the stash: nothing, leaves it in the L2 to be written back, or writes it through.  A stash that the L2s (32 MB) cannot
 // hold leaves them line by line while the pass reads, and costs it less when it does so at once: 128 requests of 1-8 K tokens (200
-// MB) 517.5 -> 512.5 us, fp8 with 40 rows 64 of 512-32 K (412 MB) 455.5 -> 450.3, 16 of 24-32 K with 36 rows (293 MB) 490.6 ->
-// 485.6; but the finish kernel finds less of a small one: 32 requests of 4096 tokens (42 MB) 130.8 -> 132.0.  The host chooses, by what
-// max_seq_len allows (a choice per tile on the chip costs as much as it gives).
+// MB) 518.3 -> 513.5 us, fp8 with 40 rows 64 of 512-32 K (412 MB) 457.2 -> 450.5, 16 of 24-32 K with 36 rows (293 MB) 495.7 ->
+// 489.7 (medians of four turns, which differ by 0.2 %); but the finish kernel finds less of a small one: 32 requests of 4096 tokens, 42 MB
+// 124.2 -> 125.1.  In between: bf16 with 20 rows 77 MB 230.2 -> 228.2, 105 310.5 -> 308.1, 126 358.4 -> 355.4, 190 552.9 -> 549.1; fp8 with 40 rows
+// 63 MB 82.2 -> 82.5, 126 146.7 -> 146.7, 170 186.5 -> 185.9.  The host chooses, by what max_seq_len allows, and knows no lengths: the line
+// lies so high that a bound of some times the contexts does not put a small stash beyond it (one that does, 32 requests of 1.5 K tokens
+// under 32 K: 64.0 -> 64.5; of 4096 134.2 -> 134.1).  A choice on the chip costs what it gives: per tile, and once per workgroup with whole
+// copies of the pass (128 requests of 1-8 K tokens 517.4, 16 of 24-32 K with 36 rows, which then spill, 489.3).
+// A unified batch keeps the plain stores whatever its size: 26 of 128 requests of 24-32 K tokens verifying (233 MB) take 793 us.
 enum { kNoStash = 0, kStashKept = 1, kStashThrough = 2 };
 constexpr int64_t kThroughBytes = int64_t{192} << 20;
 

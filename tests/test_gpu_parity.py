@@ -251,7 +251,7 @@ def test_two_pass_variant_with_fp32_probabilities():
 
 
 def test_generic_kernels_on_a_matrix_core_shape():
-    """PILLAR_FLAG_GENERIC_KERNELS: the vector-ALU kernels on a shape the matrix-core kernels normally take, against
+    """PILLAR_FLAG_GENERIC_KERNELS: the generic kernels on a shape the matrix-core kernels normally take, against
     the oracle, and against the matrix-core result (two implementations of one definition)."""
     w = small(119, B=3, Hq=16, Hkv=4, spec_k=4, seq_lens=[6, 300, 1100], budgets=[6, 40, 64])
     slow, _ = round_trip(w, what="generic kernels, bf16", flags=pa.PILLAR_FLAG_GENERIC_KERNELS)
